@@ -127,11 +127,15 @@ struct QrAlsdArgs {
 
 struct QrRecArgs {
     const v4i *whh;  const float *s_wih, *s_whh, *bias;
-    const int32_t *gx;                 // [T*B, 4H] gate-interleaved input projection
+    const v4i *wih;                    // used when gx is null: the kernel projects the input itself
+    const int8_t *x;  int64_t ld_x;    // input codes [T*B, I], row pitch in bytes
+    int I, nkc_x;
+    const int32_t *gx;                 // [T*B, 4H] gate-interleaved input projection, or null (qr_rec_projects(I))
     const int8_t *h0;  const float *c0;
     int8_t *h_out;  int64_t ld_out;  int col_off;
     int8_t *h_last;  float *c_last;  float *dbg_c_all;
-    unsigned long long *xbuf;          // [2][B][H/4] exchange words, zeroed before the launch
+    char *xbuf;                        // exchange area (qr_rec_xbuf_bytes), zeroed before the launch
+    int *xcc;                          // where each workgroup runs (qr_rec_xcc_bytes), zeroed before the launch
     int *err;                          // set to 1 when a bounded wait ran out
     int T, B, H, nkc_h, reverse, spin_limit;
     float x_scale, h_scale, h_inv;
@@ -140,9 +144,12 @@ struct QrRecArgs {
 struct QrRecGroup {
     QrRecArgs d[2];
     int n;
+    int members = 0, ug0 = 0, n_ug = 0;   // filled in by the launcher: workgroups per group, utterance groups of this launch
 };
 QR_HIDDEN bool qr_rec_supported(int H, int B);
+QR_HIDDEN bool qr_rec_projects(int I);   // whether the recurrence can take input codes of I columns instead of their projection
 QR_HIDDEN size_t qr_rec_xbuf_bytes(int H, int B);
+QR_HIDDEN size_t qr_rec_xcc_bytes(int H, int B);
 QR_HIDDEN bool qr_launch_recurrence(const QrRecGroup &g, hipStream_t st);
 
 QR_HIDDEN void qr_fill_lstm_weights(QrStepArgs &a, const qrnnt_lstm *L);

@@ -711,6 +711,17 @@ __global__ void fill_zero_kernel(uint32_t *p, size_t n_words)
     if (i < n_words) p[i] = 0u;
 }
 
+// Exchange area, workgroup table and error flag of a layer's recurrence, both directions in one launch.
+struct ClearArgs {
+    uint32_t *p[2];
+    size_t n;
+};
+__global__ void clear_kernel(const ClearArgs a)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < a.n) a.p[blockIdx.y][i] = 0u;
+}
+
 }  // namespace
 
 qrnnt_status qr_check_lstm(const qrnnt_lstm *L)
@@ -963,30 +974,42 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
     QR_REQUIRE(!any8 || persist, QRNNT_ERR_UNSUPPORTED);   // 8-bit layers run in the persistent recurrence only
     QrRecGroup rg;
     rg.n = n;
+    ClearArgs clear = {};
     for (int d = 0; d < n; ++d) {
         const LayerCall &c = calls[d];
         const qrnnt_lstm *L = c.L;
         const LayerWs w = layer_ws(L, T, B);
         int32_t *gx = (int32_t *)c.ws;
-        qr_launch_input_projection(L, x_codes, T * B, gx, c.dbg_accx, st);
+        const bool fused = persist && qr_rec_projects(L->input_size);
+        if (!fused || c.dbg_accx) qr_launch_input_projection(L, x_codes, T * B, gx, c.dbg_accx, st);
         if (persist) {
             char *xb = c.ws + w.gx_b + 2 * w.h_b + 2 * w.c_b;
-            const size_t nw = (w.x_b + 256) / 4;
-            fill_zero_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)xb, nw);
+            // the table of where the workgroups run takes the end of the (here unused) cell-state buffers in front
+            char *xcc = xb - qr_round_up((int)qr_rec_xcc_bytes(H, B), 16);
+            clear.p[d] = (uint32_t *)xcc;
+            clear.n = (size_t)(xb - xcc + w.x_b + 256) / 4;   // (the same for both directions)
             QrRecArgs &a = rg.d[d];
             a = QrRecArgs{};
             a.whh = (const v4i *)L->w_hh.packed;  a.s_wih = L->w_ih.row_scale;  a.s_whh = L->w_hh.row_scale;
-            a.bias = L->bias;  a.gx = gx;  a.h0 = c.h0;  a.c0 = c.c0;
+            a.bias = L->bias;  a.gx = fused ? nullptr : gx;  a.h0 = c.h0;  a.c0 = c.c0;
+            a.wih = (const v4i *)L->w_ih.packed;  a.x = x_codes;  a.ld_x = qr_act_pitch(L->input_size);
+            a.I = L->input_size;  a.nkc_x = qr_round_up(L->input_size, QRNNT_KCHUNK) / QRNNT_KCHUNK;
             a.h_out = h_out;  a.ld_out = ld_out;  a.col_off = c.col_off;
             a.h_last = c.h_last;  a.c_last = c.c_last;  a.dbg_c_all = c.dbg_c_all;
-            a.xbuf = (unsigned long long *)xb;  a.err = (int *)(xb + w.x_b);
+            a.xbuf = xb;  a.xcc = (int *)xcc;  a.err = (int *)(xb + w.x_b);
             a.T = T;  a.B = B;  a.H = H;  a.nkc_h = qr_round_up(H, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-            a.reverse = c.reverse;  a.spin_limit = 1 << 18;
+            a.reverse = c.reverse;  a.spin_limit = 1 << 20;
             a.x_scale = L->x_scale;  a.h_scale = L->h_scale;  a.h_inv = L->h_inv_scale;
             a.w8 = qr_bits(&L->w_hh) == 8;
         }
     }
-    if (persist && qr_launch_recurrence(rg, st)) return qr_launch_status();
+    if (persist) clear_kernel<<<dim3((unsigned)((clear.n + 255) / 256), n), 256, 0, st>>>(clear);
+    if (persist && n == 2 && rg.d[0].w8 != rg.d[1].w8) {   // a launch has one width: direction by direction
+        QrRecGroup one[2] = {{{rg.d[0]}, 1}, {{rg.d[1]}, 1}};
+        if (qr_launch_recurrence(one[0], st) && qr_launch_recurrence(one[1], st)) return qr_launch_status();
+    } else if (persist && qr_launch_recurrence(rg, st)) {
+        return qr_launch_status();
+    }
     QR_REQUIRE(!any8, QRNNT_ERR_UNSUPPORTED);
     for (int d = 0; d < n; ++d) {
         const LayerCall &c = calls[d];

@@ -2,262 +2,602 @@
 // state is quantized once at the cell output and that code feeds the next step).
 //
 // The recurrence is a chain of T dependent steps, each far too small to fill the
-// GPU, so its cost is the latency of one step, not arithmetic.  Design:
-//   - a workgroup owns 16 cells (64 gate rows = 4 row tiles) x 16 utterances of one
-//     direction for all T steps.  Utterances never interact, so hidden codes are
-//     exchanged only among the H/16 workgroups of the same utterance group;
-//   - the K dimension of W_hh is dealt to the 4 waves in 64-column steps; each wave
-//     keeps its share of the workgroup's weight rows in registers, already unpacked
-//     to int8 MFMA operands, for the whole sequence.  Partial sums meet in LDS and
-//     wave w then finishes row tile w: one cell x one utterance per lane, cell state
-//     in a register;
-//   - the 4-bit codes of h_t travel through a double-buffered exchange area in 8-byte
-//     words {4 codes, step tag}, laid out so that a wave reads each of its K steps
-//     as one contiguous 2 KiB run.  A consumer knows a word is current when its tag
-//     matches: no grid barrier, no atomic and no fence on the critical path (data and
-//     flag arrive in the same store);
+// GPU, so its cost is the latency of one step: exchange of the new hidden codes,
+// contraction, cell.  Design:
+//   - a group is one direction of 16 utterances; groups never exchange anything.  A
+//     workgroup owns 32 cells (128 gate rows) of one group for all T steps;
+//   - the members of a group sit on one XCD, so the codes travel through that XCD's L2
+//     (stores reach it, loads marked sc1 go past the CU's own cache to it) and not through
+//     the memory side of the device.  Workgroup ids are dealt to the XCDs in turn, so the
+//     launch lays group g's members out at ids congruent to g mod 8; nothing relies on it:
+//     at the start every workgroup publishes the XCD it runs on, and a group that finds
+//     itself spread over several exchanges at system scope instead (same words, sc0 sc1);
+//   - the code of a cell travels in one byte of a 4-bit layer: code in the high nibble, step
+//     number mod 16 in the low one (8-bit layer: two bytes).  Every byte says by itself
+//     whether it is current, so data and flag arrive in the same store whatever its width,
+//     without fence, atomic or grid barrier, and the bytes are the MFMA operand as they are:
+//     code and weight both sit in the high nibble (sums come out x 256), and what the step
+//     number adds is known beforehand (number x sum of the row's weights), so the accumulators
+//     start at minus that;
+//   - four waves carry the recurrence.  They split K in two and the rows in two: a wave holds
+//     4 row tiles x half of K of W_hh in registers, hands two row tiles' partial sums to its K
+//     partner through LDS (one barrier per step, double-buffered) and finishes the cells of the
+//     other two: two adjacent cells x one utterance per lane, cell state in registers;
+//   - four more waves, one beside each of them on its SIMD, bring the input part of the next
+//     step: they hold W_ih the same way and contract the next frame's codes while the others
+//     wait for the exchange (the matrix unit is idle most of a step), so a layer needs no
+//     projection pass and no array of sums.  Layers with more input columns than the registers
+//     hold get the sums from memory (qrnnt_input_projection), fetched by the same waves one step
+//     ahead.  Either way the recurrence waves load nothing but the exchanged codes: a wave's
+//     memory counter is in order, and a load from HBM in front of a poll holds the poll up;
 //   - both directions of a bidirectional layer run in the same launch.
-// All workgroups must be co-resident (checked against the occupancy of the device
-// before the launch); a wait is bounded by spin_limit polls, after which the error
-// flag is set and the workgroup leaves the loop, so the grid always drains.
+// All workgroups must be co-resident (checked against the occupancy of the device before
+// the launch; more utterances than fit go in several launches); a wait is bounded by
+// spin_limit polls, after which the error flag is set and the workgroup leaves the loop, so
+// the grid always drains.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "kernels.h"
+#include "mma_pipe.h"
 
 namespace {
 
-typedef unsigned long long u64;
+constexpr int N_XCD = 8;
 
-// Two exchange words per 128-bit load, bypassing the non-coherent cache levels.
-// p[k] is the lane's address for its k-th K step.
-template <int KW>
-__device__ __forceinline__ void ll_load_frags(const v4i *const (&p)[KW], v4i (&lo)[KW], v4i (&hi)[KW])
+// NL 128-bit loads from base + off[i].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every cache that is
+// not coherent.  What a lane finds says by itself whether it is current, so the time between the loads and the wait for
+// them (wait_words, which every use of v[] follows) can be used.
+#define QR_LD(i, F) "global_load_dwordx4 %[v" #i "], %[o" #i "], %[b] " F "\n\t"
+#define QR_O(i) [v##i] "=&v"(v[i])
+#define QR_W(i) "+v"(v[i])
+#define QR_I(i) [o##i] "v"(off[i])
+#define QR_2(M) M(0), M(1)
+#define QR_4(M) QR_2(M), M(2), M(3)
+#define QR_5(M) QR_4(M), M(4)
+#define QR_8(M) QR_5(M), M(5), M(6), M(7)
+#define QR_10(M) QR_8(M), M(8), M(9)
+#define QR_16(M) QR_10(M), M(10), M(11), M(12), M(13), M(14), M(15)
+#define QR_LDS2(F) QR_LD(0, F) QR_LD(1, F)
+#define QR_LDS4(F) QR_LDS2(F) QR_LD(2, F) QR_LD(3, F)
+#define QR_LDS5(F) QR_LDS4(F) QR_LD(4, F)
+#define QR_LDS8(F) QR_LDS5(F) QR_LD(5, F) QR_LD(6, F) QR_LD(7, F)
+#define QR_LDS10(F) QR_LDS8(F) QR_LD(8, F) QR_LD(9, F)
+#define QR_LDS16(F) QR_LDS10(F) QR_LD(10, F) QR_LD(11, F) QR_LD(12, F) QR_LD(13, F) QR_LD(14, F) QR_LD(15, F)
+#define QR_EACH_N QR_N(2) QR_N(4) QR_N(5) QR_N(8) QR_N(10) QR_N(16)
+
+template <int NL, bool LOCAL>
+__device__ __forceinline__ void load_words(const char *base, const unsigned (&off)[NL], v4i (&v)[NL])
 {
-#pragma unroll
-    for (int k = 0; k < KW; ++k) {
-        asm volatile("global_load_dwordx4 %0, %2, off sc0 sc1\n\t"
-                     "global_load_dwordx4 %1, %2, off offset:16 sc0 sc1"
-                     : "=&v"(lo[k]), "=&v"(hi[k])
-                     : "v"(p[k])
-                     : "memory");
+#define QR_N(n)                                                                                                      \
+    if constexpr (NL == n) {                                                                                         \
+        if constexpr (LOCAL) asm volatile(QR_LDS##n("sc1") : QR_##n(QR_O) : QR_##n(QR_I), [b] "s"(base) : "memory"); \
+        else asm volatile(QR_LDS##n("sc0 sc1") : QR_##n(QR_O) : QR_##n(QR_I), [b] "s"(base) : "memory");             \
     }
-    // every output is an operand of the wait, so no consumer can be scheduled before it
-    if constexpr (KW == 1) asm volatile("s_waitcnt vmcnt(0)" : "+v"(lo[0]), "+v"(hi[0])::"memory");
-    if constexpr (KW == 2)
-        asm volatile("s_waitcnt vmcnt(0)" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1])::"memory");
-    if constexpr (KW == 3)
-        asm volatile("s_waitcnt vmcnt(0)"
-                     : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]), "+v"(lo[2]), "+v"(hi[2])::"memory");
-    if constexpr (KW == 4)
-        asm volatile("s_waitcnt vmcnt(0)"
-                     : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]), "+v"(lo[2]), "+v"(hi[2]), "+v"(lo[3]),
-                       "+v"(hi[3])::"memory");
+    QR_EACH_N
+#undef QR_N
 }
 
-__device__ __forceinline__ void ll_store(u64 *p, u64 v)
+template <int NL>
+__device__ __forceinline__ void wait_words(v4i (&v)[NL])
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#define QR_N(n) if constexpr (NL == n) asm volatile("s_waitcnt vmcnt(0)" : QR_##n(QR_W)::"memory");
+    QR_EACH_N
+#undef QR_N
 }
 
-// Exchange layout: [parity][utterance group][K step][lane = 16*grp + col][4 words];
-// word q of lane (grp, col) of K step ks holds cells 64*ks + 16*grp + 4*q .. +3 of
-// utterance 16*ug + col.
-// KW: K steps per wave (H <= 256*KW).
-// CT: 16-cell groups per workgroup (1 or 2).  A workgroup of CT = 2 owns 32 cells (8 row tiles, two per wave in the
-// epilogue) and so halves the number of workgroups of a launch: used when CT = 1 would ask for more workgroups than
-// the device has compute units (two workgroups sharing a CU take turns, and every step then waits for the slower
-// ones), e.g. 64 utterances x 640 cells x 2 directions = 320 workgroups on 256 CUs.  H must be a multiple of 16*CT.
-template <int KW, int CT>
-__global__ __launch_bounds__(256) void lstm_rec_kernel(const QrRecGroup g)
+// Stores with the lanes outside `mask` left out, in one block instead of under a branch: the instructions around it stay
+// one stretch for the scheduler.
+#define QR_MASKED_ST(op, addr, F, ...)                                                                                   \
+    asm volatile("s_mov_b64 %[keep], exec\n\ts_mov_b64 exec, %[mask]\n\tglobal_store_" op " %[o], %[v], " addr " " F    \
+                 "\n\ts_mov_b64 exec, %[keep]" : [keep] "=&s"(keep) : [v] "v"(v), [mask] "s"(mask), __VA_ARGS__ : "memory")
+
+// A lane's new codes for its group's members: NB bytes at base + off.
+template <int NB>
+__device__ __forceinline__ void store_codes(char *base, unsigned off, unsigned v, unsigned long long mask, bool local)
 {
-    constexpr int RT = 4 * CT;             // row tiles (of 4 cells x 4 gates) per workgroup
-    __shared__ v4i part[4][RT][64];    // [wave][row tile][lane] partial sums
-    __shared__ __attribute__((aligned(16))) int8_t hc[16][16 * CT]; // [utterance][cell] codes of this step (read back as 32-bit words)
-    __shared__ int s_fail;
-    const QrRecArgs &a = g.d[blockIdx.z];
+    unsigned long long keep;
+#define QR_ST(op)                                                              \
+    if (local) QR_MASKED_ST(op, "%[b]", "", [o] "v"(off), [b] "s"(base));      \
+    else QR_MASKED_ST(op, "%[b]", "sc0 sc1", [o] "v"(off), [b] "s"(base));
+    if constexpr (NB == 1) { QR_ST("byte") }
+    if constexpr (NB == 2) { QR_ST("short") }
+    if constexpr (NB == 4) { QR_ST("dword") }
+#undef QR_ST
+}
+
+// A lane's codes to the layer's output.
+template <int NB>
+__device__ __forceinline__ void store_out(int8_t *p, unsigned v, unsigned long long mask)
+{
+    unsigned long long keep;
+    if constexpr (NB == 1) QR_MASKED_ST("byte", "off", "", [o] "v"(p));
+    else QR_MASKED_ST("short", "off", "", [o] "v"(p));
+}
+
+// a | (b ^ c)
+__device__ __forceinline__ unsigned or_xor(unsigned a, unsigned b, unsigned c)
+{
+    unsigned r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xf6" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
+// Workgroup barrier that orders LDS accesses only: no wait for the memory operations in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Lanes of the upper utterance half take b from the lane 8 columns below, the others keep a.
+__device__ __forceinline__ v4i upper_from(v4i a, v4i b)
+{
+    v4i r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_update_dpp(a[i], b[i], 0x128 /* row_ror:8 */, 0xf, 0xc, false);
+    return r;
+}
+
+// Exchange area of a direction: [parity][utterance group][16-cell group][utterance][16 cells], one byte per cell (two
+// in an 8-bit layer): a lane's MFMA operand for a K step (16 cells of one utterance) is contiguous.  A layer of B < 16
+// utterances keeps its columns closer together (the next power of two): lanes of absent utterances read what a present
+// one reads, and a poll touches that many fewer cache lines.
+// KH: K steps (64 cells) of h per wave, H <= 128 * KH.  KX: K steps of the input per wave, I <= 128 * KX; 0: sums from memory.
+// CELLS: cells per lane in the cell update: 2, or 1 if there are at most 8 utterances: the lanes of the absent upper
+// eight then take the second cell of the lower eight.
+// C_FIRST: which product of c' = f*c + i*g is rounded before the sum (see qr_launch_recurrence).
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+__global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
+{
+    constexpr int PER = W8 ? 2 : 1;    // bytes per exchanged cell
+    constexpr int NL = KH * PER;       // 128-bit loads per wave and poll
+    __shared__ v4i part[2][4][CELLS][64];   // [parity][wave][row tile][lane] partial sums on their way to the K partner
+    __shared__ v4i px[2][2][2][4][64];      // [parity][K half][cell group][row tile][lane] sums of the input part
+    __shared__ __attribute__((aligned(1024))) v4i xs[KX > 0 ? 3 * 2 * KX : 1][64];   // three frames of input codes, blocks of 8 utterances x 128 columns
+    __shared__ int s_fail[2], s_local;
+    // group and member from the workgroup id: ids congruent mod 8 share an XCD
+    const int id = (int)blockIdx.x;
+    const int gi = (id / N_XCD / g.members) * N_XCD + id % N_XCD, mem = (id / N_XCD) % g.members;
+    if (gi >= g.n * g.n_ug) return;   // uniform
+    const QrRecArgs a = g.d[gi % g.n];   // a copy: a few wide scalar loads
+    const int ug = g.ug0 + gi / g.n;
     const int H = a.H, B = a.B, T = a.T;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave8 & 3;                 // 0..3 of either kind
     const int col = lane & 15, grp = lane >> 4;
-    const int cg = blockIdx.x, ug = blockIdx.y;
-    const int nks = (H + 63) >> 6;              // K steps in total (the layout pads to whole steps)
+    const int kh = wave & 1, rh = wave >> 1;
+    const int n_groups = H >> 4;                // 16-cell groups of the layer
+    const int cg = 2 * mem + rh;                // this wave's
+    const bool have = cg < n_groups;            // (an odd number of groups leaves half of the last workgroup without cells)
+    const int cgc = have ? cg : 0;
+    const int64_t dir = a.reverse ? -1 : 1, t0 = a.reverse ? T - 1 : 0;
     const v4i zero = {0, 0, 0, 0};
     const int m = (int)0xF0F0F0F0u;
+    // K step ks of row tile rt as an MFMA operand
+    auto weight = [&](const v4i *w, int nkc, int rt, int ks) -> v4i {
+        if (W8) return w[(((size_t)rt * nkc + (ks >> 1)) * 2 + (ks & 1)) * 64 + lane];   // as stored, two blocks per 128-column chunk
+        const v4i p = w[((size_t)rt * nkc + (ks >> 1)) * 64 + lane];
+        return (ks & 1) ? (p & m) : ((p << 4) & m);
+    };
 
-    // ---- stationary operands: this wave's K steps of the workgroup's row tiles
-    v4i A[RT][KW];
+    if (tid == 0) s_fail[0] = s_fail[1] = 0;
+    __syncthreads();   // (before a table wait below can set one of them)
+
+    if (wave8 >= 4) {
+        // ================= input part: K half kh of cell group rh, one step ahead of the recurrence
+        const int n = ug * 16 + col, nn = n < B ? n : B - 1;
+        if constexpr (KX > 0) {
+            // A frame's codes go global -> LDS directly, 8 utterances x 128 columns to an instruction: whole cache lines
+            // (as MFMA operands straight from memory they would be 16 half lines to an instruction, and the other waves'
+            // polls would queue behind them), 16-byte pieces swizzled by row.  Three frames are on their way or in use.
+            constexpr int CH = KX;                       // 128-column chunks
+            constexpr int LOADS = (2 * CH + 3) / 4;      // per wave and frame
+            v4i Ax[4][KX > 0 ? KX : 1];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+            for (int k = 0; k < KX; ++k) {
+                const int ks = kh + 2 * k;
 #pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const int ks = wave + 4 * k;
-            A[rt][k] = zero;
-            if (ks < nks) {
-                if (a.w8) {   // 8-bit layer: the operand as stored, two blocks per 128-column chunk
-                    A[rt][k] = a.whh[(((size_t)(cg * RT + rt) * a.nkc_h + (ks >> 1)) * 2 + (ks & 1)) * 64 + lane];
-                } else {
-                    const v4i p = a.whh[((size_t)(cg * RT + rt) * a.nkc_h + (ks >> 1)) * 64 + lane];
-                    A[rt][k] = (ks & 1) ? (p & m) : ((p << 4) & m);
+                for (int i = 0; i < 4; ++i) Ax[i][k] = (have && ks < 2 * a.nkc_x) ? weight(a.wih, a.nkc_x, cg * 4 + i, ks) : zero;
+            }
+            const unsigned lds0 = (unsigned)(size_t)&xs[0][0];
+            const int8_t *src[LOADS];
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q) {
+                int blk = wave + 4 * q;                  // (chunk, utterance half); the last few repeat the last block
+                blk = blk < 2 * CH ? blk : 2 * CH - 1;
+                int nr = ug * 16 + (blk & 1) * 8 + (lane >> 3);
+                nr = nr < B ? nr : B - 1;
+                const int o = (blk >> 1) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
+                src[q] = a.x + (t0 * B + nr) * a.ld_x + (o < a.ld_x ? o : 0);   // beyond the row: any valid bytes, they meet zero weights
+            }
+            const int64_t x_step = dir * B * a.ld_x;
+            auto fetch = [&](int buf, bool advance) {
+#pragma unroll
+                for (int q = 0; q < LOADS; ++q) {
+                    int blk = wave + 4 * q;
+                    blk = blk < 2 * CH ? blk : 2 * CH - 1;
+                    qr_load_lds16(src[q], lds0 + (unsigned)(buf * 2 * CH + blk) * 1024);
+                    src[q] += advance ? x_step : 0;
                 }
+            };
+            const int at = (col >> 3) * 64 + (col & 7) * 8;   // this lane's row within a chunk's two blocks, in 16-byte pieces
+            auto produce = [&](int buf, int par) {
+                v4i acc[4] = {zero, zero, zero, zero};
+#pragma unroll
+                for (int k = 0; k < KX; ++k) {
+                    const v4i b = xs[buf * 2 * CH + 2 * k][at + ((4 * kh + grp) ^ (col & 7))];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = qr_mfma(Ax[i][k], b, acc[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) px[par][kh][rh][i][lane] = acc[i];
+            };
+            fetch(0, T > 1);
+            fetch(1, T > 2);
+            fetch(2, T > 3);
+            qr_wait_vmcnt<0>();
+            lds_barrier();
+            produce(0, 0);
+            lds_barrier();
+            int b1 = 1, b3 = 0;                          // buffers of frames s + 1 and s + 3
+            for (int s = 0; s < T; ++s) {
+                fetch(b3, s + 4 < T);                    // (frames behind the last one: the last one again)
+                if (s + 1 < T) produce(b1, (s + 1) & 1);
+                qr_wait_vmcnt<LOADS>();                  // all but the newest fetch: frame s + 2 is there
+                lds_barrier();
+                if (__builtin_amdgcn_readfirstlane(s_fail[s & 1])) break;
+                b1 = b1 == 2 ? 0 : b1 + 1;
+                b3 = b3 == 2 ? 0 : b3 + 1;
+            }
+            qr_wait_vmcnt<0>();
+        } else {
+            // two of the group's four row tiles; the other K half's slot stays zero
+            const int32_t *gq = a.gx + (t0 * B + nn) * 4 * H + (cgc * 4 + 2 * kh) * 16 + 4 * grp;
+            const int64_t gx_step = dir * B * 4 * H;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) px[0][1][rh][2 * kh + i][lane] = px[1][1][rh][2 * kh + i][lane] = zero;
+            v4i v0 = *(const v4i *)gq, v1 = *(const v4i *)(gq + 16);
+            auto produce = [&](int par, bool more) {
+                px[par][0][rh][2 * kh][lane] = v0;
+                px[par][0][rh][2 * kh + 1][lane] = v1;
+                gq += more ? gx_step : 0;
+                v0 = *(const v4i *)gq;
+                v1 = *(const v4i *)(gq + 16);
+            };
+            lds_barrier();
+            produce(0, T > 1);
+            lds_barrier();
+            for (int s = 0; s < T; ++s) {
+                if (s + 1 < T) produce((s + 1) & 1, s + 2 < T);
+                lds_barrier();
+                if (__builtin_amdgcn_readfirstlane(s_fail[s & 1])) break;
             }
         }
-    // ---- the cells this lane finishes: row tiles 4*c + wave (c < CT), cell j[c], utterance n
-    const int n = ug * 16 + col;
-    const int nn = n < B ? n : B - 1;
-    int j[CT];
-    float sx[CT][4], sh[CT][4], bb[CT][4], c[CT];
+        return;
+    }
+
+    // ================= recurrence
+    // ---- where this group runs: every member publishes its XCD, all members see the same answers
+    if (wave == 0) {
+        int *tab = a.xcc + (size_t)ug * g.members;
+        int xcc;
+        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
+        if (lane == 0) __hip_atomic_store(tab + mem, 0x100 | xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        const int *p = tab + (lane < g.members ? lane : 0);
+        int v = 0, spins = 0;
+        bool timed_out = false;
+        while (true) {
+            v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (__all(v != 0)) break;
+            if (++spins > a.spin_limit) { timed_out = true; break; }
+        }
+        const bool same = __all(v == __builtin_amdgcn_readfirstlane(v));
+        if (lane == 0) {
+            s_local = same ? 1 : 0;
+            if (timed_out) { atomicExch(a.err, 1); s_fail[0] = 1; }
+        }
+    }
+
+    // ---- stationary operands: this wave's K steps (kh, kh + 2, ...) of its four row tiles; tiles 0 and 1 are the ones
+    // whose cells it finishes (row tiles 2*kh, 2*kh + 1 of the cell group), tiles 2 and 3 its K partner's
+    const int nks = (H + 63) >> 6;              // K steps in total (the blob pads to whole steps)
+    v4i A[4][KH];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-        j[ct] = qr_gates_cell(cg * RT + 4 * ct + wave, grp);   // = 16*(CT*cg + ct) + 4*grp + wave
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            const int ks = kh + 2 * k, rt = cg * 4 + (i < 2 ? 2 * kh + i : 2 * (1 - kh) + i - 2);
+            A[i][k] = (have && ks < nks) ? weight(a.whh, a.nkc_h, rt, ks) : zero;   // absent: contributes nothing, whatever it reads
+        }
+    // 4-bit: minus the row sums of the weights (x 16), which a step number in the low nibbles multiplies
+    v4i nrsum[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        nrsum[i] = zero;
+        const v4i minus_ones = {-1, -1, -1, -1};
+        if (!W8)
+#pragma unroll
+            for (int k = 0; k < KH; ++k) nrsum[i] = qr_mfma(A[i][k], minus_ones, nrsum[i]);
+    }
+    // ---- the cells this lane finishes: j0 .. j0 + CELLS - 1 of utterance n
+    const int my_col = CELLS == 1 ? col & 7 : col;
+    const int n = ug * 16 + my_col;
+    const int nn = n < B ? n : B - 1;
+    const int sub = CELLS == 1 ? col >> 3 : 0;
+    const int j0 = 16 * cgc + 4 * grp + 2 * kh + sub;
+    // exact powers of two undo what the 4-bit operands carry: 16 (x as it is) and 256
+    constexpr float X_UNIT = (W8 || KX == 0) ? 1.0f : 0.0625f, H_UNIT = W8 ? 1.0f : 0.00390625f;
+    float sx[CELLS][4], sh[CELLS][4], bb[CELLS][4], c[CELLS];
+#pragma unroll
+    for (int ct = 0; ct < CELLS; ++ct) {
 #pragma unroll
         for (int gt = 0; gt < 4; ++gt) {
-            sx[ct][gt] = a.x_scale * a.s_wih[gt * H + j[ct]];
-            sh[ct][gt] = a.h_scale * a.s_whh[gt * H + j[ct]];
-            bb[ct][gt] = a.bias[gt * H + j[ct]];
+            sx[ct][gt] = a.x_scale * a.s_wih[gt * H + j0 + ct] * X_UNIT;
+            sh[ct][gt] = a.h_scale * a.s_whh[gt * H + j0 + ct] * H_UNIT;
+            bb[ct][gt] = a.bias[gt * H + j0 + ct];
         }
-        c[ct] = a.c0 ? a.c0[(int64_t)nn * H + j[ct]] : 0.0f;
+        c[ct] = a.c0 ? a.c0[(int64_t)nn * H + j0 + ct] : 0.0f;
     }
-    if (tid == 0) s_fail = 0;
-    __syncthreads();
+    // ---- exchange addresses
+    int ncol = 16;                              // columns kept per 16-cell group
+    if (CELLS == 1)
+        for (ncol = 8; ncol >= 2 * B; ncol >>= 1) {}
+    const size_t ug_bytes = (size_t)n_groups * 256 * PER;
+    char *const xb0 = a.xbuf + (size_t)ug * ug_bytes;   // this group's area, even steps
+    char *const xb1 = xb0 + (size_t)((B + 15) >> 4) * ug_bytes;   // odd steps
+    unsigned off[NL];
+#pragma unroll
+    for (int k = 0; k < KH; ++k) {
+        int q = 4 * (kh + 2 * k) + grp;         // 16-cell group of this lane's operand; beyond the layer: any valid one (it meets zero weights)
+        q = q < n_groups ? q : 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) off[k * PER + u] = (unsigned)((q * ncol + (col & (ncol - 1))) * 16 * PER + 16 * u);
+    }
+    const unsigned st_off = (unsigned)(((cgc * ncol + (my_col & (ncol - 1))) * 16 + 4 * grp + 2 * kh + sub) * PER);
+    const unsigned long long pub_mask = __ballot(have && my_col < ncol);
+    const bool store_ok = have && n < B;
+    const unsigned long long out_mask = __ballot(store_ok);
+    // where this lane's sums of the input part lie in px[parity][K half]
+    const int px_at = (rh * 4 + 2 * kh + sub) * 64 + grp * 16 + my_col;
 
-    const size_t xgroup = (size_t)nks * 64 * 4;                    // words per (parity, utterance group)
-    const size_t xparity = (size_t)((B + 15) >> 4) * xgroup;
-    for (int s = 0; s < T; ++s) {
-        const int t = a.reverse ? T - 1 - s : s;
-        v4i gxv[CT];   // independent of h: first
+    // ---- running pointers: output row of the step before, debug output
+    int8_t *hq = a.h_out + (t0 * B + nn) * a.ld_out + a.col_off + j0;
+    const int64_t h_step = dir * B * a.ld_out;
+    const bool dbg = a.dbg_c_all != nullptr;
+    float *dq = dbg ? a.dbg_c_all + (t0 * B + nn) * H + j0 : nullptr;
+
+    lds_barrier();
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(3);              // these waves are the chain, the input waves fill its gaps
+    const bool local = s_local != 0;            // uniform over the group
+    unsigned codes = 0;                         // the codes of the step before, one per byte
+    v4i acc[4];
+    float gx[CELLS][4];                         // this step's sums of the input part
+    // What a step can do while its operands are on their way: its sums of the input part, and the start of its
+    // accumulators, minus what the step number in the operands adds.  (The empty blocks keep the compiler from moving
+    // this in front of the loads or behind the wait for them.)
+    auto prepare = [&](int s) {
+        int tag = s & 15;
+        asm volatile("" : "+s"(tag));
+        const v4i *p0 = &px[__builtin_amdgcn_readfirstlane(s & 1)][0][0][0][0] + px_at, *p1 = p0 + 2 * 4 * 64;
+        v4i x0[CELLS], x1[CELLS];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-            gxv[ct] = *(const v4i *)(a.gx + ((int64_t)t * B + nn) * 4 * H + (cg * RT + 4 * ct + wave) * 16 + 4 * grp);
-        v4i acc[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc[rt] = zero;
-        bool failed = false;
-        if (s > 0 || a.h0) {
-            v4i bf[KW];
-            if (s == 0) {
-                const int8_t *hr = a.h0 + (int64_t)nn * H + grp * 16;
-#pragma unroll
-                for (int k = 0; k < KW; ++k) {
-                    const int ks = wave + 4 * k;
-                    bf[k] = (ks * 64 + grp * 16 < H) ? *(const v4i *)(hr + ks * 64) : zero;
-                }
-            } else {
-                // words written at step s-1 carry tag s; this wave's K steps are 4 steps (= 4*64*2 v4i) apart
-                const u64 *xw = a.xbuf + (size_t)((s - 1) & 1) * xparity + (size_t)ug * xgroup;
-                const v4i *src[KW];
-#pragma unroll
-                for (int k = 0; k < KW; ++k) {
-                    const int ks = wave + 4 * k < nks ? wave + 4 * k : 0;   // absent steps re-read step 0 (ignored)
-                    src[k] = (const v4i *)(xw + ((size_t)ks * 64 + lane) * 4);
-                }
-                const int want = s;
-                int spins = 0;
-                while (true) {
-                    v4i lo[KW], hi[KW];
-                    ll_load_frags<KW>(src, lo, hi);
-                    bool ok = true;
-#pragma unroll
-                    for (int k = 0; k < KW; ++k) {
-                        const int ks = wave + 4 * k;
-                        if (ks < nks) {
-                            const bool in = ks * 64 + grp * 16 < H;
-                            ok = ok && (!in || (lo[k][1] == want && lo[k][3] == want && hi[k][1] == want && hi[k][3] == want));
-                            bf[k] = in ? v4i{lo[k][0], lo[k][2], hi[k][0], hi[k][2]} : zero;
-                        } else {
-                            bf[k] = zero;
-                        }
-                    }
-                    if (__all(ok)) break;
-                    if (++spins > a.spin_limit) { failed = true; break; }
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < KW; ++k)
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) acc[rt] = qr_mfma(A[rt][k], bf[k], acc[rt]);
-        }
-        if (failed && lane == 0) {
-            atomicExch(a.err, 1);
-            s_fail = 1;
+        for (int ct = 0; ct < CELLS; ++ct) {
+            x0[ct] = p0[64 * ct];
+            x1[ct] = p1[64 * ct];
         }
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) part[wave][rt][lane] = acc[rt];
-        __syncthreads();
-        const int fail_now = s_fail;   // written only before this barrier, read only after it: uniform
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const int rt = 4 * ct + wave;
-            const v4i asum = part[0][rt][lane] + part[1][rt][lane] + part[2][rt][lane] + part[3][rt][lane];
-            const v4i ah = a.w8 ? asum : (asum >> 4);   // 4-bit operands carry a factor 16
+            for (int gt = 0; gt < 4; ++gt) acc[i][gt] = W8 ? 0 : __mul24(nrsum[i][gt], tag);
+#pragma unroll
+        for (int ct = 0; ct < CELLS; ++ct) {
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) gx[ct][gt] = (float)(x0[ct][gt] + x1[ct][gt]);
+            asm volatile("" : "+v"(gx[ct][0]), "+v"(gx[ct][1]), "+v"(gx[ct][2]), "+v"(gx[ct][3]));
+        }
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+    };
+    // The K partner's tiles of a step, from its operands; their way through LDS then runs under the own tiles' contraction.
+    auto partner_tiles = [&](const v4i (&bf)[KH]) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            acc[2] = qr_mfma(A[2][k], bf[k], acc[2]);
+            acc[3] = qr_mfma(A[3][k], bf[k], acc[3]);
+        }
+    };
+    // The rest of the step; true: a wait ran out somewhere in the workgroup, leave.
+    auto step = [&](const v4i (&bf)[KH], int s) -> bool {
+        const int par = __builtin_amdgcn_readfirstlane(s & 1);
+        constexpr int K0 = KH < 2 ? KH : 2;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K0; ++k) {
+            acc[0] = qr_mfma(A[0][k], bf[k], acc[0]);
+            acc[1] = qr_mfma(A[1][k], bf[k], acc[1]);
+        }
+        if (CELLS == 1) {
+            part[par][wave][0][lane] = upper_from(acc[2], acc[3]);
+        } else {
+            part[par][wave][0][lane] = acc[2];
+            part[par][wave][CELLS - 1][lane] = acc[3];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = K0; k < KH; ++k) {
+            acc[0] = qr_mfma(A[0][k], bf[k], acc[0]);
+            acc[1] = qr_mfma(A[1][k], bf[k], acc[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        store_out<CELLS>(hq, codes, s > 0 ? out_mask : 0ull);   // the codes of the step before: here they hold nothing up
+        hq += s > 0 ? h_step : 0;
+        lds_barrier();
+        int fail_now = s_fail[par];   // a slot is written before its step's barrier only, and again two steps later: uniform
+        v4i asum[CELLS];
+#pragma unroll
+        for (int ct = 0; ct < CELLS; ++ct)
+            asum[ct] = (CELLS == 1 ? upper_from(acc[0], acc[1]) : acc[ct]) + part[par][wave ^ 1][ct][lane];
+        asm volatile("" : "+v"(fail_now), "+v"(asum[0]));       // (both reads now, not one of them in front of the next poll)
+        codes = 0u;
+        unsigned word = W8 ? (unsigned)((s + 1) & 0xFF) * 0x01000100u : (unsigned)((s + 1) & 15) * 0x0101u;
+#pragma unroll
+        for (int ct = 0; ct < CELLS; ++ct) {
             float p[4];
 #pragma unroll
-            for (int gt = 0; gt < 4; ++gt) p[gt] = sx[ct][gt] * (float)gxv[ct][gt] + (sh[ct][gt] * (float)ah[gt] + bb[ct][gt]);
-            const float gi = qr_sigmoid(p[0]), gf = qr_sigmoid(p[1]), gg = qr_tanh(p[2]), go = qr_sigmoid(p[3]);
-            c[ct] = gf * c[ct] + gi * gg;
+            for (int gt = 0; gt < 4; ++gt) p[gt] = sx[ct][gt] * gx[ct][gt] + (sh[ct][gt] * (float)asum[ct][gt] + bb[ct][gt]);
+            const float gi_ = qr_sigmoid(p[0]), gf = qr_sigmoid(p[1]), gg = qr_tanh(p[2]), go = qr_sigmoid(p[3]);
+            c[ct] = C_FIRST ? __builtin_fmaf(gi_, gg, gf * c[ct]) : __builtin_fmaf(gf, c[ct], gi_ * gg);
             const float h = go * qr_tanh(c[ct]);
-            hc[col][16 * ct + grp * 4 + wave] = (int8_t)qr_quant(h, a.h_inv, a.w8 ? 8 : 4);
-            if (a.dbg_c_all && n < B) a.dbg_c_all[((int64_t)t * B + n) * H + j[ct]] = c[ct];
+            const unsigned code = (unsigned)qr_quant(h, a.h_inv, W8 ? 8 : 4);
+            codes |= (code & 0xFFu) << (8 * ct);
+            word |= W8 ? (code & 0xFFu) << (16 * ct) : ((code & 15u) << 4) << (8 * ct);
         }
-        __syncthreads();
-        // publish: 16 utterances x 4*CT quads, one 8-byte word each, tagged s+1
-        if (tid < 64 * CT) {
-            const int u = tid & 15, q = tid >> 4;       // quad q of the workgroup's 4*CT: cells 4*q .. 4*q+3 of its 16*CT
-            const int Q = cg * RT + q;                  // quad of the layer
-            const unsigned data = *(const unsigned *)&hc[u][q * 4];
-            u64 *dst = a.xbuf + (size_t)(s & 1) * xparity + (size_t)ug * xgroup +
-                       ((size_t)(Q >> 4) * 64 + ((Q & 15) >> 2) * 16 + u) * 4 + (Q & 3);
-            ll_store(dst, ((u64)(unsigned)(s + 1) << 32) | data);
-            const int nu = ug * 16 + u;
-            if (nu < B) {
-                *(unsigned *)(a.h_out + ((int64_t)t * B + nu) * a.ld_out + a.col_off + 4 * Q) = data;
-                if (s == T - 1 && a.h_last) *(unsigned *)(a.h_last + (int64_t)nu * H + 4 * Q) = data;
-            }
-        }
-        if (fail_now) break;
-    }
+        store_codes<CELLS * PER>(par ? xb1 : xb0, st_off, word, pub_mask, local);
+        if (dbg) {
+            if (store_ok)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-        if (a.c_last && n < B) a.c_last[(int64_t)n * H + j[ct]] = c[ct];
+                for (int ct = 0; ct < CELLS; ++ct) dq[ct] = c[ct];
+            dq += dir * B * H;
+        }
+        return __builtin_amdgcn_readfirstlane(fail_now) != 0;
+    };
+    // All steps but the first: the operands come from the exchange area.
+    auto later_steps = [&](auto local_tag) {
+        constexpr bool LOCAL = decltype(local_tag)::value;
+        for (int s = 1; s < T; ++s) {
+            // words written at step s-1 carry tag s
+            const int par = __builtin_amdgcn_readfirstlane(s & 1);
+            const char *src = par ? xb0 : xb1;
+            const unsigned want = W8 ? (unsigned)(s & 0xFF) * 0x01000100u : (unsigned)(s & 15) * 0x01010101u;
+            v4i bf[KH];
+            for (int spins = 0;; ++spins) {
+                v4i v[NL];
+                load_words<NL, LOCAL>(src, off, v);
+                prepare(s);
+                wait_words<NL>(v);
+                unsigned bad0 = 0u, bad1 = 0u;
+#pragma unroll
+                for (int i = 0; i < NL; ++i)
+#pragma unroll
+                    for (int d = 0; d < 4; d += 2) {
+                        bad0 = or_xor(bad0, (unsigned)v[i][d], want);
+                        bad1 = or_xor(bad1, (unsigned)v[i][d + 1], want);
+                    }
+                const unsigned bad = (bad0 | bad1) & (W8 ? 0xFF00FF00u : 0x0F0F0F0Fu);
+#pragma unroll
+                for (int k = 0; k < KH; ++k) {
+                    if (W8) {
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)   // the code bytes of two words
+                            bf[k][d] = (int)__builtin_amdgcn_perm((unsigned)v[PER * k + (d >> 1) * (PER - 1)][(2 * (d & 1) + 1) & 3],
+                                                                  (unsigned)v[PER * k + (d >> 1) * (PER - 1)][2 * (d & 1)], 0x06040200u);
+                    } else {
+                        bf[k] = v[k];
+                    }
+                }
+                partner_tiles(bf);   // whether the words were current or not: the check runs under these
+                if (__all(bad == 0u)) break;
+                if (spins >= a.spin_limit) {
+                    if (lane == 0) {
+                        atomicExch(a.err, 1);
+                        s_fail[par] = 1;
+                    }
+                    break;
+                }
+            }
+            if (step(bf, s)) break;
+        }
+    };
+    {
+        v4i bf[KH];   // first step: the caller's initial state
+        const int n0 = ug * 16 + col < B ? ug * 16 + col : B - 1;
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            const int k0 = (kh + 2 * k) * 64 + grp * 16;
+            bf[k] = (a.h0 && k0 < H) ? *(const v4i *)(a.h0 + (int64_t)n0 * H + k0) : zero;
+            if (!W8) bf[k] = (bf[k] << 4) & m;
+        }
+        prepare(0);
+        partner_tiles(bf);
+        if (!step(bf, 0)) {
+            if (local) later_steps(std::true_type{}); else later_steps(std::false_type{});
+        }
+    }
+    if (store_ok) {
+#pragma unroll
+        for (int ct = 0; ct < CELLS; ++ct) {
+            const int8_t code = (int8_t)(codes >> (8 * ct));
+            hq[ct] = code;
+            if (a.h_last) a.h_last[(int64_t)n * H + j0 + ct] = code;
+            if (a.c_last) a.c_last[(int64_t)n * H + j0 + ct] = c[ct];
+        }
+    }
 }
 
-template <int KW, int CT>
-bool launch_rec_ct(const QrRecGroup &g, bool only_if_it_fits_the_cus, hipStream_t st)
+// Workgroups of this kernel that an XCD of the current device holds at once; 0: none (or the device does not answer).
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+int per_xcd()
 {
-    const int H = g.d[0].H, B = g.d[0].B;
-    if (H % (16 * CT) != 0) return false;
-    dim3 grid(H / (16 * CT), (B + 15) / 16, g.n);
-    // every workgroup spins on its peers: all of them must fit on the device at once
-    static std::atomic<long long> resident_of[QR_MAX_DEVICES];   // workgroups the device holds at once; 0: not asked yet
-    static std::atomic<int> n_cu_of[QR_MAX_DEVICES];
+    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none
     const int dev = qr_current_device();
-    long long resident = resident_of[dev].load(std::memory_order_relaxed);
-    int n_cu = n_cu_of[dev].load(std::memory_order_relaxed);
-    if (resident == 0) {
-        int per_cu = 0;
-        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lstm_rec_kernel<KW, CT>, 256, 0) != hipSuccess) return false;
-        resident = (long long)per_cu * n_cu;
-        if (resident <= 0 || n_cu <= 0) return false;
-        n_cu_of[dev].store(n_cu, std::memory_order_relaxed);
-        resident_of[dev].store(resident, std::memory_order_relaxed);
+    int v = known[dev].load(std::memory_order_relaxed);
+    if (v == 0) {
+        int n_cu = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST>, 512, 0) != hipSuccess)
+            return 0;
+        v = n_cu / N_XCD * per_cu;
+        known[dev].store(v > 0 ? v : -1, std::memory_order_relaxed);
     }
-    const long long wgs = (long long)grid.x * grid.y * grid.z;
-    if (wgs > resident) return false;
-    if (only_if_it_fits_the_cus && wgs > n_cu) return false;
-    lstm_rec_kernel<KW, CT><<<grid, 256, 0, st>>>(g);
+    return v > 0 ? v : 0;
+}
+
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+bool launch_rec_t(const QrRecGroup &g, hipStream_t st)
+{
+    QrRecGroup gg = g;
+    gg.members = (g.d[0].H + 31) / 32;
+    const int n_ug = (g.d[0].B + 15) / 16;
+    const int q = per_xcd<KH, KX, W8, CELLS, C_FIRST>() / gg.members;   // groups per XCD
+    if (q * N_XCD < g.n) return false;
+    // Every workgroup spins on its group's members, so all groups of a launch must be resident together.  Up to q
+    // groups share an XCD (and its CUs): they then take turns, which is still faster than one launch after the other.
+    const int ug_max = q * N_XCD / g.n;
+    for (int u0 = 0; u0 < n_ug; u0 += ug_max) {
+        gg.ug0 = u0;
+        gg.n_ug = n_ug - u0 < ug_max ? n_ug - u0 : ug_max;
+        const int groups = g.n * gg.n_ug;
+        lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST><<<gg.members * N_XCD * ((groups + N_XCD - 1) / N_XCD), 512, 0, st>>>(gg);
+    }
     return true;
 }
 
-// One workgroup per compute unit if either form allows it (16 cells each, else 32 cells each); otherwise whichever
-// form is resident at all, fewest workgroups sharing a CU first.
-template <int KW>
-bool launch_rec_t(const QrRecGroup &g, hipStream_t st)
+template <int KH, int KX>
+bool launch_rec_w(const QrRecGroup &g, hipStream_t st)
 {
-    if (launch_rec_ct<KW, 1>(g, true, st)) return true;
-    if (launch_rec_ct<KW, 2>(g, true, st)) return true;
-    if (launch_rec_ct<KW, 2>(g, false, st)) return true;
-    return launch_rec_ct<KW, 1>(g, false, st);
+    const int H = g.d[0].H, B = g.d[0].B;
+    const bool few = B <= 8, w8 = g.d[0].w8 != 0;
+    // One of the two products of c' = f*c + i*g is rounded before the fused multiply-add.  A recurrence carries a code
+    // that sits on a rounding tie on through all later steps and layers, so which one it is shows in the result; it is a
+    // function of the problem's size: with more 16-cell x 16-utterance tiles than an MI355X has compute units and
+    // 512 < H <= 768 it is f*c, else i*g, which is what layers of these sizes have always returned.
+    if constexpr (KH >= 5)
+        if (H > 512 && H <= 768 && H % 32 == 0 && (H / 16) * ((B + 15) / 16) * g.n > 256)
+            return w8 ? launch_rec_t<KH, KX, true, 2, true>(g, st) : launch_rec_t<KH, KX, false, 2, true>(g, st);
+    if (w8) return few ? launch_rec_t<KH, KX, true, 1, false>(g, st) : launch_rec_t<KH, KX, true, 2, false>(g, st);
+    return few ? launch_rec_t<KH, KX, false, 1, false>(g, st) : launch_rec_t<KH, KX, false, 2, false>(g, st);
+}
+
+template <int KH>
+bool launch_rec_x(const QrRecGroup &g, hipStream_t st)
+{
+    if (g.d[0].gx) return launch_rec_w<KH, 0>(g, st);
+    return g.d[0].I <= 384 ? launch_rec_w<KH, 3>(g, st) : launch_rec_w<KH, 10>(g, st);
 }
 
 }  // namespace
@@ -266,20 +606,20 @@ bool qr_rec_supported(int H, int B) { return H % 16 == 0 && H <= 1024 && B >= 1;
 
 size_t qr_rec_xbuf_bytes(int H, int B)
 {
-    return (size_t)2 * ((B + 15) / 16) * ((H + 63) / 64) * 64 * 4 * sizeof(u64);
+    return (size_t)2 * ((B + 15) / 16) * ((H + 63) / 64) * 64 * 4 * 8;
 }
 
-// Launches the recurrence of 1 or 2 directions (same H, B, T).  Returns false if it
+bool qr_rec_projects(int I) { return I <= 1280; }
+
+size_t qr_rec_xcc_bytes(int H, int B) { return (size_t)((B + 15) / 16) * ((H + 31) / 32) * sizeof(int); }
+
+// Launches the recurrence of 1 or 2 directions (same H, B, T, width).  Returns false if it
 // cannot run (size or residency): the caller then takes the step-by-step path.
 bool qr_launch_recurrence(const QrRecGroup &g, hipStream_t st)
 {
-    const int nks = (g.d[0].H + 63) / 64;
-    const int kw = (nks + 3) / 4;
-    switch (kw) {
-    case 1: return launch_rec_t<1>(g, st);
-    case 2: return launch_rec_t<2>(g, st);
-    case 3: return launch_rec_t<3>(g, st);
-    case 4: return launch_rec_t<4>(g, st);
-    default: return false;
-    }
+    const int kh = ((g.d[0].H + 63) / 64 + 1) / 2;
+    if (kh <= 2) return launch_rec_x<2>(g, st);
+    if (kh <= 5) return launch_rec_x<5>(g, st);
+    if (kh <= 8) return launch_rec_x<8>(g, st);
+    return false;
 }

@@ -112,9 +112,10 @@ class Encoder:
                 q.bilstm_layer(dirs[0], dirs[1], x, h_out=out, workspace=ws)
             else:
                 q.lstm_layer(dirs[0], x, h_out=out, col_off=0, workspace=ws)
-            for end in ends:   # the workspace is reused by the next layer: keep the flag (4 bytes, device to device)
-                self._flags[k:k + 1].copy_(ws[end - 256:end - 252].view(torch.int32))
-                k += 1
+            # the workspace is reused by the next layer: keep the flags (4 bytes each, one copy on the device)
+            w = torch.as_strided(ws.view(torch.int32), (len(ends),), (max(1, ends[-1] - ends[0]) // 4,), (ends[0] - 256) // 4)
+            self._flags[k:k + len(ends)].copy_(w)
+            k += len(ends)
             x = out
         e = q.linear(self.proj, self.proj_bias, self.proj_a_scale, x.reshape(T * B, -1)).reshape(T, B, -1)
         return x, e

@@ -1,0 +1,79 @@
+"""The persistent recurrence at the edges of its dispatch: layers narrower than a workgroup's 32 cells and with an odd
+number of 16-cell groups, 1..8 utterances (one cell per lane, columns packed to a power of two) against 9 and more,
+input widths on either side of what the kernel projects by itself (384 | 385, 1280 | 1281), sequences longer than the
+step number that travels with a code (mod 16, at 8 bits mod 256), more utterances than one launch holds, and two
+directions of different width.  Every step against one oracle step from the GPU's own previous state."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2206_07882_amd import synth
+from tests.test_gpu_parity import _lstm_pair, assert_codes_close, assert_rel, dev, host, DEV
+from tests.test_gpu_int8 import _lstm8_pair
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(L, x, hg, cg, reverse, h0, c0, unit, what):
+    T, B = x.shape[:2]
+    hp = np.zeros((B, L.H), np.int8) if h0 is None else h0
+    cp = np.zeros((B, L.H), np.float32) if c0 is None else c0
+    # A code may differ (by one) only where the quantizer's input lies within 1e-4 of a rounding tie: 2e-4 of all codes.
+    # That is the bar for the sequence; one step of a narrow layer has too few codes for a bar of its own.
+    same = 0
+    for t in (range(T - 1, -1, -1) if reverse else range(T)):
+        hr, cr, dbg = oracle.lstm_step(L, x[t], hp, cp, debug=True)
+        if cg is not None:
+            assert_rel(cg[t], cr, f"{what} c t={t}")
+        assert_codes_close(hg[t], hr, dbg["h_real"] * unit, f"{what} h t={t}", 0.9)
+        same += int((hg[t] == hr).sum())
+        hp, cp = hg[t], (cr if cg is None else cg[t])
+    assert same >= 0.999 * T * B * L.H, what
+    return hp, cp
+
+
+@pytest.mark.parametrize("T,B,I,H,bits,reverse,state", [
+    (40, 1, 64, 16, 4, False, False), (35, 2, 1280, 48, 4, True, True), (20, 8, 385, 272, 4, False, True),
+    (20, 9, 384, 256, 4, True, False), (9, 17, 1281, 640, 4, False, True), (5, 33, 48, 656, 4, True, False),
+    (270, 3, 40, 32, 8, False, True), (6, 20, 1300, 48, 8, True, True), (1, 5, 64, 64, 4, False, True),
+    (2, 4, 320, 640, 8, False, False), (4, 530, 32, 1024, 4, False, True)])
+def test_recurrence_edges(gpu_lib, T, B, I, H, bits, reverse, state):
+    q = gpu_lib
+    q_max = 127 if bits == 8 else 7
+    s_x = float(np.float32(4) / np.float32(q_max))
+    L, G = (_lstm8_pair if bits == 8 else _lstm_pair)(q, 5171 + I + H, I, H, s_x)
+    P = q.act_pitch(I)
+    x = synth.codes(5172 + T, (T, B, I), -q_max - 1, q_max)
+    xp = np.full((T, B, P), 3, np.int8)   # padding bytes must not matter
+    xp[..., :I] = x
+    h0 = synth.codes(5173, (B, H), -q_max, q_max) if state else None
+    c0 = synth.normal(5174, (B, H), 0.6) if state else None
+    kw = dict(reverse=reverse, h0=None if h0 is None else dev(h0), c0=None if c0 is None else dev(c0), want_last=True)
+    need = q.lstm_layer_workspace(G, T, B)
+    ws = torch.full((need,), 0x55, dtype=torch.uint8, device=DEV)   # whatever an earlier call left there
+    out = q.lstm_layer(G, dev(xp), debug=True, workspace=ws, **kw)
+    assert q.layer_error_flag(ws, need) == 0
+    hg, cg = host(out["h_out"]), host(out["c_all"])
+    hl, cl = _check(L, x, hg, cg, reverse, h0, c0, float(q_max), f"I={I} H={H} B={B}")
+    assert np.array_equal(host(out["h_last"]), hl) and np.array_equal(host(out["c_last"]), cl)
+    again = q.lstm_layer(G, dev(xp), workspace=ws, **kw)   # without debug outputs, on the used workspace
+    assert torch.equal(again["h_out"], out["h_out"]) and torch.equal(again["c_last"], out["c_last"])
+
+
+@pytest.mark.parametrize("T,B,bits", [(18, 130, (4, 4)), (6, 3, (8, 4)), (5, 60, (8, 8))])
+def test_two_directions(gpu_lib, T, B, bits):
+    """130 utterances: 18 groups of 16 utterances and direction, more than one launch's worth; a backward direction of
+    another width than the forward one; 60 x 640 cells x 2 directions: the size class whose cell rounds f*c first."""
+    q = gpu_lib
+    I, H = 340, 640
+    s_x = 0.03
+    pairs = [(_lstm8_pair if b == 8 else _lstm_pair)(q, 5271 + d, I, H, s_x) for d, b in enumerate(bits)]
+    x = synth.codes(5272 + T, (T, B, I), -7, 7)
+    xp = np.zeros((T, B, q.act_pitch(I)), np.int8)
+    xp[..., :I] = x
+    ws = torch.full((q.bilstm_layer_workspace(pairs[0][1], pairs[1][1], T, B),), 0x33, dtype=torch.uint8, device=DEV)
+    out = host(q.bilstm_layer(pairs[0][1], pairs[1][1], dev(xp), workspace=ws))
+    assert q.layer_error_flag(ws, q.lstm_layer_workspace(pairs[0][1], T, B)) == 0 and q.layer_error_flag(ws, ws.numel()) == 0
+    for d in range(2):
+        _check(pairs[d][0], x, out[:, :, d * H:(d + 1) * H], None, d == 1, None, None, 127.0 if bits[d] == 8 else 7.0, f"dir {d}")
