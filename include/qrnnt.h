@@ -441,9 +441,8 @@ qrnnt_status qrnnt_decode_alsd(const qrnnt_model *m, const float *enc_proj, int3
 /* qrnnt_decode_alsd with options.  QRNNT_ALSD_REUSE: reuse of cached hypotheses (Sec. 4.1 names it as what
  * makes the decoding time fall sub-linearly at small beams).  The states of the prediction network and of the
  * LMs after a label sequence depend on that sequence alone; with this flag a label pick whose resulting
- * sequence a live hypothesis of the current beam already holds takes over that hypothesis' states (the slot
- * becomes an inactive row of the network advance, copied from that hypothesis) instead of advancing the
- * networks from its own parent.  Results are bit for bit those of qrnnt_decode_alsd; sequences are compared
+ * sequence a live hypothesis of the current beam already holds takes over that hypothesis' states (both then
+ * name the same row of the state pool) instead of advancing the networks from its own parent.  Results are bit for bit those of qrnnt_decode_alsd; sequences are compared
  * by (length, 64-bit hash) as in the recombination.  The cache is the current beam: a sequence that left the
  * beam is not remembered.  stats [device] int32[2] or NULL: the call adds the number of label picks that kept
  * their slot to stats[0] and the number of those that reused states to stats[1] (the caller zeroes it). */

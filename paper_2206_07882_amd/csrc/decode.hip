@@ -11,25 +11,25 @@ namespace {
 
 
 struct NetBuf {
-    int8_t *h[QRNNT_MAX_LAYERS];   // [NB][N][H]
-    float *c[QRNNT_MAX_LAYERS];    // [NB][N][H]
-    float *y;                      // [NB][N][out_rows]
+    int8_t *h[QRNNT_MAX_LAYERS];   // [pool + 1][H]; the last row stays zero: the state before the first symbol
+    float *c[QRNNT_MAX_LAYERS];    // [pool + 1][H]
+    float *y;                      // [pool][out_rows]
     int32_t *gx0;                  // [V][4*H0]: input projection of layer 0 for every token
     float *tab0;                   // the same as fp32 pre-activation contributions (scales, bias folded in)
-    int8_t *mid_q;                 // [N][M]: codes of the bottleneck's output (consumed in the same advance)
+    int8_t *mid_q;                 // [pool][M]: codes of the bottleneck's output (consumed in the same advance)
 };
 
 struct Plan {
     int T, B, W, N, R, NB, V, J, max_sym;
+    int P;               // rows of the state pool per utterance (route.h): the beam's and those of the labels of a frame / an iteration
     NetBuf net[3];
     float *score;        // [NB][B][W]
-    int32_t *node, *len; // [NB][N]
-    int32_t *parent_idx, *token;  uint8_t *active;        // [N]
+    int32_t *node, *len, *row; // [NB][N]
+    int32_t *free_rows, *n_taken;                         // [B][P], [B]
     float *nx_score;  v4i *nx_info;  int32_t *nx_count; // [B][R*W], [B]
-    int32_t *beam_src;   // [N]
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
-    v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the slots that carry a label into round v of the frame, and how many
+    v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the hypotheses that carry a label into round v of the frame, and how many
     size_t total;
 };
 
@@ -47,34 +47,41 @@ struct Carver {
 const qrnnt_net *net_of(const qrnnt_model *m, int k) { return k == 0 ? &m->pred : (k == 1 ? &m->lm_src : &m->lm_ext); }
 bool net_used(const qrnnt_model *m, int k) { return k == 0 || (k == 1 ? m->use_src != 0 : m->use_ext != 0); }
 
-void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws, Plan &p)
+// Network buffers: states and outputs of P rows per utterance, one row of zeros behind them.
+void take_nets(const qrnnt_model *m, Plan &p, Carver &cv)
 {
-    p.T = T; p.B = B; p.W = W; p.N = B * W; p.max_sym = max_sym;
-    p.R = max_sym + 1; p.NB = max_sym + 2; p.V = m->V; p.J = m->joint_out.cols;
-    Carver cv{(char *)ws, 0};
-    const size_t N = (size_t)p.N, NB = (size_t)p.NB;
+    const size_t pool = (size_t)p.B * p.P;
     for (int k = 0; k < 3; ++k) {
         if (!net_used(m, k)) continue;
         const qrnnt_net *net = net_of(m, k);
         for (int l = 0; l < net->n_layers; ++l) {
-            p.net[k].h[l] = cv.take<int8_t>(NB * N * net->layer[l].hidden_size);
-            p.net[k].c[l] = cv.take<float>(NB * N * net->layer[l].hidden_size);
+            p.net[k].h[l] = cv.take<int8_t>((pool + 1) * net->layer[l].hidden_size);
+            p.net[k].c[l] = cv.take<float>((pool + 1) * net->layer[l].hidden_size);
         }
-        p.net[k].y = cv.take<float>(NB * N * net->out.rows);
+        p.net[k].y = cv.take<float>(pool * net->out.rows);
         p.net[k].gx0 = cv.take<int32_t>((size_t)m->V * 4 * net->layer[0].hidden_size);
         p.net[k].tab0 = cv.take<float>((size_t)m->V * 4 * net->layer[0].hidden_size);
-        p.net[k].mid_q = net->mid.packed ? cv.take<int8_t>(N * net->mid.rows) : nullptr;
+        p.net[k].mid_q = net->mid.packed ? cv.take<int8_t>(pool * net->mid.rows) : nullptr;
     }
+}
+
+void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws, Plan &p)
+{
+    p.T = T; p.B = B; p.W = W; p.N = B * W; p.max_sym = max_sym;
+    p.R = max_sym + 1; p.NB = max_sym + 2; p.V = m->V; p.J = m->joint_out.cols;
+    p.P = W * (max_sym + 1);
+    Carver cv{(char *)ws, 0};
+    const size_t N = (size_t)p.N, NB = (size_t)p.NB;
+    take_nets(m, p, cv);
     p.score = cv.take<float>(NB * N);
     p.node = cv.take<int32_t>(NB * N);
     p.len = cv.take<int32_t>(NB * N);
-    p.parent_idx = cv.take<int32_t>(N);
-    p.token = cv.take<int32_t>(N);
-    p.active = cv.take<uint8_t>(N);
+    p.row = cv.take<int32_t>(NB * N);
+    p.free_rows = cv.take<int32_t>((size_t)B * p.P);
+    p.n_taken = cv.take<int32_t>(B);
     p.nx_score = cv.take<float>((size_t)B * p.R * W);
     p.nx_info = cv.take<v4i>((size_t)B * p.R * W);
     p.nx_count = cv.take<int32_t>(B);
-    p.beam_src = cv.take<int32_t>(N);
     const size_t pool = 1 + (size_t)T * max_sym * N;
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
@@ -90,22 +97,28 @@ __global__ void fill_words_kernel(uint32_t *p, size_t n_words, uint32_t v)
     if (i < n_words) p[i] = v;
 }
 
-// Start of an utterance: slot 0 holds the empty sequence with score 0, every slot
-// is fed the start symbol from the zero state.
-__global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0, int32_t *parent_idx, int32_t *token,
-                                   uint8_t *active, int32_t *nx_count, int32_t *node_tok, int32_t *node_prev, int N,
-                                   int W, int B, int start_symbol)
+// Start of an utterance: slot 0 holds the empty sequence with score 0 and advances from the zero state (row B*P) into
+// the utterance's first row with the start symbol; the other slots are empty.
+__global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0, int32_t *row0, int32_t *free_rows, int32_t *n_taken,
+                                   int32_t *nx_count, v4i *rows, int32_t *n_rows, int32_t *node_tok, int32_t *node_prev,
+                                   int W, int B, int P, int start_symbol)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n == 0) { node_tok[0] = -1; node_prev[0] = 0; }
-    if (n < B) nx_count[n] = 0;
-    if (n >= N) return;
+    if (n == 0) { node_tok[0] = -1; node_prev[0] = 0; *n_rows = B; }
+    if (n < B) {
+        if (nx_count) nx_count[n] = 0;
+        if (n_taken) n_taken[n] = 0;
+        rows[n] = v4i{n * P, B * P, start_symbol, 0};
+    }
+    if (n < B * P) {   // (the last entry of an utterance is never looked at)
+        const int i = n % P;
+        free_rows[n] = i + 1 < P ? n + 1 : n;
+    }
+    if (n >= B * W) return;
     score0[n] = (n % W == 0) ? 0.0f : -INFINITY;
     node0[n] = 0;
     len0[n] = 0;
-    parent_idx[n] = n;
-    token[n] = start_symbol;
-    active[n] = 1;
+    row0[n] = (n / W) * P;
 }
 
 __global__ void backtrack_kernel(const float *__restrict__ score, const int32_t *__restrict__ node,
@@ -175,14 +188,12 @@ qrnnt_status check_model(const qrnnt_model *m)
     return QRNNT_OK;
 }
 
-// All used networks consume `token` and move from buffer src to buffer dst.  Layer l
+// The networks advance for the *n_rows hypotheses listed in p.rows, (row written, row read, token) each.  Layer l
 // of every network goes out as one grouped launch (the networks are independent).
-// n_rows (optional): only the hypotheses p.rows[0 .. *n_rows) advance (recurrent and output layers; the rows
-// that did not advance are not read afterwards).
-void advance_nets(const qrnnt_model *m, const Plan &p, int src, int dst, int n_embed_rows, const int32_t *gate,
-                  const int32_t *n_rows, hipStream_t st)
+void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, const int32_t *n_rows, hipStream_t st)
 {
-    const size_t N = (size_t)p.N;
+    const int pool = p.B * p.P;
+    const int32_t *const from_list = (const int32_t *)p.rows;   // row and token of an entry take the place of these arrays
     int max_layers = 0;
     for (int k = 0; k < 3; ++k)
         if (net_used(m, k) && net_of(m, k)->n_layers > max_layers) max_layers = net_of(m, k)->n_layers;
@@ -190,7 +201,7 @@ void advance_nets(const qrnnt_model *m, const Plan &p, int src, int dst, int n_e
         QrStepGroup g;
         g.n = 0;
         g.gate = gate;
-        g.rows = n_rows ? p.rows : nullptr;
+        g.rows = p.rows;
         g.n_rows = n_rows;
         for (int k = 0; k < 3; ++k) {
             if (!net_used(m, k)) continue;
@@ -204,19 +215,16 @@ void advance_nets(const qrnnt_model *m, const Plan &p, int src, int dst, int n_e
             if (l == 0) {
                 // The input of layer 0 is one of V embedding rows, so its integer input
                 // projection is a table lookup (exactly the sums the contraction would give).
-                a.x = net->embed_codes;  a.ld_x = qr_act_pitch(L->input_size);  a.x_row = p.token;  a.n_x_rows = n_embed_rows;
+                a.x = net->embed_codes;  a.ld_x = qr_act_pitch(L->input_size);  a.x_row = from_list;  a.n_x_rows = p.V;
                 a.gx = p.net[k].gx0;  a.ld_gx = 4 * (int64_t)H;  a.tabf = p.net[k].tab0;
             } else {
-                a.x = p.net[k].h[l - 1] + (size_t)dst * N * L->input_size;  a.ld_x = L->input_size;
-                a.x_row = nullptr;  a.n_x_rows = p.N;
+                a.x = p.net[k].h[l - 1];  a.ld_x = L->input_size;
+                a.x_row = nullptr;  a.n_x_rows = pool;
             }
-            a.parent = p.parent_idx;  a.n_slots = p.N;
-            a.h_prev = p.net[k].h[l] + (size_t)src * N * H;  a.ld_hp = (int64_t)H;
-            a.c_prev = p.net[k].c[l] + (size_t)src * N * H;
-            a.active = p.active;
-            a.h_next = p.net[k].h[l] + (size_t)dst * N * H;  a.ld_hn = (int64_t)H;
-            a.c_next = p.net[k].c[l] + (size_t)dst * N * H;
-            a.N = p.N;
+            a.parent = from_list;  a.n_slots = pool + 1;
+            a.h_prev = a.h_next = p.net[k].h[l];  a.ld_hp = a.ld_hn = (int64_t)H;   // no row is both read and written
+            a.c_prev = a.c_next = p.net[k].c[l];
+            a.N = p.N;  a.n_out = pool;
         }
         qr_launch_lstm_step_group(g, l == 0, st);
     }
@@ -225,7 +233,7 @@ void advance_nets(const qrnnt_model *m, const Plan &p, int src, int dst, int n_e
     QrLinearGroup lg, lg2;
     lg.n = lg2.n = 0;
     lg.gate = lg2.gate = gate;
-    lg.rows = lg2.rows = n_rows ? p.rows : nullptr;
+    lg.rows = lg2.rows = p.rows;
     lg.n_rows = lg2.n_rows = n_rows;
     for (int k = 0; k < 3; ++k) {
         if (!net_used(m, k)) continue;
@@ -236,25 +244,53 @@ void advance_nets(const qrnnt_model *m, const Plan &p, int src, int dst, int n_e
         out.w = (const v4i *)net->out.packed;
         out.nkc = qr_round_up(net->out.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
         out.rows = net->out.rows;  out.s_w = net->out.row_scale;  out.bias = net->out_bias;
-        out.K = net->out.cols;  out.N = p.N;  out.w8 = qr_bits(&net->out) == 8;
-        out.y = p.net[k].y + (size_t)dst * N * net->out.rows;  out.log_softmax = net->log_softmax;
+        out.K = net->out.cols;  out.N = p.N;  out.n_out = pool;  out.w8 = qr_bits(&net->out) == 8;
+        out.y = p.net[k].y;  out.log_softmax = net->log_softmax;
         if (has_mid) {
             QrLinearArgs &la = lg.p[lg.n++];
             la = QrLinearArgs{};
             la.w = (const v4i *)net->mid.packed;
             la.nkc = qr_round_up(net->mid.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
             la.rows = net->mid.rows;  la.s_w = net->mid.row_scale;  la.bias = net->mid_bias;  la.a_scale = net->out_a_scale;
-            la.act = p.net[k].h[top] + (size_t)dst * N * net->mid.cols;  la.K = net->mid.cols;  la.N = p.N;
+            la.act = p.net[k].h[top];  la.K = net->mid.cols;  la.N = p.N;  la.n_out = pool;
             la.q_out = p.net[k].mid_q;  la.q_inv = net->mid_inv_scale;  la.q_bits = qr_bits(&net->out);  la.w8 = qr_bits(&net->mid) == 8;
             out.a_scale = net->mid_scale;  out.act = p.net[k].mid_q;
             lg2.p[lg2.n++] = out;
         } else {
-            out.a_scale = net->out_a_scale;  out.act = p.net[k].h[top] + (size_t)dst * N * net->out.cols;
+            out.a_scale = net->out_a_scale;  out.act = p.net[k].h[top];
             lg.p[lg.n++] = out;
         }
     }
     qr_launch_linear_group(lg, st);
     if (lg2.n) qr_launch_linear_group(lg2, st);
+}
+
+// Everything a search starts from: a row of zero states, the first layers' input tables, empty counters and lists
+// (p.live and p.n_rows: n_counters words each), and the start symbol consumed by the empty sequence of every utterance.
+void start_decode(const qrnnt_model *m, const Plan &p, size_t n_counters, int32_t *n_taken, int32_t *nx_count, hipStream_t st)
+{
+    auto fill = [&](void *at, size_t nw) {
+        fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)at, nw, 0u);
+    };
+    const size_t pool = (size_t)p.B * p.P;
+    for (int k = 0; k < 3; ++k) {
+        if (!net_used(m, k)) continue;
+        const qrnnt_net *net = net_of(m, k);
+        for (int l = 0; l < net->n_layers; ++l) {
+            const size_t H = (size_t)net->layer[l].hidden_size;
+            fill(p.net[k].h[l] + pool * H, H / 4);
+            fill(p.net[k].c[l] + pool * H, H);
+        }
+        qr_launch_input_projection(&net->layer[0], net->embed_codes, p.V, p.net[k].gx0, nullptr, st);
+        qr_launch_gx_table(&net->layer[0], p.net[k].gx0, p.V, p.net[k].tab0, st);
+    }
+    fill(p.live, n_counters);
+    fill(p.n_rows, n_counters);
+    // the start symbol's list is counted in the first counter, which no round uses
+    decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, nx_count,
+                                                                       p.rows, p.n_rows, p.node_tok, p.node_prev, p.W, p.B, p.P,
+                                                                       m->blank);
+    advance_nets(m, p, nullptr, p.n_rows, st);
 }
 
 }  // namespace
@@ -296,46 +332,9 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
     hipStream_t st = (hipStream_t)stream;
     const int N = p.N, V = p.V;
     const size_t Ns = (size_t)N;
-    const int ZB = p.NB - 1;   // second A0 buffer; holds the zero state before the first frame
-    const int n_embed_rows = V;
+    const int ZB = p.NB - 1;   // the beam's buffer in every second frame (else 0)
 
-    // zero state in buffer ZB, then every slot consumes the start symbol into buffer 0
-    for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k)) continue;
-        const qrnnt_net *net = net_of(m, k);
-        for (int l = 0; l < net->n_layers; ++l) {
-            const size_t H = (size_t)net->layer[l].hidden_size;
-            size_t nw = Ns * H / 4;
-            fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)(p.net[k].h[l] + (size_t)ZB * Ns * H), nw, 0u);
-            nw = Ns * H;
-            fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)(p.net[k].c[l] + (size_t)ZB * Ns * H), nw, 0u);
-        }
-    }
-    for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k)) continue;
-        qr_launch_input_projection(&net_of(m, k)->layer[0], net_of(m, k)->embed_codes, V, p.net[k].gx0, nullptr, st);
-        qr_launch_gx_table(&net_of(m, k)->layer[0], p.net[k].gx0, V, p.net[k].tab0, st);
-    }
-    fill_words_kernel<<<1, 256, 0, st>>>((uint32_t *)p.live, 2 * (size_t)(max_sym + 2), 0u);
-    fill_words_kernel<<<1, 256, 0, st>>>((uint32_t *)p.n_rows, 2 * (size_t)(max_sym + 2), 0u);
-    decode_init_kernel<<<(N + 255) / 256 + 1, 256, 0, st>>>(p.score, p.node, p.len, p.parent_idx, p.token, p.active,
-                                                            p.nx_count, p.node_tok, p.node_prev, N, W, B, m->blank);
-    advance_nets(m, p, ZB, 0, n_embed_rows, nullptr, nullptr, st);
-
-    // The state rows a new beam slot takes over from its source (copied by the first joint + selection kernel of
-    // the next frame, see joint_route_kernel)
-    QrGatherTable tb = {};
-    for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k)) continue;
-        const qrnnt_net *net = net_of(m, k);
-        for (int l = 0; l < net->n_layers; ++l) {
-            tb.base[tb.n] = (char *)p.net[k].h[l];  tb.row_bytes[tb.n++] = net->layer[l].hidden_size;
-            tb.base[tb.n] = (char *)p.net[k].c[l];  tb.row_bytes[tb.n++] = net->layer[l].hidden_size * 4;
-        }
-        tb.base[tb.n] = (char *)p.net[k].y;  tb.row_bytes[tb.n++] = net->out.rows * 4;
-    }
-    tb.beam_src = p.beam_src;  tb.N = N;  tb.src_limit = p.NB * N;
-    const QrGatherTable no_copy = {};
+    start_decode(m, p, 2 * (max_sym + 2), p.n_taken, p.nx_count, st);
 
     QrJointArgs ja = {};
     ja.enc = enc_proj;  ja.n_enc_rows = T * B;  ja.frame_row = nullptr;  ja.rows_per_utt = W;
@@ -352,44 +351,39 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
             const int cur = (v == 0) ? a0 : v;
             const int nxt = v + 1;   // only used when v < max_sym
             ja.frame_base = t * B;
-            // first round of a frame after the first: the beam's cached outputs are still where their sources left
-            // them (read through beam_src); this kernel's spare workgroups move all state rows into buffer `cur`
-            const bool moving = (v == 0 && t > 0);
-            const size_t yb = moving ? 0 : (size_t)cur;
-            ja.pred = p.net[0].y + yb * Ns * p.J;
-            ja.lp_src = m->use_src ? p.net[1].y + yb * Ns * V : nullptr;
-            ja.lp_ext = m->use_ext ? p.net[2].y + yb * Ns * V : nullptr;
-            ja.row_idx = moving ? p.beam_src : nullptr;
-            ja.row_idx_buf = cur;
-            tb.dst_buf = cur;
+            ja.pred = p.net[0].y;
+            ja.lp_src = m->use_src ? p.net[1].y : nullptr;
+            ja.lp_ext = m->use_ext ? p.net[2].y : nullptr;
+            ja.row_idx = p.row + (size_t)cur * Ns;
             const int last = (v == max_sym);
             QrRouteArgs ra = {};
             ra.score_src = p.score + (size_t)cur * Ns;
-            ra.B = B;  ra.W = W;  ra.V = V;  ra.R = p.R;  ra.blank = m->blank;  ra.src_buf = cur;  ra.last_round = last;
+            ra.B = B;  ra.W = W;  ra.V = V;  ra.R = p.R;  ra.blank = m->blank;  ra.last_round = last;
             ra.node_base = 1 + (t * max_sym + v) * N;
             ra.node_src = p.node + (size_t)cur * Ns;  ra.len_src = p.len + (size_t)cur * Ns;
             ra.score_dst = p.score + (size_t)nxt * Ns;  ra.node_dst = p.node + (size_t)nxt * Ns;
             ra.len_dst = p.len + (size_t)nxt * Ns;
-            ra.parent_idx = p.parent_idx;  ra.token = p.token;  ra.active = p.active;
+            ra.row_src = p.row + (size_t)cur * Ns;  ra.row_dst = p.row + (size_t)nxt * Ns;
+            ra.P = p.P;  ra.free_rows = p.free_rows;  ra.n_taken = p.n_taken;
             ra.nx_score = p.nx_score;  ra.nx_info = p.nx_info;  ra.nx_count = p.nx_count;
             ra.node_tok = p.node_tok;  ra.node_prev = p.node_prev;
             ra.fe_dst_buf = (a0 == 0) ? ZB : 0;
             ra.fe_score_all = p.score;
-            ra.fe_node_all_w = p.node;  ra.fe_len_all_w = p.len;  ra.beam_src = p.beam_src;
+            ra.fe_node_all_w = p.node;  ra.fe_len_all_w = p.len;  ra.fe_row_all_w = p.row;
             if (early) {   // live[t&1][v] = utterances that carried a label into round v of this frame
                 int32_t *lv = p.live + (size_t)(t & 1) * (max_sym + 2), *lo = p.live + (size_t)((t + 1) & 1) * (max_sym + 2);
                 ra.gate = v > 0 ? lv + v : nullptr;
                 ra.live_next = lv + v + 1;
                 ra.live_clear = lo + v + 1;
             }
-            // n_rows[t&1][v] = slots that carry a label into round v of this frame, listed in p.rows
+            // n_rows[t&1][v] = hypotheses that carry a label into round v of this frame, listed in p.rows
             ra.rows_next = p.rows;
             ra.n_rows_next = p.n_rows + (size_t)(t & 1) * (max_sym + 2) + v + 1;
             ra.n_rows_clear = p.n_rows + (size_t)((t + 1) & 1) * (max_sym + 2) + v + 1;
-            qr_launch_joint_route(ja, ra, moving ? tb : no_copy, st);
-            if (!last) advance_nets(m, p, cur, nxt, n_embed_rows, early ? ra.live_next : nullptr, ra.n_rows_next, st);
+            qr_launch_joint_route(ja, ra, st);
+            if (!last) advance_nets(m, p, early ? ra.live_next : nullptr, ra.n_rows_next, st);
         }
-        a0 = (a0 == 0) ? ZB : 0;   // the new beam's buffer; its state rows follow in the next frame's first kernel
+        a0 = (a0 == 0) ? ZB : 0;   // the new beam's buffer
     }
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(p.score + (size_t)a0 * Ns, p.node + (size_t)a0 * Ns,
                                                    p.len + (size_t)a0 * Ns, p.node_tok, p.node_prev, N, max_len,
@@ -403,7 +397,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
 namespace {
 
 struct AlsdPlan {
-    Plan p;                        // network buffers (2 state buffers), parent_idx / token / active, label trie
+    Plan p;                        // network buffers, beam (2 buffers), label trie, lists
     unsigned long long *hash;      // [2][N]
     float *fin_score;  int32_t *fin_node, *fin_len;   // [N]
     int n_iter;
@@ -415,29 +409,17 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     p = Plan{};
     p.T = T; p.B = B; p.W = W; p.N = B * W; p.max_sym = 0;
     p.R = 1; p.NB = 2; p.V = m->V; p.J = m->joint_out.cols;
+    p.P = 2 * W;   // the beam's rows and those of an iteration's labels
     ap.n_iter = T + u_max;
     Carver cv{(char *)ws, 0};
     const size_t N = (size_t)p.N, NB = 2;
-    for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k)) continue;
-        const qrnnt_net *net = net_of(m, k);
-        for (int l = 0; l < net->n_layers; ++l) {
-            p.net[k].h[l] = cv.take<int8_t>(NB * N * net->layer[l].hidden_size);
-            p.net[k].c[l] = cv.take<float>(NB * N * net->layer[l].hidden_size);
-        }
-        p.net[k].y = cv.take<float>(NB * N * net->out.rows);
-        p.net[k].gx0 = cv.take<int32_t>((size_t)m->V * 4 * net->layer[0].hidden_size);
-        p.net[k].tab0 = cv.take<float>((size_t)m->V * 4 * net->layer[0].hidden_size);
-        p.net[k].mid_q = net->mid.packed ? cv.take<int8_t>(N * net->mid.rows) : nullptr;
-    }
+    take_nets(m, p, cv);
     p.score = cv.take<float>(NB * N);
     p.node = cv.take<int32_t>(NB * N);
     p.len = cv.take<int32_t>(NB * N);
     ap.hash = cv.take<unsigned long long>(NB * N);
-    p.parent_idx = cv.take<int32_t>(N);
-    p.token = cv.take<int32_t>(N);
-    p.active = cv.take<uint8_t>(N);
-    p.nx_count = cv.take<int32_t>(B);
+    p.row = cv.take<int32_t>(NB * N);
+    p.free_rows = cv.take<int32_t>((size_t)B * p.P);
     ap.fin_score = cv.take<float>(N);
     ap.fin_node = cv.take<int32_t>(N);
     ap.fin_len = cv.take<int32_t>(N);
@@ -445,7 +427,8 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
     p.live = cv.take<int32_t>((size_t)ap.n_iter + 2);
-    p.rows = nullptr;  p.n_rows = nullptr;
+    p.rows = cv.take<v4i>(N);
+    p.n_rows = cv.take<int32_t>((size_t)ap.n_iter + 2);
     p.total = (cv.off + 255) / 256 * 256;
 }
 
@@ -494,32 +477,14 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
     const int N = p.N, V = p.V;
     const size_t Ns = (size_t)N;
 
-    // zero state in buffer 1, then every slot consumes the start symbol into buffer 0
-    for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k)) continue;
-        const qrnnt_net *net = net_of(m, k);
-        for (int l = 0; l < net->n_layers; ++l) {
-            const size_t H = (size_t)net->layer[l].hidden_size;
-            size_t nw = Ns * H / 4;
-            fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)(p.net[k].h[l] + Ns * H), nw, 0u);
-            nw = Ns * H;
-            fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)(p.net[k].c[l] + Ns * H), nw, 0u);
-        }
-        qr_launch_input_projection(&net->layer[0], net->embed_codes, V, p.net[k].gx0, nullptr, st);
-        qr_launch_gx_table(&net->layer[0], p.net[k].gx0, V, p.net[k].tab0, st);
-    }
     {
-        size_t nw = (size_t)ap.n_iter + 2;
-        fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)p.live, nw, 0u);
-        nw = 2 * Ns * 2;
+        const size_t nw = 2 * Ns * 2;
         fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)ap.hash, nw, 0u);
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_score, Ns, 0xFF800000u);   // -inf
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_node, Ns, 0u);
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_len, Ns, 0u);
     }
-    decode_init_kernel<<<(N + 255) / 256 + 1, 256, 0, st>>>(p.score, p.node, p.len, p.parent_idx, p.token, p.active,
-                                                            p.nx_count, p.node_tok, p.node_prev, N, W, B, m->blank);
-    advance_nets(m, p, 1, 0, V, nullptr, nullptr, st);
+    start_decode(m, p, (size_t)ap.n_iter + 2, nullptr, nullptr, st);
 
     QrJointArgs ja = {};
     ja.enc = enc_proj;  ja.n_enc_rows = T * B;  ja.frame_row = nullptr;  ja.rows_per_utt = W;  ja.frame_base = 0;
@@ -533,27 +498,30 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
     int cur = 0;
     for (int i = 0; i < ap.n_iter; ++i) {
         const int nxt = cur ^ 1;
-        ja.pred = p.net[0].y + (size_t)cur * Ns * p.J;
-        ja.lp_src = m->use_src ? p.net[1].y + (size_t)cur * Ns * V : nullptr;
-        ja.lp_ext = m->use_ext ? p.net[2].y + (size_t)cur * Ns * V : nullptr;
+        ja.pred = p.net[0].y;
+        ja.lp_src = m->use_src ? p.net[1].y : nullptr;
+        ja.lp_ext = m->use_ext ? p.net[2].y : nullptr;
+        ja.row_idx = p.row + (size_t)cur * Ns;
         QrRouteArgs ra = {};
         ra.score_src = p.score + (size_t)cur * Ns;
-        ra.B = B;  ra.W = W;  ra.V = V;  ra.R = 1;  ra.blank = m->blank;  ra.src_buf = cur;  ra.last_round = 0;
+        ra.B = B;  ra.W = W;  ra.V = V;  ra.R = 1;  ra.blank = m->blank;  ra.last_round = 0;
         ra.node_base = 1 + i * N;
         ra.node_src = p.node + (size_t)cur * Ns;  ra.len_src = p.len + (size_t)cur * Ns;
         ra.score_dst = p.score + (size_t)nxt * Ns;  ra.node_dst = p.node + (size_t)nxt * Ns;
         ra.len_dst = p.len + (size_t)nxt * Ns;
-        ra.parent_idx = p.parent_idx;  ra.token = p.token;  ra.active = p.active;
+        ra.row_src = p.row + (size_t)cur * Ns;  ra.row_dst = p.row + (size_t)nxt * Ns;
+        ra.P = p.P;  ra.free_rows = p.free_rows;
         ra.node_tok = p.node_tok;  ra.node_prev = p.node_prev;
         ra.gate = i > 0 ? p.live + i : nullptr;   // live[i]: utterances with a live hypothesis entering iteration i
         ra.live_next = p.live + i + 1;
+        ra.rows_next = p.rows;  ra.n_rows_next = p.n_rows + i + 1;
         QrAlsdArgs sa = {};
         sa.iter = i;  sa.T = T;  sa.u_max = u_max;
         sa.hash_src = ap.hash + (size_t)cur * Ns;  sa.hash_dst = ap.hash + (size_t)nxt * Ns;
         sa.fin_score = ap.fin_score;  sa.fin_node = ap.fin_node;  sa.fin_len = ap.fin_len;
         sa.reuse = (flags & QRNNT_ALSD_REUSE) ? 1 : 0;  sa.stats = stats;
         qr_launch_joint_alsd(ja, ra, sa, st);
-        if (i + 1 < ap.n_iter) advance_nets(m, p, cur, nxt, V, ra.live_next, nullptr, st);
+        if (i + 1 < ap.n_iter) advance_nets(m, p, ra.live_next, ra.n_rows_next, st);
         cur = nxt;
     }
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(ap.fin_score, ap.fin_node, ap.fin_len, p.node_tok, p.node_prev, N,

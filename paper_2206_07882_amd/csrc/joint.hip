@@ -120,61 +120,13 @@ __global__ __launch_bounds__(256) void joint_fuse_kernel(const QrJointArgs a)
 // ALSD: the same joint + selection inside the alignment-length synchronous search (route.h, qr_alsd_route):
 // every hypothesis reads its own encoder frame (iteration - labels so far), a blank at the last frame
 // finishes a hypothesis instead of being a candidate, labels beyond the cap are no candidates.
-// Workgroups beyond the B utterances (time-synchronous search, first round of a frame) copy the state rows of the
-// new beam from their sources into the beam's buffer, four slots of one tensor per wave: that copy only has to be
-// done before the next network advance, so it runs here, on the CUs this kernel leaves idle, instead of in a launch
-// of its own.  The joint of this round reads its inputs through the same source indices (QrJointArgs.row_idx).
 template <int NTW, bool ALSD>
-__global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, const QrRouteArgs r, const QrAlsdArgs s,
-                                                          const QrGatherTable gt)
+__global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, const QrRouteArgs r, const QrAlsdArgs s)
 {
     __shared__ v4i lds[4 * 4 * 64];
     __shared__ float cand[16 * NTW * 64];   // the utterance's candidates by flat index (second attempt of the selection)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!ALSD && (int)blockIdx.x >= r.B) {   // uniform per workgroup
-        // A wave moves the rows of 4 consecutive slots of one tensor.  This kernel's register footprint allows only
-        // 8 waves per CU, so what keeps the copy near the memory rate is the amount each wave has in flight: all
-        // loads of its (up to) four rows are issued before the first store, 16 KiB per wave for 4 KiB rows.
-        const int nq = (gt.N + 3) >> 2;
-        const int quad = ((int)blockIdx.x - r.B) * 4 + wave;
-        if (quad >= nq * gt.n) return;
-        const int t = quad / nq, n0 = (quad - t * nq) * 4;
-        const int rb = gt.row_bytes[t];
-        const char *sp[4];
-        char *dp[4];
-        bool ok[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int n = n0 + u;
-            const int src = n < gt.N ? gt.beam_src[n] : -1;   // an empty rank keeps whatever the destination holds (its score is -inf)
-            ok[u] = src >= 0 && src < gt.src_limit;
-            sp[u] = gt.base[t] + (size_t)(ok[u] ? src : 0) * rb;
-            dp[u] = gt.base[t] + ((size_t)gt.dst_buf * gt.N + (n < gt.N ? n : 0)) * rb;
-        }
-        if ((rb & 15) == 0 && ((uintptr_t)gt.base[t] & 15) == 0) {
-            const int n16 = rb >> 4;
-            for (int i0 = 0; i0 < n16; i0 += 256) {
-                v4i tmp[4][4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (ok[u] && i0 + v * 64 + lane < n16) tmp[u][v] = ((const v4i *)sp[u])[i0 + v * 64 + lane];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (ok[u] && i0 + v * 64 + lane < n16) ((v4i *)dp[u])[i0 + v * 64 + lane] = tmp[u][v];
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (ok[u])
-                    for (int i = lane; i < rb / 4; i += 64) ((uint32_t *)dp[u])[i] = ((const uint32_t *)sp[u])[i];
-        }
-        return;
-    }
     const int col = lane & 15, grp = lane >> 4;
     const int b = blockIdx.x;
     const int W = r.W, V = a.V, J = a.J;
@@ -196,16 +148,15 @@ __global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, c
     constexpr int PER = 16 * NTW;
     float val[PER];
     float *fin_new = (float *)lds + 256;   // ALSD: value of hypothesis w finishing now; wave 0's own part of the buffer
-    QrAlsdOwn own = {};
+    QrOwn own = {};
+    QrAlsdOwn alsd_own = {};
     int nx0 = 0;   // length of the utterance's candidate list before this round
     if (ALSD && wave == 0) {
         fin_new[lane] = -INFINITY;
-        own = qr_alsd_load_own(r, s, b, lane);
+        alsd_own = qr_alsd_load_own(r, s, b, lane);
     }
     if (!ALSD && wave == 0) {   // what the routing will need of this lane's hypothesis (its blank picks carry it into the candidate list)
-        const int o = b * W + (lane < W ? lane : 0);
-        own.node = r.node_src[o];
-        own.len = r.len_src[o];
+        own = qr_load_own(r, b, lane);
         nx0 = r.nx_count[b];
     }
     // per-token constants of this lane's 16 tokens (fetched behind the first tile's operands, see qr_head_mma)
@@ -215,11 +166,7 @@ __global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, c
         const int w = nt * 16 + col;
         const bool wv = w < W;
         const int n = b * W + (wv ? w : W - 1);
-        int64_t nrow = n;   // row of the cached network outputs that hypothesis n reads
-        if (!ALSD && a.row_idx) {
-            const int src = a.row_idx[n];
-            nrow = src >= 0 ? (int64_t)src : (int64_t)a.row_idx_buf * a.N + n;
-        }
+        const int64_t nrow = a.row_idx[n];   // where this hypothesis' network outputs are
         const float *p = a.pred + nrow * J + grp * 16;
         const float *e = e_utt;
         int len_w = 0, t_w = 0;
@@ -366,10 +313,10 @@ __global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, c
     }
     if (ALSD) {
         __builtin_amdgcn_wave_barrier();
-        qr_alsd_route(r, s, b, lane, my_c, my_v, fin_new[lane], own);
+        qr_alsd_route(r, s, b, lane, my_c, my_v, fin_new[lane], alsd_own, (unsigned *)lds);
         return;
     }
-    const int cnt = qr_route_picks(r, b, lane, my_c, my_v, own.node, own.len, nx0);
+    const int cnt = qr_route_picks(r, b, lane, my_c, my_v, own, nx0);
     if (r.last_round) {   // the frame is complete for this utterance: prune its candidate list to the new beam
         __threadfence();
         qr_frame_end(r, b, lane, cnt, (unsigned *)lds, (int *)lds + 64);
@@ -378,21 +325,20 @@ __global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, c
 
 }  // namespace
 
-void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, const QrGatherTable &gt, hipStream_t st)
+void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, hipStream_t st)
 {
     const QrAlsdArgs none = {};
-    const unsigned grid = (unsigned)(r.B + (gt.n > 0 ? (((gt.N + 3) / 4) * gt.n + 3) / 4 : 0));   // copy: 4 slots per wave, 4 waves per workgroup
-    if (r.W <= 16) joint_route_kernel<1, false><<<grid, 256, 0, st>>>(a, r, none, gt);
-    else if (r.W <= 32) joint_route_kernel<2, false><<<grid, 256, 0, st>>>(a, r, none, gt);
-    else joint_route_kernel<4, false><<<grid, 256, 0, st>>>(a, r, none, gt);
+    const unsigned grid = (unsigned)r.B;
+    if (r.W <= 16) joint_route_kernel<1, false><<<grid, 256, 0, st>>>(a, r, none);
+    else if (r.W <= 32) joint_route_kernel<2, false><<<grid, 256, 0, st>>>(a, r, none);
+    else joint_route_kernel<4, false><<<grid, 256, 0, st>>>(a, r, none);
 }
 
 void qr_launch_joint_alsd(const QrJointArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
-    const QrGatherTable none = {};
-    if (r.W <= 16) joint_route_kernel<1, true><<<r.B, 256, 0, st>>>(a, r, s, none);
-    else if (r.W <= 32) joint_route_kernel<2, true><<<r.B, 256, 0, st>>>(a, r, s, none);
-    else joint_route_kernel<4, true><<<r.B, 256, 0, st>>>(a, r, s, none);
+    if (r.W <= 16) joint_route_kernel<1, true><<<r.B, 256, 0, st>>>(a, r, s);
+    else if (r.W <= 32) joint_route_kernel<2, true><<<r.B, 256, 0, st>>>(a, r, s);
+    else joint_route_kernel<4, true><<<r.B, 256, 0, st>>>(a, r, s);
 }
 
 void qr_launch_joint(const QrJointArgs &a, hipStream_t st)

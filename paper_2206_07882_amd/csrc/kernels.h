@@ -24,6 +24,7 @@ struct QrStepArgs {
     int32_t *dbg_accx, *dbg_acch;
     float *dbg_gates;
     int I, H, N, nkc_x, nkc_h;
+    int n_out;                         // rows of h_next / c_next (N, or more where a list names them: see QrStepGroup.rows)
     float x_scale, h_scale, h_inv;
 };
 
@@ -34,8 +35,9 @@ struct QrStepGroup {
     const int32_t *gate;               // optional [device]: the launch does nothing when *gate == 0
     // optional [device] (same N, parent and x_row arrays for all members): the launch advances the hypotheses
     // listed in rows[0 .. *n_rows) and leaves every other row of the outputs untouched.  An entry is
-    // (hypothesis n, parent[n], x_row[n], unused): what the kernel would otherwise fetch through n, so that
-    // the list adds no link to its chain of dependent loads.  Entries beyond the end may hold anything.
+    // (output row n < n_out, parent[n], x_row[n], unused): what the kernel would otherwise fetch through n, so that
+    // the list adds no link to its chain of dependent loads.  Entries beyond the end may hold anything.  N is the
+    // largest length the list can have; of parent and x_row only whether they are null matters.
     const v4i *rows = nullptr;
     const int32_t *n_rows = nullptr;
     // filled in by the launcher of the tiled kernel: row blocks of all members together, compute units of the device,
@@ -49,6 +51,7 @@ struct QrLinearArgs {
     const float *s_w, *bias;
     float a_scale;
     const int8_t *act;  int K, N;
+    int n_out;                         // rows of act and of the outputs (N, or more where a list names them)
     float *y;  int32_t *dbg_acc;
     int log_softmax;
     int8_t *q_out;  float q_inv;  int q_bits;   // optional: codes of y under the next layer's input quantizer, [N, rows]
@@ -65,17 +68,6 @@ struct QrLinearGroup {
     const int32_t *n_rows = nullptr;
 };
 
-// State tensors of the decoder ([buffers][N][row]): what a new beam slot copies from its source (buffer, slot).
-#define QR_MAX_GATHER 32
-struct QrGatherTable {
-    char *base[QR_MAX_GATHER];
-    int row_bytes[QR_MAX_GATHER];
-    int n;                             // 0: nothing to copy
-    const int32_t *beam_src;           // [N] flat source row (buffer * N + slot) of every new beam slot, -1: empty rank
-    int N, dst_buf;
-    int src_limit;                     // flat source rows are below this (buffers x N); anything else is skipped
-};
-
 struct QrJointArgs {
     const float *enc;  int n_enc_rows;
     const int32_t *frame_row;          // per-row encoder row, or null: row = frame_base + n / rows_per_utt
@@ -88,34 +80,32 @@ struct QrJointArgs {
     int N, J, V, blank, nkc;
     float *lp_out;  int8_t *dbg_zq;  float *fused;
     int w8;                            // 8-bit output layer: 8-bit weights and an 8-bit quantizer on z
-    const int32_t *row_idx;            // optional (decoding loop): hypothesis n reads row row_idx[n] of pred / lp_src / lp_ext
-                                       // (which then point at buffer 0 of those arrays); < 0: row n of buffer row_idx_buf
-    int row_idx_buf;
+    const int32_t *row_idx;            // decoding loop: hypothesis n reads row row_idx[n] of pred / lp_src / lp_ext
 };
 
 struct QrRouteArgs {
     const float *score_src;                         // [B,W] of the current round
-    int B, W, V, R, blank, src_buf, last_round, node_base;
-    const int32_t *node_src, *len_src;              // [N] of the current round
-    float *score_dst;  int32_t *node_dst, *len_dst; // [N] of the next round
-    int32_t *parent_idx, *token;  uint8_t *active;  // [N] inputs of the next network advance
-    float *nx_score;  v4i *nx_info;  int32_t *nx_count;   // the frame's candidate list; info = (flat source (buffer, slot), trie node, length, -)
+    int B, W, V, R, blank, last_round, node_base;
+    const int32_t *node_src, *len_src, *row_src;    // [N] of the current round; row: where the networks' states and outputs are
+    float *score_dst;  int32_t *node_dst, *len_dst, *row_dst;   // [N] of the next round
+    // Rows of the state pool: utterance b owns rows b*P .. b*P + P-1.  free_rows[b*P + i]: its free ones;
+    // n_taken[b]: how many of them this frame's earlier rounds have taken.
+    int P;  int32_t *free_rows, *n_taken;
+    float *nx_score;  v4i *nx_info;  int32_t *nx_count;   // the frame's candidate list; info = (pool row, trie node, length, -)
     int32_t *node_tok, *node_prev;                  // label trie
     // end of the frame (used when last_round): the W best of the candidate list become the beam in buffer fe_dst_buf
     int fe_dst_buf;
-    float *fe_score_all;  int32_t *fe_node_all_w, *fe_len_all_w;
-    int32_t *beam_src;                              // [N] flat source (buffer, slot) of every new beam slot, or -1
+    float *fe_score_all;  int32_t *fe_node_all_w, *fe_len_all_w, *fe_row_all_w;
     // early stop (all optional): the round is dead when *gate == 0; an utterance that picked a label
     // adds 1 to *live_next; workgroup 0 clears *live_clear for a later frame
     const int32_t *gate;  int32_t *live_next, *live_clear;
-    // list of the slots that carry a label into the next round (optional, see QrStepGroup.rows): every utterance
-    // appends its slots at rows_next[old *n_rows_next ...]; workgroup 0 clears *n_rows_clear for a later frame
+    // list of the hypotheses that took a label (see QrStepGroup.rows): every utterance appends its own at
+    // rows_next[old *n_rows_next ...]; workgroup 0 clears *n_rows_clear for a later frame
     v4i *rows_next;  int32_t *n_rows_next, *n_rows_clear;
 };
 
-// One direction of the persistent recurrence (see recurrence.hip).
-// Alignment-length synchronous search: what one iteration needs beyond QrRouteArgs (of which it uses score/node/len
-// src and dst, parent_idx/token/active, the label trie, node_base, gate and live_next).
+// Alignment-length synchronous search: what one iteration needs beyond QrRouteArgs (of which it uses score/node/len/row
+// src and dst, the pool rows, the label trie, node_base, gate, live_next and the list of rows).
 struct QrAlsdArgs {
     int iter, T, u_max;                              // hypothesis w stands at frame iter - len[w]
     const unsigned long long *hash_src;              // [N] hash of the label sequence (recombination key, with the length)
@@ -125,6 +115,7 @@ struct QrAlsdArgs {
     int32_t *stats;                                  // optional [device] int32[2]: += label picks that kept their slot, += those that reused states
 };
 
+// One direction of the persistent recurrence (see recurrence.hip).
 struct QrRecArgs {
     const v4i *whh;  const float *s_wih, *s_whh, *bias;
     const v4i *wih;                    // used when gx is null: the kernel projects the input itself
@@ -162,7 +153,7 @@ QR_HIDDEN void qr_launch_input_projection(const qrnnt_lstm *L, const int8_t *x_c
 QR_HIDDEN void qr_launch_linear_group(const QrLinearGroup &g, hipStream_t st);
 QR_HIDDEN void qr_launch_linear(const QrLinearArgs &a, hipStream_t st);
 QR_HIDDEN void qr_launch_joint(const QrJointArgs &a, hipStream_t st);
-QR_HIDDEN void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, const QrGatherTable &gt, hipStream_t st);
+QR_HIDDEN void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, hipStream_t st);
 QR_HIDDEN void qr_launch_joint_alsd(const QrJointArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st);
 QR_HIDDEN void qr_launch_beam(const float *score, const float *fused, int B, int W, int V, int blank, int force_blank,
                               int32_t *parent_out, int32_t *token_out, float *score_out, hipStream_t st);

@@ -24,7 +24,7 @@ __global__ __launch_bounds__(256) void linear_head_kernel(const QrLinearGroup g)
         const int n_cnt = *g.n_rows;
         if ((int)blockIdx.x * 16 >= n_cnt) return;   // uniform per block
         nv = nv && (int)blockIdx.x * 16 + col < n_cnt;
-        n = e[0] < 0 ? 0 : (e[0] >= a.N ? a.N - 1 : e[0]);
+        n = e[0] < 0 ? 0 : (e[0] >= a.n_out ? a.n_out - 1 : e[0]);
     }
     const int8_t *arow = a.act + (int64_t)n * a.K + grp * 16;
     const int K = a.K;
@@ -130,6 +130,7 @@ void qr_launch_linear(const QrLinearArgs &a, hipStream_t st)
 {
     QrLinearGroup g;
     g.p[0] = a;
+    g.p[0].n_out = a.N;
     g.n = 1;
     g.gate = nullptr;
     g.rows = nullptr;

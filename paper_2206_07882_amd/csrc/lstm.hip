@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
         const int n_cnt = *g.n_rows;
         if (n0 >= n_cnt) return;   // uniform
         n_ok = n0 + col < n_cnt;
-        nn = e[0] < 0 ? 0 : (e[0] >= N ? N - 1 : e[0]);
+        nn = e[0] < 0 ? 0 : (e[0] >= a.n_out ? a.n_out - 1 : e[0]);
         s = a.parent ? e[1] : nn;
         xr = a.x_row ? e[2] : nn;
     } else {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256, (USE_GX && !DBG) ? 3 : 2) void lstm_step_pipe_
             int fl = (i * 2 + wn) * 16 + col;                                 // the column this lane finishes in tile i
             fl = fl < (P::BN >> width) ? fl : 0;
             const v4i el_i = se[se0 + logical(rl)], ef_i = se[se0 + fl];
-            auto hyp = [&](int r) { return r < 0 ? 0 : (r >= N ? N - 1 : r); };
+            auto hyp = [&](int r) { return r < 0 ? 0 : (r >= a.n_out ? a.n_out - 1 : r); };
             ld_n[i] = hyp(el_i[0]);
             ld_s[i] = a.parent ? el_i[1] : ld_n[i];
             ld_x[i] = (!USE_GX && a.x_row) ? el_i[2] : ld_n[i];
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(256, (USE_GX && !DBG) ? 3 : 2) void lstm_step_pipe_
     if (a.active) {
 #pragma unroll
         for (int nt = 0; nt < NTV; ++nt) {
-            act[nt] = a.active[n_of[nt] < N ? n_of[nt] : N - 1];
+            act[nt] = a.active[n_of[nt] < a.n_out ? n_of[nt] : a.n_out - 1];
 #pragma unroll
             for (int q = 0; q < MQ; ++q) hp_code[q][nt] = *(const int *)(a.h_prev + (int64_t)src_of[nt] * a.ld_hp + jb[q]);
         }
@@ -572,7 +572,8 @@ void launch_pipe(const QrStepGroup &g, hipStream_t st)
         const QrStepArgs &a = g.p[i];
         dbg = dbg || a.dbg_accx || a.dbg_acch || a.dbg_gates;
         tab = tab && a.tabf != nullptr;
-        fast = fast && a.H % (8 * MT) == 0 && a.N % P::BN == 0 && a.H % QRNNT_KCHUNK == 0 &&
+        // (columns behind the end of a list store nothing in either variant)
+        fast = fast && a.H % (8 * MT) == 0 && (g.rows || a.N % P::BN == 0) && a.H % QRNNT_KCHUNK == 0 &&
                (USE_GX || a.I % QRNNT_KCHUNK == 0);
     }
     // with debug outputs: the debug build of the same variant (same body, same tile walk, same narrow instances)
@@ -811,7 +812,7 @@ static qrnnt_status make_step_args(QrStepArgs &a, const qrnnt_lstm *L, const int
     a.parent = parent;  a.n_slots = n_slots;
     a.h_prev = h_prev;  a.ld_hp = L->hidden_size;  a.c_prev = c_prev;  a.active = active;
     a.h_next = h_next;  a.ld_hn = L->hidden_size;  a.c_next = c_next;
-    a.N = N;
+    a.N = a.n_out = N;
     return QRNNT_OK;
 }
 
@@ -1031,7 +1032,7 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
         a.ld_gx = 4 * (int64_t)H;
         a.n_x_rows = B;   // rows of the step's slice of gx (row indices are clamped into [0, n_x_rows))
         a.n_slots = B;
-        a.N = B;
+        a.N = a.n_out = B;
         a.ld_hn = ld_out;
         const float *c_prev = c.c0 ? c.c0 : cbuf[0];
         int cur = c.c0 ? 0 : 1;   // next c buffer to write

@@ -3,21 +3,69 @@
 // candidate list, label picks become the slots of the next round in selection
 // order (prefix counts by ballot), the remaining slots die.  Runs in one wave:
 // lane r < W holds pick r as (flat candidate index c = parent*V + token, or -1; score v).
+//
+// The networks' states and outputs after a label sequence are written once, into a row of a pool, and never move: a
+// hypothesis names its row.  A label pick takes a free row of its utterance, a blank pick goes on with its parent's,
+// and what no hypothesis of the new beam names is free again.  Only label picks cost an advance of the networks.
+// (64 x 16 hypotheses: copying a new beam's rows was 25 MB read and written per frame, 4.5 us of the frame's 224 us;
+// the alignment-length search passed every row through the networks, 63 us an iteration against 50.)
 #pragma once
 
 #include "kernels.h"
 #include "select.h"
 
+// What lane w < W of the routing wave knows about hypothesis w of the current round: fetched at the start of the
+// kernel, so that nothing in the routing waits for memory.
+struct QrOwn {
+    int node, len, row;
+    int free_row;                      // the utterance's w-th free row of the pool
+    int taken;                         // its rows taken by earlier rounds of the frame (uniform)
+};
+
+__device__ __forceinline__ QrOwn qr_load_own(const QrRouteArgs &a, int b, int lane)
+{
+    const int o = b * a.W + (lane < a.W ? lane : 0);
+    QrOwn own;
+    own.node = a.node_src[o];
+    own.len = a.len_src[o];
+    own.row = a.row_src[o];
+    own.taken = a.n_taken ? a.n_taken[b] : 0;
+    int f = own.taken + lane;          // (a pick never needs more than there are, see the pool's size in decode.hip)
+    f = f < a.P ? f : a.P - 1;
+    own.free_row = a.free_rows[(size_t)b * a.P + f];
+    return own;
+}
+
+// The utterance's free rows for what follows: all of its P rows except the ones that lanes with `held` name.
+// mask: 64 words of LDS, private to the calling wave (P <= 64 * 17 bits).
+__device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, int lane, bool held, int row, unsigned *mask)
+{
+    __builtin_amdgcn_wave_barrier();
+    mask[lane] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    const int rel = row - b * a.P;
+    if (held && rel >= 0 && rel < a.P) atomicOr(mask + (rel >> 5), 1u << (rel & 31));
+    __builtin_amdgcn_wave_barrier();
+    int n = 0;
+    for (int i0 = 0; i0 < a.P; i0 += 64) {
+        const int i = i0 + lane;
+        const bool is_free = i < a.P && ((mask[i >> 5] >> (i & 31)) & 1u) == 0u;
+        const unsigned long long fm = __ballot(is_free);
+        const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(fm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)fm, 0u));
+        if (is_free) a.free_rows[(size_t)b * a.P + pos] = b * a.P + i;
+        n += (int)__popcll(fm);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Returns the length of the utterance's candidate list after this round (uniform).
-// own_node / own_len: trie node and length of hypothesis `lane` of the current round (fetched at the start of the
-// kernel, so that the routing does not wait for memory); a pick reads its parent's from that lane.
+// own: hypothesis `lane` of the current round; a pick reads its parent's from that lane.
 // nx0: the length of the utterance's candidate list before this round (a.nx_count[b], fetched early as well).
-__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, int own_node,
-                                              int own_len, int nx0)
+__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0)
 {
     if (lane == 0 && b == 0 && a.live_clear) *a.live_clear = 0;
     if (lane == 0 && b == 0 && a.n_rows_clear) *a.n_rows_clear = 0;
-    const int W = a.W, V = a.V, N = a.B * a.W;
+    const int W = a.W, V = a.V;
     const bool in = lane < W;
     const bool found = in && c >= 0;
     const int par = found ? c / V : 0, tok = found ? c - (c / V) * V : 0;
@@ -25,51 +73,51 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     const bool is_lab = found && tok != a.blank && !a.last_round;
     const unsigned long long bm = __ballot(is_blank), lm = __ballot(is_lab);
     const unsigned long long lt = (1ull << lane) - 1ull;
-    const int src_slot = b * W + par;
-    const int par_node = __shfl(own_node, par), par_len = __shfl(own_len, par);
+    const int par_node = __shfl(own.node, par), par_len = __shfl(own.len, par), par_row = __shfl(own.row, par);
+    const int k_lab = (int)__popcll(lm & lt);            // this pick's number among the label picks
+    const int new_row = __shfl(own.free_row, k_lab);
     if (is_blank) {
         const int e = nx0 + __popcll(bm & lt);
         a.nx_score[(size_t)b * a.R * W + e] = v;
-        a.nx_info[(size_t)b * a.R * W + e] = v4i{a.src_buf * N + src_slot, par_node, par_len, 0};
+        a.nx_info[(size_t)b * a.R * W + e] = v4i{par_row, par_node, par_len, 0};
     }
     const int cnt = nx0 + __popcll(bm);
     if (lane == 0) a.nx_count[b] = cnt;
     if (a.last_round) return cnt;
     const int n_lab = __popcll(lm);
     if (lane == 0 && n_lab > 0 && a.live_next) atomicAdd(a.live_next, 1);
-    if (a.rows_next && n_lab > 0) {   // uniform; the order of the utterances in the list does not matter
+    if (n_lab > 0) {   // uniform; the order of the utterances in the list does not matter
         int base = 0;
-        if (lane == 0) base = atomicAdd(a.n_rows_next, n_lab);
+        if (lane == 0) {
+            base = atomicAdd(a.n_rows_next, n_lab);
+            a.n_taken[b] = own.taken + n_lab;
+        }
         base = __builtin_amdgcn_readfirstlane(base);
-        if (is_lab) a.rows_next[base + (int)__popcll(lm & lt)] = v4i{b * W + (int)__popcll(lm & lt), src_slot, tok, 0};
+        if (is_lab) a.rows_next[base + k_lab] = v4i{new_row, par_row, tok, 0};
     }
     if (is_lab) {
-        const int dst = b * W + __popcll(lm & lt);
+        const int dst = b * W + k_lab;
         const int id = a.node_base + dst;
         a.node_tok[id] = tok;
         a.node_prev[id] = par_node;
         a.score_dst[dst] = v;
         a.node_dst[dst] = id;
         a.len_dst[dst] = par_len + 1;
-        a.parent_idx[dst] = src_slot;
-        a.token[dst] = tok;
-        a.active[dst] = 1;
+        a.row_dst[dst] = new_row;
     }
     if (in && lane >= n_lab) {
         const int dst = b * W + lane;
         a.score_dst[dst] = -INFINITY;
         a.node_dst[dst] = 0;
         a.len_dst[dst] = 0;
-        a.parent_idx[dst] = dst;
-        a.token[dst] = a.blank;
-        a.active[dst] = 0;
+        a.row_dst[dst] = b * a.P;   // any row of the utterance
     }
     return cnt;
 }
 
 // End of a frame for utterance b (one wave): the new beam is the W best of the cnt candidates by
 // (score descending, insertion order); slot r of buffer fe_dst_buf takes score, trie node and length
-// that its candidate carried along, beam_src[r] tells the state copy where the states are.  The candidates of the
+// that its candidate carried along, and the pool row its states are in.  The candidates of the
 // current round were stored by this same wave a moment ago: they are read back from L2 (agent-scope
 // loads after a fence), not through the CU's vector cache.
 // sk / sc: 64 words of LDS each, private to the calling wave (pruned selection of select.h).
@@ -89,42 +137,44 @@ __device__ __forceinline__ void qr_frame_end(const QrRouteArgs &a, int b, int la
     } else {
         qr_select_from_mem(score_at, cnt, W, lane, c, v);
     }
+    int row = b * a.P;
     if (lane < W) {
-        const int dst = b * W + lane;
-        const size_t o = (size_t)a.fe_dst_buf * N + dst;
+        const size_t o = (size_t)a.fe_dst_buf * N + b * W + lane;
         if (c >= 0) {
             // what the candidate carried along when it joined the list: three independent loads, no second hop
             const int *info = (const int *)(a.nx_info + (size_t)b * R * W + c);
-            const int src = __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            row = __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int node = __hip_atomic_load(info + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int len = __hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             a.fe_score_all[o] = v;
             a.fe_node_all_w[o] = node;
             a.fe_len_all_w[o] = len;
-            a.beam_src[dst] = src;
         } else {
             a.fe_score_all[o] = -INFINITY;
             a.fe_node_all_w[o] = 0;
             a.fe_len_all_w[o] = 0;
-            a.beam_src[dst] = -1;
         }
+        a.fe_row_all_w[o] = row;
     }
-    if (lane == 0) a.nx_count[b] = 0;
+    qr_list_free_rows(a, b, lane, lane < W && c >= 0, row, sk);
+    if (lane == 0) {
+        a.nx_count[b] = 0;
+        a.n_taken[b] = 0;
+    }
 }
 
 // One iteration of the alignment-length synchronous search for utterance b (one wave; Sec. 2 names the search,
 // the algorithm is the published one).  Lane r < W holds pick r (flat candidate index c = parent*V + token or -1,
 // score v) and, as fin_new, the score with which hypothesis r of the current beam finishes now (-inf: it does not).
-//   - pick r becomes slot r of the next beam: a blank keeps the parent's sequence and state (the network
-//     advance copies inactive rows through), a label extends it;
+//   - pick r becomes slot r of the next beam: a blank keeps the parent's sequence and state, a label extends it;
 //   - recombination: picks that stand for the same label sequence (same length and same 64-bit sequence hash)
 //     are one hypothesis; the best-ranked keeps its slot with log(sum exp(scores)), the others die;
 //   - the running list of the W best finished hypotheses takes the new ones in, ordered by (score descending,
 //     insertion order), new ones in slot order.
-// What lane w < W of the routing wave knows about hypothesis w of the current beam and rank w of the finished
-// list: fetched at the start of the kernel, so that nothing in the routing waits for memory.
+// What lane w < W of the routing wave knows, beyond QrOwn, about hypothesis w of the current beam and rank w of the
+// finished list.
 struct QrAlsdOwn {
-    int len, node;
+    QrOwn h;
     unsigned long long hash;
     float score;
     float fin_score;  int fin_node, fin_len;
@@ -134,27 +184,26 @@ __device__ __forceinline__ QrAlsdOwn qr_alsd_load_own(const QrRouteArgs &a, cons
 {
     const int own = b * a.W + (lane < a.W ? lane : 0);
     QrAlsdOwn o;
-    o.len = a.len_src[own];  o.node = a.node_src[own];  o.hash = s.hash_src[own];  o.score = a.score_src[own];
+    o.h = qr_load_own(a, b, lane);  o.hash = s.hash_src[own];  o.score = a.score_src[own];
     o.fin_score = s.fin_score[own];  o.fin_node = s.fin_node[own];  o.fin_len = s.fin_len[own];
     return o;
 }
 
 __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsdArgs &s, int b, int lane, int c, float v,
-                                              float fin_new, const QrAlsdOwn &o)
+                                              float fin_new, const QrAlsdOwn &o, unsigned *mask)
 {
     const int W = a.W, V = a.V;
     const bool in = lane < W;
     const bool found = in && c >= 0;
     const int par = found ? c / V : 0, tok = found ? c - (c / V) * V : a.blank;
     const bool is_lab = found && tok != a.blank;
-    const int src_slot = b * W + par;
-    const int own = b * W + (in ? lane : 0);
     // the parent's sequence, taken from the lane that holds it
-    const int len_p = __shfl(o.len, par);
-    const int node_p = __shfl(o.node, par);
+    const int len_p = __shfl(o.h.len, par);
+    const int node_p = __shfl(o.h.node, par);
+    const int row_p = __shfl(o.h.row, par);
     const unsigned long long hash_p = ((unsigned long long)(unsigned)__shfl((int)(unsigned)(o.hash >> 32), par) << 32) |
                                       (unsigned long long)(unsigned)__shfl((int)(unsigned)o.hash, par);
-    const int own_node = o.node, own_len = o.len;
+    const int own_node = o.h.node, own_len = o.h.len;
     const int new_len = len_p + (is_lab ? 1 : 0);
     const unsigned long long new_hash = is_lab ? hash_p * 0x9E3779B97F4A7C15ull + (unsigned long long)(tok + 1) : hash_p;
     const int h_lo = (int)(unsigned)new_hash, h_hi = (int)(unsigned)(new_hash >> 32);
@@ -183,14 +232,14 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     if (lane == 0 && km != 0ull && a.live_next) atomicAdd(a.live_next, 1);
     // Reuse of cached hypotheses (Sec. 4.1): the networks' states after a label sequence depend on the sequence
     // alone.  When a live hypothesis of the current beam already holds the sequence this label pick produces (the
-    // usual case: y + k is in the beam and y proposes k again one frame later), the new slot takes over that
-    // hypothesis' states as an inactive row of the advance instead of stepping the networks from y.
+    // usual case: y + k is in the beam and y proposes k again one frame later), the new slot names that
+    // hypothesis' row instead of stepping the networks from y.
     int reuse_slot = -1;
     if (s.reuse) {   // uniform
         const int o_hlo = (int)(unsigned)o.hash, o_hhi = (int)(unsigned)(o.hash >> 32);
         for (int j = 0; j < W; ++j) {
             const bool live_j = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o.score), j)) > -INFINITY;
-            const bool same = live_j && __builtin_amdgcn_readlane(o.len, j) == new_len &&
+            const bool same = live_j && __builtin_amdgcn_readlane(o.h.len, j) == new_len &&
                               __builtin_amdgcn_readlane(o_hlo, j) == h_lo && __builtin_amdgcn_readlane(o_hhi, j) == h_hi;
             if (same && keep && is_lab && reuse_slot < 0) reuse_slot = j;
         }
@@ -199,6 +248,18 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
         const int n_req = (int)__popcll(__ballot(keep && is_lab)), n_hit = (int)__popcll(__ballot(reuse_slot >= 0));
         if (lane == 0 && n_req) atomicAdd(s.stats, n_req);
         if (lane == 0 && n_hit) atomicAdd(s.stats + 1, n_hit);
+    }
+    const bool steps = keep && is_lab && reuse_slot < 0;   // the networks advance for this pick
+    const unsigned long long sm = __ballot(steps);
+    const int k_step = (int)__popcll(sm & ((1ull << lane) - 1ull));
+    const int new_row = __shfl(o.h.free_row, k_step);
+    const int reuse_row = __shfl(o.h.row, reuse_slot >= 0 ? reuse_slot : 0);
+    const int row = steps ? new_row : (reuse_slot >= 0 ? reuse_row : row_p);
+    if (sm != 0ull) {   // uniform; the order of the utterances in the list does not matter
+        int base = 0;
+        if (lane == 0) base = atomicAdd(a.n_rows_next, (int)__popcll(sm));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (steps) a.rows_next[base + k_step] = v4i{new_row, row_p, tok, 0};
     }
     if (in) {
         const int dst = b * W + lane;
@@ -213,19 +274,16 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
             a.node_dst[dst] = node;
             a.len_dst[dst] = new_len;
             s.hash_dst[dst] = new_hash;
-            a.parent_idx[dst] = reuse_slot >= 0 ? b * W + reuse_slot : src_slot;
-            a.token[dst] = tok;
-            a.active[dst] = (is_lab && reuse_slot < 0) ? 1 : 0;
+            a.row_dst[dst] = row;
         } else {
             a.score_dst[dst] = -INFINITY;
             a.node_dst[dst] = 0;
             a.len_dst[dst] = 0;
             s.hash_dst[dst] = 0ull;
-            a.parent_idx[dst] = dst;
-            a.token[dst] = a.blank;
-            a.active[dst] = 0;
+            a.row_dst[dst] = b * a.P;   // any row of the utterance
         }
     }
+    qr_list_free_rows(a, b, lane, keep, row, mask);
     // finished hypotheses
     const float fn = in ? fin_new : -INFINITY;
     if (__ballot(fn > -INFINITY) == 0ull) return;   // uniform
