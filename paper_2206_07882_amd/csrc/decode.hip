@@ -13,10 +13,9 @@ namespace {
 struct NetBuf {
     int8_t *h[QRNNT_MAX_LAYERS];   // [pool + 1][H]; the last row stays zero: the state before the first symbol
     float *c[QRNNT_MAX_LAYERS];    // [pool + 1][H]
-    float *y;                      // [pool][out_rows]
     int32_t *gx0;                  // [V][4*H0]: input projection of layer 0 for every token
     float *tab0;                   // the same as fp32 pre-activation contributions (scales, bias folded in)
-    int8_t *mid_q;                 // [pool][M]: codes of the bottleneck's output (consumed in the same advance)
+    int8_t *mid_q;                 // [pool][M]: codes of the bottleneck's output
 };
 
 struct Plan {
@@ -58,7 +57,6 @@ void take_nets(const qrnnt_model *m, Plan &p, Carver &cv)
             p.net[k].h[l] = cv.take<int8_t>((pool + 1) * net->layer[l].hidden_size);
             p.net[k].c[l] = cv.take<float>((pool + 1) * net->layer[l].hidden_size);
         }
-        p.net[k].y = cv.take<float>(pool * net->out.rows);
         p.net[k].gx0 = cv.take<int32_t>((size_t)m->V * 4 * net->layer[0].hidden_size);
         p.net[k].tab0 = cv.take<float>((size_t)m->V * 4 * net->layer[0].hidden_size);
         p.net[k].mid_q = net->mid.packed ? cv.take<int8_t>(pool * net->mid.rows) : nullptr;
@@ -228,41 +226,49 @@ void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, cons
         }
         qr_launch_lstm_step_group(g, l == 0, st);
     }
-    // Output layers: one grouped launch; a network with a bottleneck sends that layer (fused with the
-    // quantizer of its output) in the first launch and its output layer in a second one.
-    QrLinearGroup lg, lg2;
-    lg.n = lg2.n = 0;
-    lg.gate = lg2.gate = gate;
-    lg.rows = lg2.rows = p.rows;
-    lg.n_rows = lg2.n_rows = n_rows;
+    // The output layers belong to the round that reads them (joint.hip); a bottleneck in front of one is a layer of the
+    // advance, fused with the quantizer of its output.
+    QrLinearGroup lg;
+    lg.n = 0;
+    lg.gate = gate;
+    lg.rows = p.rows;
+    lg.n_rows = n_rows;
+    for (int k = 0; k < 3; ++k) {
+        if (!net_used(m, k) || net_of(m, k)->mid.packed == nullptr) continue;
+        const qrnnt_net *net = net_of(m, k);
+        QrLinearArgs &la = lg.p[lg.n++];
+        la = QrLinearArgs{};
+        la.w = (const v4i *)net->mid.packed;
+        la.nkc = qr_round_up(net->mid.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
+        la.rows = net->mid.rows;  la.s_w = net->mid.row_scale;  la.bias = net->mid_bias;  la.a_scale = net->out_a_scale;
+        la.act = p.net[k].h[net->n_layers - 1];  la.K = net->mid.cols;  la.N = p.N;  la.n_out = pool;
+        la.q_out = p.net[k].mid_q;  la.q_inv = net->mid_inv_scale;  la.q_bits = qr_bits(&net->out);  la.w8 = qr_bits(&net->mid) == 8;
+    }
+    if (lg.n) qr_launch_linear_group(lg, st);
+}
+
+// What a decoding round reads of the model.
+QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj)
+{
+    QrRoundArgs ja = {};
     for (int k = 0; k < 3; ++k) {
         if (!net_used(m, k)) continue;
         const qrnnt_net *net = net_of(m, k);
-        const int top = net->n_layers - 1;
-        const bool has_mid = net->mid.packed != nullptr;
-        QrLinearArgs out = QrLinearArgs{};
-        out.w = (const v4i *)net->out.packed;
-        out.nkc = qr_round_up(net->out.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-        out.rows = net->out.rows;  out.s_w = net->out.row_scale;  out.bias = net->out_bias;
-        out.K = net->out.cols;  out.N = p.N;  out.n_out = pool;  out.w8 = qr_bits(&net->out) == 8;
-        out.y = p.net[k].y;  out.log_softmax = net->log_softmax;
-        if (has_mid) {
-            QrLinearArgs &la = lg.p[lg.n++];
-            la = QrLinearArgs{};
-            la.w = (const v4i *)net->mid.packed;
-            la.nkc = qr_round_up(net->mid.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-            la.rows = net->mid.rows;  la.s_w = net->mid.row_scale;  la.bias = net->mid_bias;  la.a_scale = net->out_a_scale;
-            la.act = p.net[k].h[top];  la.K = net->mid.cols;  la.N = p.N;  la.n_out = pool;
-            la.q_out = p.net[k].mid_q;  la.q_inv = net->mid_inv_scale;  la.q_bits = qr_bits(&net->out);  la.w8 = qr_bits(&net->mid) == 8;
-            out.a_scale = net->mid_scale;  out.act = p.net[k].mid_q;
-            lg2.p[lg2.n++] = out;
-        } else {
-            out.a_scale = net->out_a_scale;  out.act = p.net[k].h[top];
-            lg.p[lg.n++] = out;
-        }
+        QrHeadArgs &h = ja.head[k];
+        h.w = (const v4i *)net->out.packed;  h.s_w = net->out.row_scale;  h.bias = net->out_bias;
+        h.K = net->out.cols;  h.nkc = qr_round_up(net->out.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
+        h.w8 = qr_bits(&net->out) == 8;  h.log_softmax = net->log_softmax;
+        h.act = net->mid.packed ? p.net[k].mid_q : p.net[k].h[net->n_layers - 1];
+        h.a_scale = net->mid.packed ? net->mid_scale : net->out_a_scale;
     }
-    qr_launch_linear_group(lg, st);
-    if (lg2.n) qr_launch_linear_group(lg2, st);
+    ja.enc = enc_proj;
+    ja.w = (const v4i *)m->joint_out.packed;  ja.s_w = m->joint_out.row_scale;  ja.b_out = m->joint_bias;
+    ja.z_scale = m->z_scale;  ja.z_inv = m->z_inv_scale;
+    ja.lambda_src = m->lambda_src;  ja.lambda_ext = m->lambda_ext;  ja.rho = m->rho;
+    ja.J = p.J;  ja.V = p.V;  ja.blank = m->blank;
+    ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
+    ja.w8 = qr_bits(&m->joint_out) == 8;
+    return ja;
 }
 
 // Everything a search starts from: a row of zero states, the first layers' input tables, empty counters and lists
@@ -336,14 +342,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
 
     start_decode(m, p, 2 * (max_sym + 2), p.n_taken, p.nx_count, st);
 
-    QrJointArgs ja = {};
-    ja.enc = enc_proj;  ja.n_enc_rows = T * B;  ja.frame_row = nullptr;  ja.rows_per_utt = W;
-    ja.w = (const v4i *)m->joint_out.packed;  ja.s_w = m->joint_out.row_scale;  ja.b_out = m->joint_bias;
-    ja.z_scale = m->z_scale;  ja.z_inv = m->z_inv_scale;
-    ja.lambda_src = m->lambda_src;  ja.lambda_ext = m->lambda_ext;  ja.rho = m->rho;
-    ja.N = N;  ja.J = p.J;  ja.V = V;  ja.blank = m->blank;
-    ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-    ja.w8 = qr_bits(&m->joint_out) == 8;
+    QrRoundArgs ja = round_args(m, p, enc_proj);
 
     int a0 = 0;   // buffer of the beam at the current frame
     for (int t = 0; t < T; ++t) {
@@ -351,10 +350,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
             const int cur = (v == 0) ? a0 : v;
             const int nxt = v + 1;   // only used when v < max_sym
             ja.frame_base = t * B;
-            ja.pred = p.net[0].y;
-            ja.lp_src = m->use_src ? p.net[1].y : nullptr;
-            ja.lp_ext = m->use_ext ? p.net[2].y : nullptr;
-            ja.row_idx = p.row + (size_t)cur * Ns;
+            ja.row = p.row + (size_t)cur * Ns;
             const int last = (v == max_sym);
             QrRouteArgs ra = {};
             ra.score_src = p.score + (size_t)cur * Ns;
@@ -380,7 +376,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
             ra.rows_next = p.rows;
             ra.n_rows_next = p.n_rows + (size_t)(t & 1) * (max_sym + 2) + v + 1;
             ra.n_rows_clear = p.n_rows + (size_t)((t + 1) & 1) * (max_sym + 2) + v + 1;
-            qr_launch_joint_route(ja, ra, st);
+            qr_launch_search_round(ja, ra, st);
             if (!last) advance_nets(m, p, early ? ra.live_next : nullptr, ra.n_rows_next, st);
         }
         a0 = (a0 == 0) ? ZB : 0;   // the new beam's buffer
@@ -486,22 +482,12 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
     }
     start_decode(m, p, (size_t)ap.n_iter + 2, nullptr, nullptr, st);
 
-    QrJointArgs ja = {};
-    ja.enc = enc_proj;  ja.n_enc_rows = T * B;  ja.frame_row = nullptr;  ja.rows_per_utt = W;  ja.frame_base = 0;
-    ja.w = (const v4i *)m->joint_out.packed;  ja.s_w = m->joint_out.row_scale;  ja.b_out = m->joint_bias;
-    ja.z_scale = m->z_scale;  ja.z_inv = m->z_inv_scale;
-    ja.lambda_src = m->lambda_src;  ja.lambda_ext = m->lambda_ext;  ja.rho = m->rho;
-    ja.N = N;  ja.J = p.J;  ja.V = V;  ja.blank = m->blank;
-    ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-    ja.w8 = qr_bits(&m->joint_out) == 8;
+    QrRoundArgs ja = round_args(m, p, enc_proj);
 
     int cur = 0;
     for (int i = 0; i < ap.n_iter; ++i) {
         const int nxt = cur ^ 1;
-        ja.pred = p.net[0].y;
-        ja.lp_src = m->use_src ? p.net[1].y : nullptr;
-        ja.lp_ext = m->use_ext ? p.net[2].y : nullptr;
-        ja.row_idx = p.row + (size_t)cur * Ns;
+        ja.row = p.row + (size_t)cur * Ns;
         QrRouteArgs ra = {};
         ra.score_src = p.score + (size_t)cur * Ns;
         ra.B = B;  ra.W = W;  ra.V = V;  ra.R = 1;  ra.blank = m->blank;  ra.last_round = 0;
@@ -520,7 +506,7 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
         sa.hash_src = ap.hash + (size_t)cur * Ns;  sa.hash_dst = ap.hash + (size_t)nxt * Ns;
         sa.fin_score = ap.fin_score;  sa.fin_node = ap.fin_node;  sa.fin_len = ap.fin_len;
         sa.reuse = (flags & QRNNT_ALSD_REUSE) ? 1 : 0;  sa.stats = stats;
-        qr_launch_joint_alsd(ja, ra, sa, st);
+        qr_launch_search_round_alsd(ja, ra, sa, st);
         if (i + 1 < ap.n_iter) advance_nets(m, p, ra.live_next, ra.n_rows_next, st);
         cur = nxt;
     }

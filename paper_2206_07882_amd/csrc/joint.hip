@@ -109,236 +109,473 @@ __global__ __launch_bounds__(256) void joint_fuse_kernel(const QrJointArgs a)
         }
 }
 
-// Decoding-loop variant: one block per utterance does the joint + fusion for its W
-// hypotheses (NTW column tiles of 16), and wave 0, which ends up holding every fused
-// score of the utterance in registers, goes straight on to select the W best
-// (parent, token) extensions and to route them (route.h).  The fused scores never
-// touch memory and a decoding round saves a launch.
-// Lane (grp, col) of wave 0 holds, in slot s = 16*nt + 4*mt + i, the candidate
-// (hypothesis w = 16*nt + col, token k = 16*mt + 4*grp + i); its flat index
-// w*V + k grows with s, so the first best slot of a lane is its lowest index.
-// ALSD: the same joint + selection inside the alignment-length synchronous search (route.h, qr_alsd_route):
-// every hypothesis reads its own encoder frame (iteration - labels so far), a blank at the last frame
-// finishes a hypothesis instead of being a candidate, labels beyond the cap are no candidates.
-template <int NTW, bool ALSD>
-__global__ __launch_bounds__(256) void joint_route_kernel(const QrJointArgs a, const QrRouteArgs r, const QrAlsdArgs s)
+// Contraction of one network's output layer inside the decoding-round kernel: NB chunks of 128 columns per batch, all
+// loads of a batch before its first MFMA.  w + woff[mt]: this lane's 16 bytes of chunk 0 of row tile mt; act: this
+// lane's 16 columns of chunk 0 of its hypothesis' codes (K columns in all).  Chunks c0, c0 + step, ...
+// Memory answers in order: the caller requests the row number behind `row` before this asks for the weights, so that
+// the codes follow the weights without a second round trip.  then(): more loads to go with the first batch's codes.
+template <bool W8, int NB, class Then>
+__device__ __forceinline__ void qr_round_mma(const v4i *w, const unsigned (&woff)[4], const int8_t *acts, int row, int K, int nkc,
+                                             int c0, int step, int grp, v4i (&acc)[4], Then &&then)
 {
-    __shared__ v4i lds[4 * 4 * 64];
-    __shared__ float cand[16 * NTW * 64];   // the utterance's candidates by flat index (second attempt of the selection)
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = (int)0xF0F0F0F0u;
+    for (int kc0 = c0; kc0 < nkc; kc0 += NB * step) {
+        v4i p[NB][4][W8 ? 2 : 1], x0[NB], x1[NB];
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+            int kc = kc0 + it * step;
+            kc = kc < nkc ? kc : nkc - 1;   // uniform; what lies beyond the end is not contracted
+            const char *base = (const char *)w + (size_t)kc * (W8 ? 2048 : 1024);
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                p[it][mt][0] = *(const v4i *)(base + woff[mt]);
+                if (W8) p[it][mt][W8 ? 1 : 0] = *(const v4i *)(base + 1024 + woff[mt]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (kc0 == c0) then();
+        const int8_t *act = acts + (int64_t)row * K + grp * 16;
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+            int kc = kc0 + it * step;
+            kc = kc < nkc ? kc : nkc - 1;
+            // (columns beyond K meet zero weights: any valid bytes do)
+            const int k = kc * QRNNT_KCHUNK;
+            x0[it] = *(const v4i *)(act + (k + grp * 16 < K ? k : -grp * 16));
+            x1[it] = *(const v4i *)(act + (k + 64 + grp * 16 < K ? k + 64 : -grp * 16));
+        }
+#pragma unroll
+        for (int it = 0; it < NB; ++it)
+            if (kc0 + it * step < nkc)   // uniform
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    const v4i f = p[it][mt][0];
+                    acc[mt] = qr_mfma(W8 ? f : ((f << 4) & m), x0[it], acc[mt]);
+                    acc[mt] = qr_mfma(W8 ? p[it][mt][W8 ? 1 : 0] : (f & m), x1[it], acc[mt]);
+                }
+    }
+}
+
+// Maximum / sum over the 16 lanes of a row, the same bits in each of them.
+template <class Op>
+__device__ __forceinline__ float qr_row_reduce(float x, Op &&op)
+{
+#define QR_ROW_STEP(ctrl) x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true)));
+    QR_ROW_STEP(0xB1)    // quad_perm [1,0,3,2]
+    QR_ROW_STEP(0x4E)    // quad_perm [2,3,0,1]
+    QR_ROW_STEP(0x141)   // row_half_mirror
+    QR_ROW_STEP(0x140)   // row_mirror
+#undef QR_ROW_STEP
+    return x;
+}
+
+// A candidate of a selection in one word: larger is better under (value descending, index ascending); 0: none.
+typedef unsigned long long QrCand;
+__device__ __forceinline__ QrCand qr_cand(unsigned key, int idx) { return ((QrCand)key << 32) | (unsigned)~idx; }
+__device__ __forceinline__ int qr_cand_index(QrCand c) { return (int)~(unsigned)c; }
+__device__ __forceinline__ float qr_cand_value(QrCand c) { return qr_key_float((unsigned)(c >> 32)); }
+
+// Rank of every one of the M candidates in list[] (no two equal): the best W go to best[rank].  256 threads: four count
+// for one candidate, 64 candidates at a time.
+__device__ __forceinline__ void qr_rank(const QrCand *list, int M, int W, int tid, QrCand *best)
+{
+    for (int i0 = 0; i0 < M; i0 += 64) {   // uniform
+        const int i = i0 + (tid >> 2);
+        const QrCand mine = list[i < M ? i : 0];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = tid & 3; j < M; j += 4) rank += list[j] > mine ? 1 : 0;
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, true);
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, true);
+        if ((tid & 3) == 0 && i < M && rank < W) best[rank] = mine;
+    }
+}
+
+// One decoding round of an utterance in one workgroup: output layers of the three networks, joint, log-softmax and
+// fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
+// (route.h), and after the last round of a frame the new beam.  Between the networks' top hidden codes and the picks
+// nothing touches memory.
+//   contraction, waves 0-3: the prediction network's output layer and the joint.  A wave owns 64-column blocks of the
+//     joint: it contracts the 64 rows of the output layer that produce them, 16 to an MFMA, dealt so that a lane ends
+//     up with the 16 consecutive columns that are its operand of the joint's contraction (row r of tile mt is row
+//     16*(r/4) + 4*mt + r%4 of the block).
+//   contraction, waves 4-5, 6-7: output layer of the source and of the external LM, K split in two.
+//   scores, waves 0-3: the partial sums meet in LDS (16-byte pieces swizzled by token quartet); 16 lanes share a
+//     hypothesis, four tokens each, and form the three log-softmaxes and the fused score together.
+//   selection, waves 0-3: the W-th best of the best ones of 64 groups of candidates or more bounds the W-th best
+//     candidate from below; what passes the bound is gathered in LDS and ranked by counting.
+// The kernel is bound by its chain of dependent steps, and the chain by one compute unit's path to L2 (150 KB of weights
+// and 80 KB of codes, 64 bytes a cycle) and by single waves running straight-line code, hence the split of every step
+// over four waves.  Measured, one utterance at beam 16: 10.1 us, where a launch for
+// the output layers and one for joint, selection and routing in single waves took 7.0 + 10.9 us.
+// ALSD: the same inside the alignment-length synchronous search (route.h, qr_alsd_route): every hypothesis reads its
+// own encoder frame (iteration - labels so far), a blank at the last frame finishes a hypothesis instead of being a
+// candidate, labels beyond the cap are no candidates.
+template <int NTW, bool ALSD>
+__global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
+{
+    constexpr int MAX_LIST = ALSD ? 1 : 16 * NTW * 17;   // a frame's candidates: W blanks in each of at most 17 rounds
+    __shared__ v4i sums[8][4][64];          // [wave][row tile][lane, swizzled] partial sums; then the gathered candidates
+    __shared__ unsigned group_best[NTW * 256];
+    __shared__ QrCand list[MAX_LIST], best[64], best_fe[64];
+    __shared__ int list_row[MAX_LIST], list_node[MAX_LIST], list_len[MAX_LIST];
+    __shared__ float fin_new[64];           // ALSD: value of hypothesis w finishing now
+    __shared__ __attribute__((aligned(16))) float jc[3][2][64];   // row scales and biases: joint, source LM, external LM
+    __shared__ __attribute__((aligned(16))) float pc[4][2][64];   // [wave] those of the prediction network's 64 rows at hand
+    __shared__ unsigned mask[64];
+    __shared__ int n_cand, n_list;
+    QrCand *const gathered = (QrCand *)&sums[0][0][0];
+    static_assert(sizeof(sums) >= 16 * 4 * 64 * sizeof(QrCand), "all candidates of 64 hypotheses x 64 tokens");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
     const int b = blockIdx.x;
     const int W = r.W, V = a.V, J = a.J;
-    if (r.gate && *r.gate == 0) {   // uniform: no utterance carried a label into this round, nothing can be picked
-        if (ALSD) return;           // no live hypothesis anywhere: the finals stay as they are
-        if (wave == 0) {
-            if (lane == 0 && b == 0 && r.live_clear) *r.live_clear = 0;
-            if (lane == 0 && b == 0 && r.n_rows_clear) *r.n_rows_clear = 0;
-            if (r.last_round) qr_frame_end(r, b, lane, r.nx_count[b], (unsigned *)lds, (int *)lds + 64);
+    const bool frame_end = !ALSD && r.last_round;
+    const int n_entries = r.R * W;
+    const size_t nx = (size_t)b * n_entries;
+    const v4i zero = {0, 0, 0, 0};
+    const int m = (int)0xF0F0F0F0u;
+
+    // The new beam of the frame: the W best of the candidate list in LDS (n_list of them) by (score descending,
+    // insertion order), each with its trie node, length and pool row; the rows it does not name are free again.
+    auto finish_frame = [&]() {
+        __syncthreads();
+        if (wave < 4) qr_rank(list, n_list, W, tid, best_fe);
+        __syncthreads();
+        if (wave != 0) return;
+        const QrCand p = best_fe[lane];
+        const bool found = lane < W && p != 0;
+        const int c = found ? qr_cand_index(p) : 0;
+        int row = b * r.P;
+        if (lane < W) {
+            const size_t o = (size_t)r.fe_dst_buf * r.B * W + b * W + lane;
+            row = found ? list_row[c] : row;
+            r.fe_score_all[o] = found ? qr_cand_value(p) : -INFINITY;
+            r.fe_node_all_w[o] = found ? list_node[c] : 0;
+            r.fe_len_all_w[o] = found ? list_len[c] : 0;
+            r.fe_row_all_w[o] = row;
         }
+        if (lane == 0) {
+            r.nx_count[b] = 0;
+            r.n_taken[b] = 0;
+        }
+        qr_list_free_rows(r, b, lane, found, row, mask);
+    };
+    auto list_entry = [&](int e, float v, const v4i &info) {
+        list[e] = qr_cand(qr_float_key(v + 0.0f), e);   // + 0: one key per value
+        list_row[e] = info[0];
+        list_node[e] = info[1];
+        list_len[e] = info[2];
+    };
+
+    if (!ALSD && r.gate && *r.gate == 0) {   // uniform: no utterance carried a label into this round, nothing can be picked
+        if (tid == 0 && b == 0 && r.live_clear) *r.live_clear = 0;
+        if (tid == 0 && b == 0 && r.n_rows_clear) *r.n_rows_clear = 0;
+        if (!frame_end) return;
+        const int n0 = r.nx_count[b];
+        for (int e = tid; e < n0; e += 512) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
+        if (tid == 0) n_list = n0;
+        if (tid < 64) best_fe[tid] = 0;
+        finish_frame();
         return;
     }
-    int fr = a.frame_base + b;
-    fr = fr < 0 ? 0 : (fr >= a.n_enc_rows ? a.n_enc_rows - 1 : fr);
-    const float *e_utt = a.enc + (int64_t)fr * J + grp * 16;
-    const float z_inv = a.z_inv;
-    const int zbits = a.w8 ? 8 : 4;
+
     const int n_row_tiles = (V + 15) >> 4;
-    constexpr int PER = 16 * NTW;
-    float val[PER];
-    float *fin_new = (float *)lds + 256;   // ALSD: value of hypothesis w finishing now; wave 0's own part of the buffer
+    if (wave >= 4) {   // (the waves with less to do)
+        const int k = (wave - 4) * 64 + lane;
+        if (k < 64) best[k] = 0;
+        else if (k < 128) best_fe[k - 64] = 0;
+        else if (k < 192) fin_new[k - 128] = -INFINITY;
+        else if (k == 192) n_cand = 0;
+        const int kk = lane < V ? lane : V - 1;
+        if (wave < 7) {
+            const int q = wave - 4;   // joint, source LM, external LM
+            const float *sw = q == 0 ? a.s_w : a.head[q].s_w, *bs = q == 0 ? a.b_out : a.head[q].bias;
+            jc[q][0][lane] = sw ? (q == 0 ? a.z_scale : a.head[q].a_scale) * sw[kk] : 0.0f;
+            jc[q][1][lane] = bs ? bs[kk] : 0.0f;
+        }
+    }
+    // What the routing wave and the scoring threads will need: requested first, used last.
     QrOwn own = {};
     QrAlsdOwn alsd_own = {};
-    int nx0 = 0;   // length of the utterance's candidate list before this round
-    if (ALSD && wave == 0) {
-        fin_new[lane] = -INFINITY;
-        alsd_own = qr_alsd_load_own(r, s, b, lane);
-    }
-    if (!ALSD && wave == 0) {   // what the routing will need of this lane's hypothesis (its blank picks carry it into the candidate list)
+    QrAlsdFinished finished = {};
+    int nx0 = 0;                // length of the utterance's candidate list before this round
+    float sc[NTW];              // the thread's hypotheses in the scores (16 * nt + tid / 16): running score, length
+    int len_t[NTW];
+    if (wave == 0) {
         own = qr_load_own(r, b, lane);
-        nx0 = r.nx_count[b];
+        if (ALSD) alsd_own = qr_alsd_load_own(r, s, b, lane);
+        else nx0 = r.nx_count[b];
     }
-    // per-token constants of this lane's 16 tokens (fetched behind the first tile's operands, see qr_head_mma)
-    float wscale[4][4], wbias[4][4];
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) {
+        const int w = nt * 16 + ((tid >> 4) & 15);
+        const int n = b * W + (w < W ? w : W - 1);
+        sc[nt] = wave < 4 ? r.score_src[n] : 0.0f;
+        len_t[nt] = (ALSD && wave < 4) ? r.len_src[n] : 0;
+    }
+    unsigned key[NTW][4];
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
         const int w = nt * 16 + col;
-        const bool wv = w < W;
-        const int n = b * W + (wv ? w : W - 1);
-        const int64_t nrow = a.row_idx[n];   // where this hypothesis' network outputs are
-        const float *p = a.pred + nrow * J + grp * 16;
-        const float *e = e_utt;
-        int len_w = 0, t_w = 0;
-        if (ALSD) {   // this hypothesis' own frame
-            len_w = r.len_src[n];
-            t_w = s.iter - len_w;
-            t_w = t_w < 0 ? 0 : (t_w > s.T - 1 ? s.T - 1 : t_w);
-            e = a.enc + ((int64_t)t_w * r.B + b) * J + grp * 16;
-        }
-        auto bload = [&](int kb) -> QrJointRaw {
-            QrJointRaw raw = {};
-            if (kb * 64 + grp * 16 < J) {
+        const int n = b * W + (w < W ? w : W - 1);
+        const int row = a.row[n];
+        if (nt > 0) __syncthreads();   // what the previous tile left in LDS has been read
+        v4i acc[4] = {zero, zero, zero, zero};
+        if (wave < 4) {
+            const QrHeadArgs &h = a.head[0];
+            const int n_pred_tiles = J >> 4;
+            const int zbits = a.w8 ? 8 : 4;
+            const int len = ALSD ? r.len_src[n] : 0;
+            for (int jb = wave; jb * 64 < J; jb += 4) {
+                const bool jv = jb * 64 + grp * 16 < J;
+                const int j0 = jv ? jb * 64 + grp * 16 : 0;   // this lane's 16 columns
+                // row constants of the block
+                const int j = jb * 64 + lane < J ? jb * 64 + lane : J - 1;
+                const float sw = h.s_w[j], bs = h.bias ? h.bias[j] : 0.0f;   // of row `lane` of the block
+                int rt = 4 * jb + (col >> 2);
+                rt = rt < n_pred_tiles ? rt : n_pred_tiles - 1;
+                unsigned woff[4];   // (a matrix of 2 GiB would have to have 4 million rows)
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    raw.e[d] = *(const v4f *)(e + kb * 64 + 4 * d);
-                    raw.p[d] = *(const v4f *)(p + kb * 64 + 4 * d);
-                }
-            }
-            return raw;
-        };
-        auto bmake = [&](const QrJointRaw &raw, int kb) -> v4i {
-            v4i bq = {0, 0, 0, 0};
-            if (kb * 64 + grp * 16 < J) {
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    uint32_t word = 0;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float z = qr_tanh(raw.e[d][i] * raw.p[d][i]);
-                        word |= (uint32_t)(qr_quant(z, z_inv, zbits) & 0xFF) << (8 * i);
+                for (int mt = 0; mt < 4; ++mt) woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + (grp * 16 + 4 * mt + (col & 3)) * 16;
+                v4f e[4];
+                auto load_frame = [&]() {
+                    int64_t fr = a.frame_base + b;
+                    if (ALSD) {   // this hypothesis' own frame
+                        int t_w = s.iter - len;
+                        t_w = t_w < 0 ? 0 : (t_w > s.T - 1 ? s.T - 1 : t_w);
+                        fr = (int64_t)t_w * r.B + b;
                     }
-                    bq[d] = (int)word;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) e[d] = *(const v4f *)(a.enc + fr * J + j0 + 4 * d);
+                };
+                v4i accp[4] = {zero, zero, zero, zero};
+                if (h.w8) qr_round_mma<true, NTW == 1 ? 3 : 1>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
+                else qr_round_mma<false, NTW == 1 ? 6 : 2>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
+                // the block's weights of the joint arrive while its codes are formed
+                v4i wj[4];
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
+                    wj[mt] = a.w8 ? a.w[((size_t)rt * a.nkc * 2 + jb) * 64 + lane] : a.w[((size_t)rt * a.nkc + (jb >> 1)) * 64 + lane];
                 }
-            }
-            return bq;
-        };
-        // LM log-probabilities, the running score and (first tile) the per-token constants: what only the
-        // epilogue of wave 0 needs
-        float ls[4][4], le[4][4], sc = 0.0f;
-        auto epilogue_loads = [&]() {
-            if (wave == 0) {
-                sc = r.score_src[(int64_t)b * W + (wv ? w : W - 1)];
+                // the wave's own 64 constants change places: a lane takes those of its 16 columns
+                pc[wave][0][lane] = h.a_scale * sw;
+                pc[wave][1][lane] = bs;
+                __builtin_amdgcn_wave_barrier();
+                v4i z = zero;
+                if (jv)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const v4f swd = *(const v4f *)&pc[wave][0][grp * 16 + 4 * d], bsd = *(const v4f *)&pc[wave][1][grp * 16 + 4 * d];
+                        uint32_t word = 0;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int sum = h.w8 ? accp[d][i] : (accp[d][i] >> 4);   // 4-bit operands carry a factor 16
+                            const float p = swd[i] * (float)sum + bsd[i];
+                            word |= (uint32_t)(qr_quant(qr_tanh(e[d][i] * p), a.z_inv, zbits) & 0xFF) << (8 * i);
+                        }
+                        z[d] = (int)word;
+                    }
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int k = mt * 16 + grp * 4 + i;
-                        const int kk = k < V ? k : V - 1;
-                        ls[mt][i] = a.lp_src ? a.lp_src[nrow * V + kk] : 0.0f;
-                        le[mt][i] = a.lp_ext ? a.lp_ext[nrow * V + kk] : 0.0f;
-                        if (nt == 0) {
-                            wscale[mt][i] = a.z_scale * a.s_w[kk];
-                            wbias[mt][i] = a.b_out ? a.b_out[kk] : 0.0f;
-                        }
-                    }
+                    acc[mt] = qr_mfma(a.w8 ? wj[mt] : ((jb & 1) ? (wj[mt] & m) : ((wj[mt] << 4) & m)), z, acc[mt]);
             }
-        };
-        v4i acc[4];
-        if (nt > 0) __syncthreads();   // the reduction buffer of the previous tile has been read
-        qr_head_mma<1>(a.w, a.nkc, n_row_tiles, 0, J, bload, bmake, epilogue_loads, acc, lds, a.w8 != 0);
-        if (wave == 0) {
-            float v[4][4];
-            float m = -INFINITY;
+        } else {
+            const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
+            // besides, the frame's candidates so far (the last round's list), the list of finished hypotheses
+            float e_score = 0.0f;
+            v4i e_info = zero;
+            const int e0 = tid - 256;
+            if (frame_end && nt == 0 && e0 < n_entries) {
+                e_score = r.nx_score[nx + e0];
+                e_info = r.nx_info[nx + e0];
+            }
+            if (ALSD && nt == 0 && wave == 5) finished = qr_alsd_load_finished(r, s, b, lane);
+            if (h.w) {   // uniform
+                unsigned woff[4];
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = mt * 16 + grp * 4 + i;
-                    v[mt][i] = k < V ? wscale[mt][i] * (float)acc[mt][i] + wbias[mt][i] : -INFINITY;
-                    m = fmaxf(m, v[mt][i]);
+                for (int mt = 0; mt < 4; ++mt) {
+                    const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
+                    woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
                 }
-            m = fmaxf(m, __shfl_xor(m, 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
+                if (h.w8) qr_round_mma<true, NTW == 1 ? 2 : 1>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
+                else qr_round_mma<false, NTW == 1 ? 4 : 2>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
+            }
+            if (frame_end && nt == 0) {
+                if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
+                for (int e = e0 + 256; e < n_entries; e += 256) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][grp * 16 + (col ^ (4 * mt + grp))] = acc[mt];
+        if (ALSD && r.gate && *r.gate == 0) return;   // uniform: no live hypothesis anywhere, the finals stay as they are
+        __syncthreads();
+        if (wave >= 4) continue;
+
+        // ---- scores: hypothesis 16 * nt + hc, tokens 4 * quad .. 4 * quad + 3
+        const int hc = tid >> 4, quad = lane & 15, mt = quad >> 2;
+        const int at = (quad & 3) * 16 + (hc ^ quad), k0 = 4 * quad;
+        auto add = [](float x, float y) { return x + y; };
+        auto max_of = [](float x, float y) { return fmaxf(x, y); };
+        v4f v[3];   // joint, source LM, external LM
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bool w8 = q == 0 ? a.w8 != 0 : a.head[q].w8 != 0;
+            v4i t = sums[q == 0 ? 0 : 2 + 2 * q][mt][at] + sums[q == 0 ? 1 : 3 + 2 * q][mt][at];
+            if (q == 0) t += sums[2][mt][at] + sums[3][mt][at];
+            t = w8 ? t : (t >> 4);   // 4-bit operands carry a factor 16
+            const v4f ws = *(const v4f *)&jc[q][0][k0], wb = *(const v4f *)&jc[q][1][k0];
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[q][i] = k0 + i < V ? ws[i] * (float)t[i] + wb[i] : -INFINITY;
+                mx = fmaxf(mx, v[q][i]);
+            }
+            mx = qr_row_reduce(mx, max_of);
             float sum = 0.0f;
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sum += (mt * 16 + grp * 4 + i < V) ? qr_exp(v[mt][i] - m) : 0.0f;
-            sum += __shfl_xor(sum, 16);
-            sum += __shfl_xor(sum, 32);
-            const float lse = m + qr_log(sum);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = mt * 16 + grp * 4 + i;
-                    float f = v[mt][i] - lse;
-                    if (k != a.blank) {
-                        if (a.lp_src) f -= a.lambda_src * ls[mt][i];
-                        if (a.lp_ext) f += a.lambda_ext * le[mt][i];
-                        f += a.rho;
-                    }
-                    // an empty slot (score -inf) offers nothing, whatever its rows of the network outputs hold
-                    bool ok = wv && k < V && sc > -INFINITY && (ALSD || !r.last_round || k == a.blank);
-                    if (ALSD) {
-                        if (k != a.blank && len_w >= s.u_max) ok = false;      // label cap
-                        if (k == a.blank && t_w == s.T - 1) {                  // a blank at the last frame finishes w
-                            if (ok && sc > -INFINITY) fin_new[w] = sc + f;
-                            ok = false;
-                        }
-                    }
-                    val[nt * 16 + mt * 4 + i] = ok ? (sc + f) + 0.0f : -INFINITY;   // + 0: one key per value
-                }
+            for (int i = 0; i < 4; ++i) sum += qr_exp(v[q][i] - mx);   // (exp(-inf) = 0 behind the last token)
+            sum = qr_row_reduce(sum, add);
+            float lse = mx + qr_log(sum);
+            if (q > 0 && !a.head[q].log_softmax) lse = 0.0f;
+            v[q] = v[q] - lse;
         }
+        const int ws_ = nt * 16 + hc;
+        int t_w = s.iter - len_t[nt];
+        t_w = t_w < 0 ? 0 : (t_w > s.T - 1 ? s.T - 1 : t_w);
+        unsigned top = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = k0 + i;
+            float f = v[0][i];
+            if (k != a.blank) {
+                if (a.head[1].w) f -= a.lambda_src * v[1][i];
+                if (a.head[2].w) f += a.lambda_ext * v[2][i];
+                f += a.rho;
+            }
+            // an empty slot (score -inf) offers nothing, whatever its row of the networks' states holds
+            bool ok = ws_ < W && k < V && sc[nt] > -INFINITY && (ALSD || !r.last_round || k == a.blank);
+            if (ALSD) {
+                if (k != a.blank && len_t[nt] >= s.u_max) ok = false;      // label cap
+                if (k == a.blank && t_w == s.T - 1) {                      // a blank at the last frame finishes the hypothesis
+                    if (ok) fin_new[ws_] = sc[nt] + f;
+                    ok = false;
+                }
+            }
+            const float val = (sc[nt] + f) + 0.0f;   // + 0: one key per value
+            key[nt][i] = (ok && val > -INFINITY) ? qr_float_key(val) : 0u;
+            top = key[nt][i] > top ? key[nt][i] : top;
+        }
+        group_best[nt * 256 + tid] = top;
     }
-    if (wave != 0) return;
+    if (wave == 0) own.free_row = qr_free_row(r, b, lane, own.taken);
+    __syncthreads();
 
     // ---- the W best under (value descending, flat index ascending)
-    const int cbase = col * V + grp * 4;   // flat index of slot s: cbase + (s>>4)*16*V + ((s>>2)&3)*16 + (s&3)
-    auto index_of = [&](int s) { return cbase + (s >> 4) * 16 * V + ((s >> 2) & 3) * 16 + (s & 3); };
-    float last_v = INFINITY;
-    int last_c = -1, my_c = -1;
-    float my_v = -INFINITY;
-    bool fast = qr_select_pruned<PER>(val, index_of, W, lane, (unsigned *)lds, (int *)lds + 64, my_c, my_v);
-    if (!fast) {   // uniform
-        // More than 64 candidates passed the bound: the MFMA layout keeps a hypothesis' tokens in 4 lanes, and when
-        // the best candidates of the utterance belong to one or two hypotheses a lane's best says little.  The
-        // candidates change places through LDS (lane l takes the flat indices l, l + 64, ...: every hypothesis is
-        // then spread over all lanes and the bound is tight) and the pruned selection runs again.
+    if (wave < 4) {
+        // Up to 16 hypotheses: 64 groups, lane l looks at quartet l % 16 of hypotheses l / 16 + 4, 8, ...  More: every
+        // quartet of every hypothesis is a group (with 64 groups 64 picks would bound nothing: 1.6 ms a frame at W = 64).
+        // Distances from the best of all make the bits that tell candidates apart come early, and 16 of them will do.
+        constexpr int NG = NTW == 1 ? 1 : 4 * NTW;   // groups per lane
+        unsigned g[NG], all = 0u;
 #pragma unroll
-        for (int sl = 0; sl < PER; ++sl) {
-            const int w = (sl >> 4) * 16 + col, k = ((sl >> 2) & 3) * 16 + grp * 4 + (sl & 3);
-            if (w < W && k < V) cand[w * V + k] = val[sl];
+        for (int i = 0; i < NG; ++i) g[i] = 0u;
+#pragma unroll
+        for (int i = 0; i < 4 * NTW; ++i) {
+            const unsigned o = group_best[i * 64 + lane];
+            g[i % NG] = o > g[i % NG] ? o : g[i % NG];
+            all = o > all ? o : all;
         }
-        __builtin_amdgcn_wave_barrier();
-        const int n_cand = W * V;
+        all = qr_wave_reduce_u32<true>(all);
+        const float v_max = qr_key_float(all);
+        auto nearness = [&](unsigned k) -> unsigned {   // larger is nearer; 0: no candidate (the best may be +inf: no difference then)
+            return k == 0u ? 0u : (k == all ? 0x7FFFFFFFu : 0x7FFFFFFFu - __float_as_uint(v_max - qr_key_float(k)));
+        };
 #pragma unroll
-        for (int sl = 0; sl < PER; ++sl) val[sl] = (lane + 64 * sl < n_cand) ? cand[lane + 64 * sl] : -INFINITY;
-        __builtin_amdgcn_wave_barrier();
-        auto index_t = [&](int sl) { return lane + 64 * sl; };
-        fast = qr_select_pruned<PER>(val, index_t, W, lane, (unsigned *)lds, (int *)lds + 64, my_c, my_v);
-        for (int rd = 0; !fast && rd < W; ++rd) {   // general case: W rounds of arg-best
-            float bv = -INFINITY;
-            int bc = 0x7fffffff;
+        for (int i = 0; i < NG; ++i) g[i] = nearness(g[i]);
+        unsigned T = 0u;
+        for (int bit = 30; bit >= 15; --bit) {
+            const unsigned trial = T | (1u << bit);
+            int cnt = 0;
 #pragma unroll
-            for (int sl = 0; sl < PER; ++sl) {
-                const int c = lane + 64 * sl;
-                const float v = val[sl];
-                const bool ok = v > -INFINITY && (v < last_v || (v == last_v && c > last_c));
-                if (ok && v > bv) { bv = v; bc = c; }   // slots are visited in index order: first best wins
+            for (int i = 0; i < NG; ++i) cnt += (int)__popcll(__ballot(g[i] >= trial));
+            if (cnt >= W) T = trial;   // uniform
+            if (cnt == W) break;
+        }
+        T = T ? T : 1u;   // fewer than W groups hold a candidate: every candidate passes
+        int n_keep = 0;
+        bool keep[NTW][4];
+        unsigned long long bal[NTW][4];
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                keep[nt][i] = nearness(key[nt][i]) >= T;
+                bal[nt][i] = __ballot(keep[nt][i]);
+                n_keep += (int)__popcll(bal[nt][i]);
             }
-            if (!qr_select_round(bv, bc, rd, lane, last_v, last_c, my_c, my_v)) break;
+        int base = 0;
+        if (lane == 0 && n_keep) base = atomicAdd(&n_cand, n_keep);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned long long bm = bal[nt][i];
+                const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bm, 0u));
+                if (keep[nt][i]) gathered[pos] = qr_cand(key[nt][i], (nt * 16 + (tid >> 4)) * V + 4 * (lane & 15) + i);
+                base += (int)__popcll(bm);
+            }
+    }
+    __syncthreads();
+    if (wave < 4) qr_rank(gathered, n_cand, W, tid, best);
+    __syncthreads();
+    if (wave == 0) {
+        const QrCand p = best[lane];
+        const bool found = lane < W && p != 0;
+        const int my_c = found ? qr_cand_index(p) : -1;
+        const float my_v = found ? qr_cand_value(p) : -INFINITY;
+        if (ALSD) {
+            alsd_own.h = own;
+            qr_alsd_route(r, s, b, lane, my_c, my_v, alsd_own, mask);
+        } else {
+            const int cnt = qr_route_picks(r, b, lane, my_c, my_v, own, nx0, [&](int e, float v, const v4i &info) {
+                if (frame_end) {
+                    list_entry(e, v, info);
+                } else {
+                    r.nx_score[nx + e] = v;
+                    r.nx_info[nx + e] = info;
+                }
+            });
+            if (lane == 0) {
+                if (frame_end) n_list = cnt;
+                else r.nx_count[b] = cnt;
+            }
         }
     }
-    if (ALSD) {
-        __builtin_amdgcn_wave_barrier();
-        qr_alsd_route(r, s, b, lane, my_c, my_v, fin_new[lane], alsd_own, (unsigned *)lds);
-        return;
-    }
-    const int cnt = qr_route_picks(r, b, lane, my_c, my_v, own, nx0);
-    if (r.last_round) {   // the frame is complete for this utterance: prune its candidate list to the new beam
-        __threadfence();
-        qr_frame_end(r, b, lane, cnt, (unsigned *)lds, (int *)lds + 64);
-    }
+    if (ALSD && wave == 5) qr_alsd_finish(s, b, W, lane, fin_new[lane], finished);
+    if (frame_end) finish_frame();
 }
 
 }  // namespace
 
-void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, hipStream_t st)
+void qr_launch_search_round(const QrRoundArgs &a, const QrRouteArgs &r, hipStream_t st)
 {
     const QrAlsdArgs none = {};
     const unsigned grid = (unsigned)r.B;
-    if (r.W <= 16) joint_route_kernel<1, false><<<grid, 256, 0, st>>>(a, r, none);
-    else if (r.W <= 32) joint_route_kernel<2, false><<<grid, 256, 0, st>>>(a, r, none);
-    else joint_route_kernel<4, false><<<grid, 256, 0, st>>>(a, r, none);
+    if (r.W <= 16) search_round_kernel<1, false><<<grid, 512, 0, st>>>(a, r, none);
+    else if (r.W <= 32) search_round_kernel<2, false><<<grid, 512, 0, st>>>(a, r, none);
+    else search_round_kernel<4, false><<<grid, 512, 0, st>>>(a, r, none);
 }
 
-void qr_launch_joint_alsd(const QrJointArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
+void qr_launch_search_round_alsd(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
-    if (r.W <= 16) joint_route_kernel<1, true><<<r.B, 256, 0, st>>>(a, r, s);
-    else if (r.W <= 32) joint_route_kernel<2, true><<<r.B, 256, 0, st>>>(a, r, s);
-    else joint_route_kernel<4, true><<<r.B, 256, 0, st>>>(a, r, s);
+    if (r.W <= 16) search_round_kernel<1, true><<<r.B, 512, 0, st>>>(a, r, s);
+    else if (r.W <= 32) search_round_kernel<2, true><<<r.B, 512, 0, st>>>(a, r, s);
+    else search_round_kernel<4, true><<<r.B, 512, 0, st>>>(a, r, s);
 }
 
 void qr_launch_joint(const QrJointArgs &a, hipStream_t st)

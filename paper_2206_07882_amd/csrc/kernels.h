@@ -80,7 +80,24 @@ struct QrJointArgs {
     int N, J, V, blank, nkc;
     float *lp_out;  int8_t *dbg_zq;  float *fused;
     int w8;                            // 8-bit output layer: 8-bit weights and an 8-bit quantizer on z
-    const int32_t *row_idx;            // decoding loop: hypothesis n reads row row_idx[n] of pred / lp_src / lp_ext
+};
+
+// A decoding round (joint.hip): output layers, joint and fusion of every utterance's hypotheses.
+struct QrHeadArgs {                    // output layer of one network
+    const v4i *w;                      // null: the network is not used
+    const float *s_w, *bias;
+    const int8_t *act;                 // [pool][K] codes it reads
+    int K, nkc, w8, log_softmax;
+    float a_scale;
+};
+struct QrRoundArgs {
+    QrHeadArgs head[3];                // prediction network (J rows), source and external LM (V rows)
+    const float *enc;  int frame_base; // time-synchronous search: utterance b reads row frame_base + b
+    const int32_t *row;                // [N] pool row of every hypothesis
+    const v4i *w;  const float *s_w;  const float *b_out;   // the joint's output layer
+    float z_scale, z_inv;
+    float lambda_src, lambda_ext, rho;
+    int J, V, blank, nkc, w8;
 };
 
 struct QrRouteArgs {
@@ -153,7 +170,7 @@ QR_HIDDEN void qr_launch_input_projection(const qrnnt_lstm *L, const int8_t *x_c
 QR_HIDDEN void qr_launch_linear_group(const QrLinearGroup &g, hipStream_t st);
 QR_HIDDEN void qr_launch_linear(const QrLinearArgs &a, hipStream_t st);
 QR_HIDDEN void qr_launch_joint(const QrJointArgs &a, hipStream_t st);
-QR_HIDDEN void qr_launch_joint_route(const QrJointArgs &a, const QrRouteArgs &r, hipStream_t st);
-QR_HIDDEN void qr_launch_joint_alsd(const QrJointArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st);
+QR_HIDDEN void qr_launch_search_round(const QrRoundArgs &a, const QrRouteArgs &r, hipStream_t st);
+QR_HIDDEN void qr_launch_search_round_alsd(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st);
 QR_HIDDEN void qr_launch_beam(const float *score, const float *fused, int B, int W, int V, int blank, int force_blank,
                               int32_t *parent_out, int32_t *token_out, float *score_out, hipStream_t st);

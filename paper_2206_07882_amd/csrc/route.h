@@ -18,8 +18,8 @@
 // kernel, so that nothing in the routing waits for memory.
 struct QrOwn {
     int node, len, row;
-    int free_row;                      // the utterance's w-th free row of the pool
-    int taken;                         // its rows taken by earlier rounds of the frame (uniform)
+    int taken;                         // rows of the pool that earlier rounds of the frame have taken (uniform)
+    int free_row;                      // the utterance's w-th free row after those (qr_free_row)
 };
 
 __device__ __forceinline__ QrOwn qr_load_own(const QrRouteArgs &a, int b, int lane)
@@ -30,10 +30,15 @@ __device__ __forceinline__ QrOwn qr_load_own(const QrRouteArgs &a, int b, int la
     own.len = a.len_src[o];
     own.row = a.row_src[o];
     own.taken = a.n_taken ? a.n_taken[b] : 0;
-    int f = own.taken + lane;          // (a pick never needs more than there are, see the pool's size in decode.hip)
-    f = f < a.P ? f : a.P - 1;
-    own.free_row = a.free_rows[(size_t)b * a.P + f];
+    own.free_row = 0;
     return own;
+}
+
+__device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane, int taken)
+{
+    int f = taken + lane;              // (a pick never needs more than there are, see the pool's size in decode.hip)
+    f = f < a.P ? f : a.P - 1;
+    return a.free_rows[(size_t)b * a.P + f];
 }
 
 // The utterance's free rows for what follows: all of its P rows except the ones that lanes with `held` name.
@@ -60,8 +65,10 @@ __device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, i
 
 // Returns the length of the utterance's candidate list after this round (uniform).
 // own: hypothesis `lane` of the current round; a pick reads its parent's from that lane.
-// nx0: the length of the utterance's candidate list before this round (a.nx_count[b], fetched early as well).
-__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0)
+// nx0: the length of the utterance's candidate list before this round (a.nx_count[b], fetched early as well);
+// add(e, score, info) puts a candidate at its end.
+template <class Add>
+__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0, Add &&add)
 {
     if (lane == 0 && b == 0 && a.live_clear) *a.live_clear = 0;
     if (lane == 0 && b == 0 && a.n_rows_clear) *a.n_rows_clear = 0;
@@ -77,23 +84,21 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     const int k_lab = (int)__popcll(lm & lt);            // this pick's number among the label picks
     const int new_row = __shfl(own.free_row, k_lab);
     if (is_blank) {
-        const int e = nx0 + __popcll(bm & lt);
-        a.nx_score[(size_t)b * a.R * W + e] = v;
-        a.nx_info[(size_t)b * a.R * W + e] = v4i{par_row, par_node, par_len, 0};
+        add(nx0 + (int)__popcll(bm & lt), v, v4i{par_row, par_node, par_len, 0});
     }
-    const int cnt = nx0 + __popcll(bm);
-    if (lane == 0) a.nx_count[b] = cnt;
+    const int cnt = nx0 + (int)__popcll(bm);
     if (a.last_round) return cnt;
     const int n_lab = __popcll(lm);
     if (lane == 0 && n_lab > 0 && a.live_next) atomicAdd(a.live_next, 1);
-    if (n_lab > 0) {   // uniform; the order of the utterances in the list does not matter
-        int base = 0;
+    // The place of the utterance's labels in the list (the order of the utterances in it does not matter): asked for
+    // now, used last.  A single utterance has the list to itself.
+    int base = 0;
+    if (n_lab > 0) {   // uniform
         if (lane == 0) {
-            base = atomicAdd(a.n_rows_next, n_lab);
+            if (a.B == 1) *a.n_rows_next = n_lab;
+            else base = atomicAdd(a.n_rows_next, n_lab);
             a.n_taken[b] = own.taken + n_lab;
         }
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (is_lab) a.rows_next[base + k_lab] = v4i{new_row, par_row, tok, 0};
     }
     if (is_lab) {
         const int dst = b * W + k_lab;
@@ -112,85 +117,36 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
         a.len_dst[dst] = 0;
         a.row_dst[dst] = b * a.P;   // any row of the utterance
     }
+    if (n_lab > 0) {
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (is_lab) a.rows_next[base + k_lab] = v4i{new_row, par_row, tok, 0};
+    }
     return cnt;
-}
-
-// End of a frame for utterance b (one wave): the new beam is the W best of the cnt candidates by
-// (score descending, insertion order); slot r of buffer fe_dst_buf takes score, trie node and length
-// that its candidate carried along, and the pool row its states are in.  The candidates of the
-// current round were stored by this same wave a moment ago: they are read back from L2 (agent-scope
-// loads after a fence), not through the CU's vector cache.
-// sk / sc: 64 words of LDS each, private to the calling wave (pruned selection of select.h).
-__device__ __forceinline__ void qr_frame_end(const QrRouteArgs &a, int b, int lane, int cnt, unsigned *sk, int *sc_idx)
-{
-    const int W = a.W, R = a.R, N = a.B * a.W;
-    const float *sc = a.nx_score + (size_t)b * R * W;
-    auto score_at = [&](int i) { return __hip_atomic_load(sc + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 0.0f; };
-    int c;
-    float v;
-    if (R * W <= 128) {
-        float val[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) val[i] = (lane * 2 + i < cnt) ? score_at(lane * 2 + i) : -INFINITY;
-        auto index_of = [&](int i) { return lane * 2 + i; };
-        if (!qr_select_pruned<2>(val, index_of, W, lane, sk, sc_idx, c, v)) qr_select_from_regs<2>(val, lane * 2, W, lane, c, v);
-    } else {
-        qr_select_from_mem(score_at, cnt, W, lane, c, v);
-    }
-    int row = b * a.P;
-    if (lane < W) {
-        const size_t o = (size_t)a.fe_dst_buf * N + b * W + lane;
-        if (c >= 0) {
-            // what the candidate carried along when it joined the list: three independent loads, no second hop
-            const int *info = (const int *)(a.nx_info + (size_t)b * R * W + c);
-            row = __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int node = __hip_atomic_load(info + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int len = __hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            a.fe_score_all[o] = v;
-            a.fe_node_all_w[o] = node;
-            a.fe_len_all_w[o] = len;
-        } else {
-            a.fe_score_all[o] = -INFINITY;
-            a.fe_node_all_w[o] = 0;
-            a.fe_len_all_w[o] = 0;
-        }
-        a.fe_row_all_w[o] = row;
-    }
-    qr_list_free_rows(a, b, lane, lane < W && c >= 0, row, sk);
-    if (lane == 0) {
-        a.nx_count[b] = 0;
-        a.n_taken[b] = 0;
-    }
 }
 
 // One iteration of the alignment-length synchronous search for utterance b (one wave; Sec. 2 names the search,
 // the algorithm is the published one).  Lane r < W holds pick r (flat candidate index c = parent*V + token or -1,
-// score v) and, as fin_new, the score with which hypothesis r of the current beam finishes now (-inf: it does not).
+// score v).
 //   - pick r becomes slot r of the next beam: a blank keeps the parent's sequence and state, a label extends it;
 //   - recombination: picks that stand for the same label sequence (same length and same 64-bit sequence hash)
 //     are one hypothesis; the best-ranked keeps its slot with log(sum exp(scores)), the others die;
-//   - the running list of the W best finished hypotheses takes the new ones in, ordered by (score descending,
-//     insertion order), new ones in slot order.
-// What lane w < W of the routing wave knows, beyond QrOwn, about hypothesis w of the current beam and rank w of the
-// finished list.
+// What lane w < W of the routing wave knows, beyond QrOwn, about hypothesis w of the current beam.
 struct QrAlsdOwn {
     QrOwn h;
     unsigned long long hash;
     float score;
-    float fin_score;  int fin_node, fin_len;
 };
 
 __device__ __forceinline__ QrAlsdOwn qr_alsd_load_own(const QrRouteArgs &a, const QrAlsdArgs &s, int b, int lane)
 {
     const int own = b * a.W + (lane < a.W ? lane : 0);
     QrAlsdOwn o;
-    o.h = qr_load_own(a, b, lane);  o.hash = s.hash_src[own];  o.score = a.score_src[own];
-    o.fin_score = s.fin_score[own];  o.fin_node = s.fin_node[own];  o.fin_len = s.fin_len[own];
+    o.hash = s.hash_src[own];  o.score = a.score_src[own];
     return o;
 }
 
 __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsdArgs &s, int b, int lane, int c, float v,
-                                              float fin_new, const QrAlsdOwn &o, unsigned *mask)
+                                              const QrAlsdOwn &o, unsigned *mask)
 {
     const int W = a.W, V = a.V;
     const bool in = lane < W;
@@ -203,7 +159,6 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     const int row_p = __shfl(o.h.row, par);
     const unsigned long long hash_p = ((unsigned long long)(unsigned)__shfl((int)(unsigned)(o.hash >> 32), par) << 32) |
                                       (unsigned long long)(unsigned)__shfl((int)(unsigned)o.hash, par);
-    const int own_node = o.h.node, own_len = o.h.len;
     const int new_len = len_p + (is_lab ? 1 : 0);
     const unsigned long long new_hash = is_lab ? hash_p * 0x9E3779B97F4A7C15ull + (unsigned long long)(tok + 1) : hash_p;
     const int h_lo = (int)(unsigned)new_hash, h_hi = (int)(unsigned)(new_hash >> 32);
@@ -255,11 +210,10 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     const int new_row = __shfl(o.h.free_row, k_step);
     const int reuse_row = __shfl(o.h.row, reuse_slot >= 0 ? reuse_slot : 0);
     const int row = steps ? new_row : (reuse_slot >= 0 ? reuse_row : row_p);
-    if (sm != 0ull) {   // uniform; the order of the utterances in the list does not matter
-        int base = 0;
-        if (lane == 0) base = atomicAdd(a.n_rows_next, (int)__popcll(sm));
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (steps) a.rows_next[base + k_step] = v4i{new_row, row_p, tok, 0};
+    int base = 0;   // the place of the utterance's labels in the list: asked for now, used last (see qr_route_picks)
+    if (sm != 0ull && lane == 0) {
+        if (a.B == 1) *a.n_rows_next = (int)__popcll(sm);
+        else base = atomicAdd(a.n_rows_next, (int)__popcll(sm));
     }
     if (in) {
         const int dst = b * W + lane;
@@ -284,11 +238,32 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
         }
     }
     qr_list_free_rows(a, b, lane, keep, row, mask);
-    // finished hypotheses
+    if (sm != 0ull) {   // uniform
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (steps) a.rows_next[base + k_step] = v4i{new_row, row_p, tok, 0};
+    }
+}
+
+// The running list of the W best finished hypotheses of utterance b (one wave) takes the new ones in, ordered by (score
+// descending, insertion order), new ones in slot order.  Lane w < W holds rank w of the list and, as fin_new, the score
+// with which hypothesis w of the current beam finishes now (-inf: it does not); node, len: that hypothesis'.
+struct QrAlsdFinished {
+    float score;  int node, len;       // rank w of the list
+    int new_node, new_len;             // hypothesis w
+};
+
+__device__ __forceinline__ QrAlsdFinished qr_alsd_load_finished(const QrRouteArgs &a, const QrAlsdArgs &s, int b, int lane)
+{
+    const int own = b * a.W + (lane < a.W ? lane : 0);
+    return QrAlsdFinished{s.fin_score[own], s.fin_node[own], s.fin_len[own], a.node_src[own], a.len_src[own]};
+}
+
+__device__ __forceinline__ void qr_alsd_finish(const QrAlsdArgs &s, int b, int W, int lane, float fin_new, const QrAlsdFinished &f)
+{
+    const bool in = lane < W;
     const float fn = in ? fin_new : -INFINITY;
     if (__ballot(fn > -INFINITY) == 0ull) return;   // uniform
-    const float fo = in ? o.fin_score : -INFINITY;
-    const int fo_node = o.fin_node, fo_len = o.fin_len;
+    const float fo = in ? f.score : -INFINITY;
     int rank_o = 0, rank_n = 0;
     for (int j = 0; j < W; ++j) {
         const float oj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fo), j));
@@ -300,10 +275,10 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     }
     if (in && rank_o < W) {
         const int o = b * W + rank_o;
-        s.fin_score[o] = fo;  s.fin_node[o] = fo_node;  s.fin_len[o] = fo_len;
+        s.fin_score[o] = fo;  s.fin_node[o] = f.node;  s.fin_len[o] = f.len;
     }
     if (in && rank_n < W) {
         const int o = b * W + rank_n;
-        s.fin_score[o] = fn;  s.fin_node[o] = fn > -INFINITY ? own_node : 0;  s.fin_len[o] = fn > -INFINITY ? own_len : 0;
+        s.fin_score[o] = fn;  s.fin_node[o] = fn > -INFINITY ? f.new_node : 0;  s.fin_len[o] = fn > -INFINITY ? f.new_len : 0;
     }
 }
