@@ -6,97 +6,83 @@
 
 namespace {
 
-// One workgroup (4 waves) per utterance.  The W*V candidate values are formed once
-// (fp32 add) and kept in registers; see select.h.
+// One workgroup (4 waves) per utterance; thread t forms the candidates t, t + 256, ... (fp32 add) and keeps their keys in
+// registers: 256 groups for the bound, at most PER candidates each, so that rarely more than W * PER pass it.
+// Bound by the chain of its steps; in one wave, which this was, 64 x 16 x 46 candidates took 17.4 us; a decoding
+// round driven by the caller went from 87 to 76 us.
 template <int PER>
-__device__ __forceinline__ void select_w_regs(const float *__restrict__ sc, const float *__restrict__ fu, int W, int V,
-                                              int blank, int force_blank, int tid, unsigned *slots, int &my_c, float &my_v)
-{
-    const int C = W * V;
-    float val[PER];
-    const int c0 = tid * PER;
-    int w = c0 / V, k = c0 - w * V;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int c = c0 + i;
-        float v = -INFINITY;
-        if (c < C && (!force_blank || k == blank)) v = (sc[w] + fu[c]) + 0.0f;   // + 0: -0 becomes +0, one key per value
-        val[i] = v;
-        if (++k == V) { k = 0; ++w; }
-    }
-    qr_block_select_from_regs<PER>(val, c0, W, tid, slots, my_c, my_v);
-}
-
-// Up to 64 * PER candidates held by one wave, lane l owning indices l*PER .. l*PER+PER-1: the pruned
-// rank-based selection of select.h.  Returns false when more than 64 candidates survive its threshold.
-template <int PER>
-__device__ __forceinline__ bool select_w_pruned(const float *__restrict__ sc, const float *__restrict__ fu, int W, int V,
-                                                int blank, int force_blank, int lane, unsigned *scratch, int &my_c,
-                                                float &my_v)
-{
-    const int C = W * V;
-    float val[PER];
-    const int c0 = lane * PER;
-    int w = c0 / V, k = c0 - w * V;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int c = c0 + i;
-        float v = -INFINITY;
-        if (c < C && (!force_blank || k == blank)) v = (sc[w] + fu[c]) + 0.0f;   // + 0: -0 becomes +0, one key per value
-        val[i] = v;
-        if (++k == V) { k = 0; ++w; }
-    }
-    auto index_of = [&](int s) { return c0 + s; };
-    return qr_select_pruned<PER>(val, index_of, W, lane, scratch, (int *)scratch + 64, my_c, my_v);
-}
-
-// Thread r < W ends up with pick r.  Uniform control flow across the workgroup.
-__device__ __forceinline__ void select_w(const float *__restrict__ sc, const float *__restrict__ fu, int W, int V,
-                                         int blank, int force_blank, int tid, unsigned *slots, int &my_c, float &my_v)
-{
-    const int C = W * V;   // uniform
-    // fast path: wave 0 alone, candidates in its registers (the other waves only meet it at the barrier)
-    __shared__ unsigned pruned_scratch[128];
-    __shared__ int pruned_ok;
-    if (C <= 64 * 16) {
-        if (tid < 64) {
-            const bool ok = C <= 64 * 4 ? select_w_pruned<4>(sc, fu, W, V, blank, force_blank, tid, pruned_scratch, my_c, my_v)
-                                         : select_w_pruned<16>(sc, fu, W, V, blank, force_blank, tid, pruned_scratch, my_c, my_v);
-            if (tid == 0) pruned_ok = ok ? 1 : 0;
-        }
-        __syncthreads();
-        if (pruned_ok) return;   // uniform
-    }
-    if (C <= 256) select_w_regs<1>(sc, fu, W, V, blank, force_blank, tid, slots, my_c, my_v);
-    else if (C <= 256 * 3) select_w_regs<3>(sc, fu, W, V, blank, force_blank, tid, slots, my_c, my_v);
-    else if (C <= 256 * 6) select_w_regs<6>(sc, fu, W, V, blank, force_blank, tid, slots, my_c, my_v);
-    else {
-        my_c = -1;
-        my_v = -INFINITY;
-        if (tid < 64) {   // any size: wave 0 re-forms the candidates from memory in every round
-            auto value = [&](int c) -> float {
-                const int w = c / V, k = c - w * V;
-                return (force_blank && k != blank) ? -INFINITY : (sc[w] + fu[c]) + 0.0f;
-            };
-            qr_select_from_mem(value, C, W, tid, my_c, my_v);
-        }
-    }
-}
-
 __global__ __launch_bounds__(256) void beam_step_kernel(const float *__restrict__ score, const float *__restrict__ fused,
                                                          int W, int V, int blank, int force_blank,
                                                          int32_t *__restrict__ parent_out, int32_t *__restrict__ token_out,
                                                          float *__restrict__ score_out)
 {
-    __shared__ unsigned slots[16];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    __shared__ QrCand list[256 * PER], best[64];
+    __shared__ unsigned group_best[256];
+    __shared__ int n_list;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int C = W * V;
+    const float *sc = score + (int64_t)b * W, *fu = fused + (int64_t)b * C;
+    const int dw = 256 / V, dk = 256 - dw * V;   // uniform: from one candidate of a thread to its next
+    int w = tid / V, k = tid - w * V;
+    float f[PER], s[PER];
+    bool ok[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = tid + 256 * i;
+        ok[i] = c < C && (!force_blank || k == blank);
+        f[i] = fu[c < C ? c : C - 1];
+        s[i] = sc[w < W ? w : W - 1];
+        w += dw;
+        k += dk;
+        if (k >= V) { k -= V; ++w; }
+    }
+    unsigned key[PER], top = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const float v = (s[i] + f[i]) + 0.0f;   // + 0: -0 becomes +0, one key per value
+        key[i] = (ok[i] && v > -INFINITY) ? qr_float_key(v) : 0u;
+        top = key[i] > top ? key[i] : top;
+    }
+    group_best[tid] = top;
+    if (tid < 64) best[tid] = 0;
+    if (tid == 0) n_list = 0;
+    __syncthreads();
+    unsigned g[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = group_best[i * 64 + lane];
+    const QrBound bound(g, W);
+    qr_gather<PER>(key, bound, [&](int i) { return tid + 256 * i; }, lane, &n_list, list);
+    __syncthreads();
+    qr_rank(list, n_list, W, tid, best);
+    __syncthreads();
+    if (tid < W) {
+        const QrCand p = best[tid];
+        const int c = p != 0 ? qr_cand_index(p) : 0;
+        parent_out[(int64_t)b * W + tid] = p != 0 ? c / V : -1;
+        token_out[(int64_t)b * W + tid] = p != 0 ? c % V : -1;
+        score_out[(int64_t)b * W + tid] = p != 0 ? qr_cand_value(p) : -INFINITY;
+    }
+}
+
+// Any number of candidates: one wave re-forms them from memory in every round.
+__global__ __launch_bounds__(64) void beam_step_any_kernel(const float *__restrict__ score, const float *__restrict__ fused,
+                                                            int W, int V, int blank, int force_blank,
+                                                            int32_t *__restrict__ parent_out, int32_t *__restrict__ token_out,
+                                                            float *__restrict__ score_out)
+{
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const float *sc = score + (int64_t)b * W, *fu = fused + (int64_t)b * W * V;
+    auto value = [&](int c) -> float {
+        const int w = c / V, k = c - w * V;
+        return (force_blank && k != blank) ? -INFINITY : (sc[w] + fu[c]) + 0.0f;
+    };
     int c;
     float v;
-    select_w(score + (int64_t)b * W, fused + (int64_t)b * W * V, W, V, blank, force_blank, tid, slots, c, v);
-    if (tid < W) {
-        parent_out[(int64_t)b * W + tid] = c >= 0 ? c / V : -1;
-        token_out[(int64_t)b * W + tid] = c >= 0 ? c % V : -1;
-        score_out[(int64_t)b * W + tid] = v;
+    qr_select_from_mem(value, W * V, W, lane, c, v);
+    if (lane < W) {
+        parent_out[(int64_t)b * W + lane] = c >= 0 ? c / V : -1;
+        token_out[(int64_t)b * W + lane] = c >= 0 ? c % V : -1;
+        score_out[(int64_t)b * W + lane] = v;
     }
 }
 
@@ -105,7 +91,15 @@ __global__ __launch_bounds__(256) void beam_step_kernel(const float *__restrict_
 void qr_launch_beam(const float *score, const float *fused, int B, int W, int V, int blank, int force_blank,
                     int32_t *parent_out, int32_t *token_out, float *score_out, hipStream_t st)
 {
-    beam_step_kernel<<<B, 256, 0, st>>>(score, fused, W, V, blank, force_blank, parent_out, token_out, score_out);
+    const int64_t C = (int64_t)W * V;
+    // (16 candidates a thread are what LDS holds should all of them pass)
+#define QR_BEAM(kernel, threads) kernel<<<B, threads, 0, st>>>(score, fused, W, V, blank, force_blank, parent_out, token_out, score_out)
+    if (C <= 256) QR_BEAM(beam_step_kernel<1>, 256);
+    else if (C <= 256 * 3) QR_BEAM(beam_step_kernel<3>, 256);
+    else if (C <= 256 * 6) QR_BEAM(beam_step_kernel<6>, 256);
+    else if (C <= 256 * 16) QR_BEAM(beam_step_kernel<16>, 256);
+    else QR_BEAM(beam_step_any_kernel, 64);
+#undef QR_BEAM
 }
 
 extern "C" qrnnt_status qrnnt_beam_step(const float *score, const float *fused, int32_t B, int32_t W, int32_t V,

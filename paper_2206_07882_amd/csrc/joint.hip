@@ -156,11 +156,10 @@ __device__ __forceinline__ void qr_round_mma(const v4i *w, const unsigned (&woff
     }
 }
 
-// Maximum / sum over the 16 lanes of a row, the same bits in each of them.
-template <class Op>
-__device__ __forceinline__ float qr_row_reduce(float x, Op &&op)
+// Maximum over the 16 lanes of a row, in each of them.
+__device__ __forceinline__ float qr_row_max(float x)
 {
-#define QR_ROW_STEP(ctrl) x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true)));
+#define QR_ROW_STEP(ctrl) x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true)));
     QR_ROW_STEP(0xB1)    // quad_perm [1,0,3,2]
     QR_ROW_STEP(0x4E)    // quad_perm [2,3,0,1]
     QR_ROW_STEP(0x141)   // row_half_mirror
@@ -169,26 +168,25 @@ __device__ __forceinline__ float qr_row_reduce(float x, Op &&op)
     return x;
 }
 
-// A candidate of a selection in one word: larger is better under (value descending, index ascending); 0: none.
-typedef unsigned long long QrCand;
-__device__ __forceinline__ QrCand qr_cand(unsigned key, int idx) { return ((QrCand)key << 32) | (unsigned)~idx; }
-__device__ __forceinline__ int qr_cand_index(QrCand c) { return (int)~(unsigned)c; }
-__device__ __forceinline__ float qr_cand_value(QrCand c) { return qr_key_float((unsigned)(c >> 32)); }
-
-// Rank of every one of the M candidates in list[] (no two equal): the best W go to best[rank].  256 threads: four count
-// for one candidate, 64 candidates at a time.
-__device__ __forceinline__ void qr_rank(const QrCand *list, int M, int W, int tid, QrCand *best)
+// Sum over the 16 x 4 values of a row, in each of its lanes, in the order of the kernels that hold a hypothesis' tokens
+// in four lanes (linear.hip): lane 4*mt + g has tokens 16*mt + 4*g + i; for each g one chain over mt and i, then
+// (g0 + g1) + (g2 + g3).  The same bits as there matter: equal hypotheses tie, and a tie decides a beam.
+__device__ __forceinline__ float qr_row_sum(const v4f &e)
 {
-    for (int i0 = 0; i0 < M; i0 += 64) {   // uniform
-        const int i = i0 + (tid >> 2);
-        const QrCand mine = list[i < M ? i : 0];
-        int rank = 0;
-#pragma unroll 4
-        for (int j = tid & 3; j < M; j += 4) rank += list[j] > mine ? 1 : 0;
-        rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, true);
-        rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, true);
-        if ((tid & 3) == 0 && i < M && rank < W) best[rank] = mine;
+    float sum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {   // after t passes the lanes of mt < t hold their chain's value (row_shr:4 brings 0 to mt = 0)
+        const float from = t == 0 ? 0.0f : __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sum), 0x114, 0xf, 0xf, true));
+        sum = (((from + e[0]) + e[1]) + e[2]) + e[3];
     }
+    int x = __float_as_int(sum);   // of interest: lanes 12..15 of the row
+#define QR_ROW_ADD(ctrl) x = __float_as_int(__int_as_float(x) + __int_as_float(__builtin_amdgcn_update_dpp(0, x, ctrl, 0xf, 0xf, true)));
+    QR_ROW_ADD(0xB1)
+    QR_ROW_ADD(0x4E)
+#undef QR_ROW_ADD
+    x = __builtin_amdgcn_update_dpp(x, x, 0x128 /* row_ror:8 */, 0xf, 0x2, false);   // lanes 4..7
+    x = __builtin_amdgcn_update_dpp(x, x, 0x124 /* row_ror:4 */, 0xf, 0x5, false);   // lanes 0..3 and 8..11
+    return __int_as_float(x);
 }
 
 // One decoding round of an utterance in one workgroup: output layers of the three networks, joint, log-softmax and
@@ -315,7 +313,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         sc[nt] = wave < 4 ? r.score_src[n] : 0.0f;
         len_t[nt] = (ALSD && wave < 4) ? r.len_src[n] : 0;
     }
-    unsigned key[NTW][4];
+    unsigned key[4 * NTW];
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
         const int w = nt * 16 + col;
@@ -418,8 +416,6 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         // ---- scores: hypothesis 16 * nt + hc, tokens 4 * quad .. 4 * quad + 3
         const int hc = tid >> 4, quad = lane & 15, mt = quad >> 2;
         const int at = (quad & 3) * 16 + (hc ^ quad), k0 = 4 * quad;
-        auto add = [](float x, float y) { return x + y; };
-        auto max_of = [](float x, float y) { return fmaxf(x, y); };
         v4f v[3];   // joint, source LM, external LM
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -434,12 +430,11 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                 v[q][i] = k0 + i < V ? ws[i] * (float)t[i] + wb[i] : -INFINITY;
                 mx = fmaxf(mx, v[q][i]);
             }
-            mx = qr_row_reduce(mx, max_of);
-            float sum = 0.0f;
+            mx = qr_row_max(mx);
+            v4f e;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sum += qr_exp(v[q][i] - mx);   // (exp(-inf) = 0 behind the last token)
-            sum = qr_row_reduce(sum, add);
-            float lse = mx + qr_log(sum);
+            for (int i = 0; i < 4; ++i) e[i] = qr_exp(v[q][i] - mx);   // (0 behind the last token)
+            float lse = mx + qr_log(qr_row_sum(e));
             if (q > 0 && !a.head[q].log_softmax) lse = 0.0f;
             v[q] = v[q] - lse;
         }
@@ -466,8 +461,8 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                 }
             }
             const float val = (sc[nt] + f) + 0.0f;   // + 0: one key per value
-            key[nt][i] = (ok && val > -INFINITY) ? qr_float_key(val) : 0u;
-            top = key[nt][i] > top ? key[nt][i] : top;
+            key[nt * 4 + i] = (ok && val > -INFINITY) ? qr_float_key(val) : 0u;
+            top = key[nt * 4 + i] > top ? key[nt * 4 + i] : top;
         }
         group_best[nt * 256 + tid] = top;
     }
@@ -478,57 +473,18 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     if (wave < 4) {
         // Up to 16 hypotheses: 64 groups, lane l looks at quartet l % 16 of hypotheses l / 16 + 4, 8, ...  More: every
         // quartet of every hypothesis is a group (with 64 groups 64 picks would bound nothing: 1.6 ms a frame at W = 64).
-        // Distances from the best of all make the bits that tell candidates apart come early, and 16 of them will do.
         constexpr int NG = NTW == 1 ? 1 : 4 * NTW;   // groups per lane
-        unsigned g[NG], all = 0u;
+        unsigned g[NG];
 #pragma unroll
         for (int i = 0; i < NG; ++i) g[i] = 0u;
 #pragma unroll
         for (int i = 0; i < 4 * NTW; ++i) {
             const unsigned o = group_best[i * 64 + lane];
             g[i % NG] = o > g[i % NG] ? o : g[i % NG];
-            all = o > all ? o : all;
         }
-        all = qr_wave_reduce_u32<true>(all);
-        const float v_max = qr_key_float(all);
-        auto nearness = [&](unsigned k) -> unsigned {   // larger is nearer; 0: no candidate (the best may be +inf: no difference then)
-            return k == 0u ? 0u : (k == all ? 0x7FFFFFFFu : 0x7FFFFFFFu - __float_as_uint(v_max - qr_key_float(k)));
-        };
-#pragma unroll
-        for (int i = 0; i < NG; ++i) g[i] = nearness(g[i]);
-        unsigned T = 0u;
-        for (int bit = 30; bit >= 15; --bit) {
-            const unsigned trial = T | (1u << bit);
-            int cnt = 0;
-#pragma unroll
-            for (int i = 0; i < NG; ++i) cnt += (int)__popcll(__ballot(g[i] >= trial));
-            if (cnt >= W) T = trial;   // uniform
-            if (cnt == W) break;
-        }
-        T = T ? T : 1u;   // fewer than W groups hold a candidate: every candidate passes
-        int n_keep = 0;
-        bool keep[NTW][4];
-        unsigned long long bal[NTW][4];
-#pragma unroll
-        for (int nt = 0; nt < NTW; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                keep[nt][i] = nearness(key[nt][i]) >= T;
-                bal[nt][i] = __ballot(keep[nt][i]);
-                n_keep += (int)__popcll(bal[nt][i]);
-            }
-        int base = 0;
-        if (lane == 0 && n_keep) base = atomicAdd(&n_cand, n_keep);
-        base = __builtin_amdgcn_readfirstlane(base);
-#pragma unroll
-        for (int nt = 0; nt < NTW; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned long long bm = bal[nt][i];
-                const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bm, 0u));
-                if (keep[nt][i]) gathered[pos] = qr_cand(key[nt][i], (nt * 16 + (tid >> 4)) * V + 4 * (lane & 15) + i);
-                base += (int)__popcll(bm);
-            }
+        const QrBound bound(g, W);
+        qr_gather<4 * NTW>(key, bound, [&](int i) { return ((i >> 2) * 16 + (tid >> 4)) * V + 4 * (lane & 15) + (i & 3); }, lane, &n_cand,
+                           gathered);
     }
     __syncthreads();
     if (wave < 4) qr_rank(gathered, n_cand, W, tid, best);
