@@ -40,9 +40,9 @@ struct QrStepGroup {
     // largest length the list can have; of parent and x_row only whether they are null matters.
     const v4i *rows = nullptr;
     const int32_t *n_rows = nullptr;
-    // filled in by the launcher of the tiled kernel: row blocks of all members together, compute units of the device,
+    // filled in by the launcher of the tiled kernel: row blocks of all members together, workgroups the device holds at once,
     // and (launches without a list) log2 of how many times narrower than the full column block a workgroup's share is
-    int row_blocks = 0, n_cu = 0, width = 0;
+    int row_blocks = 0, n_resident = 0, width = 0;
     int col_block0 = 0;                // first column block of this launch (a grid's z extent is limited to 65535)
 };
 

@@ -18,9 +18,9 @@ namespace {
 // (what keeps the whole matrix in flight across the chip), and the partial sums meet in LDS.
 // Wave 0 then finishes the 4 cells, one (cell, hypothesis) per lane.  N = 16 is exactly one
 // 16-column MFMA tile, so the matrix cores serve this regime too: the kernel is bound by the
-// weight stream and by its chain of dependent loads, which is kept to two links: the weight
-// loads (which depend on nothing) go first, then the row indices, then everything that
-// depends on them, including what the cell update will need.
+// weight stream and by its chain of dependent loads, which is kept to two links: the row indices
+// go first, then the weight loads (which depend on nothing), then, while those arrive, everything
+// that depends on the indices, including what the cell update will need.
 // Grid: x = row tiles, y = column tiles, z = problem of a group.
 constexpr int SMALL_BATCH = 4;   // chunks per wave per batch (K <= 2048 in one batch)
 
@@ -42,7 +42,19 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
     const int nkx = USE_GX ? 0 : a.nkc_x;
     const int total = nkx + a.nkc_h;
 
-    // ---- first batch of weight fragments: independent of every index
+    // ---- indices first (memory answers in order: what hangs on them can then go out while the weights arrive), then the
+    // first batch of weight fragments, which depends on nothing
+    bool n_ok = n0 + col < N;
+    int nn = n_ok ? n0 + col : N - 1;
+    v4i entry = zero;
+    int s = nn, xr = nn;
+    if (g.rows) {   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
+        entry = g.rows[nn];
+    } else {
+        if (a.parent) s = a.parent[nn];
+        if (a.x_row) xr = a.x_row[nn];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     v4i pa[SMALL_BATCH];
     auto load_weights = [&](int v0) {
 #pragma unroll
@@ -57,22 +69,14 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
         }
     };
     load_weights(wave);
-
-    // ---- indices, then everything that hangs on them
-    bool n_ok = n0 + col < N;
-    int nn = n_ok ? n0 + col : N - 1;
-    int s, xr;
-    if (g.rows) {   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
-        const v4i e = g.rows[nn];
+    __builtin_amdgcn_sched_barrier(0);
+    if (g.rows) {
         const int n_cnt = *g.n_rows;
         if (n0 >= n_cnt) return;   // uniform
         n_ok = n0 + col < n_cnt;
-        nn = e[0] < 0 ? 0 : (e[0] >= a.n_out ? a.n_out - 1 : e[0]);
-        s = a.parent ? e[1] : nn;
-        xr = a.x_row ? e[2] : nn;
-    } else {
-        s = a.parent ? a.parent[nn] : nn;
-        xr = a.x_row ? a.x_row[nn] : nn;
+        nn = entry[0] < 0 ? 0 : (entry[0] >= a.n_out ? a.n_out - 1 : entry[0]);
+        s = a.parent ? entry[1] : nn;
+        xr = a.x_row ? entry[2] : nn;
     }
     const int n = nn;
     s = s < 0 ? 0 : (s >= a.n_slots ? a.n_slots - 1 : s);
@@ -196,8 +200,10 @@ void launch_small(const QrStepGroup &g, hipStream_t st)
 // TAB (with USE_GX): the looked-up input part is an fp32 table that already holds
 // gate_k * (x_scale * s_wih[r] * sum + bias[r]) (see qr_launch_gx_table): one fused multiply-add per gate
 // is all that is left of the dequantisation.
+constexpr int step_workgroups_per_cu(bool use_gx, bool dbg) { return (use_gx && !dbg) ? 3 : 2; }
+
 template <int MT, int NT, int S, bool USE_GX, bool TAB, bool DBG, bool FAST>
-__global__ __launch_bounds__(256, (USE_GX && !DBG) ? 3 : 2) void lstm_step_pipe_kernel(const QrStepGroup g)
+__global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm_step_pipe_kernel(const QrStepGroup g)
 {
     using P = QrPipe<MT, NT, S>;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -239,9 +245,13 @@ __global__ __launch_bounds__(256, (USE_GX && !DBG) ? 3 : 2) void lstm_step_pipe_
     constexpr bool HALF_OK = true;   // every variant has the narrower instances (the debug build of each included)
     // With a list the problem has *n_rows rows, row j standing for the hypothesis of entry j.
     //  * A workgroup takes 32*NT, 16*NT or 8*NT consecutive entries (width 0, 1, 2): the narrowest width at which the
-    //    launch's column blocks still cover the list and the working workgroups do not outnumber the compute units
-    //    (beyond that, narrower only means fetching the weights more often), so that a short list is spread over
-    //    more workgroups, each of which then runs the half- or quarter-width instance of the body below.
+    //    launch's column blocks still cover the list and the working workgroups are resident all at once (beyond that,
+    //    narrower only means fetching the weights more often), so that a short list is spread over more workgroups,
+    //    each of which then runs the half- or quarter-width instance of the body below.  A chunk costs a wave 745 cycles
+    //    of its own instruction stream at quarter width and 1250 at full width, with next to no waiting for memory:
+    //    what helps is a second and third wave on the SIMD.  (As many workgroups as compute units, the line before:
+    //    first layers of 768 and 2 x 1024 cells, 256 / 512 entries 11.9 / 16.5 us, now 10.9 / 15.2; second layers, 384
+    //    entries, 16.8 against 15.5 us; of 2048 cells, first layer, 384 entries, 24.1 against 20.4 us.)
     //  * The 16-column tiles of a workgroup's entries are dealt to the two column halves of the wave grid in turn
     //    (logical tile 2*nt + wn sits at wave column wn, position nt), so that every wave holds the same number of
     //    live tiles; a workgroup at full width whose share of the list ends within its first half runs the
@@ -266,11 +276,11 @@ __global__ __launch_bounds__(256, (USE_GX && !DBG) ? 3 : 2) void lstm_step_pipe_
             se[tid] = rows[j < N ? j : N - 1];
         }
         const int n_cnt = *g.n_rows;
-        if (HALF_OK) {   // uniform: the narrowest width that covers the list and does not ask for more workgroups than CUs
+        if (HALF_OK) {   // uniform: the narrowest width that covers the list in one round of workgroups
 #pragma unroll
             for (int w = 1; w <= 2; ++w) {
                 const int per = P::BN >> w;
-                if (per * (g.col_block0 + (int)gridDim.z) >= n_cnt && g.row_blocks * ((n_cnt + per - 1) / per) <= g.n_cu) width = w;
+                if (per * (g.col_block0 + (int)gridDim.z) >= n_cnt && g.row_blocks * ((n_cnt + per - 1) / per) <= g.n_resident) width = w;
             }
         }
         const int n0w = width == 2 ? n0q : (width == 1 ? n0h : n0);
@@ -542,7 +552,7 @@ void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
     QrStepGroup gg = g;
     int gx = 0, max_n = 0;
     gg.row_blocks = 0;
-    gg.n_cu = n_cu;
+    gg.n_resident = n_cu * step_workgroups_per_cu(USE_GX, DBG);
     for (int i = 0; i < g.n; ++i) {
         const int rb = ((g.p[i].H >> 2) + 2 * MT - 1) / (2 * MT);
         gx = rb > gx ? rb : gx;
@@ -550,11 +560,11 @@ void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
         gg.row_blocks += rb;
     }
     // Without a list the width is chosen here, by the rule the kernel applies to a list's length: the narrowest
-    // share per workgroup at which the working workgroups do not outnumber the compute units.
+    // share per workgroup at which the working workgroups are resident all at once.
     gg.width = 0;
     if (!g.rows)
         for (int w = 1; w <= 2; ++w)
-            if (gg.row_blocks * ((max_n + (P::BN >> w) - 1) / (P::BN >> w)) <= n_cu) gg.width = w;
+            if (gg.row_blocks * ((max_n + (P::BN >> w) - 1) / (P::BN >> w)) <= gg.n_resident) gg.width = w;
     const int per = P::BN >> gg.width;
     const int gz = (max_n + per - 1) / per;
     for (int z0 = 0; z0 < gz; z0 += 65535) {   // a grid's z extent ends at 65535
