@@ -184,6 +184,208 @@ void launch_small(const QrStepGroup &g, hipStream_t st)
     lstm_step_small_kernel<USE_GX><<<dim3(max_rt, (max_n + 15) / 16, g.n), 256, 0, st>>>(g);
 }
 
+// Between the two: some dozens to some hundreds of hypotheses.  A workgroup owns 4 row tiles (16 cells) x 2 column tiles
+// (32 hypotheses); its 8 waves split K (the input part to waves 0-3, the recurrent part to waves 4-7; with a looked-up
+// input part all eight share the recurrent one), so no operand is wanted by two waves and every one goes from memory to
+// registers, a whole batch of chunks in flight per wave, without a ring, its barriers and its index arithmetic.  One
+// exchange through LDS adds the partial sums, after which wave w finishes tile w, one (cell, hypothesis) per lane.
+// Bound by its chain (arguments, list entry, codes, contraction, exchange, cell) while one round of workgroups covers
+// the list, by the path from L2 to the compute units beyond (a column block fetches the weights again, and codes in half
+// lines).  Measured against the tiled kernel: see split_n_max.
+// The arithmetic behind the sums is the tiled kernel's, so that a layer's results do not depend on which one ran.
+// Grid: x = groups of 4 row tiles, y = problem of a group, z = column blocks.
+
+
+template <bool USE_GX, bool TAB>
+__global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGroup g)
+{
+    __shared__ v4i part[8][8][64];   // [wave][tile: 4 * column tile + row tile][lane]
+    if (g.gate && *g.gate == 0) return;   // uniform: a decoding round without any live hypothesis
+    const QrStepArgs a = g.p[blockIdx.y];
+    const int H = a.H, N = a.N;
+    const int rt0 = blockIdx.x * 4;
+    const int n0 = (g.col_block0 + (int)blockIdx.z) * 32;
+    if (rt0 >= (H >> 2) || n0 >= N) return;   // uniform
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    const v4i zero = {0, 0, 0, 0};
+    const int m = (int)0xF0F0F0F0u;
+
+    // ---- row indices first, then the weights of the first batch, then what hangs on the indices
+    int nn[2], s[2], xr[2];
+    v4i entry[2] = {zero, zero};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int j = n0 + 16 * i + col;
+        nn[i] = s[i] = xr[i] = j < N ? j : N - 1;
+        if (g.rows) {
+            entry[i] = g.rows[nn[i]];   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
+        } else {
+            if (a.parent) s[i] = a.parent[nn[i]];
+            if (a.x_row) xr[i] = a.x_row[nn[i]];
+        }
+    }
+    const bool is_x = !USE_GX && wave < 4;
+    constexpr int STEP = USE_GX ? 8 : 4, SPLIT_BATCH = USE_GX ? 1 : 2;   // chunks between a wave's, chunks per batch
+    const int first = USE_GX ? wave : wave & 3;
+    const int nkc = is_x ? a.nkc_x : a.nkc_h, K = is_x ? a.I : H;
+    const v4i *w = is_x ? a.wih : a.whh;
+    __builtin_amdgcn_sched_barrier(0);
+    v4i pa[SPLIT_BATCH][4];
+    auto load_weights = [&](int v0) {
+#pragma unroll
+        for (int it = 0; it < SPLIT_BATCH; ++it) {
+            int kc = v0 + it * STEP;
+            kc = kc < nkc ? kc : nkc - 1;   // uniform; what lies beyond the end is not contracted
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) pa[it][mt] = (w + ((size_t)(rt0 + mt) * nkc + kc) * 64)[lane];
+        }
+    };
+    load_weights(first);
+    __builtin_amdgcn_sched_barrier(0);
+    int n_live = N;
+    if (g.rows) {
+        n_live = *g.n_rows;
+        if (n0 >= n_live) return;   // uniform
+        n_live = n_live < N ? n_live : N;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            nn[i] = entry[i][0] < 0 ? 0 : (entry[i][0] >= a.n_out ? a.n_out - 1 : entry[i][0]);
+            s[i] = a.parent ? entry[i][1] : nn[i];
+            xr[i] = a.x_row ? entry[i][2] : nn[i];
+        }
+    }
+    const int8_t *row[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        s[i] = s[i] < 0 ? 0 : (s[i] >= a.n_slots ? a.n_slots - 1 : s[i]);
+        xr[i] = xr[i] < 0 ? 0 : (xr[i] >= a.n_x_rows ? a.n_x_rows - 1 : xr[i]);
+        row[i] = is_x ? a.x + (int64_t)xr[i] * a.ld_x + grp * 16 : a.h_prev + (int64_t)s[i] * a.ld_hp + grp * 16;
+    }
+    // this wave's tile: row tile rt0 + mt, column tile nt; cell j of hypothesis n
+    const int mt_o = wave & 3, nt_o = wave >> 2;
+    const int n = nt_o ? nn[1] : nn[0], src = nt_o ? s[1] : s[0], xsrc = nt_o ? xr[1] : xr[0];
+    const int rt = rt0 + mt_o, j = qr_gates_cell(rt, grp);
+    const bool n_ok = n0 + 16 * nt_o + col < n_live;
+
+    v4i acc[2][4];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[nt][mt] = zero;
+    float sx[4], sh[4], bb[4], cp = 0.0f;
+    int act = 1, hp_code = 0;
+    v4i gxv = zero;
+    for (int v0 = first; v0 == first || v0 < nkc; v0 += SPLIT_BATCH * STEP) {   // at least once: the loads of the cell
+        if (v0 != first) load_weights(v0);
+        v4i b0[SPLIT_BATCH][2], b1[SPLIT_BATCH][2];
+#pragma unroll
+        for (int it = 0; it < SPLIT_BATCH; ++it) {
+            int kc = v0 + it * STEP;
+            kc = kc < nkc ? kc : nkc - 1;
+            // (columns beyond K meet zero weights: any valid bytes do)
+            const int k = kc * QRNNT_KCHUNK;
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                b0[it][nt] = *(const v4i *)(row[nt] + (k + grp * 16 < K ? k : -grp * 16));
+                b1[it][nt] = *(const v4i *)(row[nt] + (k + 64 + grp * 16 < K ? k + 64 : -grp * 16));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (v0 == first) {   // what the cell will need, behind the first operands
+            cp = a.c_prev[(int64_t)src * H + j];
+            if (USE_GX) gxv = *(const v4i *)((TAB ? (const int32_t *)a.tabf : a.gx) + (int64_t)xsrc * a.ld_gx + rt * 16 + 4 * grp);
+            if (a.active) {
+                act = a.active[n];
+                hp_code = a.h_prev[(int64_t)src * a.ld_hp + j];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < SPLIT_BATCH; ++it)
+            if (v0 + it * STEP < nkc)   // uniform
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    v4i lo, hi;
+                    qr_unpack(pa[it][mt], lo, hi);
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt) {
+                        acc[nt][mt] = qr_mfma(lo, b0[it][nt], acc[nt][mt]);
+                        acc[nt][mt] = qr_mfma(hi, b1[it][nt], acc[nt][mt]);
+                    }
+                }
+    }
+    // (the row constants come from the XCD's own cache and arrive during the exchange)
+#pragma unroll
+    for (int gt = 0; gt < 4; ++gt) {
+        sh[gt] = a.s_whh[gt * H + j];
+        if (!TAB) sx[gt] = a.s_wih[gt * H + j];
+        if (!TAB) bb[gt] = a.bias[gt * H + j];
+    }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) part[wave][4 * nt + mt][lane] = acc[nt][mt];
+    __syncthreads();
+    v4i ax = zero, ah = zero;   // 16 x the sums
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        ax += part[q][wave][lane];
+        ah += part[4 + q][wave][lane];
+    }
+    if (USE_GX) ah += ax;
+
+    float p[4];
+#pragma unroll
+    for (int gt = 0; gt < 4; ++gt) {
+        const float k = gt == 2 ? -2.885390081777927f : -1.4426950408889634f;   // the constant its activation feeds to exp2
+        const float shk = sh[gt] * a.h_scale * (0.0625f * k);
+        if (TAB) {
+            p[gt] = __builtin_fmaf(shk, (float)ah[gt], __int_as_float(gxv[gt]));
+        } else if (USE_GX) {
+            p[gt] = __builtin_fmaf(sx[gt] * a.x_scale * k, (float)gxv[gt], __builtin_fmaf(shk, (float)ah[gt], bb[gt] * k));
+        } else {
+            p[gt] = __builtin_fmaf(shk, (float)ah[gt], __builtin_fmaf(sx[gt] * a.x_scale * (0.0625f * k), (float)ax[gt], bb[gt] * k));
+        }
+    }
+    const float gi = qr_sigmoid_scaled(p[0]), gf = qr_sigmoid_scaled(p[1]);
+    const float gg = 2.0f * qr_sigmoid_scaled(p[2]) - 1.0f, go = qr_sigmoid_scaled(p[3]);
+    const float c1 = __builtin_fmaf(gf, cp, gi * gg);
+    const float rc = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.885390081777927f * c1));
+    const float hq = go * (2.0f * a.h_inv * rc - a.h_inv);
+    const bool on = act != 0;
+    const int code = on ? (int)fminf(fmaxf(__builtin_rintf(hq), -8.0f), 7.0f) : hp_code;
+    if (!n_ok) return;
+    a.c_next[(int64_t)n * H + j] = on ? c1 : cp;
+    a.h_next[(int64_t)n * a.ld_hn + j] = (int8_t)code;
+    if (a.h_copy) a.h_copy[(int64_t)n * H + j] = (int8_t)code;
+    if (a.dbg_accx && (!USE_GX || !TAB))
+#pragma unroll
+        for (int gt = 0; gt < 4; ++gt) a.dbg_accx[(int64_t)n * 4 * H + gt * H + j] = USE_GX ? gxv[gt] : (ax[gt] >> 4);
+    if (a.dbg_acch)
+#pragma unroll
+        for (int gt = 0; gt < 4; ++gt) a.dbg_acch[(int64_t)n * 4 * H + gt * H + j] = ah[gt] >> 4;
+    if (a.dbg_gates && on) {
+        float *dg = a.dbg_gates + (int64_t)n * 4 * H + j;
+        dg[0] = gi; dg[H] = gf; dg[2 * H] = gg; dg[3 * H] = go;
+    }
+}
+
+template <bool USE_GX>
+void launch_split(const QrStepGroup &g, hipStream_t st)
+{
+    int max_n = 0, max_rg = 0;
+    bool tab = USE_GX;
+    for (int i = 0; i < g.n; ++i) {
+        max_n = g.p[i].N > max_n ? g.p[i].N : max_n;
+        max_rg = (g.p[i].H >> 4) > max_rg ? (g.p[i].H >> 4) : max_rg;
+        tab = tab && g.p[i].tabf != nullptr;
+    }
+    const dim3 grid(max_rg, g.n, (max_n + 31) / 32);
+    if (tab) lstm_step_split_kernel<USE_GX, USE_GX><<<grid, 512, 0, st>>>(g);
+    else lstm_step_split_kernel<USE_GX, false><<<grid, 512, 0, st>>>(g);
+}
+
 // Compute-bound variant (many hypotheses): multi-stage LDS ring, see mma_pipe.h.
 // Grid: x = blocks of 32*MT gate rows (8*MT cells), z = blocks of 32*NT hypotheses (or of a half or a
 // quarter of that: few hypotheses are spread over more workgroups, which then run a narrower instance
@@ -559,13 +761,14 @@ void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
         max_n = g.p[i].N > max_n ? g.p[i].N : max_n;
         gg.row_blocks += rb;
     }
-    // Without a list the width is chosen here, by the rule the kernel applies to a list's length: the narrowest
-    // share per workgroup at which the working workgroups are resident all at once.
-    gg.width = 0;
-    if (!g.rows)
-        for (int w = 1; w <= 2; ++w)
-            if (gg.row_blocks * ((max_n + (P::BN >> w) - 1) / (P::BN >> w)) <= gg.n_resident) gg.width = w;
-    const int per = P::BN >> gg.width;
+    // The width for max_n columns, by the rule the kernel applies to a list's length: the narrowest share per workgroup
+    // at which the working workgroups are resident all at once.  Without a list it is the launch's; with one it sizes
+    // the grid, so that a list of any length finds the blocks for its own width.
+    int width = 0;
+    for (int w = 1; w <= 2; ++w)
+        if (gg.row_blocks * ((max_n + (P::BN >> w) - 1) / (P::BN >> w)) <= gg.n_resident) width = w;
+    gg.width = g.rows ? 0 : width;
+    const int per = P::BN >> width;
     const int gz = (max_n + per - 1) / per;
     for (int z0 = 0; z0 < gz; z0 += 65535) {   // a grid's z extent ends at 65535
         gg.col_block0 = z0;
@@ -597,6 +800,13 @@ void launch_pipe(const QrStepGroup &g, hipStream_t st)
     else launch_pipe_f<MT, NT, S, USE_GX, false, false, false>(g, st);
 }
 
+// Hypothesis counts up to this go to the kernel that splits K over a workgroup's waves; what counts is how many advance,
+// and a list holds a third to a half of its hypotheses in most rounds.  Measured (this kernel / the tiled one, us):
+// second layers of 2 x 1024 cells 32 of 64 7.7 / 11.9, 64 of 128 7.5 / 11.1, 104 of 208 10.2 / 11.3, 208 of 208
+// 15.1 / 13.0; of 768 and 2048 cells 52 of 208 9.9 / 17.2, 104 of 208 14.7 / 17.6, 208 of 208 22.7 / 20.2.  A looked-up
+// input part halves the work that is split: first layers of 768 and 2 x 1024 cells 64 of 128 7.4 / 7.8, 104 of 208 11.2 / 8.8.
+static int split_n_max(bool use_gx, bool list) { return (use_gx ? 64 : 128) * (list ? 2 : 1); }
+
 // Hypothesis counts up to this go to the weight-streaming kernel.
 static int small_n_max()
 {
@@ -612,6 +822,7 @@ void launch_step_t(const QrStepArgs &a, hipStream_t st)
     g.n = 1;
     g.gate = nullptr;
     if (a.N <= small_n_max()) launch_small<USE_GX>(g, st);
+    else if (a.N <= split_n_max(USE_GX, g.rows != nullptr)) launch_split<USE_GX>(g, st);
     else launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);
 }
 
@@ -785,13 +996,15 @@ void qr_launch_lstm_step(const QrStepArgs &a, bool use_gx, hipStream_t st)
 template <bool USE_GX>
 static void launch_group_t(const QrStepGroup &g, hipStream_t st)
 {
-    // one launch when every member is in the compute-bound regime, else member by member
-    bool all_big = true, all_small = true;
+    // one launch when every member is in the same regime, else member by member
+    bool all_big = true, all_split = true, all_small = true;
     for (int i = 0; i < g.n; ++i) {
-        all_big = all_big && g.p[i].N > small_n_max();
+        all_big = all_big && g.p[i].N > split_n_max(USE_GX, g.rows != nullptr);
+        all_split = all_split && g.p[i].N > small_n_max() && g.p[i].N <= split_n_max(USE_GX, g.rows != nullptr);
         all_small = all_small && g.p[i].N <= small_n_max();
     }
     if (all_big) launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);
+    else if (all_split) launch_split<USE_GX>(g, st);
     else if (all_small) launch_small<USE_GX>(g, st);
     else
         for (int i = 0; i < g.n; ++i) launch_step_t<USE_GX>(g.p[i], st);
