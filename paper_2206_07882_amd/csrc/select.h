@@ -91,10 +91,12 @@ template <int PER, class IndexOf>
 __device__ __forceinline__ void qr_gather(const unsigned (&key)[PER], const QrBound &bound, IndexOf &&index_of, int lane, int *n, QrCand *list)
 {
     unsigned long long pass[PER];
+    bool in[PER];
     int n_pass = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        pass[i] = __ballot(bound.passes(key[i]));
+        in[i] = bound.passes(key[i]);
+        pass[i] = __ballot(in[i]);
         n_pass += (int)__popcll(pass[i]);
     }
     int base = 0;
@@ -103,7 +105,7 @@ __device__ __forceinline__ void qr_gather(const unsigned (&key)[PER], const QrBo
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(pass[i] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)pass[i], 0u));
-        if ((pass[i] >> lane) & 1ull) list[pos] = qr_cand(key[i], index_of(i));
+        if (in[i]) list[pos] = qr_cand(key[i], index_of(i));
         base += (int)__popcll(pass[i]);
     }
 }
