@@ -95,22 +95,42 @@ def load():
         lib.qrnnt_decode_alsd_workspace.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32]
         lib.qrnnt_diag_mfma_form_name.restype = C.c_char_p
         lib.qrnnt_act_pitch.restype = C.c_int32
+        # the calls of a caller-driven round: with their types declared, plain numbers and addresses go in as they are
+        vp, i32, f32 = C.c_void_p, C.c_int32, C.c_float
+        lib.qrnnt_linear.argtypes = [vp, vp, f32, vp, i32, i32, vp, vp, vp]
+        lib.qrnnt_linear_quant.argtypes = [vp, vp, f32, vp, i32, f32, i32, vp, vp]
+        lib.qrnnt_joint_fuse.argtypes = [vp, i32, vp, vp, vp, vp, f32, f32, vp, vp, f32, f32, f32, i32, i32, vp, vp, vp, vp]
+        lib.qrnnt_beam_step.argtypes = [vp, vp, i32, i32, i32, i32, i32, vp, vp, vp, vp]
+        lib.qrnnt_lstm_step_group.argtypes = [vp, i32, vp]
+        lib.qrnnt_lstm_step_group_listed.argtypes = [vp, i32, vp, vp, vp]
         _lib = lib
     return _lib
 
 
-def _ptr(t: Optional[torch.Tensor], dtype=None):
+def _addr(t: Optional[torch.Tensor], dtype=None):
+    """Address of a checked tensor, for functions whose argument types are declared (see load)."""
     if t is None:
         return None
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptr(t: Optional[torch.Tensor], dtype=None):
+    return None if t is None else C.c_void_p(_addr(t, dtype))
+
+
+def _stream_handle() -> int:
+    """The current stream of the current device, without the Stream object that torch.cuda.current_stream makes."""
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_stream_handle())
 
 
 def _check(status: int, where: str):
@@ -207,9 +227,8 @@ def linear(w: QMat, bias: Optional[torch.Tensor], a_scale: float, a: torch.Tenso
     y = torch.empty((N, w.rows), dtype=torch.float32, device=a.device)
     acc = torch.empty((N, w.rows), dtype=torch.int32, device=a.device) if want_acc else None
     cw = w.c()
-    _check(load().qrnnt_linear(C.byref(cw), _ptr(bias, torch.float32), C.c_float(a_scale), _ptr(a, torch.int8),
-                               C.c_int32(N), C.c_int32(1 if log_softmax else 0), _ptr(y), _ptr(acc), _stream()),
-           "qrnnt_linear")
+    _check(load().qrnnt_linear(C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N,
+                               1 if log_softmax else 0, y.data_ptr(), _addr(acc), _stream_handle()), "qrnnt_linear")
     return (y, acc) if want_acc else y
 
 
@@ -218,9 +237,8 @@ def linear_quant(w: QMat, bias: Optional[torch.Tensor], a_scale: float, a: torch
     N = a.shape[0]
     q = torch.empty((N, w.rows), dtype=torch.int8, device=a.device)
     cw = w.c()
-    _check(load().qrnnt_linear_quant(C.byref(cw), _ptr(bias, torch.float32), C.c_float(a_scale), _ptr(a, torch.int8),
-                                     C.c_int32(N), C.c_float(inv_scale), C.c_int32(bits), _ptr(q, torch.int8), _stream()),
-           "qrnnt_linear_quant")
+    _check(load().qrnnt_linear_quant(C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N, inv_scale,
+                                     bits, q.data_ptr(), _stream_handle()), "qrnnt_linear_quant")
     return q
 
 
@@ -304,11 +322,10 @@ class StepGroup:
         """list [>= N, 4] int32 and n_list [1] int32 (device): only the listed hypotheses advance
         (qrnnt_lstm_step_group_listed)."""
         if list is None:
-            _check(load().qrnnt_lstm_step_group(self.arr, C.c_int32(self.n), _stream()), "qrnnt_lstm_step_group")
+            _check(load().qrnnt_lstm_step_group(self.arr, self.n, _stream_handle()), "qrnnt_lstm_step_group")
         else:
-            _check(load().qrnnt_lstm_step_group_listed(self.arr, C.c_int32(self.n), _ptr(list, torch.int32),
-                                                       _ptr(n_list, torch.int32), _stream()),
-                   "qrnnt_lstm_step_group_listed")
+            _check(load().qrnnt_lstm_step_group_listed(self.arr, self.n, _addr(list, torch.int32), _addr(n_list, torch.int32),
+                                                       _stream_handle()), "qrnnt_lstm_step_group_listed")
 
 
 def input_projection(L: Lstm, x_codes: torch.Tensor, gx: Optional[torch.Tensor] = None, debug: bool = False):
@@ -414,12 +431,10 @@ def joint_fuse(enc_proj, frame_row, pred_proj, w_out: QMat, b_out, lp_src, lp_ex
     lp = torch.empty((N, V), dtype=torch.float32, device=dev) if want_lp else None
     zq = torch.zeros((N, J), dtype=torch.int8, device=dev) if want_zq else None
     cw = w_out.c()
-    st = load().qrnnt_joint_fuse(_ptr(enc2, torch.float32), C.c_int32(enc2.shape[0]), _ptr(frame_row, torch.int32),
-                                 _ptr(pred_proj, torch.float32), C.byref(cw), _ptr(b_out, torch.float32),
-                                 C.c_float(z_scale), C.c_float(z_inv_scale), _ptr(lp_src, torch.float32),
-                                 _ptr(lp_ext, torch.float32), C.c_float(lambda_src), C.c_float(lambda_ext),
-                                 C.c_float(rho), C.c_int32(N), C.c_int32(blank), _ptr(lp), _ptr(zq), _ptr(fused),
-                                 _stream())
+    st = load().qrnnt_joint_fuse(_addr(enc2, torch.float32), enc2.shape[0], _addr(frame_row, torch.int32),
+                                 _addr(pred_proj, torch.float32), C.byref(cw), _addr(b_out, torch.float32), z_scale,
+                                 z_inv_scale, _addr(lp_src, torch.float32), _addr(lp_ext, torch.float32), lambda_src,
+                                 lambda_ext, rho, N, blank, _addr(lp), _addr(zq), fused.data_ptr(), _stream_handle())
     _check(st, "qrnnt_joint_fuse")
     return fused, lp, zq
 
@@ -431,9 +446,8 @@ def beam_step(score: torch.Tensor, fused: torch.Tensor, blank: int = 0, force_bl
     par = torch.empty((B, W), dtype=torch.int32, device=dev)
     tok = torch.empty((B, W), dtype=torch.int32, device=dev)
     ns = torch.empty((B, W), dtype=torch.float32, device=dev)
-    st = load().qrnnt_beam_step(_ptr(score, torch.float32), _ptr(fused, torch.float32), C.c_int32(B), C.c_int32(W),
-                                C.c_int32(V), C.c_int32(blank), C.c_int32(1 if force_blank else 0), _ptr(par),
-                                _ptr(tok), _ptr(ns), _stream())
+    st = load().qrnnt_beam_step(_addr(score, torch.float32), _addr(fused, torch.float32), B, W, V, blank,
+                                1 if force_blank else 0, par.data_ptr(), tok.data_ptr(), ns.data_ptr(), _stream_handle())
     _check(st, "qrnnt_beam_step")
     return par, tok, ns
 
