@@ -109,53 +109,6 @@ __global__ __launch_bounds__(256) void joint_fuse_kernel(const QrJointArgs a)
         }
 }
 
-// Contraction of one network's output layer inside the decoding-round kernel: NB chunks of 128 columns per batch, all
-// loads of a batch before its first MFMA.  w + woff[mt]: this lane's 16 bytes of chunk 0 of row tile mt; act: this
-// lane's 16 columns of chunk 0 of its hypothesis' codes (K columns in all).  Chunks c0, c0 + step, ...
-// Memory answers in order: the caller requests the row number behind `row` before this asks for the weights, so that
-// the codes follow the weights without a second round trip.  then(): more loads to go with the first batch's codes.
-template <bool W8, int NB, class Then>
-__device__ __forceinline__ void qr_round_mma(const v4i *w, const unsigned (&woff)[4], const int8_t *acts, int row, int K, int nkc,
-                                             int c0, int step, int grp, v4i (&acc)[4], Then &&then)
-{
-    const int m = (int)0xF0F0F0F0u;
-    for (int kc0 = c0; kc0 < nkc; kc0 += NB * step) {
-        v4i p[NB][4][W8 ? 2 : 1], x0[NB], x1[NB];
-#pragma unroll
-        for (int it = 0; it < NB; ++it) {
-            int kc = kc0 + it * step;
-            kc = kc < nkc ? kc : nkc - 1;   // uniform; what lies beyond the end is not contracted
-            const char *base = (const char *)w + (size_t)kc * (W8 ? 2048 : 1024);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                p[it][mt][0] = *(const v4i *)(base + woff[mt]);
-                if (W8) p[it][mt][W8 ? 1 : 0] = *(const v4i *)(base + 1024 + woff[mt]);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (kc0 == c0) then();
-        const int8_t *act = acts + (int64_t)row * K + grp * 16;
-#pragma unroll
-        for (int it = 0; it < NB; ++it) {
-            int kc = kc0 + it * step;
-            kc = kc < nkc ? kc : nkc - 1;
-            // (columns beyond K meet zero weights: any valid bytes do)
-            const int k = kc * QRNNT_KCHUNK;
-            x0[it] = *(const v4i *)(act + (k + grp * 16 < K ? k : -grp * 16));
-            x1[it] = *(const v4i *)(act + (k + 64 + grp * 16 < K ? k + 64 : -grp * 16));
-        }
-#pragma unroll
-        for (int it = 0; it < NB; ++it)
-            if (kc0 + it * step < nkc)   // uniform
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    const v4i f = p[it][mt][0];
-                    acc[mt] = qr_mfma(W8 ? f : ((f << 4) & m), x0[it], acc[mt]);
-                    acc[mt] = qr_mfma(W8 ? p[it][mt][W8 ? 1 : 0] : (f & m), x1[it], acc[mt]);
-                }
-    }
-}
-
 // Maximum over the 16 lanes of a row, in each of them.
 __device__ __forceinline__ float qr_row_max(float x)
 {
@@ -349,8 +302,8 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                     for (int d = 0; d < 4; ++d) e[d] = *(const v4f *)(a.enc + fr * J + j0 + 4 * d);
                 };
                 v4i accp[4] = {zero, zero, zero, zero};
-                if (h.w8) qr_round_mma<true, NTW == 1 ? 3 : 1>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
-                else qr_round_mma<false, NTW == 1 ? 6 : 2>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
+                if (h.w8) qr_chunk_mma<true, NTW == 1 ? 3 : 1>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
+                else qr_chunk_mma<false, NTW == 1 ? 6 : 2>(h.w, woff, h.act, row, h.K, h.nkc, 0, 1, grp, accp, load_frame);
                 // the block's weights of the joint arrive while its codes are formed
                 v4i wj[4];
 #pragma unroll
@@ -399,8 +352,8 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                     const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
                     woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
                 }
-                if (h.w8) qr_round_mma<true, NTW == 1 ? 2 : 1>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
-                else qr_round_mma<false, NTW == 1 ? 4 : 2>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
+                if (h.w8) qr_chunk_mma<true, NTW == 1 ? 2 : 1>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
+                else qr_chunk_mma<false, NTW == 1 ? 4 : 2>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
             }
             if (frame_end && nt == 0) {
                 if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
