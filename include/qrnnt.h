@@ -468,6 +468,15 @@ int32_t qrnnt_diag_mfma_forms(void);
 const char *qrnnt_diag_mfma_form_name(int32_t form);
 qrnnt_status qrnnt_diag_mfma_rate(int32_t form, int32_t iters, float *sink, double *tops_out, void *stream);
 
+/* qrnnt_lstm_layer on a route that it takes by itself only under conditions that are hard to bring about (tests compare
+ * the routes).  route: 0 as qrnnt_lstm_layer, or QRNNT_DIAG_STEPWISE: as if the device could not hold the persistent
+ * kernel, one launch per time step (4-bit layers only). */
+#define QRNNT_DIAG_STEPWISE 1
+qrnnt_status qrnnt_diag_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, int32_t T, int32_t B, int32_t reverse,
+                                   const int8_t *h0, const float *c0, int8_t *h_out, int32_t ld_out, int32_t col_off,
+                                   int8_t *h_last, float *c_last, int32_t *dbg_accx, float *dbg_c_all, int32_t route,
+                                   void *workspace, size_t workspace_bytes, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1170,6 +1170,7 @@ struct LayerCall {
     int8_t *h_last;  float *c_last;
     int32_t *dbg_accx;  float *dbg_c_all;
     char *ws;
+    int32_t route;                     // 0, or a route that qrnnt_diag_lstm_layer asks for
 };
 
 qrnnt_status check_layer_call(const LayerCall &c, const int8_t *x_codes, int T, int B, const int8_t *h_out, int ld_out)
@@ -1227,11 +1228,12 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
             a.w8 = qr_bits(&L->w_hh) == 8;
         }
     }
+    const bool refused = (calls[0].route & QRNNT_DIAG_STEPWISE) != 0;
     if (persist) clear_kernel<<<dim3((unsigned)((clear.n + 255) / 256), n), 256, 0, st>>>(clear);
-    if (persist && n == 2 && rg.d[0].w8 != rg.d[1].w8) {   // a launch has one width: direction by direction
+    if (persist && !refused && n == 2 && rg.d[0].w8 != rg.d[1].w8) {   // a launch has one width: direction by direction
         QrRecGroup one[2] = {{{rg.d[0]}, 1}, {{rg.d[1]}, 1}};
         if (qr_launch_recurrence(one[0], st) && qr_launch_recurrence(one[1], st)) return qr_launch_status();
-    } else if (persist && qr_launch_recurrence(rg, st)) {
+    } else if (persist && !refused && qr_launch_recurrence(rg, st)) {
         return qr_launch_status();
     }
     QR_REQUIRE(!any8, QRNNT_ERR_UNSUPPORTED);
@@ -1240,6 +1242,8 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
         const qrnnt_lstm *L = c.L;
         const LayerWs w = layer_ws(L, T, B);
         int32_t *gx = (int32_t *)c.ws;
+        // the persistent kernel would have formed the sums of the input part itself
+        if (persist && qr_rec_projects(L->input_size) && !c.dbg_accx) qr_launch_input_projection(L, x_codes, T * B, gx, nullptr, st);
         int8_t *hbuf = (int8_t *)(c.ws + w.gx_b);
         float *cbuf[2] = {(float *)(c.ws + w.gx_b + 2 * w.h_b), (float *)(c.ws + w.gx_b + 2 * w.h_b + w.c_b)};
         if (c.h0 == nullptr) {
@@ -1286,17 +1290,34 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
 
 }  // namespace
 
+static qrnnt_status one_layer(const LayerCall &c, const int8_t *x_codes, int T, int B, int8_t *h_out, int ld_out,
+                              size_t workspace_bytes, void *stream)
+{
+    qrnnt_status s = check_layer_call(c, x_codes, T, B, h_out, ld_out);
+    if (s != QRNNT_OK) return s;
+    QR_REQUIRE(workspace_bytes >= layer_ws(c.L, T, B).total, QRNNT_ERR_WORKSPACE);
+    return run_layer(&c, 1, x_codes, T, B, h_out, ld_out, (hipStream_t)stream);
+}
+
 extern "C" qrnnt_status qrnnt_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, int32_t T, int32_t B,
                                          int32_t reverse, const int8_t *h0, const float *c0, int8_t *h_out,
                                          int32_t ld_out, int32_t col_off, int8_t *h_last, float *c_last,
                                          int32_t *dbg_accx, float *dbg_c_all, void *workspace, size_t workspace_bytes,
                                          void *stream)
 {
-    LayerCall c = {L, reverse, h0, c0, col_off, h_last, c_last, dbg_accx, dbg_c_all, (char *)workspace};
-    qrnnt_status s = check_layer_call(c, x_codes, T, B, h_out, ld_out);
-    if (s != QRNNT_OK) return s;
-    QR_REQUIRE(workspace_bytes >= layer_ws(L, T, B).total, QRNNT_ERR_WORKSPACE);
-    return run_layer(&c, 1, x_codes, T, B, h_out, ld_out, (hipStream_t)stream);
+    return one_layer({L, reverse, h0, c0, col_off, h_last, c_last, dbg_accx, dbg_c_all, (char *)workspace, 0}, x_codes, T, B,
+                     h_out, ld_out, workspace_bytes, stream);
+}
+
+extern "C" qrnnt_status qrnnt_diag_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, int32_t T, int32_t B,
+                                              int32_t reverse, const int8_t *h0, const float *c0, int8_t *h_out,
+                                              int32_t ld_out, int32_t col_off, int8_t *h_last, float *c_last,
+                                              int32_t *dbg_accx, float *dbg_c_all, int32_t route, void *workspace,
+                                              size_t workspace_bytes, void *stream)
+{
+    QR_REQUIRE((route & ~QRNNT_DIAG_STEPWISE) == 0, QRNNT_ERR_RANGE);
+    return one_layer({L, reverse, h0, c0, col_off, h_last, c_last, dbg_accx, dbg_c_all, (char *)workspace, route}, x_codes, T, B,
+                     h_out, ld_out, workspace_bytes, stream);
 }
 
 extern "C" size_t qrnnt_bilstm_layer_workspace(const qrnnt_lstm *fwd, const qrnnt_lstm *bwd, int32_t T, int32_t B)
@@ -1312,8 +1333,8 @@ extern "C" qrnnt_status qrnnt_bilstm_layer(const qrnnt_lstm *fwd, const qrnnt_ls
     QR_REQUIRE(fwd->hidden_size > 0 && fwd->hidden_size == bwd->hidden_size && fwd->input_size == bwd->input_size,
                QRNNT_ERR_SHAPE);
     const int H = fwd->hidden_size;
-    LayerCall c[2] = {{fwd, 0, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, (char *)workspace},
-                      {bwd, 1, nullptr, nullptr, H, nullptr, nullptr, nullptr, nullptr, nullptr}};
+    LayerCall c[2] = {{fwd, 0, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, (char *)workspace, 0},
+                      {bwd, 1, nullptr, nullptr, H, nullptr, nullptr, nullptr, nullptr, nullptr, 0}};
     if (T > 0 && B > 0 && workspace) c[1].ws = (char *)workspace + layer_ws(fwd, T, B).total;
     for (int d = 0; d < 2; ++d) {
         qrnnt_status s = check_layer_call(c[d], x_codes, T, B, h_out, 2 * H);
@@ -1359,7 +1380,7 @@ extern "C" qrnnt_status qrnnt_lstm_layer_static(const qrnnt_lstm *L, const int8_
                                                 void *stream)
 {
     // validation first (needs no GPU): a dummy non-null workspace address stands in until the size is known to fit
-    LayerCall c = {L, reverse, h0, c0, col_off, h_last, c_last, nullptr, nullptr, (char *)(uintptr_t)256};
+    LayerCall c = {L, reverse, h0, c0, col_off, h_last, c_last, nullptr, nullptr, (char *)(uintptr_t)256, 0};
     qrnnt_status s = check_layer_call(c, x_codes, T, B, h_out, ld_out);
     if (s != QRNNT_OK) return s;
     QR_REQUIRE(layer_ws(L, T, B).total <= QR_STATIC_WS_BYTES, QRNNT_ERR_WORKSPACE);

@@ -64,7 +64,7 @@ EXPORTS = ["qrnnt_status_str", "qrnnt_abi_version", "qrnnt_pack_int4_bytes", "qr
            "qrnnt_bilstm_layer_workspace", "qrnnt_bilstm_layer", "qrnnt_lstm_layer_static",
            "qrnnt_joint_fuse", "qrnnt_beam_step", "qrnnt_decode_workspace", "qrnnt_decode", "qrnnt_decode_ex",
            "qrnnt_decode_alsd_workspace", "qrnnt_decode_alsd", "qrnnt_decode_alsd_ex",
-           "qrnnt_diag_mfma_forms", "qrnnt_diag_mfma_form_name", "qrnnt_diag_mfma_rate"]
+           "qrnnt_diag_mfma_forms", "qrnnt_diag_mfma_form_name", "qrnnt_diag_mfma_rate", "qrnnt_diag_lstm_layer"]
 
 DECODE_EARLY_STOP = 1
 
@@ -355,7 +355,8 @@ def lstm_layer_workspace(L: Lstm, T: int, B: int) -> int:
 
 
 def lstm_layer(L: Lstm, x_codes: torch.Tensor, reverse: bool = False, h0=None, c0=None, h_out=None, col_off: int = 0,
-               want_last: bool = False, debug: bool = False, workspace: Optional[torch.Tensor] = None):
+               want_last: bool = False, debug: bool = False, workspace: Optional[torch.Tensor] = None, route: int = 0):
+    """route: 0, or the DIAG_ one to take instead of the layer's own choice (qrnnt_diag_lstm_layer)."""
     T, B, I = x_codes.shape
     dev = x_codes.device
     H = L.H
@@ -371,15 +372,18 @@ def lstm_layer(L: Lstm, x_codes: torch.Tensor, reverse: bool = False, h0=None, c
     accx = torch.zeros((T, B, 4 * H), dtype=torch.int32, device=dev) if debug else None
     c_all = torch.zeros((T, B, H), dtype=torch.float32, device=dev) if debug else None
     cl = L.c()
-    st = load().qrnnt_lstm_layer(C.byref(cl), _ptr(x_codes, torch.int8), C.c_int32(T), C.c_int32(B),
-                                 C.c_int32(1 if reverse else 0), _ptr(h0, torch.int8), _ptr(c0, torch.float32),
-                                 _ptr(h_out, torch.int8), C.c_int32(ld), C.c_int32(col_off), _ptr(h_last), _ptr(c_last),
-                                 _ptr(accx), _ptr(c_all), _ptr(workspace), C.c_size_t(workspace.numel()), _stream())
-    _check(st, "qrnnt_lstm_layer")
+    fn, name = (load().qrnnt_diag_lstm_layer, "qrnnt_diag_lstm_layer") if route else (load().qrnnt_lstm_layer, "qrnnt_lstm_layer")
+    st = fn(C.byref(cl), _ptr(x_codes, torch.int8), C.c_int32(T), C.c_int32(B),
+            C.c_int32(1 if reverse else 0), _ptr(h0, torch.int8), _ptr(c0, torch.float32),
+            _ptr(h_out, torch.int8), C.c_int32(ld), C.c_int32(col_off), _ptr(h_last), _ptr(c_last),
+            _ptr(accx), _ptr(c_all), *((C.c_int32(route),) if route else ()), _ptr(workspace),
+            C.c_size_t(workspace.numel()), _stream())
+    _check(st, name)
     return dict(h_out=h_out, h_last=h_last, c_last=c_last, accx=accx, c_all=c_all)
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20
+DIAG_STEPWISE = 1
 
 
 def lstm_layer_static(L: Lstm, x_codes: torch.Tensor, h_out: torch.Tensor, reverse: bool = False, h0=None, c0=None,

@@ -77,3 +77,25 @@ def test_two_directions(gpu_lib, T, B, bits):
     assert q.layer_error_flag(ws, q.lstm_layer_workspace(pairs[0][1], T, B)) == 0 and q.layer_error_flag(ws, ws.numel()) == 0
     for d in range(2):
         _check(pairs[d][0], x, out[:, :, d * H:(d + 1) * H], None, d == 1, None, None, 127.0 if bits[d] == 8 else 7.0, f"dir {d}")
+
+
+@pytest.mark.parametrize("T,B,I,H,reverse,state", [(7, 3, 340, 640, False, True), (5, 20, 1280, 48, True, False),
+                                                   (6, 40, 64, 768, False, True)])
+def test_refused_recurrence_runs_step_by_step(gpu_lib, T, B, I, H, reverse, state):
+    """A device that cannot hold the persistent kernel: the layer goes step by step, with sums of the input part that the
+    persistent kernel would have formed by itself (the workspace holds whatever an earlier call left there)."""
+    q = gpu_lib
+    s_x = float(np.float32(4) / np.float32(7))
+    L, G = _lstm_pair(q, 5371 + I + H, I, H, s_x)
+    x = synth.codes(5372 + T, (T, B, I), -8, 7)
+    xp = np.zeros((T, B, q.act_pitch(I)), np.int8)
+    xp[..., :I] = x
+    h0 = synth.codes(5373, (B, H), -7, 7) if state else None
+    c0 = synth.normal(5374, (B, H), 0.6) if state else None
+    need = q.lstm_layer_workspace(G, T, B)
+    ws = torch.full((need,), 0x55, dtype=torch.uint8, device=DEV)
+    out = q.lstm_layer(G, dev(xp), reverse=reverse, h0=None if h0 is None else dev(h0), c0=None if c0 is None else dev(c0),
+                       want_last=True, workspace=ws, route=q.DIAG_STEPWISE)
+    assert q.layer_error_flag(ws, need) == 0
+    hl, _ = _check(L, x, host(out["h_out"]), None, reverse, h0, c0, 7.0, f"step by step H={H}")
+    assert np.array_equal(host(out["h_last"]), hl)
