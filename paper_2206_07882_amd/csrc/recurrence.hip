@@ -47,45 +47,18 @@ namespace {
 
 constexpr int N_XCD = 8;
 
-// NL 128-bit loads from base + off[i].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every cache that is
-// not coherent.  What a lane finds says by itself whether it is current, so the time between the loads and the wait for
-// them (wait_words, which every use of v[] follows) can be used.
-#define QR_LD(i, F) "global_load_dwordx4 %[v" #i "], %[o" #i "], %[b] " F "\n\t"
-#define QR_O(i) [v##i] "=&v"(v[i])
-#define QR_W(i) "+v"(v[i])
-#define QR_I(i) [o##i] "v"(off[i])
-#define QR_2(M) M(0), M(1)
-#define QR_4(M) QR_2(M), M(2), M(3)
-#define QR_5(M) QR_4(M), M(4)
-#define QR_8(M) QR_5(M), M(5), M(6), M(7)
-#define QR_10(M) QR_8(M), M(8), M(9)
-#define QR_16(M) QR_10(M), M(10), M(11), M(12), M(13), M(14), M(15)
-#define QR_LDS2(F) QR_LD(0, F) QR_LD(1, F)
-#define QR_LDS4(F) QR_LDS2(F) QR_LD(2, F) QR_LD(3, F)
-#define QR_LDS5(F) QR_LDS4(F) QR_LD(4, F)
-#define QR_LDS8(F) QR_LDS5(F) QR_LD(5, F) QR_LD(6, F) QR_LD(7, F)
-#define QR_LDS10(F) QR_LDS8(F) QR_LD(8, F) QR_LD(9, F)
-#define QR_LDS16(F) QR_LDS10(F) QR_LD(10, F) QR_LD(11, F) QR_LD(12, F) QR_LD(13, F) QR_LD(14, F) QR_LD(15, F)
-#define QR_EACH_N QR_N(2) QR_N(4) QR_N(5) QR_N(8) QR_N(10) QR_N(16)
-
+// NL 128-bit loads from `bytes` bytes at base, at off[i].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every
+// cache that is not coherent.  What a lane finds says by itself whether it is current, so the time between the loads and
+// the first use of v[] can be used; the compiler places the wait, in front of whatever touches v[] first, a spill included.
 template <int NL, bool LOCAL>
-__device__ __forceinline__ void load_words(const char *base, const unsigned (&off)[NL], v4i (&v)[NL])
+__device__ __forceinline__ void load_words(const char *base, unsigned bytes, const unsigned (&off)[NL], v4i (&v)[NL])
 {
-#define QR_N(n)                                                                                                      \
-    if constexpr (NL == n) {                                                                                         \
-        if constexpr (LOCAL) asm volatile(QR_LDS##n("sc1") : QR_##n(QR_O) : QR_##n(QR_I), [b] "s"(base) : "memory"); \
-        else asm volatile(QR_LDS##n("sc0 sc1") : QR_##n(QR_O) : QR_##n(QR_I), [b] "s"(base) : "memory");             \
-    }
-    QR_EACH_N
-#undef QR_N
-}
-
-template <int NL>
-__device__ __forceinline__ void wait_words(v4i (&v)[NL])
-{
-#define QR_N(n) if constexpr (NL == n) asm volatile("s_waitcnt vmcnt(0)" : QR_##n(QR_W)::"memory");
-    QR_EACH_N
-#undef QR_N
+    constexpr int SC0 = 1, SC1 = 16;
+    const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000 /* raw bytes */);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) v[i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off[i], 0, LOCAL ? SC1 : SC0 | SC1);
+    asm volatile("" ::: "memory");   // every poll loads anew
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Stores with the lanes outside `mask` left out, in one block instead of under a branch: the instructions around it stay
@@ -477,9 +450,9 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             v4i bf[KH];
             for (int spins = 0;; ++spins) {
                 v4i v[NL];
-                load_words<NL, LOCAL>(src, off, v);
+                load_words<NL, LOCAL>(src, (unsigned)ug_bytes, off, v);
                 prepare(s);
-                wait_words<NL>(v);
+                __builtin_amdgcn_sched_barrier(0);
                 unsigned bad0 = 0u, bad1 = 0u;
 #pragma unroll
                 for (int i = 0; i < NL; ++i)

@@ -1,0 +1,29 @@
+"""Loads written in inline asm have to wait for their data inside the same statement: the compiler takes the output
+registers as written once the statement is over and may move, spill or reuse them while the load is still in flight.
+(Loads that go to LDS have no output register.)"""
+import glob
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2206_07882_amd", "csrc")
+LOAD = re.compile(r"\b(?:global_load|buffer_load|flat_load|scratch_load|s_load|ds_read|ds_load)_(?!lds)\w+")
+
+
+def _unwaited(text):
+    # runs of string literals (what a macro puts between them included): a statement's code
+    runs = re.findall(r'"(?:[^"\\\n]|\\.)*"(?:[^;"{}()\n]*\\?\n?\s*"(?:[^"\\\n]|\\.)*")*', text)
+    return [LOAD.search(r).group(0) for r in runs if LOAD.search(r) and "s_waitcnt" not in r]
+
+
+def test_asm_loads_wait_in_their_own_statement():
+    files = sorted(glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.hip")))
+    assert len(files) > 10
+    found = {os.path.basename(f): _unwaited(open(f).read()) for f in files}
+    assert not any(found.values()), {k: v for k, v in found.items() if v}
+
+
+def test_the_search_finds_what_it_looks_for():
+    assert _unwaited('asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(v) : "v"(p));') == ["global_load_dwordx4"]
+    assert _unwaited('#define LD(i) "buffer_load_dword %[v" #i "], %[o], %[r], 0 offen"') == ["buffer_load_dword"]
+    assert not _unwaited('asm volatile("global_load_dword %0, %1, off\\n\\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p));')
+    assert not _unwaited('asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p));')
