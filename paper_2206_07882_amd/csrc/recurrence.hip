@@ -47,16 +47,17 @@ namespace {
 
 constexpr int N_XCD = 8;
 
-// NL 128-bit loads from `bytes` bytes at base, at off[i].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every
+// PER 128-bit loads from `bytes` bytes at base at each off[k].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every
 // cache that is not coherent.  What a lane finds says by itself whether it is current, so the time between the loads and
 // the first use of v[] can be used; the compiler places the wait, in front of whatever touches v[] first, a spill included.
-template <int NL, bool LOCAL>
-__device__ __forceinline__ void load_words(const char *base, unsigned bytes, const unsigned (&off)[NL], v4i (&v)[NL])
+template <int KH, int PER, bool LOCAL>
+__device__ __forceinline__ void load_words(const char *base, unsigned bytes, const unsigned (&off)[KH], v4i (&v)[KH * PER])
 {
     constexpr int SC0 = 1, SC1 = 16;
     const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000 /* raw bytes */);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) v[i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off[i], 0, LOCAL ? SC1 : SC0 | SC1);
+    for (int i = 0; i < KH * PER; ++i)
+        v[i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off[i / PER] + 16 * (i % PER), 0, LOCAL ? SC1 : SC0 | SC1);
     asm volatile("" ::: "memory");   // every poll loads anew
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -131,6 +132,12 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     __shared__ v4i part[2][4][CELLS][64];   // [parity][wave][row tile][lane] partial sums on their way to the K partner
     __shared__ v4i px[2][2][2][4][64];      // [parity][K half][cell group][row tile][lane] sums of the input part
     __shared__ __attribute__((aligned(1024))) v4i xs[KX > 0 ? 3 * 2 * KX : 1][64];   // three frames of input codes, blocks of 8 utterances x 128 columns
+    // Where the weights leave no registers for them (up to 57 spilled), what a lane needs once a step lies in LDS: row
+    // scales and biases of its cells, row sums of its wave's weights.  50 steps of 2 x 768 cells at 320 inputs and 32
+    // utterances: 4-bit 88 -> 76 us, 8-bit 158 -> 119 us.
+    constexpr bool PARK = KH >= 8 && (W8 || CELLS == 2);
+    __shared__ v4f pk[PARK ? CELLS : 1][3][PARK ? 256 : 1];
+    __shared__ v4i pk_rsum[PARK && !W8 ? 4 : 1][PARK && !W8 ? 256 : 1];
     __shared__ int s_fail[2], s_local;
     // group and member from the workgroup id: ids congruent mod 8 share an XCD
     const int id = (int)blockIdx.x;
@@ -289,6 +296,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
         }
     // 4-bit: minus the row sums of the weights (x 16), which a step number in the low nibbles multiplies
     v4i nrsum[4];
+    const int pt = wave * 64 + lane;            // this lane's place in what is parked
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         nrsum[i] = zero;
@@ -296,6 +304,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
         if (!W8)
 #pragma unroll
             for (int k = 0; k < KH; ++k) nrsum[i] = qr_mfma(A[i][k], minus_ones, nrsum[i]);
+        if constexpr (PARK && !W8) pk_rsum[i][pt] = nrsum[i];
     }
     // ---- the cells this lane finishes: j0 .. j0 + CELLS - 1 of utterance n
     const int my_col = CELLS == 1 ? col & 7 : col;
@@ -305,7 +314,8 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     const int j0 = 16 * cgc + 4 * grp + 2 * kh + sub;
     // exact powers of two undo what the 4-bit operands carry: 16 (x as it is) and 256
     constexpr float X_UNIT = (W8 || KX == 0) ? 1.0f : 0.0625f, H_UNIT = W8 ? 1.0f : 0.00390625f;
-    float sx[CELLS][4], sh[CELLS][4], bb[CELLS][4], c[CELLS];
+    v4f sx[CELLS], sh[CELLS], bb[CELLS];
+    float c[CELLS];
 #pragma unroll
     for (int ct = 0; ct < CELLS; ++ct) {
 #pragma unroll
@@ -313,6 +323,11 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             sx[ct][gt] = a.x_scale * a.s_wih[gt * H + j0 + ct] * X_UNIT;
             sh[ct][gt] = a.h_scale * a.s_whh[gt * H + j0 + ct] * H_UNIT;
             bb[ct][gt] = a.bias[gt * H + j0 + ct];
+        }
+        if constexpr (PARK) {
+            pk[ct][0][pt] = sx[ct];
+            pk[ct][1][pt] = sh[ct];
+            pk[ct][2][pt] = bb[ct];
         }
         c[ct] = a.c0 ? a.c0[(int64_t)nn * H + j0 + ct] : 0.0f;
     }
@@ -323,13 +338,12 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     const size_t ug_bytes = (size_t)n_groups * 256 * PER;
     char *const xb0 = a.xbuf + (size_t)ug * ug_bytes;   // this group's area, even steps
     char *const xb1 = xb0 + (size_t)((B + 15) >> 4) * ug_bytes;   // odd steps
-    unsigned off[NL];
+    unsigned off[KH];
 #pragma unroll
     for (int k = 0; k < KH; ++k) {
         int q = 4 * (kh + 2 * k) + grp;         // 16-cell group of this lane's operand; beyond the layer: any valid one (it meets zero weights)
         q = q < n_groups ? q : 0;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) off[k * PER + u] = (unsigned)((q * ncol + (col & (ncol - 1))) * 16 * PER + 16 * u);
+        off[k] = (unsigned)((q * ncol + (col & (ncol - 1))) * 16 * PER);
     }
     const unsigned st_off = (unsigned)(((cgc * ncol + (my_col & (ncol - 1))) * 16 + 4 * grp + 2 * kh + sub) * PER);
     const unsigned long long pub_mask = __ballot(have && my_col < ncol);
@@ -353,28 +367,38 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     float gx[CELLS][4];                         // this step's sums of the input part
     // What a step can do while its operands are on their way: its sums of the input part, and the start of its
     // accumulators, minus what the step number in the operands adds.  (The empty blocks keep the compiler from moving
-    // this in front of the loads or behind the wait for them.)
-    auto prepare = [&](int s) {
-        int tag = s & 15;
-        asm volatile("" : "+s"(tag));
+    // this in front of the loads or behind the wait for them.)  Where registers are short the sums wait for the end of
+    // the contraction.
+    constexpr bool LATE_X = PARK && W8;
+    auto load_x = [&](int s, v4i (&x0)[CELLS], v4i (&x1)[CELLS]) {
         const v4i *p0 = &px[__builtin_amdgcn_readfirstlane(s & 1)][0][0][0][0] + px_at, *p1 = p0 + 2 * 4 * 64;
-        v4i x0[CELLS], x1[CELLS];
 #pragma unroll
         for (int ct = 0; ct < CELLS; ++ct) {
             x0[ct] = p0[64 * ct];
             x1[ct] = p1[64 * ct];
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int gt = 0; gt < 4; ++gt) acc[i][gt] = W8 ? 0 : __mul24(nrsum[i][gt], tag);
+    };
+    auto add_x = [&](const v4i (&x0)[CELLS], const v4i (&x1)[CELLS]) {
 #pragma unroll
         for (int ct = 0; ct < CELLS; ++ct) {
 #pragma unroll
             for (int gt = 0; gt < 4; ++gt) gx[ct][gt] = (float)(x0[ct][gt] + x1[ct][gt]);
             asm volatile("" : "+v"(gx[ct][0]), "+v"(gx[ct][1]), "+v"(gx[ct][2]), "+v"(gx[ct][3]));
         }
-        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+    };
+    auto prepare = [&](int s) {
+        int tag = s & 15;
+        if (!W8) asm volatile("" : "+s"(tag));
+        v4i x0[CELLS], x1[CELLS];
+        if (!LATE_X) load_x(s, x0, x1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (PARK && !W8) nrsum[i] = pk_rsum[i][pt];
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) acc[i][gt] = W8 ? 0 : __mul24(nrsum[i][gt], tag);
+        }
+        if (!LATE_X) add_x(x0, x1);
+        if (!W8) asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
     };
     // The K partner's tiles of a step, from its operands; their way through LDS then runs under the own tiles' contraction.
     auto partner_tiles = [&](const v4i (&bf)[KH]) {
@@ -407,6 +431,11 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             acc[1] = qr_mfma(A[1][k], bf[k], acc[1]);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (LATE_X) {                               // (in front of the barrier behind which they are overwritten)
+            v4i x0[CELLS], x1[CELLS];
+            load_x(s, x0, x1);
+            add_x(x0, x1);
+        }
         store_out<CELLS>(hq, codes, s > 0 ? out_mask : 0ull);   // the codes of the step before: here they hold nothing up
         hq += s > 0 ? h_step : 0;
         lds_barrier();
@@ -420,6 +449,11 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
         unsigned word = W8 ? (unsigned)((s + 1) & 0xFF) * 0x01000100u : (unsigned)((s + 1) & 15) * 0x0101u;
 #pragma unroll
         for (int ct = 0; ct < CELLS; ++ct) {
+            if constexpr (PARK) {
+                sx[ct] = pk[ct][0][pt];
+                sh[ct] = pk[ct][1][pt];
+                bb[ct] = pk[ct][2][pt];
+            }
             float p[4];
 #pragma unroll
             for (int gt = 0; gt < 4; ++gt) p[gt] = sx[ct][gt] * gx[ct][gt] + (sh[ct][gt] * (float)asum[ct][gt] + bb[ct][gt]);
@@ -450,7 +484,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             v4i bf[KH];
             for (int spins = 0;; ++spins) {
                 v4i v[NL];
-                load_words<NL, LOCAL>(src, (unsigned)ug_bytes, off, v);
+                load_words<KH, PER, LOCAL>(src, (unsigned)ug_bytes, off, v);
                 prepare(s);
                 __builtin_amdgcn_sched_barrier(0);
                 unsigned bad0 = 0u, bad1 = 0u;
