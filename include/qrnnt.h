@@ -247,21 +247,25 @@ qrnnt_status qrnnt_lstm_step_group_listed(const qrnnt_step_desc *steps, int32_t 
 
 size_t qrnnt_lstm_layer_workspace(const qrnnt_lstm *L, int32_t T, int32_t B);
 
-/* x_codes [device] [T,B,I] int8 (row pitch qrnnt_act_pitch(I)).  The input projection of all T*B frames is
- * one integer GEMM; the recurrence then runs t = 0..T-1 (T-1..0 if reverse).
+/* x_codes [device] [T,B,I] int8 (row pitch qrnnt_act_pitch(I)).  The recurrence runs t = 0..T-1 (T-1..0 if
+ * reverse); up to I = 1280 it contracts the input codes of each step by itself, for wider inputs the projection of
+ * all T*B frames is one integer GEMM in front of it.
  * Output codes go to h_out[(t*B + b)*ld_out + col_off + j], so the two
  * directions of a bidirectional layer fill the two halves of [T,B,2H] (both
  * use the FIX +-1 grid, Sec. 3.2).  h0/c0 [device] [B,H] or NULL (zero state,
  * as Sec. 3.4 assumes).  h_last/c_last [device] [B,H] or NULL.  Debug
  * [device] or NULL: dbg_accx int32 [T,B,4H] (source row order), dbg_c_all fp32
  * [T,B,H].  All utterances have length T.
- * The recurrence runs as one persistent kernel (H/16 x ceil(B/16) workgroups per
- * direction, exchanging hidden codes through the workspace) when H <= 1024 and all
- * of those workgroups fit on the device at once (as reported by the runtime's
- * occupancy query for an otherwise idle device); otherwise as one fused launch per
- * time step (4-bit layers only: an 8-bit layer that cannot take the persistent path
- * returns QRNNT_ERR_UNSUPPORTED).  The persistent kernel's waits are bounded: if one
- * ever runs out (e.g. other work keeps part of the device busy), the int32 at
+ * The recurrence runs as one persistent kernel when H <= 1024: a group of ceil(H/32)
+ * workgroups, one per compute unit of one XCD, for every 16 utterances and direction,
+ * exchanging hidden codes through the workspace; more groups than the device holds at
+ * once go in several launches.  If not even one group fits (as reported by the runtime's
+ * occupancy query) the layer takes one fused launch per time step (4-bit layers only:
+ * an 8-bit layer that cannot take the persistent path returns QRNNT_ERR_UNSUPPORTED).
+ * Layers may run on several streams at the same time, each with its own workspace.  A
+ * group that does not get all of its compute units within about the time that the layer
+ * takes goes ahead on those it has: the same results, more slowly.  Waits inside a group
+ * are bounded: if one ever runs out, the int32 at
  * workspace + qrnnt_lstm_layer_workspace(L, T, B) - 256 is set to 1 and the outputs
  * are invalid; it is 0 after every other call. */
 qrnnt_status qrnnt_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, int32_t T, int32_t B, int32_t reverse,
@@ -469,9 +473,12 @@ const char *qrnnt_diag_mfma_form_name(int32_t form);
 qrnnt_status qrnnt_diag_mfma_rate(int32_t form, int32_t iters, float *sink, double *tops_out, void *stream);
 
 /* qrnnt_lstm_layer on a route that it takes by itself only under conditions that are hard to bring about (tests compare
- * the routes).  route: 0 as qrnnt_lstm_layer, or QRNNT_DIAG_STEPWISE: as if the device could not hold the persistent
- * kernel, one launch per time step (4-bit layers only). */
+ * the routes).  route: 0 as qrnnt_lstm_layer, or
+ *   QRNNT_DIAG_STEPWISE: as if the device could not hold the persistent kernel, one launch per time step (4-bit layers);
+ *   QRNNT_DIAG_SPREAD:   as if the workgroups of a group ran on several XCDs;
+ *   n << 8 (1..32):      as if only n workgroups of a group were resident together. */
 #define QRNNT_DIAG_STEPWISE 1
+#define QRNNT_DIAG_SPREAD 2
 qrnnt_status qrnnt_diag_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, int32_t T, int32_t B, int32_t reverse,
                                    const int8_t *h0, const float *c0, int8_t *h_out, int32_t ld_out, int32_t col_off,
                                    int8_t *h_last, float *c_last, int32_t *dbg_accx, float *dbg_c_all, int32_t route,

@@ -143,21 +143,24 @@ struct QrRecArgs {
     int8_t *h_out;  int64_t ld_out;  int col_off;
     int8_t *h_last;  float *c_last;  float *dbg_c_all;
     char *xbuf;                        // exchange area (qr_rec_xbuf_bytes), zeroed before the launch
-    int *xcc;                          // where each workgroup runs (qr_rec_xcc_bytes), zeroed before the launch
+    unsigned long long *admit;         // one word per utterance group (qr_rec_admit_bytes), zeroed before the launch
+    float *c_buf;                      // [B][H]: cell states of a group whose members are not resident together
     int *err;                          // set to 1 when a bounded wait ran out
     int T, B, H, nkc_h, reverse, spin_limit;
+    int admit_ticks;                   // how long a group waits for all of its members, in 10 ns
+    int spread, n_come;                // diagnostics: exchange at system scope; only so many members of a group come in time
     float x_scale, h_scale, h_inv;
     int w8;                            // 8-bit layer: 8-bit W_hh blob and an 8-bit hidden-state quantizer
 };
 struct QrRecGroup {
     QrRecArgs d[2];
     int n;
-    int members = 0, ug0 = 0, n_ug = 0;   // filled in by the launcher: workgroups per group, utterance groups of this launch
+    int group0 = 0, group_end = 0;     // filled in by the launcher: which groups (direction + n * utterance group) go out
 };
 QR_HIDDEN bool qr_rec_supported(int H, int B);
 QR_HIDDEN bool qr_rec_projects(int I);   // whether the recurrence can take input codes of I columns instead of their projection
 QR_HIDDEN size_t qr_rec_xbuf_bytes(int H, int B);
-QR_HIDDEN size_t qr_rec_xcc_bytes(int H, int B);
+QR_HIDDEN size_t qr_rec_admit_bytes(int B);
 QR_HIDDEN bool qr_launch_recurrence(const QrRecGroup &g, hipStream_t st);
 
 QR_HIDDEN void qr_fill_lstm_weights(QrStepArgs &a, const qrnnt_lstm *L);

@@ -1209,10 +1209,10 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
         if (!fused || c.dbg_accx) qr_launch_input_projection(L, x_codes, T * B, gx, c.dbg_accx, st);
         if (persist) {
             char *xb = c.ws + w.gx_b + 2 * w.h_b + 2 * w.c_b;
-            // the table of where the workgroups run takes the end of the (here unused) cell-state buffers in front
-            char *xcc = xb - qr_round_up((int)qr_rec_xcc_bytes(H, B), 16);
-            clear.p[d] = (uint32_t *)xcc;
-            clear.n = (size_t)(xb - xcc + w.x_b + 256) / 4;   // (the same for both directions)
+            // the admission words take the end of the second cell-state buffer in front, which is not used here
+            char *admit = xb - qr_round_up((int)qr_rec_admit_bytes(B), 16);
+            clear.p[d] = (uint32_t *)admit;
+            clear.n = (size_t)(xb - admit + w.x_b + 256) / 4;   // (the same for both directions)
             QrRecArgs &a = rg.d[d];
             a = QrRecArgs{};
             a.whh = (const v4i *)L->w_hh.packed;  a.s_wih = L->w_ih.row_scale;  a.s_whh = L->w_hh.row_scale;
@@ -1221,9 +1221,15 @@ qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int
             a.I = L->input_size;  a.nkc_x = qr_round_up(L->input_size, QRNNT_KCHUNK) / QRNNT_KCHUNK;
             a.h_out = h_out;  a.ld_out = ld_out;  a.col_off = c.col_off;
             a.h_last = c.h_last;  a.c_last = c.c_last;  a.dbg_c_all = c.dbg_c_all;
-            a.xbuf = xb;  a.xcc = (int *)xcc;  a.err = (int *)(xb + w.x_b);
+            a.xbuf = xb;  a.admit = (unsigned long long *)admit;  a.err = (int *)(xb + w.x_b);
+            a.c_buf = (float *)(c.ws + w.gx_b + 2 * w.h_b);
             a.T = T;  a.B = B;  a.H = H;  a.nkc_h = qr_round_up(H, QRNNT_KCHUNK) / QRNNT_KCHUNK;
-            a.reverse = c.reverse;  a.spin_limit = 1 << 20;
+            a.reverse = c.reverse;  a.spin_limit = 1 << 18;
+            // 100 us and 1.25 us a step: another recurrence of this length that has the compute units will be over by then
+            a.admit_ticks = T < 5000000 ? 10000 + 125 * T : 1 << 30;
+            a.spread = (c.route & QRNNT_DIAG_SPREAD) != 0;
+            a.n_come = c.route >> 8;
+            if (a.n_come) a.admit_ticks = 2000;
             a.x_scale = L->x_scale;  a.h_scale = L->h_scale;  a.h_inv = L->h_inv_scale;
             a.w8 = qr_bits(&L->w_hh) == 8;
         }
@@ -1315,7 +1321,8 @@ extern "C" qrnnt_status qrnnt_diag_lstm_layer(const qrnnt_lstm *L, const int8_t 
                                               int32_t *dbg_accx, float *dbg_c_all, int32_t route, void *workspace,
                                               size_t workspace_bytes, void *stream)
 {
-    QR_REQUIRE((route & ~QRNNT_DIAG_STEPWISE) == 0, QRNNT_ERR_RANGE);
+    QR_REQUIRE(route >= 0 && (route & 0xFF & ~(QRNNT_DIAG_STEPWISE | QRNNT_DIAG_SPREAD)) == 0 && route >> 8 <= 32,
+               QRNNT_ERR_RANGE);
     return one_layer({L, reverse, h0, c0, col_off, h_last, c_last, dbg_accx, dbg_c_all, (char *)workspace, route}, x_codes, T, B,
                      h_out, ld_out, workspace_bytes, stream);
 }

@@ -10,8 +10,8 @@
 //     (stores reach it, loads marked sc1 go past the CU's own cache to it) and not through
 //     the memory side of the device.  Workgroup ids are dealt to the XCDs in turn, so the
 //     launch lays group g's members out at ids congruent to g mod 8; nothing relies on it:
-//     at the start every workgroup publishes the XCD it runs on, and a group that finds
-//     itself spread over several exchanges at system scope instead (same words, sc0 sc1);
+//     at the start every workgroup counts itself in for the XCD it runs on, and a group that
+//     finds itself spread over several exchanges at system scope instead (same words, sc0 sc1);
 //   - the code of a cell travels in one byte of a 4-bit layer: code in the high nibble, step
 //     number mod 16 in the low one (8-bit layer: two bytes).  Every byte says by itself
 //     whether it is current, so data and flag arrive in the same store whatever its width,
@@ -31,10 +31,14 @@
 //     ahead.  Either way the recurrence waves load nothing but the exchanged codes: a wave's
 //     memory counter is in order, and a load from HBM in front of a poll holds the poll up;
 //   - both directions of a bidirectional layer run in the same launch.
-// All workgroups must be co-resident (checked against the occupancy of the device before
-// the launch; more utterances than fit go in several launches); a wait is bounded by
-// spin_limit polls, after which the error flag is set and the workgroup leaves the loop, so
-// the grid always drains.
+// A workgroup spins on its group's members, so these have to be resident together.  A launch
+// asks for no more than an idle device holds (more utterances go in several launches), but
+// recurrences of several streams, graphs or processes can each get part of an XCD and then
+// wait for each other.  So a group first counts its members in; when they have not all come
+// after about the time the layer takes, those that have come divide the group's cells among
+// them and whoever comes later leaves at once (shared_steps: slower, the same results).
+// Behind that every wait is for a resident workgroup; it is bounded by spin_limit polls all
+// the same, after which the error flag is set and the workgroup leaves, so the grid drains.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -45,7 +49,76 @@
 
 namespace {
 
-constexpr int N_XCD = 8;
+// A group's admission word: how many of its members have come, 6 bits for each XCD they run on (the ninth field: any
+// other), whether it went ahead without the rest, and with how many.
+typedef unsigned long long u64;
+constexpr u64 ADMIT_SHORT = 1ull << 63;
+constexpr int ADMIT_FIELDS = 9, ADMIT_N_SHIFT = 54;
+static_assert(6 * ADMIT_FIELDS <= ADMIT_N_SHIFT && ADMIT_N_SHIFT + 6 <= 63, "fields do not overlap");
+__device__ __forceinline__ int admit_count(u64 w)
+{
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < ADMIT_FIELDS; ++i) n += (int)((w >> (6 * i)) & 63);
+    return n;
+}
+__device__ __forceinline__ bool admit_one_xcd(u64 w, int members)
+{
+    bool one = false;
+#pragma unroll
+    for (int i = 0; i < ADMIT_FIELDS - 1; ++i) one = one || (int)((w >> (6 * i)) & 63) == members;
+    return one;
+}
+
+// What a workgroup does: all members have come, on one XCD or not; or it is one of the first `n` and takes the cells
+// (32 at a time) number rank, rank + n, ...; or it is not needed.
+enum { REC_LOCAL, REC_SPREAD, REC_SHARED, REC_LEAVE };
+struct RecAdmission {
+    int mode, rank, n;
+};
+// What a workgroup adds to the word to count itself in.
+__device__ __forceinline__ u64 admit_field()
+{
+    int xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
+    return 1ull << (6 * (xcc < ADMIT_FIELDS - 1 ? xcc : ADMIT_FIELDS - 1));
+}
+// One wave, w: what counting itself in returned to lane 0.  All that happens to the word are atomics, and both ends (all
+// have come; ADMIT_SHORT) are final.
+__device__ __forceinline__ RecAdmission admit(u64 *word, u64 w, int members, int max_ticks, int lane)
+{
+    const u64 t0 = wall_clock64();   // 100 MHz
+    auto uniform = [](u64 v) {
+        return ((u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+    };
+    w = uniform(w);
+    RecAdmission r = {REC_LEAVE, admit_count(w), 0};
+    if (w & ADMIT_SHORT) return r;
+    w += admit_field();
+    while (true) {
+        const int n = admit_count(w);
+        if (w & ADMIT_SHORT) {
+            r.mode = REC_SHARED;
+            r.n = (int)((w >> ADMIT_N_SHIFT) & 63);
+            return r;
+        }
+        if (n == members) {
+            r.mode = admit_one_xcd(w, members) ? REC_LOCAL : REC_SPREAD;
+            return r;
+        }
+        if (wall_clock64() - t0 > (u64)max_ticks) {
+            u64 seen = w;
+            if (lane == 0)
+                __hip_atomic_compare_exchange_strong(word, &seen, w | ADMIT_SHORT | ((u64)n << ADMIT_N_SHIFT), __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            seen = uniform(seen);
+            w = seen == w ? (w | ADMIT_SHORT | ((u64)n << ADMIT_N_SHIFT)) : seen;
+        } else {
+            __builtin_amdgcn_s_sleep(1);
+            w = uniform(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
+    }
+}
 
 // PER 128-bit loads from `bytes` bytes at base at each off[k].  LOCAL: past the CU's cache to the XCD's L2; otherwise past every
 // cache that is not coherent.  What a lane finds says by itself whether it is current, so the time between the loads and
@@ -116,6 +189,147 @@ __device__ __forceinline__ v4i upper_from(v4i a, v4i b)
     return r;
 }
 
+// The cell of Sec. 3.4 from the sums of its gates; returns the code of its output.
+template <bool W8, bool C_FIRST>
+__device__ __forceinline__ int rec_cell(const v4f &sx, const v4f &sh, const v4f &bb, const float (&gx)[4], const v4i &ah, float h_inv, float &c)
+{
+    float p[4];
+#pragma unroll
+    for (int gt = 0; gt < 4; ++gt) p[gt] = __builtin_fmaf(sx[gt], gx[gt], __builtin_fmaf(sh[gt], (float)ah[gt], bb[gt]));
+    const float gi = qr_sigmoid(p[0]), gf = qr_sigmoid(p[1]), gg = qr_tanh(p[2]), go = qr_sigmoid(p[3]);
+    c = C_FIRST ? __builtin_fmaf(gi, gg, gf * c) : __builtin_fmaf(gf, c, gi * gg);
+    return qr_quant(go * qr_tanh(c), h_inv, W8 ? 8 : 4);
+}
+
+// K step ks of row tile rt as an MFMA operand.
+template <bool W8>
+__device__ __forceinline__ v4i rec_weight(const v4i *w, int nkc, int rt, int ks, int lane)
+{
+    if (W8) return w[(((size_t)rt * nkc + (ks >> 1)) * 2 + (ks & 1)) * 64 + lane];   // as stored, two blocks per 128-column chunk
+    const int m = (int)0xF0F0F0F0u;
+    const v4i p = w[((size_t)rt * nkc + (ks >> 1)) * 64 + lane];
+    return (ks & 1) ? (p & m) : ((p << 4) & m);
+}
+
+// All T steps of a group by n of its workgroups (this one is number rank), each taking 32 cells at a time: the way out
+// when the group's members are not resident together.  Weights come from L2 in every step (all of a tile's before the
+// first is used), the cell states stay in memory, the codes go through the exchange area at device scope, 16 columns to
+// a 16-cell group.  hl, xl: LDS for the operands of a step, 64 * 2 * KH and 64 * 2 * KX pieces.
+// Bound by the weight stream of the workgroup with the most cells, 2 us for 32 cells: 640 cells, 1280 inputs, one utterance
+// take 38 us a step with one workgroup, 10.3 with 4, 5.4 with 10; 0.96 with all 20.
+template <int KH, int KX, bool W8, bool C_FIRST>
+__device__ __forceinline__ void shared_steps(const QrRecArgs &a, int ug, int members, int rank, int n, char *xb0, char *xb1, v4i *hl,
+                                             v4i *xl, int *s_fail)
+{
+    constexpr int PER = W8 ? 2 : 1, KXA = KX > 0 ? KX : 1;
+    constexpr float X_UNIT = (W8 || KX == 0) ? 1.0f : 0.0625f, H_UNIT = W8 ? 1.0f : 0.00390625f;
+    const int H = a.H, B = a.B, T = a.T;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    const int n_groups = H >> 4, x_pieces = KX > 0 ? (int)(a.ld_x >> 4) : 0;
+    const int u = ug * 16 + col, uu = u < B ? u : B - 1;
+    const v4i zero = {0, 0, 0, 0};
+    const int m = (int)0xF0F0F0F0u;
+    for (int e = tid; e < KH * 128; e += 512) hl[e] = zero;    // what lies behind the layer's last group and
+    for (int e = tid; e < KX * 128; e += 512) xl[e] = zero;    // column stays zero
+    __syncthreads();
+    for (int s = 0; s < T; ++s) {
+        const int t = a.reverse ? T - 1 - s : s;
+        // ---- the frame and the codes of the step before, as MFMA operands: piece 16 * group + utterance
+        for (int e = tid; e < x_pieces * 16; e += 512) {
+            const int n0 = ug * 16 + (e & 15) < B ? ug * 16 + (e & 15) : B - 1;
+            xl[e] = *(const v4i *)(a.x + ((int64_t)t * B + n0) * a.ld_x + (e >> 4) * 16);
+        }
+        for (int e = tid; e < n_groups * 16; e += 512) {
+            v4i v = zero;
+            if (s == 0) {
+                const int n0 = ug * 16 + (e & 15) < B ? ug * 16 + (e & 15) : B - 1;
+                if (a.h0) v = *(const v4i *)(a.h0 + (int64_t)n0 * H + (e >> 4) * 16);
+                hl[e] = W8 ? v : ((v << 4) & m);
+                continue;
+            }
+            const u64 *src = (const u64 *)(((s - 1) & 1 ? xb1 : xb0) + (size_t)e * 16 * PER);
+            const u64 want = W8 ? 0x0100010001000100ull * (u64)(s & 0xFF) : 0x0101010101010101ull * (u64)(s & 15);
+            const u64 tags = W8 ? 0xFF00FF00FF00FF00ull : 0x0F0F0F0F0F0F0F0Full;
+            u64 q[2 * PER];
+            for (int spins = 0;; ++spins) {
+                u64 bad = 0;
+#pragma unroll
+                for (int i = 0; i < 2 * PER; ++i) {
+                    q[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    bad |= (q[i] ^ want) & tags;
+                }
+                if (bad == 0) break;
+                if (spins >= a.spin_limit) {
+                    atomicExch(a.err, 1);
+                    *s_fail = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                if (W8) v[d] = (int)__builtin_amdgcn_perm((unsigned)(q[d * PER / 2] >> 32), (unsigned)q[d * PER / 2], 0x06040200u);
+                else v[d] = (int)(unsigned)(q[d / 2] >> (32 * (d & 1))) & m;
+            }
+            hl[e] = v;
+        }
+        __syncthreads();
+        if (*s_fail) break;   // uniform
+        for (int sl = rank; sl < members; sl += n) {
+            const int cg = 2 * sl + (wave >> 2), rt = cg * 4 + (wave & 3);
+            if (cg >= n_groups) continue;   // uniform
+            const int j = qr_gates_cell(rt, grp);
+            v4i wh[KH][PER], wx[KXA][PER];
+            auto fetch = [&](const v4i *w, int nkc, int k, v4i (&f)[PER]) {   // (a chunk that the layer does not have meets zeros)
+                const v4i *p = w + ((size_t)rt * nkc + (k < nkc ? k : nkc - 1)) * (64 * PER);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) f[i] = p[64 * i + lane];
+            };
+#pragma unroll
+            for (int k = 0; k < KH; ++k) fetch(a.whh, a.nkc_h, k, wh[k]);
+#pragma unroll
+            for (int k = 0; k < KX; ++k) fetch(a.wih, a.nkc_x, k, wx[k]);
+            v4i ah = zero, ax = zero;
+            if (KX == 0) ax = *(const v4i *)(a.gx + ((int64_t)t * B + uu) * 4 * H + rt * 16 + 4 * grp);
+            v4f sx, sh, bb;
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) {
+                sx[gt] = a.x_scale * a.s_wih[gt * H + j] * X_UNIT;
+                sh[gt] = a.h_scale * a.s_whh[gt * H + j] * H_UNIT;
+                bb[gt] = a.bias[gt * H + j];
+            }
+            float *c_at = a.c_buf + (int64_t)uu * H + j;
+            float c = s > 0 ? *c_at : (a.c0 ? a.c0[(int64_t)uu * H + j] : 0.0f);
+            __builtin_amdgcn_sched_barrier(0);
+            auto tile = [&](const v4i (&f)[PER], const v4i *op, int k, v4i &acc) {   // 128 columns
+                const v4i *o = op + (8 * k + grp) * 16 + col;
+                acc = qr_mfma(W8 ? f[0] : ((f[0] << 4) & m), o[0], acc);
+                acc = qr_mfma(W8 ? f[PER - 1] : (f[0] & m), o[64], acc);
+            };
+#pragma unroll
+            for (int k = 0; k < KH; ++k) tile(wh[k], hl, k, ah);
+#pragma unroll
+            for (int k = 0; k < KX; ++k) tile(wx[k], xl, k, ax);
+            float gx[4];
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) gx[gt] = (float)ax[gt];
+            const unsigned code = (unsigned)rec_cell<W8, C_FIRST>(sx, sh, bb, gx, ah, a.h_inv, c);
+            char *dst = (s & 1 ? xb1 : xb0) + (size_t)((cg * 16 + col) * 16 + (j & 15)) * PER;
+            const unsigned tag = (unsigned)(s + 1);
+            if (W8) __hip_atomic_store((unsigned short *)dst, (unsigned short)((code & 0xFFu) | tag << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else __hip_atomic_store((unsigned char *)dst, (unsigned char)(code << 4 | (tag & 15u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (u < B) {
+                *c_at = c;
+                a.h_out[((int64_t)t * B + u) * a.ld_out + a.col_off + j] = (int8_t)code;
+                if (a.dbg_c_all) a.dbg_c_all[((int64_t)t * B + u) * H + j] = c;
+                if (s == T - 1 && a.h_last) a.h_last[(int64_t)u * H + j] = (int8_t)code;
+                if (s == T - 1 && a.c_last) a.c_last[(int64_t)u * H + j] = c;
+            }
+        }
+        __syncthreads();   // the operands have been read
+    }
+}
+
 // Exchange area of a direction: [parity][utterance group][16-cell group][utterance][16 cells], one byte per cell (two
 // in an 8-bit layer): a lane's MFMA operand for a K step (16 cells of one utterance) is contiguous.  A layer of B < 16
 // utterances keeps its columns closer together (the next power of two): lanes of absent utterances read what a present
@@ -124,27 +338,21 @@ __device__ __forceinline__ v4i upper_from(v4i a, v4i b)
 // CELLS: cells per lane in the cell update: 2, or 1 if there are at most 8 utterances: the lanes of the absent upper
 // eight then take the second cell of the lower eight.
 // C_FIRST: which product of c' = f*c + i*g is rounded before the sum (see qr_launch_recurrence).
+// Returns without a step done when the group's members have not all come (adm.mode).
 template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
-__global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
+__device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem, int members, char *xb0, char *xb1, size_t ug_bytes,
+                                             v4i (&px)[2][2][2][4][64], v4i (&xs)[KX > 0 ? 3 * 2 * KX : 1][64], int (&s_fail)[2],
+                                             RecAdmission &adm)
 {
     constexpr int PER = W8 ? 2 : 1;    // bytes per exchanged cell
     constexpr int NL = KH * PER;       // 128-bit loads per wave and poll
     __shared__ v4i part[2][4][CELLS][64];   // [parity][wave][row tile][lane] partial sums on their way to the K partner
-    __shared__ v4i px[2][2][2][4][64];      // [parity][K half][cell group][row tile][lane] sums of the input part
-    __shared__ __attribute__((aligned(1024))) v4i xs[KX > 0 ? 3 * 2 * KX : 1][64];   // three frames of input codes, blocks of 8 utterances x 128 columns
     // Where the weights leave no registers for them (up to 57 spilled), what a lane needs once a step lies in LDS: row
     // scales and biases of its cells, row sums of its wave's weights.  50 steps of 2 x 768 cells at 320 inputs and 32
     // utterances: 4-bit 88 -> 76 us, 8-bit 158 -> 119 us.
     constexpr bool PARK = KH >= 8 && (W8 || CELLS == 2);
     __shared__ v4f pk[PARK ? CELLS : 1][3][PARK ? 256 : 1];
     __shared__ v4i pk_rsum[PARK && !W8 ? 4 : 1][PARK && !W8 ? 256 : 1];
-    __shared__ int s_fail[2], s_local;
-    // group and member from the workgroup id: ids congruent mod 8 share an XCD
-    const int id = (int)blockIdx.x;
-    const int gi = (id / N_XCD / g.members) * N_XCD + id % N_XCD, mem = (id / N_XCD) % g.members;
-    if (gi >= g.n * g.n_ug) return;   // uniform
-    const QrRecArgs a = g.d[gi % g.n];   // a copy: a few wide scalar loads
-    const int ug = g.ug0 + gi / g.n;
     const int H = a.H, B = a.B, T = a.T;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -158,15 +366,10 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     const int64_t dir = a.reverse ? -1 : 1, t0 = a.reverse ? T - 1 : 0;
     const v4i zero = {0, 0, 0, 0};
     const int m = (int)0xF0F0F0F0u;
-    // K step ks of row tile rt as an MFMA operand
-    auto weight = [&](const v4i *w, int nkc, int rt, int ks) -> v4i {
-        if (W8) return w[(((size_t)rt * nkc + (ks >> 1)) * 2 + (ks & 1)) * 64 + lane];   // as stored, two blocks per 128-column chunk
-        const v4i p = w[((size_t)rt * nkc + (ks >> 1)) * 64 + lane];
-        return (ks & 1) ? (p & m) : ((p << 4) & m);
-    };
+    auto weight = [&](const v4i *w, int nkc, int rt, int ks) -> v4i { return rec_weight<W8>(w, nkc, rt, ks, lane); };
 
     if (tid == 0) s_fail[0] = s_fail[1] = 0;
-    __syncthreads();   // (before a table wait below can set one of them)
+    __syncthreads();
 
     if (wave8 >= 4) {
         // ================= input part: K half kh of cell group rh, one step ahead of the recurrence
@@ -224,6 +427,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             lds_barrier();
             produce(0, 0);
             lds_barrier();
+            if (adm.mode >= REC_SHARED) return;          // uniform
             int b1 = 1, b3 = 0;                          // buffers of frames s + 1 and s + 3
             for (int s = 0; s < T; ++s) {
                 fetch(b3, s + 4 < T);                    // (frames behind the last one: the last one again)
@@ -252,6 +456,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             lds_barrier();
             produce(0, T > 1);
             lds_barrier();
+            if (adm.mode >= REC_SHARED) return;          // uniform
             for (int s = 0; s < T; ++s) {
                 if (s + 1 < T) produce((s + 1) & 1, s + 2 < T);
                 lds_barrier();
@@ -262,25 +467,13 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     }
 
     // ================= recurrence
-    // ---- where this group runs: every member publishes its XCD, all members see the same answers
-    if (wave == 0) {
-        int *tab = a.xcc + (size_t)ug * g.members;
-        int xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
-        if (lane == 0) __hip_atomic_store(tab + mem, 0x100 | xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        const int *p = tab + (lane < g.members ? lane : 0);
-        int v = 0, spins = 0;
-        bool timed_out = false;
-        while (true) {
-            v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            if (__all(v != 0)) break;
-            if (++spins > a.spin_limit) { timed_out = true; break; }
-        }
-        const bool same = __all(v == __builtin_amdgcn_readfirstlane(v));
-        if (lane == 0) {
-            s_local = same ? 1 : 0;
-            if (timed_out) { atomicExch(a.err, 1); s_fail[0] = 1; }
-        }
+    u64 *const admit_word = a.admit + ug;
+    u64 found = 0;
+    if (wave == 0 && members > 1) {
+        if (a.n_come > 0 && mem >= a.n_come)    // diagnostic: this one comes when the others have gone ahead (or after 0.1 s)
+            for (const u64 t0 = wall_clock64(); wall_clock64() - t0 < 10000000ull;)
+                if (__hip_atomic_load(admit_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ADMIT_SHORT) break;
+        if (lane == 0) found = __hip_atomic_fetch_add(admit_word, admit_field(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
     // ---- stationary operands: this wave's K steps (kh, kh + 2, ...) of its four row tiles; tiles 0 and 1 are the ones
@@ -335,9 +528,6 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     int ncol = 16;                              // columns kept per 16-cell group
     if (CELLS == 1)
         for (ncol = 8; ncol >= 2 * B; ncol >>= 1) {}
-    const size_t ug_bytes = (size_t)n_groups * 256 * PER;
-    char *const xb0 = a.xbuf + (size_t)ug * ug_bytes;   // this group's area, even steps
-    char *const xb1 = xb0 + (size_t)((B + 15) >> 4) * ug_bytes;   // odd steps
     unsigned off[KH];
 #pragma unroll
     for (int k = 0; k < KH; ++k) {
@@ -358,10 +548,16 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     const bool dbg = a.dbg_c_all != nullptr;
     float *dq = dbg ? a.dbg_c_all + (t0 * B + nn) * H + j0 : nullptr;
 
+    if (wave == 0) {                            // (the weights were on their way meanwhile)
+        RecAdmission r = {REC_LOCAL, 0, 0};
+        if (members > 1) r = admit(admit_word, found, members, a.admit_ticks, lane);
+        if (lane == 0) adm = r;
+    }
     lds_barrier();
     lds_barrier();
+    if (adm.mode >= REC_SHARED) return;         // uniform
     __builtin_amdgcn_s_setprio(3);              // these waves are the chain, the input waves fill its gaps
-    const bool local = s_local != 0;            // uniform over the group
+    const bool local = adm.mode == REC_LOCAL && !a.spread;   // uniform over the group
     unsigned codes = 0;                         // the codes of the step before, one per byte
     v4i acc[4];
     float gx[CELLS][4];                         // this step's sums of the input part
@@ -454,13 +650,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
                 sh[ct] = pk[ct][1][pt];
                 bb[ct] = pk[ct][2][pt];
             }
-            float p[4];
-#pragma unroll
-            for (int gt = 0; gt < 4; ++gt) p[gt] = sx[ct][gt] * gx[ct][gt] + (sh[ct][gt] * (float)asum[ct][gt] + bb[ct][gt]);
-            const float gi_ = qr_sigmoid(p[0]), gf = qr_sigmoid(p[1]), gg = qr_tanh(p[2]), go = qr_sigmoid(p[3]);
-            c[ct] = C_FIRST ? __builtin_fmaf(gi_, gg, gf * c[ct]) : __builtin_fmaf(gf, c[ct], gi_ * gg);
-            const float h = go * qr_tanh(c[ct]);
-            const unsigned code = (unsigned)qr_quant(h, a.h_inv, W8 ? 8 : 4);
+            const unsigned code = (unsigned)rec_cell<W8, C_FIRST>(sx[ct], sh[ct], bb[ct], gx[ct], asum[ct], a.h_inv, c[ct]);
             codes |= (code & 0xFFu) << (8 * ct);
             word |= W8 ? (code & 0xFFu) << (16 * ct) : ((code & 15u) << 4) << (8 * ct);
         }
@@ -482,6 +672,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
             const char *src = par ? xb0 : xb1;
             const unsigned want = W8 ? (unsigned)(s & 0xFF) * 0x01000100u : (unsigned)(s & 15) * 0x01010101u;
             v4i bf[KH];
+            asm volatile(".p2align 6");   // the poll on a cache line of its own: where it lay otherwise cost up to 3 % of a step
             for (int spins = 0;; ++spins) {
                 v4i v[NL];
                 load_words<KH, PER, LOCAL>(src, (unsigned)ug_bytes, off, v);
@@ -546,40 +737,72 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     }
 }
 
-// Workgroups of this kernel that an XCD of the current device holds at once; 0: none (or the device does not answer).
 template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
-int per_xcd()
+__global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
 {
-    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none
+    __shared__ v4i px[2][2][2][4][64];      // [parity][K half][cell group][row tile][lane] sums of the input part
+    __shared__ __attribute__((aligned(1024))) v4i xs[KX > 0 ? 3 * 2 * KX : 1][64];   // three frames of input codes, blocks of 8 utterances x 128 columns
+    __shared__ int s_fail[2];
+    __shared__ RecAdmission adm;
+    // Grid: x = XCD (workgroups go out with x fastest, each to the next XCD), y = member, z = XCD's next group
+    const int gi = g.group0 + (int)(blockIdx.z * gridDim.x + blockIdx.x), mem = (int)blockIdx.y, members = (int)gridDim.y;
+    if (gi >= g.group_end) return;   // uniform
+    const int ug = gi >> (g.n - 1);  // one or two directions
+    const size_t ug_bytes = (size_t)(g.d[0].H >> 4) * 256 * (W8 ? 2 : 1);
+    {
+        const QrRecArgs a = g.d[gi & (g.n - 1)];   // a copy: a few wide scalar loads
+        char *const xb = a.xbuf + (size_t)ug * ug_bytes;   // this group's exchange area, even steps
+        member_steps<KH, KX, W8, CELLS, C_FIRST>(a, ug, mem, members, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes, ug_bytes, px, xs,
+                                                 s_fail, adm);
+    }
+    if (adm.mode == REC_SHARED) {   // uniform
+        int d = gi & (g.n - 1);
+        asm volatile("" : "+s"(d));   // a copy of its own: the one above need not outlive the loop
+        const QrRecArgs a = g.d[d];
+        char *const xb = a.xbuf + (size_t)ug * ug_bytes;
+        shared_steps<KH, KX, W8, C_FIRST>(a, ug, members, adm.rank, adm.n, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes,
+                                          &px[0][0][0][0][0], &xs[0][0], s_fail);
+    }
+}
+
+// XCDs of the current device and workgroups of this kernel that each holds at once; 0: none (or the device does not answer).
+struct RecRoom {
+    int n_xcd, per_xcd;
+};
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+RecRoom room()
+{
+    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none, else per_xcd * 64 + n_xcd
     const int dev = qr_current_device();
     int v = known[dev].load(std::memory_order_relaxed);
     if (v == 0) {
-        int n_cu = 0, per_cu = 0;
+        int n_cu = 0, n_xcd = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n_xcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST>, 512, 0) != hipSuccess)
-            return 0;
-        v = n_cu / N_XCD * per_cu;
-        known[dev].store(v > 0 ? v : -1, std::memory_order_relaxed);
+            return {0, 0};
+        n_xcd = n_xcd < 1 || n_xcd > 32 ? 8 : n_xcd;
+        v = n_cu / n_xcd * per_cu * 64 + n_xcd;
+        v = v >= 64 ? v : -1;
+        known[dev].store(v, std::memory_order_relaxed);
     }
-    return v > 0 ? v : 0;
+    return v > 0 ? RecRoom{v & 63, v >> 6} : RecRoom{0, 0};
 }
 
 template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
 bool launch_rec_t(const QrRecGroup &g, hipStream_t st)
 {
     QrRecGroup gg = g;
-    gg.members = (g.d[0].H + 31) / 32;
-    const int n_ug = (g.d[0].B + 15) / 16;
-    const int q = per_xcd<KH, KX, W8, CELLS, C_FIRST>() / gg.members;   // groups per XCD
-    if (q * N_XCD < g.n) return false;
-    // Every workgroup spins on its group's members, so all groups of a launch must be resident together.  Up to q
-    // groups share an XCD (and its CUs): they then take turns, which is still faster than one launch after the other.
-    const int ug_max = q * N_XCD / g.n;
-    for (int u0 = 0; u0 < n_ug; u0 += ug_max) {
-        gg.ug0 = u0;
-        gg.n_ug = n_ug - u0 < ug_max ? n_ug - u0 : ug_max;
-        const int groups = g.n * gg.n_ug;
-        lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST><<<gg.members * N_XCD * ((groups + N_XCD - 1) / N_XCD), 512, 0, st>>>(gg);
+    const int members = (g.d[0].H + 31) / 32;
+    const RecRoom r = room<KH, KX, W8, CELLS, C_FIRST>();
+    const int q = r.per_xcd / members;   // groups that an XCD holds together; beyond H = 512 it is one
+    if (q < 1) return false;
+    const int n_groups = g.n * ((g.d[0].B + 15) / 16), most = q * r.n_xcd;
+    for (int g0 = 0; g0 < n_groups; g0 += most) {
+        gg.group0 = g0;
+        gg.group_end = n_groups - g0 < most ? n_groups : g0 + most;
+        const int turns = (gg.group_end - g0 + r.n_xcd - 1) / r.n_xcd;
+        lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST><<<dim3(r.n_xcd, members, turns), 512, 0, st>>>(gg);
     }
     return true;
 }
@@ -618,7 +841,7 @@ size_t qr_rec_xbuf_bytes(int H, int B)
 
 bool qr_rec_projects(int I) { return I <= 1280; }
 
-size_t qr_rec_xcc_bytes(int H, int B) { return (size_t)((B + 15) / 16) * ((H + 31) / 32) * sizeof(int); }
+size_t qr_rec_admit_bytes(int B) { return (size_t)((B + 15) / 16) * sizeof(u64); }
 
 // Launches the recurrence of 1 or 2 directions (same H, B, T, width).  Returns false if it
 // cannot run (size or residency): the caller then takes the step-by-step path.

@@ -383,7 +383,7 @@ def lstm_layer(L: Lstm, x_codes: torch.Tensor, reverse: bool = False, h0=None, c
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20
-DIAG_STEPWISE = 1
+DIAG_STEPWISE, DIAG_SPREAD = 1, 2
 
 
 def lstm_layer_static(L: Lstm, x_codes: torch.Tensor, h_out: torch.Tensor, reverse: bool = False, h0=None, c0=None,

@@ -99,3 +99,64 @@ def test_refused_recurrence_runs_step_by_step(gpu_lib, T, B, I, H, reverse, stat
     assert q.layer_error_flag(ws, need) == 0
     hl, _ = _check(L, x, host(out["h_out"]), None, reverse, h0, c0, 7.0, f"step by step H={H}")
     assert np.array_equal(host(out["h_last"]), hl)
+
+
+@pytest.mark.parametrize("T,B,I,H,bits,state", [(20, 1, 64, 64, 4, True), (40, 3, 1280, 640, 4, False), (9, 17, 1300, 640, 4, True),
+                                                (6, 120, 340, 640, 4, True), (5, 8, 385, 656, 4, False), (280, 5, 40, 80, 8, True),
+                                                (6, 20, 1281, 48, 8, False), (7, 13, 340, 1024, 8, True), (4, 100, 64, 704, 8, False)])
+def test_routes_of_the_recurrence_agree(gpu_lib, T, B, I, H, bits, state):
+    """A group whose workgroups run on several XCDs, and one whose workgroups are not resident together (whoever has come
+    shares the work), return the very bits of the usual route; 120 and 100 utterances: layers that round f*c first."""
+    q = gpu_lib
+    q_max = 127 if bits == 8 else 7
+    L, G = (_lstm8_pair if bits == 8 else _lstm_pair)(q, 5471 + I + H, I, H, 0.5 / q_max)
+    xp = np.full((T, B, q.act_pitch(I)), 3, np.int8)
+    xp[..., :I] = synth.codes(5472 + T, (T, B, I), -q_max - 1, q_max)
+    h0 = dev(synth.codes(5473, (B, H), -q_max, q_max)) if state else None
+    c0 = dev(synth.normal(5474, (B, H), 0.6)) if state else None
+    need = q.lstm_layer_workspace(G, T, B)
+    x, want = dev(xp), None
+    members = (H + 31) // 32
+    for route in [0, q.DIAG_SPREAD] + [n << 8 for n in sorted({1, 2, 3, members // 2, members - 1}) if 0 < n < members]:
+        ws = torch.full((need,), 0x55, dtype=torch.uint8, device=DEV)
+        out = q.lstm_layer(G, x, reverse=state, h0=h0, c0=c0, want_last=True, debug=True, workspace=ws, route=route)
+        assert q.layer_error_flag(ws, need) == 0
+        del out["accx"]
+        want = want or out
+        for k, v in out.items():
+            assert torch.equal(v, want[k]), f"route {route:#x}: {k}"
+
+
+@pytest.mark.parametrize("B,n_streams,layers", [(1, 4, 6), (40, 3, 4)])
+def test_recurrences_on_several_streams(gpu_lib, B, n_streams, layers):
+    """Encoders on streams of their own, with workspaces of their own: each launch wants more than half of an XCD, so
+    their workgroups meet on the same compute units and groups are cut short of members."""
+    q = gpu_lib
+    T, I, H = 100, 1280, 640
+    L = [_lstm_pair(q, 5571 + d, I, H, 0.1)[1] for d in range(2)]
+    xs = [dev(synth.codes(5573 + i, (T, B, I), -7, 7)) for i in range(n_streams)]
+    need = q.bilstm_layer_workspace(L[0], L[1], T, B)
+    wss = [torch.empty((layers, need), dtype=torch.uint8, device=DEV) for _ in range(n_streams)]
+
+    def run(i):
+        x = xs[i]
+        for k in range(layers):
+            x = q.bilstm_layer(L[0], L[1], x, workspace=wss[i][k])
+        return x
+
+    want = []
+    for i in range(n_streams):
+        want.append(run(i).clone())
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(n_streams)]
+    for _ in range(3):
+        got = []
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got.append(run(i))
+        torch.cuda.synchronize()
+        for i in range(n_streams):
+            for k in range(layers):
+                assert q.layer_error_flag(wss[i][k], need) == 0
+                assert q.layer_error_flag(wss[i][k], q.lstm_layer_workspace(L[0], T, B)) == 0
+            assert torch.equal(got[i], want[i])
