@@ -42,8 +42,9 @@ __global__ __launch_bounds__(256) void linear_head_kernel(const QrLinearGroup g)
         }
     };
     // The waves take the 128-column chunks in turn: a weight fragment holds both halves of its chunk and is fetched by one
-    // wave only (by 64-column blocks, which this was, two waves fetch each: bottleneck of 256 x 2048 at 208 rows 8.0 us,
-    // now 6.6).
+    // wave only (by 64-column blocks two waves fetch each).  One chunk of a wave in flight: its loads leave registers for a
+    // third workgroup on the compute unit, which hides more than a deeper batch does at any size (4 chunks, or 2 of 8-bit
+    // weights, as this was: 256 x 2048 at 208 rows 5.4 us, now 4.6; 256 x 1280 at 32000 rows 94 us, now 46).
     const v4i zero = {0, 0, 0, 0};
     v4i acc[4] = {zero, zero, zero, zero};
     unsigned woff[4];   // (a matrix of 2 GiB would have to have 4 million rows)
@@ -52,8 +53,8 @@ __global__ __launch_bounds__(256) void linear_head_kernel(const QrLinearGroup g)
         const int rt = rt0 + mt < n_row_tiles ? rt0 + mt : n_row_tiles - 1;
         woff[mt] = (unsigned)rt * a.nkc * (a.w8 ? 2048 : 1024) + lane * 16;
     }
-    if (a.w8) qr_chunk_mma<true, 2>(a.w, woff, a.act, n, a.K, a.nkc, wave, 4, grp, acc, row_constants);
-    else qr_chunk_mma<false, 4>(a.w, woff, a.act, n, a.K, a.nkc, wave, 4, grp, acc, row_constants);
+    if (a.w8) qr_chunk_mma<true, 1>(a.w, woff, a.act, n, a.K, a.nkc, wave, 4, grp, acc, row_constants);
+    else qr_chunk_mma<false, 1>(a.w, woff, a.act, n, a.K, a.nkc, wave, 4, grp, acc, row_constants);
     if (wave != 0) {
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) lds[((wave - 1) * 4 + mt) * 64 + lane] = acc[mt];

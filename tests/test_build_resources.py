@@ -1,5 +1,6 @@
 """What the built library says about its kernels: the persistent recurrence keeps its weights in registers for a whole
-sequence and must not spill (scratch accesses would queue with its polls in the in-order memory counter)."""
+sequence and must not spill (scratch accesses would queue with its polls in the in-order memory counter); the linear layers live
+on several workgroups per compute unit."""
 import os
 import re
 import struct
@@ -43,3 +44,12 @@ def test_the_recurrence_does_not_spill():
     spilled = {n: k[".private_segment_fixed_size"] for n, k in rec.items() if k[".private_segment_fixed_size"]}
     assert not spilled
     assert max(k[".group_segment_fixed_size"] for k in rec.values()) <= 160 * 1024
+
+
+def test_linear_layers_leave_room_for_a_third_workgroup():
+    """Four waves a workgroup, 512 registers a lane and SIMD: three fit if a wave takes at most 168."""
+    qrnnt.load()
+    lin = [k for n, k in kernels().items() if "linear_head_kernel" in n]
+    assert lin
+    for k in lin:
+        assert k[".vgpr_count"] <= 168 and k[".private_segment_fixed_size"] == 0   # (accumulation registers included)
