@@ -337,7 +337,7 @@ __device__ __forceinline__ void shared_steps(const QrRecArgs &a, int ug, int mem
 // KH: K steps (64 cells) of h per wave, H <= 128 * KH.  KX: K steps of the input per wave, I <= 128 * KX; 0: sums from memory.
 // CELLS: cells per lane in the cell update: 2, or 1 if there are at most 8 utterances: the lanes of the absent upper
 // eight then take the second cell of the lower eight.
-// C_FIRST: which product of c' = f*c + i*g is rounded before the sum (see qr_launch_recurrence).
+// C_FIRST: which product of c' = f*c + i*g is rounded before the sum (see launch_rec_w).
 // Returns without a step done when the group's members have not all come (adm.mode).
 template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
 __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem, int members, char *xb0, char *xb1, size_t ug_bytes,
@@ -812,12 +812,15 @@ bool launch_rec_w(const QrRecGroup &g, hipStream_t st)
 {
     const int H = g.d[0].H, B = g.d[0].B;
     const bool few = B <= 8, w8 = g.d[0].w8 != 0;
-    // One of the two products of c' = f*c + i*g is rounded before the fused multiply-add.  A recurrence carries a code
-    // that sits on a rounding tie on through all later steps and layers, so which one it is shows in the result; it is a
-    // function of the problem's size: with more 16-cell x 16-utterance tiles than an MI355X has compute units and
-    // 512 < H <= 768 it is f*c, else i*g, which is what layers of these sizes have always returned.
+    // One of the two products of c' = f*c + i*g is rounded before the fused multiply-add.  Which one follows an earlier
+    // kernel, where the compiler had picked f*c in the form with two cells per lane and i*g in the other (up to 512 cells in
+    // both).  The former ran where 16-cell x 16-utterance tiles outnumbered 256 compute units, beyond 768 cells only as
+    // long as half of them did not.  So the last bit of a cell, and a code that sits on a rounding tie, can depend on the
+    // batch that an utterance is in; but a tie is carried on through all later steps and layers, and one order for all
+    // sizes would change what layers return.
+    const int tiles = (H / 16) * ((B + 15) / 16) * g.n;
     if constexpr (KH >= 5)
-        if (H > 512 && H <= 768 && H % 32 == 0 && (H / 16) * ((B + 15) / 16) * g.n > 256)
+        if (H > 512 && H % 32 == 0 && tiles > 256 && (H <= 768 || tiles <= 512))
             return w8 ? launch_rec_t<KH, KX, true, 2, true>(g, st) : launch_rec_t<KH, KX, false, 2, true>(g, st);
     if (w8) return few ? launch_rec_t<KH, KX, true, 1, false>(g, st) : launch_rec_t<KH, KX, true, 2, false>(g, st);
     return few ? launch_rec_t<KH, KX, false, 1, false>(g, st) : launch_rec_t<KH, KX, false, 2, false>(g, st);

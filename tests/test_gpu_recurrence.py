@@ -101,6 +101,35 @@ def test_refused_recurrence_runs_step_by_step(gpu_lib, T, B, I, H, reverse, stat
     assert np.array_equal(host(out["h_last"]), hl)
 
 
+@pytest.mark.parametrize("H,B,bits,f_first", [(640, 96, 4, False), (640, 97, 4, True), (640, 97, 8, True), (640, 8, 8, False),
+                                              (704, 80, 4, False), (704, 96, 4, True), (768, 90, 8, True), (784, 96, 4, False),
+                                              (512, 140, 4, False), (832, 100, 8, True), (1024, 64, 4, False),
+                                              (1024, 65, 4, True), (1024, 128, 4, True), (1024, 129, 4, False)])
+def test_which_product_of_the_cell_is_rounded_first(gpu_lib, H, B, bits, f_first):
+    """c' = f*c + i*g has one product rounded before the sum, f*c in some size classes and i*g in the others.  With g = 1
+    the gates can be read off exactly (c = 0 gives i, c = 2^60 gives f) and the two orders told apart bit for bit."""
+    q = gpu_lib
+    I = 64
+    G = (_lstm8_pair if bits == 8 else _lstm_pair)(q, 5671 + H, I, H, 0.1)[1]
+    bias = G.bias.clone()
+    bias[2 * H:3 * H] = 60.0
+    G = q.Lstm(G.w_ih, G.w_hh, bias, G.x_scale, G.h_scale, G.h_inv_scale)
+    x = dev(synth.codes(5672 + B, (1, B, I), -7, 7))
+
+    def cell(c0):
+        return host(q.lstm_layer(G, x, c0=dev(c0), want_last=True)["c_last"])
+
+    full = lambda v: np.full((B, H), v, np.float32)
+    i, f = cell(full(0.0)), np.ldexp(cell(full(2.0 ** 60)), -60)
+    c0 = synth.normal(5673 + B, (B, H), 0.8)
+    got = cell(c0)
+    exact = np.longdouble(f) * np.longdouble(c0)   # 48 bits of 64
+    first = np.float32(np.longdouble(exact.astype(np.float32)) + np.longdouble(i))
+    last = (exact + np.longdouble(i)).astype(np.float32)
+    assert (first != last).mean() > 0.01
+    assert np.array_equal(got, first if f_first else last)
+
+
 @pytest.mark.parametrize("T,B,I,H,bits,state", [(20, 1, 64, 64, 4, True), (40, 3, 1280, 640, 4, False), (9, 17, 1300, 640, 4, True),
                                                 (6, 120, 340, 640, 4, True), (5, 8, 385, 656, 4, False), (280, 5, 40, 80, 8, True),
                                                 (6, 20, 1281, 48, 8, False), (7, 13, 340, 1024, 8, True), (4, 100, 64, 704, 8, False)])
