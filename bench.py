@@ -194,9 +194,9 @@ def main():
             del wsa
         extra["alsd_beam_sweep"] = {"rows": sweep_a,
                                     "note": "alignment-length synchronous search, label cap T/2; 'reused' = label picks whose sequence a live "
-                                            "hypothesis of the beam already held (Sec. 4.1's reuse of cached hypotheses): they become copied "
-                                            "rows of the advance; the advance is one dense launch per layer over all slots, so on this "
-                                            "machine a reused row costs what an advanced one costs"}
+                                            "hypothesis of the beam already held (Sec. 4.1's reuse of cached hypotheses): they name that "
+                                            "hypothesis' row of the state pool and leave the list of hypotheses the networks advance for; "
+                                            "a launch over a quarter fewer columns takes nearly as long"}
         # worst case for the time-synchronous search: the blank's joint bias lowered until every pick of every round
         # is a label, so all four advances of a frame run over full lists (the headline model picks 15, 1, 15, 1 of 16)
         import copy

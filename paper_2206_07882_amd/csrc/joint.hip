@@ -155,10 +155,11 @@ __device__ __forceinline__ float qr_row_sum(const v4f &e)
 //     hypothesis, four tokens each, and form the three log-softmaxes and the fused score together.
 //   selection, waves 0-3: the W-th best of the best ones of 64 groups of candidates or more bounds the W-th best
 //     candidate from below; what passes the bound is gathered in LDS and ranked by counting.
-// The kernel is bound by its chain of dependent steps, and the chain by one compute unit's path to L2 (150 KB of weights
-// and 80 KB of codes, 64 bytes a cycle) and by single waves running straight-line code, hence the split of every step
-// over four waves.  Measured, one utterance at beam 16: 10.1 us, where a launch for
-// the output layers and one for joint, selection and routing in single waves took 7.0 + 10.9 us.
+// The kernel is bound by its chain of dependent steps, and the chain by one compute unit's path to L2 (145 KB of weights
+// and 80 KB of codes: 44 KB of them, the prediction network's fetched by four waves; 36 bytes a cycle measured) and by
+// single waves running straight-line code, hence the split of every step over four waves.  Measured, one utterance at
+// beam 16: 10.1 us, where a launch for the output layers and one for joint, selection and routing in single waves took
+// 7.0 + 10.9 us.
 // ALSD: the same inside the alignment-length synchronous search (route.h, qr_alsd_route): every hypothesis reads its
 // own encoder frame (iteration - labels so far), a blank at the last frame finishes a hypothesis instead of being a
 // candidate, labels beyond the cap are no candidates.

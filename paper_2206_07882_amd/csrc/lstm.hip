@@ -805,6 +805,8 @@ void launch_pipe(const QrStepGroup &g, hipStream_t st)
 // second layers of 2 x 1024 cells 32 of 64 7.7 / 11.9, 64 of 128 7.5 / 11.1, 104 of 208 10.2 / 11.3, 208 of 208
 // 15.1 / 13.0; of 768 and 2048 cells 52 of 208 9.9 / 17.2, 104 of 208 14.7 / 17.6, 208 of 208 22.7 / 20.2.  A looked-up
 // input part halves the work that is split: first layers of 768 and 2 x 1024 cells 64 of 128 7.4 / 7.8, 104 of 208 11.2 / 8.8.
+// Where every hypothesis of a list advances the tiled kernel is the faster one from about 200 on (256 of 256: 13.0 / 11.9 and
+// 28.0 / 24.1), but the host does not know the length, and at a half the split pays more (8.8 / 10.4 and 17.0 / 19.8).
 static int split_n_max(bool use_gx, bool list) { return (use_gx ? 64 : 128) * (list ? 2 : 1); }
 
 // Hypothesis counts up to this go to the weight-streaming kernel.
@@ -1138,6 +1140,8 @@ extern "C" qrnnt_status qrnnt_input_projection(const qrnnt_lstm *L, const int8_t
 // Workspace layout of one layer-direction:
 //   int32 gx [T*B, 4H] | h state 2 x [B,H] int8 | c state 2 x [B,H] fp32 |
 //   exchange words of the persistent recurrence | error flag
+// (gx is for layers whose input the recurrence does not project by itself and for the step-by-step form; the recurrence
+// keeps cell states only where a group is short of members, and its admission words at the end of the second c state)
 struct LayerWs {
     size_t gx_b, h_b, c_b, x_b, total;
 };
@@ -1186,8 +1190,9 @@ qrnnt_status check_layer_call(const LayerCall &c, const int8_t *x_codes, int T, 
     return QRNNT_OK;
 }
 
-// 1 or 2 directions over the same input: projections, then either the persistent
-// recurrence (both directions in one launch) or one fused launch per time step.
+// 1 or 2 directions over the same input: the persistent recurrence (both directions in
+// one launch, the projection in front of it for inputs it does not project by itself),
+// or the projections and one fused launch per time step.
 qrnnt_status run_layer(const LayerCall *calls, int n, const int8_t *x_codes, int T, int B, int8_t *h_out, int ld_out,
                        hipStream_t st)
 {

@@ -130,6 +130,11 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
 //   - pick r becomes slot r of the next beam: a blank keeps the parent's sequence and state, a label extends it;
 //   - recombination: picks that stand for the same label sequence (same length and same 64-bit sequence hash)
 //     are one hypothesis; the best-ranked keeps its slot with log(sum exp(scores)), the others die;
+//   - a label that stays takes a free row of the state pool and joins the list of those the networks advance for, or
+//     (reuse) names the row of a live hypothesis that holds its sequence; a blank goes on with its parent's row;
+//   - the rows that no slot of the next beam names are free again.
+// Hypotheses that finish (a blank at the last frame) are no candidates: qr_alsd_finish takes them.
+
 // What lane w < W of the routing wave knows, beyond QrOwn, about hypothesis w of the current beam.
 struct QrAlsdOwn {
     QrOwn h;

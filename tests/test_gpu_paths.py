@@ -45,9 +45,8 @@ def test_lstm_layer_step_by_step_form_and_initial_state(gpu_lib, T, B, I, H, rev
     launch per time step (few utterances: the weight-streaming step kernel; 40: the tiled one, with a ragged
     row block since 1040 is not a multiple of 32); H = 64 and 640 take the persistent kernel, and so does H = 32, its
     smallest exchange (two workgroups per direction: the shape the benchmark times as the latency floor of a step).
-    112 and 130 utterances make more workgroups of 16 cells than the device has compute units, so the persistent kernel
-    runs in its form with 32 cells per workgroup (two row-tile groups per wave in the cell update).  Both forms with a
-    given initial state (hidden codes and cell state), every step against one oracle step from the GPU's own
+    112 and 130 utterances make groups of 16 that are not all full (130) and more of them than one per XCD (9, of 32
+    workgroups each, in two launches).  Both forms with a given initial state (hidden codes and cell state), every step against one oracle step from the GPU's own
     previous state, final state returned."""
     q = gpu_lib
     s_x = float(np.float32(4) / np.float32(7))

@@ -2,7 +2,9 @@
 number of 16-cell groups, 1..8 utterances (one cell per lane, columns packed to a power of two) against 9 and more,
 input widths on either side of what the kernel projects by itself (384 | 385, 1280 | 1281), sequences longer than the
 step number that travels with a code (mod 16, at 8 bits mod 256), more utterances than one launch holds, and two
-directions of different width.  Every step against one oracle step from the GPU's own previous state."""
+directions of different width; 641 cells and more (constants in LDS) at both widths, 97 utterances (f*c rounded first).
+Every step against one oracle step from the GPU's own previous state.  Then the routes that an idle device does not take:
+a refused launch, a group spread over XCDs, a group short of members, several streams at once."""
 import numpy as np
 import pytest
 import torch
@@ -37,7 +39,8 @@ def _check(L, x, hg, cg, reverse, h0, c0, unit, what):
     (40, 1, 64, 16, 4, False, False), (35, 2, 1280, 48, 4, True, True), (20, 8, 385, 272, 4, False, True),
     (20, 9, 384, 256, 4, True, False), (9, 17, 1281, 640, 4, False, True), (5, 33, 48, 656, 4, True, False),
     (270, 3, 40, 32, 8, False, True), (6, 20, 1300, 48, 8, True, True), (1, 5, 64, 64, 4, False, True),
-    (2, 4, 320, 640, 8, False, False), (4, 530, 32, 1024, 4, False, True)])
+    (2, 4, 320, 640, 8, False, False), (4, 530, 32, 1024, 4, False, True), (6, 13, 340, 1024, 8, True, True),
+    (5, 7, 385, 704, 8, False, True), (4, 97, 64, 704, 8, True, False), (4, 97, 1300, 768, 4, False, True)])
 def test_recurrence_edges(gpu_lib, T, B, I, H, bits, reverse, state):
     q = gpu_lib
     q_max = 127 if bits == 8 else 7
