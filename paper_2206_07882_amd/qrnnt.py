@@ -138,6 +138,17 @@ def _check(status: int, where: str):
         raise QrnntError(status, where)
 
 
+def _call(name: str, *args):
+    """Calls a function whose argument types are declared (see load).  A value of another type is a TypeError, as it is
+    where a ctypes constructor takes it."""
+    try:
+        status = getattr(load(), name)(*args)
+    except C.ArgumentError as e:
+        raise TypeError(f"{name}: {e}") from None
+    if status != 0:
+        raise QrnntError(status, name)
+
+
 def pack_bytes(rows: int, cols: int, layout: int, bits: int = 4) -> int:
     fn = load().qrnnt_pack_int8_bytes if bits == 8 else load().qrnnt_pack_int4_bytes
     return int(fn(rows, cols, layout))
@@ -227,8 +238,8 @@ def linear(w: QMat, bias: Optional[torch.Tensor], a_scale: float, a: torch.Tenso
     y = torch.empty((N, w.rows), dtype=torch.float32, device=a.device)
     acc = torch.empty((N, w.rows), dtype=torch.int32, device=a.device) if want_acc else None
     cw = w.c()
-    _check(load().qrnnt_linear(C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N,
-                               1 if log_softmax else 0, y.data_ptr(), _addr(acc), _stream_handle()), "qrnnt_linear")
+    _call("qrnnt_linear", C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N,
+          1 if log_softmax else 0, y.data_ptr(), _addr(acc), _stream_handle())
     return (y, acc) if want_acc else y
 
 
@@ -237,8 +248,8 @@ def linear_quant(w: QMat, bias: Optional[torch.Tensor], a_scale: float, a: torch
     N = a.shape[0]
     q = torch.empty((N, w.rows), dtype=torch.int8, device=a.device)
     cw = w.c()
-    _check(load().qrnnt_linear_quant(C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N, inv_scale,
-                                     bits, q.data_ptr(), _stream_handle()), "qrnnt_linear_quant")
+    _call("qrnnt_linear_quant", C.byref(cw), _addr(bias, torch.float32), a_scale, _addr(a, torch.int8), N, inv_scale,
+          bits, q.data_ptr(), _stream_handle())
     return q
 
 
@@ -435,11 +446,10 @@ def joint_fuse(enc_proj, frame_row, pred_proj, w_out: QMat, b_out, lp_src, lp_ex
     lp = torch.empty((N, V), dtype=torch.float32, device=dev) if want_lp else None
     zq = torch.zeros((N, J), dtype=torch.int8, device=dev) if want_zq else None
     cw = w_out.c()
-    st = load().qrnnt_joint_fuse(_addr(enc2, torch.float32), enc2.shape[0], _addr(frame_row, torch.int32),
-                                 _addr(pred_proj, torch.float32), C.byref(cw), _addr(b_out, torch.float32), z_scale,
-                                 z_inv_scale, _addr(lp_src, torch.float32), _addr(lp_ext, torch.float32), lambda_src,
-                                 lambda_ext, rho, N, blank, _addr(lp), _addr(zq), fused.data_ptr(), _stream_handle())
-    _check(st, "qrnnt_joint_fuse")
+    _call("qrnnt_joint_fuse", _addr(enc2, torch.float32), enc2.shape[0], _addr(frame_row, torch.int32),
+          _addr(pred_proj, torch.float32), C.byref(cw), _addr(b_out, torch.float32), z_scale, z_inv_scale,
+          _addr(lp_src, torch.float32), _addr(lp_ext, torch.float32), lambda_src, lambda_ext, rho, N, blank, _addr(lp),
+          _addr(zq), fused.data_ptr(), _stream_handle())
     return fused, lp, zq
 
 
@@ -450,9 +460,8 @@ def beam_step(score: torch.Tensor, fused: torch.Tensor, blank: int = 0, force_bl
     par = torch.empty((B, W), dtype=torch.int32, device=dev)
     tok = torch.empty((B, W), dtype=torch.int32, device=dev)
     ns = torch.empty((B, W), dtype=torch.float32, device=dev)
-    st = load().qrnnt_beam_step(_addr(score, torch.float32), _addr(fused, torch.float32), B, W, V, blank,
-                                1 if force_blank else 0, par.data_ptr(), tok.data_ptr(), ns.data_ptr(), _stream_handle())
-    _check(st, "qrnnt_beam_step")
+    _call("qrnnt_beam_step", _addr(score, torch.float32), _addr(fused, torch.float32), B, W, V, blank,
+          1 if force_blank else 0, par.data_ptr(), tok.data_ptr(), ns.data_ptr(), _stream_handle())
     return par, tok, ns
 
 
