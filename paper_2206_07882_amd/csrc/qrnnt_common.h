@@ -118,6 +118,20 @@ __device__ __forceinline__ int qr_quant(float x, float inv_step, int bits)
 // bits field of a qrnnt_qmat: 0 is read as 4.
 static inline int qr_bits(const qrnnt_qmat *m) { return m->bits == 8 ? 8 : 4; }
 
+// Stores that go through the L2 to memory as they are made.  At the end of a kernel every XCD's L2 writes back what it
+// still holds modified before the next launch may start; for a launch that writes megabytes of state this is time during
+// which nothing else runs (11.5 MB written early in 8 us of work: 10.5 us a launch with plain stores, 9.0 with these).  Where
+// few bytes are written, or single bytes, plain stores cost less (a beam of 16 on its own: 15.0 ms, with these 15.2).
+// (s_nop 1: two wait states before the data registers of a wide store may be rewritten; the compiler does not see one here.)
+__device__ __forceinline__ void qr_store_through(float *p, v4f v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void qr_store_through(int8_t *p, unsigned v)   // 4 codes
+{
+    asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+}
+
 // Wave-wide max / min of a 32-bit unsigned value on the DPP path (row scans, then
 // the two cross-row broadcasts of gfx9), result broadcast through lane 63.
 template <bool IS_MAX>
