@@ -484,6 +484,12 @@ qrnnt_status qrnnt_diag_lstm_layer(const qrnnt_lstm *L, const int8_t *x_codes, i
                                    int8_t *h_last, float *c_last, int32_t *dbg_accx, float *dbg_c_all, int32_t route,
                                    void *workspace, size_t workspace_bytes, void *stream);
 
+/* qrnnt_decode (alsd = 0, limit = max_sym) or qrnnt_decode_alsd (alsd = 1, limit = u_max) as if of the workgroups that share
+ * a beam's work only one ever got a compute unit: that one does all of it, with the same results (tests compare them). */
+qrnnt_status qrnnt_diag_decode(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W, int32_t alsd,
+                               int32_t limit, int32_t max_len, int32_t *tokens_out, int32_t *len_out, float *score_out,
+                               void *workspace, size_t workspace_bytes, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -29,6 +29,8 @@ struct Plan {
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
     v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the hypotheses that carry a label into round v of the frame, and how many
+    unsigned long long *words;     // [B][QR_ROUND_PARTS + 1][16][64]: see QrRoundArgs.words (beams of up to 16)
+    size_t n_clear;                // 32-bit words from `live` on that start at zero: live, n_rows, words
     size_t total;
 };
 
@@ -63,6 +65,16 @@ void take_nets(const qrnnt_model *m, Plan &p, Carver &cv)
     }
 }
 
+// What starts at zero, in one piece: two sets of counters, and the words on their way between an utterance's workgroups.
+void take_cleared(Plan &p, Carver &cv, size_t n_counters)
+{
+    p.live = cv.take<int32_t>(n_counters);
+    const size_t start = cv.off - n_counters * sizeof(int32_t);
+    p.n_rows = cv.take<int32_t>(n_counters);
+    p.words = p.W <= 16 ? cv.take<unsigned long long>((size_t)p.B * (QR_ROUND_PARTS + 1) * 16 * 64) : nullptr;
+    p.n_clear = (cv.off - start) / 4;
+}
+
 void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws, Plan &p)
 {
     p.T = T; p.B = B; p.W = W; p.N = B * W; p.max_sym = max_sym;
@@ -83,9 +95,8 @@ void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws,
     const size_t pool = 1 + (size_t)T * max_sym * N;
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
-    p.live = cv.take<int32_t>(2 * (size_t)(max_sym + 2));
     p.rows = cv.take<v4i>(N);
-    p.n_rows = cv.take<int32_t>(2 * (size_t)(max_sym + 2));
+    take_cleared(p, cv, 2 * (size_t)(max_sym + 2));
     p.total = (cv.off + 255) / 256 * 256;
 }
 
@@ -248,7 +259,7 @@ void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, cons
 }
 
 // What a decoding round reads of the model.
-QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj)
+QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj, bool alone)
 {
     QrRoundArgs ja = {};
     for (int k = 0; k < 3; ++k) {
@@ -268,12 +279,15 @@ QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_pro
     ja.J = p.J;  ja.V = p.V;  ja.blank = m->blank;
     ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
     ja.w8 = qr_bits(&m->joint_out) == 8;
+    ja.words = p.words;
+    ja.ticks = alone ? 10 : 1000;   // 10 us; the other workgroups need 3
+    ja.alone = alone;
     return ja;
 }
 
 // Everything a search starts from: a row of zero states, the first layers' input tables, empty counters and lists
-// (p.live and p.n_rows: n_counters words each), and the start symbol consumed by the empty sequence of every utterance.
-void start_decode(const qrnnt_model *m, const Plan &p, size_t n_counters, int32_t *n_taken, int32_t *nx_count, hipStream_t st)
+// and the start symbol consumed by the empty sequence of every utterance.
+void start_decode(const qrnnt_model *m, const Plan &p, int32_t *n_taken, int32_t *nx_count, hipStream_t st)
 {
     auto fill = [&](void *at, size_t nw) {
         fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)at, nw, 0u);
@@ -290,8 +304,7 @@ void start_decode(const qrnnt_model *m, const Plan &p, size_t n_counters, int32_
         qr_launch_input_projection(&net->layer[0], net->embed_codes, p.V, p.net[k].gx0, nullptr, st);
         qr_launch_gx_table(&net->layer[0], p.net[k].gx0, p.V, p.net[k].tab0, st);
     }
-    fill(p.live, n_counters);
-    fill(p.n_rows, n_counters);
+    fill(p.live, p.n_clear);
     // the start symbol's list is counted in the first counter, which no round uses
     decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, nx_count,
                                                                        p.rows, p.n_rows, p.node_tok, p.node_prev, p.W, p.B, p.P,
@@ -317,10 +330,11 @@ extern "C" qrnnt_status qrnnt_decode(const qrnnt_model *m, const float *enc_proj
                            workspace_bytes, stream);
 }
 
-extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
-                                        int32_t max_sym, int32_t max_len, uint32_t flags, int32_t *tokens_out,
-                                        int32_t *len_out, float *score_out, void *workspace, size_t workspace_bytes,
-                                        void *stream)
+// alone: every utterance's other workgroups stay away (QrRoundArgs).
+static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                     int32_t max_sym, int32_t max_len, uint32_t flags, int32_t *tokens_out,
+                                     int32_t *len_out, float *score_out, void *workspace, size_t workspace_bytes,
+                                     void *stream, bool alone)
 {
     qrnnt_status s = check_model(m);
     if (s != QRNNT_OK) return s;
@@ -340,9 +354,9 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
     const size_t Ns = (size_t)N;
     const int ZB = p.NB - 1;   // the beam's buffer in every second frame (else 0)
 
-    start_decode(m, p, 2 * (max_sym + 2), p.n_taken, p.nx_count, st);
+    start_decode(m, p, p.n_taken, p.nx_count, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj);
+    QrRoundArgs ja = round_args(m, p, enc_proj, alone);
 
     int a0 = 0;   // buffer of the beam at the current frame
     for (int t = 0; t < T; ++t) {
@@ -351,6 +365,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
             const int nxt = v + 1;   // only used when v < max_sym
             ja.frame_base = t * B;
             ja.row = p.row + (size_t)cur * Ns;
+            ja.round = 1u + (unsigned)t * p.R + v;
             const int last = (v == max_sym);
             QrRouteArgs ra = {};
             ra.score_src = p.score + (size_t)cur * Ns;
@@ -385,6 +400,15 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
                                                    p.len + (size_t)a0 * Ns, p.node_tok, p.node_prev, N, max_len,
                                                    tokens_out, len_out, score_out);
     return qr_launch_status();
+}
+
+extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                        int32_t max_sym, int32_t max_len, uint32_t flags, int32_t *tokens_out,
+                                        int32_t *len_out, float *score_out, void *workspace, size_t workspace_bytes,
+                                        void *stream)
+{
+    return time_synchronous(m, enc_proj, T, B, W, max_sym, max_len, flags, tokens_out, len_out, score_out, workspace,
+                            workspace_bytes, stream, false);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -422,9 +446,8 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     const size_t pool = 1 + (size_t)ap.n_iter * N;
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
-    p.live = cv.take<int32_t>((size_t)ap.n_iter + 2);
     p.rows = cv.take<v4i>(N);
-    p.n_rows = cv.take<int32_t>((size_t)ap.n_iter + 2);
+    take_cleared(p, cv, (size_t)ap.n_iter + 2);
     p.total = (cv.off + 255) / 256 * 256;
 }
 
@@ -451,10 +474,10 @@ extern "C" qrnnt_status qrnnt_decode_alsd(const qrnnt_model *m, const float *enc
                                 workspace, workspace_bytes, stream);
 }
 
-extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
-                                             int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats,
-                                             int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,
-                                             size_t workspace_bytes, void *stream)
+static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                                 int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats,
+                                                 int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,
+                                                 size_t workspace_bytes, void *stream, bool alone)
 {
     qrnnt_status s = check_model(m);
     if (s != QRNNT_OK) return s;
@@ -480,14 +503,15 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_node, Ns, 0u);
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_len, Ns, 0u);
     }
-    start_decode(m, p, (size_t)ap.n_iter + 2, nullptr, nullptr, st);
+    start_decode(m, p, nullptr, nullptr, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj);
+    QrRoundArgs ja = round_args(m, p, enc_proj, alone);
 
     int cur = 0;
     for (int i = 0; i < ap.n_iter; ++i) {
         const int nxt = cur ^ 1;
         ja.row = p.row + (size_t)cur * Ns;
+        ja.round = 1u + (unsigned)i;
         QrRouteArgs ra = {};
         ra.score_src = p.score + (size_t)cur * Ns;
         ra.B = B;  ra.W = W;  ra.V = V;  ra.R = 1;  ra.blank = m->blank;  ra.last_round = 0;
@@ -513,4 +537,23 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(ap.fin_score, ap.fin_node, ap.fin_len, p.node_tok, p.node_prev, N,
                                                    max_len, tokens_out, len_out, score_out);
     return qr_launch_status();
+}
+
+extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                             int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats,
+                                             int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,
+                                             size_t workspace_bytes, void *stream)
+{
+    return alignment_length_synchronous(m, enc_proj, T, B, W, u_max, max_len, flags, stats, tokens_out, len_out, score_out,
+                                        workspace, workspace_bytes, stream, false);
+}
+
+extern "C" qrnnt_status qrnnt_diag_decode(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                          int32_t alsd, int32_t limit, int32_t max_len, int32_t *tokens_out, int32_t *len_out,
+                                          float *score_out, void *workspace, size_t workspace_bytes, void *stream)
+{
+    return alsd ? alignment_length_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, nullptr, tokens_out, len_out, score_out,
+                                               workspace, workspace_bytes, stream, true)
+                : time_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, tokens_out, len_out, score_out, workspace,
+                                   workspace_bytes, stream, true);
 }

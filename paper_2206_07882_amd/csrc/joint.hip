@@ -1,6 +1,9 @@
 // Joint network, log-softmax and density-ratio fusion in one kernel (Sec. 2:
 // encoder and prediction outputs are combined multiplicatively, a linear layer
 // and a log-softmax follow; Eq. 1 adds the weighted LM log-probabilities).
+#include <atomic>
+#include <type_traits>
+
 #include "head.h"
 #include "kernels.h"
 #include "route.h"
@@ -142,8 +145,30 @@ __device__ __forceinline__ float qr_row_sum(const v4f &e)
     return __int_as_float(x);
 }
 
-// One decoding round of an utterance in one workgroup: output layers of the three networks, joint, log-softmax and
-// fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
+// Four tokens (k0 ..) of an output layer from the sums of their rows, as log-probabilities if it ends in a log-softmax; the
+// 16 lanes of a row hold all tokens of a hypothesis.
+__device__ __forceinline__ v4f qr_token_values(v4i t, bool w8, const float *scale, const float *bias, int k0, int V, bool log_softmax)
+{
+    t = w8 ? t : (t >> 4);   // 4-bit operands carry a factor 16
+    const v4f ws = *(const v4f *)(scale + k0), wb = *(const v4f *)(bias + k0);
+    float mx = -INFINITY;
+    v4f v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = k0 + i < V ? ws[i] * (float)t[i] + wb[i] : -INFINITY;
+        mx = fmaxf(mx, v[i]);
+    }
+    mx = qr_row_max(mx);
+    v4f e;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = qr_exp(v[i] - mx);   // (0 behind the last token)
+    float lse = mx + qr_log(qr_row_sum(e));
+    if (!log_softmax) lse = 0.0f;
+    return v - lse;
+}
+
+// One decoding round of an utterance in one workgroup (or several: see CL): output layers of the three networks, joint,
+// log-softmax and fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
 // (route.h), and after the last round of a frame the new beam.  Between the networks' top hidden codes and the picks
 // nothing touches memory.
 //   contraction, waves 0-3: the prediction network's output layer and the joint.  A wave owns 64-column blocks of the
@@ -163,7 +188,18 @@ __device__ __forceinline__ float qr_row_sum(const v4f &e)
 // ALSD: the same inside the alignment-length synchronous search (route.h, qr_alsd_route): every hypothesis reads its
 // own encoder frame (iteration - labels so far), a blank at the last frame finishes a hypothesis instead of being a
 // candidate, labels beyond the cap are no candidates.
-template <int NTW, bool ALSD>
+// CL (up to 16 hypotheses, and all workgroups of the launch resident): an utterance has up to QR_ROUND_PARTS workgroups that
+// share the joint, 64 columns at a time (its output layer's sums add up), and one that contracts the language models' output
+// layers and forms their log-probabilities; the first one collects and goes on alone.  One compute unit's path to L2 no
+// longer bounds the round: 36 KB to a workgroup instead of 225.  What they send goes through the L2 of the XCD they run on
+// (ids congruent modulo the number of XCDs; nothing but the time depends on that), value and round number in one 8-byte
+// word, so that every word says by itself whether it is there: no flag, no order of stores.  The others wait for nobody, and
+// the first one not for long: after `ticks` it does everything itself.  The last round of a frame has blanks to offer only,
+// and no use for the language models.  Stamps of the first workgroup (one utterance at beam 16, ns after its start, one
+// workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end 9900 -> 7500; a round of three
+// launches 24.7 -> 21.9 us, of 64 utterances 37.8 -> 35.9.
+// (Two workgroups, the second with the language models: the first one's share still took 4.2 us, no gain.)
+template <int NTW, bool ALSD, bool CL>
 __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
 {
     constexpr int MAX_LIST = ALSD ? 1 : 16 * NTW * 17;   // a frame's candidates: W blanks in each of at most 17 rounds
@@ -174,16 +210,22 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     __shared__ float fin_new[64];           // ALSD: value of hypothesis w finishing now
     __shared__ __attribute__((aligned(16))) float jc[3][2][64];   // row scales and biases: joint, source LM, external LM
     __shared__ __attribute__((aligned(16))) float pc[4][2][64];   // [wave] those of the prediction network's 64 rows at hand
+    __shared__ __attribute__((aligned(16))) int8_t z_code[CL ? 16 : 1][80];   // a block's codes (the pitch spreads the rows over the banks)
+    __shared__ v4f lm_val[CL ? 2 : 1][CL ? 256 : 1];   // the language models' values for each thread of the scores
     __shared__ unsigned mask[64];
-    __shared__ int n_cand, n_list;
+    __shared__ int n_cand, n_list, missed;
     QrCand *const gathered = (QrCand *)&sums[0][0][0];
     static_assert(sizeof(sums) >= 16 * 4 * 64 * sizeof(QrCand), "all candidates of 64 hypotheses x 64 tokens");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int b = blockIdx.x;
+    // Grid: x = utterance; CL: x = XCD (workgroups go out with x fastest, each to the next XCD), y = second, first workgroup
+    // (the one that is waited for goes out first), z = XCD's next utterance
+    const int b = CL ? (int)(blockIdx.z * gridDim.x + blockIdx.x) : (int)blockIdx.x;
+    if (CL && b >= r.B) return;   // uniform
     const int W = r.W, V = a.V, J = a.J;
     const bool frame_end = !ALSD && r.last_round;
+    const bool use_lm = !frame_end && (a.head[1].w || a.head[2].w);   // (the last round's candidates are blanks)
     const int n_entries = r.R * W;
     const size_t nx = (size_t)b * n_entries;
     const v4i zero = {0, 0, 0, 0};
@@ -221,6 +263,125 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         list_len[e] = info[2];
     };
 
+    const int n_row_tiles = (V + 15) >> 4;
+    const int my_n = b * W + (col < W ? col : W - 1);   // this lane's column of the (first) tile
+    // Contraction of output layer h by this wave: chunks c0, c0 + step, ...
+    auto head_mma = [&](auto batch, const QrHeadArgs &h, int row, int c0, int step, v4i (&acc)[4]) {
+        constexpr int NB = decltype(batch)::value, NB8 = NB > 1 ? NB / 2 : 1;   // chunks in flight
+        unsigned woff[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
+            woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
+        }
+        if (h.w8) qr_chunk_mma<true, NB8>(h.w, woff, h.act, row, h.K, h.nkc, c0, step, grp, acc, [] {});
+        else qr_chunk_mma<false, NB>(h.w, woff, h.act, row, h.K, h.nkc, c0, step, grp, acc, [] {});
+    };
+    // where a lane's sums of row tile mt go, and where the thread of the scores with hypothesis hc finds those of its quad
+    auto put_sums = [&](const v4i (&acc)[4]) {
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][grp * 16 + (col ^ (4 * mt + grp))] = acc[mt];
+    };
+    // row scales and biases of the joint (q = 0) or a language model into LDS, by one wave
+    auto row_constants = [&](int q) {
+        const int kk = lane < V ? lane : V - 1;
+        const float *sw = q == 0 ? a.s_w : a.head[q].s_w, *bs = q == 0 ? a.b_out : a.head[q].bias;
+        jc[q][0][lane] = sw ? (q == 0 ? a.z_scale : a.head[q].a_scale) * sw[kk] : 0.0f;
+        jc[q][1][lane] = bs ? bs[kk] : 0.0f;
+    };
+
+    // CL: this workgroup's share of the joint: blocks of 64 columns first, first + a.parts, ...  A block: the 64 rows of the
+    // prediction network's output layer, K dealt to the eight waves; a thread adds up two columns of a hypothesis and forms
+    // their codes; waves 0-3 contract the codes with a row tile each of the joint's output layer and return its sums.
+    const int z_lane = (tid >> 1) & 63, z_hyp = z_lane & 15, z_col = (tid >> 7) * 16 + 4 * (z_lane >> 4) + 2 * (tid & 1);
+    auto joint_part = [&](int first, int row, int len) -> v4i {
+        const QrHeadArgs &h = a.head[0];
+        const int n_tiles = J >> 4, zbits = a.w8 ? 8 : 4;
+        int64_t fr = a.frame_base + b;
+        if (ALSD) {   // this hypothesis' own frame
+            int t_w = s.iter - len;
+            t_w = t_w < 0 ? 0 : (t_w > s.T - 1 ? s.T - 1 : t_w);
+            fr = (int64_t)t_w * r.B + b;
+        }
+        v4i sum = zero;
+        for (int jb = first; jb * 64 < J; jb += a.parts) {   // uniform
+            const bool jv = jb * 64 + z_col < J;
+            const int j = jv ? jb * 64 + z_col : 0;
+            unsigned woff[4];   // (a matrix of 2 GiB would have to have 4 million rows)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const int rt = 4 * jb + mt < n_tiles ? 4 * jb + mt : n_tiles - 1;
+                woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
+            }
+            v4i acc[4] = {zero, zero, zero, zero};
+            if (h.w8) qr_chunk_mma<true, 1>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
+            else qr_chunk_mma<false, 1>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
+            // what the codes need arrives while the sums meet
+            const float *const e = a.enc + fr * J + j;
+            const float e0 = e[0], e1 = e[1], sw0 = h.s_w[j], sw1 = h.s_w[j + 1];
+            const float bs0 = h.bias ? h.bias[j] : 0.0f, bs1 = h.bias ? h.bias[j + 1] : 0.0f;
+            v4i wj = zero;
+            if (wave < 4) {
+                const int rt = wave < n_row_tiles ? wave : n_row_tiles - 1;
+                wj = a.w8 ? a.w[((size_t)rt * a.nkc * 2 + jb) * 64 + lane] : a.w[((size_t)rt * a.nkc + (jb >> 1)) * 64 + lane];
+            }
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) sums[wave][mt][lane] = acc[mt];
+            __syncthreads();
+            int s0 = 0, s1 = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const int *const q = (const int *)&sums[w][tid >> 7][z_lane] + 2 * (tid & 1);
+                s0 += q[0];
+                s1 += q[1];
+            }
+            s0 = h.w8 ? s0 : (s0 >> 4);   // 4-bit operands carry a factor 16
+            s1 = h.w8 ? s1 : (s1 >> 4);
+            const float p0 = (h.a_scale * sw0) * (float)s0 + bs0, p1 = (h.a_scale * sw1) * (float)s1 + bs1;
+            const int c0 = qr_quant(qr_tanh(e0 * p0), a.z_inv, zbits), c1 = qr_quant(qr_tanh(e1 * p1), a.z_inv, zbits);
+            *(unsigned short *)&z_code[z_hyp][z_col] = (unsigned short)(jv ? (c0 & 0xFF) | (c1 & 0xFF) << 8 : 0);
+            __syncthreads();
+            if (wave < 4) {   // uniform
+                const v4i z = *(const v4i *)&z_code[col][grp * 16];
+                sum = qr_mfma(a.w8 ? wj : ((jb & 1) ? (wj & m) : ((wj << 4) & m)), z, sum);
+            }
+        }
+        return sum;
+    };
+    // Words on their way to the first workgroup: source q of a.parts + 1, hypothesis, token.
+    auto word_at = [&](int q, int hyp, int token) { return a.words + (((size_t)b * (QR_ROUND_PARTS + 1) + q) * 16 + hyp) * 64 + token; };
+    auto publish = [&](v4i v, int q, int hyp, int token) {
+        v4i *const out = (v4i *)word_at(q, hyp, token);
+        out[0] = v4i{v[0], (int)a.round, v[1], (int)a.round};
+        out[1] = v4i{v[2], (int)a.round, v[3], (int)a.round};
+    };
+
+    if (CL && blockIdx.y + 1 < gridDim.y) {   // uniform: not the first workgroup
+        if (!ALSD && r.gate && *r.gate == 0) return;   // uniform
+        const int row = a.row[my_n];
+        if (blockIdx.y + a.parts >= gridDim.y) {       // a share of the joint
+            const int part = (int)(gridDim.y - 1 - blockIdx.y);
+            const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
+            if (wave < 4) publish(sum, part, col, wave * 16 + 4 * grp);
+            return;
+        }
+        const int net = wave >> 2;                     // the language models: waves 0-3 source, 4-7 external, K split in four
+        const QrHeadArgs &h = a.head[1 + net];
+        v4i acc[4] = {zero, zero, zero, zero};
+        if (h.w) head_mma(std::integral_constant<int, 2>{}, h, row, wave & 3, 4, acc);   // uniform
+        if ((wave & 3) == 3) row_constants(1 + net);
+        put_sums(acc);
+        __syncthreads();
+        const int hc = (tid & 255) >> 4, quad = lane & 15, mt = quad >> 2, at = (quad & 3) * 16 + (hc ^ quad);
+        v4i t = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t += sums[4 * net + k][mt][at];
+        const v4f v = qr_token_values(t, h.w8 != 0, jc[1 + net][0], jc[1 + net][1], 4 * quad, V, h.log_softmax != 0);
+        publish(v4i{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])},
+                net == 0 ? 0 : QR_ROUND_PARTS, hc, 4 * quad);
+        return;
+    }
+
     if (!ALSD && r.gate && *r.gate == 0) {   // uniform: no utterance carried a label into this round, nothing can be picked
         if (tid == 0 && b == 0 && r.live_clear) *r.live_clear = 0;
         if (tid == 0 && b == 0 && r.n_rows_clear) *r.n_rows_clear = 0;
@@ -233,20 +394,13 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         return;
     }
 
-    const int n_row_tiles = (V + 15) >> 4;
     if (wave >= 4) {   // (the waves with less to do)
         const int k = (wave - 4) * 64 + lane;
         if (k < 64) best[k] = 0;
         else if (k < 128) best_fe[k - 64] = 0;
         else if (k < 192) fin_new[k - 128] = -INFINITY;
-        else if (k == 192) n_cand = 0;
-        const int kk = lane < V ? lane : V - 1;
-        if (wave < 7) {
-            const int q = wave - 4;   // joint, source LM, external LM
-            const float *sw = q == 0 ? a.s_w : a.head[q].s_w, *bs = q == 0 ? a.b_out : a.head[q].bias;
-            jc[q][0][lane] = sw ? (q == 0 ? a.z_scale : a.head[q].a_scale) * sw[kk] : 0.0f;
-            jc[q][1][lane] = bs ? bs[kk] : 0.0f;
-        }
+        else if (k == 192) n_cand = missed = 0;
+        if (wave < 7) row_constants(wave - 4);   // joint, source LM, external LM
     }
     // What the routing wave and the scoring threads will need: requested first, used last.
     QrOwn own = {};
@@ -275,7 +429,55 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         const int row = a.row[n];
         if (nt > 0) __syncthreads();   // what the previous tile left in LDS has been read
         v4i acc[4] = {zero, zero, zero, zero};
-        if (wave < 4) {
+        // waves 4-7, besides: the frame's candidates so far (the last round's list), the list of finished hypotheses
+        float e_score = 0.0f;
+        v4i e_info = zero;
+        const int e0 = tid - 256;
+        if (frame_end && nt == 0 && e0 >= 0 && e0 < n_entries) {
+            e_score = r.nx_score[nx + e0];
+            e_info = r.nx_info[nx + e0];
+        }
+        if (ALSD && nt == 0 && wave == 5) finished = qr_alsd_load_finished(r, s, b, lane);
+        // CL: the words of the other workgroups that this thread of the scores (waves 0-3: shares of the joint; waves 4-7, for
+        // the same thread of waves 0-3: language models) waits for, past this CU's cache
+        v4i word[2 * (CL ? QR_ROUND_PARTS - 1 : 1)];
+        const int n_src = wave < 4 ? a.parts - 1 : (use_lm ? 2 : 0);   // uniform
+        auto source = [&](int i) { return wave < 4 ? 1 + i : (i == 0 ? 0 : QR_ROUND_PARTS); };
+        auto request = [&]() {
+            const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)word_at(0, 0, 0), 0, (QR_ROUND_PARTS + 1) * 16 * 64 * 8, 0x00020000 /* raw bytes */);
+#pragma unroll
+            for (int i = 0; i < QR_ROUND_PARTS - 1; ++i)
+                if (i < n_src) {
+                    const unsigned off = (unsigned)((source(i) * 16 + ((tid >> 4) & 15)) * 64 + 4 * (lane & 15)) * 8;
+                    word[2 * i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off, 0, 16 /* sc1 */);
+                    word[2 * i + 1] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off + 16, 0, 16);
+                }
+            asm volatile("" ::: "memory");   // every poll loads anew
+        };
+        v4i t = zero;   // CL: sums of the other shares
+        if (CL) {
+            const v4i sum = joint_part(0, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
+            request();
+            if (wave < 4) sums[0][wave][grp * 16 + (col ^ (4 * wave + grp))] = sum;
+            for (const unsigned long long t0 = wall_clock64();; request()) {
+                bool ok = true;
+#pragma unroll
+                for (int i = 0; i < 2 * (QR_ROUND_PARTS - 1); ++i)
+                    if (i < 2 * n_src) ok = ok && (unsigned)word[i][1] == a.round && (unsigned)word[i][3] == a.round;
+                if (__all(ok)) break;
+                if (wall_clock64() - t0 > (unsigned long long)a.ticks) {
+                    if (lane == 0) missed = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < QR_ROUND_PARTS - 1; ++i) {
+                const v4i v = i < n_src ? v4i{word[2 * i][0], word[2 * i][2], word[2 * i + 1][0], word[2 * i + 1][2]} : zero;
+                if (wave < 4) t += v;
+                else if (i < 2) lm_val[i][e0] = v4f{__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3])};
+            }
+        } else if (wave < 4) {
             const QrHeadArgs &h = a.head[0];
             const int n_pred_tiles = J >> 4;
             const int zbits = a.w8 ? 8 : 4;
@@ -337,60 +539,50 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             }
         } else {
             const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
-            // besides, the frame's candidates so far (the last round's list), the list of finished hypotheses
-            float e_score = 0.0f;
-            v4i e_info = zero;
-            const int e0 = tid - 256;
-            if (frame_end && nt == 0 && e0 < n_entries) {
-                e_score = r.nx_score[nx + e0];
-                e_info = r.nx_info[nx + e0];
-            }
-            if (ALSD && nt == 0 && wave == 5) finished = qr_alsd_load_finished(r, s, b, lane);
-            if (h.w) {   // uniform
-                unsigned woff[4];
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
-                    woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
-                }
-                if (h.w8) qr_chunk_mma<true, NTW == 1 ? 2 : 1>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
-                else qr_chunk_mma<false, NTW == 1 ? 4 : 2>(h.w, woff, h.act, row, h.K, h.nkc, wave & 1, 2, grp, acc, [] {});
-            }
-            if (frame_end && nt == 0) {
-                if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
-                for (int e = e0 + 256; e < n_entries; e += 256) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
-            }
+            if (h.w && use_lm) head_mma(std::integral_constant<int, NTW == 1 ? 4 : 2>{}, h, row, wave & 1, 2, acc);   // uniform
         }
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][grp * 16 + (col ^ (4 * mt + grp))] = acc[mt];
+        if (frame_end && nt == 0 && e0 >= 0) {
+            if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
+            for (int e = e0 + 256; e < n_entries; e += 256) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
+        }
+        if (!CL) put_sums(acc);
         if (ALSD && r.gate && *r.gate == 0) return;   // uniform: no live hypothesis anywhere, the finals stay as they are
         __syncthreads();
-        if (wave >= 4) continue;
 
         // ---- scores: hypothesis 16 * nt + hc, tokens 4 * quad .. 4 * quad + 3
-        const int hc = tid >> 4, quad = lane & 15, mt = quad >> 2;
+        const int hc = (tid >> 4) & 15, quad = lane & 15, mt = quad >> 2;
         const int at = (quad & 3) * 16 + (hc ^ quad), k0 = 4 * quad;
         v4f v[3];   // joint, source LM, external LM
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const bool w8 = q == 0 ? a.w8 != 0 : a.head[q].w8 != 0;
-            v4i t = sums[q == 0 ? 0 : 2 + 2 * q][mt][at] + sums[q == 0 ? 1 : 3 + 2 * q][mt][at];
-            if (q == 0) t += sums[2][mt][at] + sums[3][mt][at];
-            t = w8 ? t : (t >> 4);   // 4-bit operands carry a factor 16
-            const v4f ws = *(const v4f *)&jc[q][0][k0], wb = *(const v4f *)&jc[q][1][k0];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[q][i] = k0 + i < V ? ws[i] * (float)t[i] + wb[i] : -INFINITY;
-                mx = fmaxf(mx, v[q][i]);
+        bool own_lm = !CL;   // the language models' sums lie in LDS
+        if (wave < 4) t += sums[0][mt][at];
+        if (!CL && wave < 4) t += sums[1][mt][at] + sums[2][mt][at] + sums[3][mt][at];
+        if (CL && __builtin_amdgcn_readfirstlane(missed)) {   // uniform: everything that should have come
+            if (wave < 4) t = sums[0][mt][at];
+            own_lm = use_lm;
+            __syncthreads();
+            for (int part = 1; part < a.parts; ++part) {
+                const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
+                if (wave < 4) sums[0][wave][grp * 16 + (col ^ (4 * wave + grp))] = sum;
+                __syncthreads();
+                if (wave < 4) t += sums[0][mt][at];
+                __syncthreads();
             }
-            mx = qr_row_max(mx);
-            v4f e;
+            if (wave >= 4 && use_lm) {
+                const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
+                if (h.w) head_mma(std::integral_constant<int, 2>{}, h, row, wave & 1, 2, acc);   // uniform
+                put_sums(acc);
+            }
+            __syncthreads();
+        }
+        if (wave >= 4) continue;
+        v[0] = qr_token_values(t, a.w8 != 0, jc[0][0], jc[0][1], k0, V, true);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = qr_exp(v[q][i] - mx);   // (0 behind the last token)
-            float lse = mx + qr_log(qr_row_sum(e));
-            if (q > 0 && !a.head[q].log_softmax) lse = 0.0f;
-            v[q] = v[q] - lse;
+        for (int q = 1; q < 3; ++q) {
+            if (!own_lm)   // uniform
+                v[q] = lm_val[q - 1][tid];
+            else
+                v[q] = qr_token_values(sums[2 + 2 * q][mt][at] + sums[3 + 2 * q][mt][at], a.head[q].w8 != 0, jc[q][0], jc[q][1], k0, V,
+                                       a.head[q].log_softmax != 0);
         }
         const int ws_ = nt * 16 + hc;
         int t_w = s.iter - len_t[nt];
@@ -472,20 +664,48 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
 
 }  // namespace
 
-void qr_launch_search_round(const QrRoundArgs &a, const QrRouteArgs &r, hipStream_t st)
+namespace {
+
+// Workgroups of search_round_kernel<1, ALSD, true> that the device holds at once.
+template <bool ALSD>
+int resident()
 {
-    const QrAlsdArgs none = {};
-    const unsigned grid = (unsigned)r.B;
-    if (r.W <= 16) search_round_kernel<1, false><<<grid, 512, 0, st>>>(a, r, none);
-    else if (r.W <= 32) search_round_kernel<2, false><<<grid, 512, 0, st>>>(a, r, none);
-    else search_round_kernel<4, false><<<grid, 512, 0, st>>>(a, r, none);
+    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none
+    const int dev = qr_current_device();
+    int n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        int n_cu = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, search_round_kernel<1, ALSD, true>, 512, 0) != hipSuccess)
+            return 0;
+        n = n_cu * per_cu > 0 ? n_cu * per_cu : -1;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return n > 0 ? n : 0;
 }
+
+template <bool ALSD>
+void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
+{
+    constexpr int N_XCD = 8;
+    const bool use_lm = (ALSD || !r.last_round) && (a.head[1].w || a.head[2].w);
+    QrRoundArgs c = a;
+    c.parts = (a.J + 63) / 64 < QR_ROUND_PARTS ? (a.J + 63) / 64 : QR_ROUND_PARTS;
+    const int wgs = c.parts + (use_lm ? 1 : 0);
+    if (r.W <= 16 && (wgs == 1 || r.B * wgs <= resident<ALSD>()))
+        search_round_kernel<1, ALSD, true><<<dim3(N_XCD, a.alone ? 1 : wgs, (r.B + N_XCD - 1) / N_XCD), 512, 0, st>>>(c, r, s);
+    else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
+    else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
+    else search_round_kernel<4, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
+}
+
+}  // namespace
+
+void qr_launch_search_round(const QrRoundArgs &a, const QrRouteArgs &r, hipStream_t st) { launch_round<false>(a, r, QrAlsdArgs{}, st); }
 
 void qr_launch_search_round_alsd(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
-    if (r.W <= 16) search_round_kernel<1, true><<<r.B, 512, 0, st>>>(a, r, s);
-    else if (r.W <= 32) search_round_kernel<2, true><<<r.B, 512, 0, st>>>(a, r, s);
-    else search_round_kernel<4, true><<<r.B, 512, 0, st>>>(a, r, s);
+    launch_round<true>(a, r, s, st);
 }
 
 void qr_launch_joint(const QrJointArgs &a, hipStream_t st)

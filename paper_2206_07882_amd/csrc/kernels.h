@@ -98,7 +98,15 @@ struct QrRoundArgs {
     float z_scale, z_inv;
     float lambda_src, lambda_ext, rho;
     int J, V, blank, nkc, w8;
+    // Beams of up to 16: values on their way between the workgroups of an utterance (joint.hip), [B][QR_ROUND_PARTS + 1][16][64]
+    // words of value and round number (never 0, no two rounds of a search the same); zeroed before the first round.
+    unsigned long long *words;
+    unsigned round;
+    int parts;                         // workgroups that share the joint (filled in by the launcher)
+    int ticks;                         // how long to wait for the others, in 10 ns
+    int alone;                         // diagnostic: the others never come
 };
+#define QR_ROUND_PARTS 4
 
 struct QrRouteArgs {
     const float *score_src;                         // [B,W] of the current round

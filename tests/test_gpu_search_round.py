@@ -1,8 +1,11 @@
 """The decoding round's kernel at the edges of what it splits: joint widths that end inside a wave's 64 columns or need
 several blocks per wave, output layers that end inside a 128-column chunk, vocabularies at the edges of the 16-row tiles,
 beams on both sides of a column tile, and mixed widths."""
+import ctypes as C
+
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from oracle import models as omodels
@@ -22,6 +25,15 @@ def _linear(seed, rows, cols):
 def test_round_at_the_edges_of_its_tiles(gpu_lib, J, V, B, W, mixed):
     from paper_2206_07882_amd import model as gmodel
     q = gpu_lib
+    m = _model(J, V, mixed)
+    T = 5
+    e = synth.normal(930 + J, (T, B, J), 1.0)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
+    _compare_beams(q.decode(G, dev(e), W, 2, max_len=2 * T), oracle.decode(M, e, W, 2, max_len=2 * T))
+    _compare_beams(q.decode_alsd(G, dev(e), W, 4), oracle.decode_alsd(M, e, W, 4))
+
+
+def _model(J, V, mixed):
     m = synth.make_model(0, weight_std=0.5)
     if mixed:
         m.mixed_precision = True
@@ -33,8 +45,27 @@ def test_round_at_the_edges_of_its_tiles(gpu_lib, J, V, B, W, mixed):
         net.embed = synth.normal(910 + i, (V, net.embed.shape[1]), 0.5)
         if net is not m.pred:
             net.out = _linear(920 + 2 * i, V, net.layers[-1].w_hh.shape[1])
-    T = 5
-    e = synth.normal(930 + J, (T, B, J), 1.0)
-    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
-    _compare_beams(q.decode(G, dev(e), W, 2, max_len=2 * T), oracle.decode(M, e, W, 2, max_len=2 * T))
-    _compare_beams(q.decode_alsd(G, dev(e), W, 4), oracle.decode_alsd(M, e, W, 4))
+    return m
+
+
+@pytest.mark.parametrize("J,V,B,W,mixed", [(256, 46, 1, 16, False), (80, 17, 9, 5, False), (272, 48, 2, 16, True), (64, 33, 3, 1, False)])
+def test_a_workgroup_left_alone_returns_the_same_beams(gpu_lib, J, V, B, W, mixed):
+    """The workgroups of a beam exchange whole numbers and the very values one of them would form: the bits are the same
+    whether the others come or not.  A launch of more than about 100 utterances has one workgroup for each: the same beams
+    (other step kernels run there, so the scores may differ in the last bits)."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    G = gmodel.model_from_float(_model(J, V, mixed), "cuda:0")
+    T, many = 6, 264 // B * B
+    e = dev(synth.normal(930 + J, (T, B, J), 1.0))
+    for alsd, limit, fn, size in ((0, 2, q.decode, q.decode_workspace), (1, 4, q.decode_alsd, q.decode_alsd_workspace)):
+        want = fn(G, e, W, limit, max_len=2 * T)
+        ws = torch.empty(size(G, T, B, W, limit), dtype=torch.uint8, device="cuda:0")
+        got = tuple(torch.empty_like(t) for t in want)
+        q._check(q.load().qrnnt_diag_decode(C.byref(G.c()), C.c_void_p(e.data_ptr()), T, B, W, alsd, limit, 2 * T,
+                                            *(C.c_void_p(t.data_ptr()) for t in got), C.c_void_p(ws.data_ptr()),
+                                            C.c_size_t(ws.numel()), q._stream()), "qrnnt_diag_decode")
+        batch = fn(G, e.repeat(1, many // B, 1).contiguous(), W, limit, max_len=2 * T)
+        for w, g in zip(want, got):
+            assert torch.equal(w, g)
+        _compare_beams(batch, [np.tile(w.cpu().numpy(), (many // B,) + (1,) * (w.dim() - 1)) for w in want])
