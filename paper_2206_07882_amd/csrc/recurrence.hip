@@ -172,6 +172,13 @@ __device__ __forceinline__ unsigned or_xor(unsigned a, unsigned b, unsigned c)
     return r;
 }
 
+// A pointer that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ char *scalar(char *p)
+{
+    const u64 v = (u64)(size_t)p;
+    return (char *)(size_t)(((u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+}
+
 // Workgroup barrier that orders LDS accesses only: no wait for the memory operations in flight.
 __device__ __forceinline__ void lds_barrier()
 {
@@ -338,8 +345,10 @@ __device__ __forceinline__ void shared_steps(const QrRecArgs &a, int ug, int mem
 // CELLS: cells per lane in the cell update: 2, or 1 if there are at most 8 utterances: the lanes of the absent upper
 // eight then take the second cell of the lower eight.
 // C_FIRST: which product of c' = f*c + i*g is rounded before the sum (see launch_rec_w).
+// NG: groups of 16 utterances that a workgroup has under way, 1, or 2 in turn (the second one need not exist): while the codes
+// of one are on their way the other one's step is done, with the same weights in registers.
 // Returns without a step done when the group's members have not all come (adm.mode).
-template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST, int NG>
 __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem, int members, char *xb0, char *xb1, size_t ug_bytes,
                                              v4i (&px)[2][2][2][4][64], v4i (&xs)[KX > 0 ? 3 * 2 * KX : 1][64], int (&s_fail)[2],
                                              RecAdmission &adm)
@@ -353,7 +362,9 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
     constexpr bool PARK = KH >= 8 && (W8 || CELLS == 2);
     __shared__ v4f pk[PARK ? CELLS : 1][3][PARK ? 256 : 1];
     __shared__ v4i pk_rsum[PARK && !W8 ? 4 : 1][PARK && !W8 ? 256 : 1];
+    static_assert(NG == 1 || (KX > 0 && CELLS == 2 && !PARK), "the forms that two groups in turn are made for");
     const int H = a.H, B = a.B, T = a.T;
+    const int ng = NG == 1 || (ug + 1) * 16 >= B ? 1 : 2;   // groups there are: turn q is step q / ng of group q % ng
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave8 & 3;                 // 0..3 of either kind
@@ -388,15 +399,17 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
                 for (int i = 0; i < 4; ++i) Ax[i][k] = (have && ks < 2 * a.nkc_x) ? weight(a.wih, a.nkc_x, cg * 4 + i, ks) : zero;
             }
             const unsigned lds0 = (unsigned)(size_t)&xs[0][0];
-            const int8_t *src[LOADS];
+            const int8_t *src[LOADS], *src2[NG > 1 ? LOADS : 1];   // of the group whose frame is fetched next, of the other one
 #pragma unroll
             for (int q = 0; q < LOADS; ++q) {
                 int blk = wave + 4 * q;                  // (chunk, utterance half); the last few repeat the last block
                 blk = blk < 2 * CH ? blk : 2 * CH - 1;
                 int nr = ug * 16 + (blk & 1) * 8 + (lane >> 3);
-                nr = nr < B ? nr : B - 1;
                 const int o = (blk >> 1) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
-                src[q] = a.x + (t0 * B + nr) * a.ld_x + (o < a.ld_x ? o : 0);   // beyond the row: any valid bytes, they meet zero weights
+                const int8_t *const x = a.x + t0 * B * a.ld_x + (o < a.ld_x ? o : 0);   // beyond the row: any valid bytes, they meet zero weights
+                src[q] = x + (int64_t)(nr < B ? nr : B - 1) * a.ld_x;
+                nr += 16;
+                if (NG > 1) src2[NG > 1 ? q : 0] = x + (int64_t)(nr < B ? nr : B - 1) * a.ld_x;
             }
             const int64_t x_step = dir * B * a.ld_x;
             auto fetch = [&](int buf, bool advance) {
@@ -406,32 +419,39 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
                     blk = blk < 2 * CH ? blk : 2 * CH - 1;
                     qr_load_lds16(src[q], lds0 + (unsigned)(buf * 2 * CH + blk) * 1024);
                     src[q] += advance ? x_step : 0;
+                    if (NG > 1 && ng > 1) {   // uniform
+                        const int8_t *const other = src2[NG > 1 ? q : 0];
+                        src2[NG > 1 ? q : 0] = src[q];
+                        src[q] = other;
+                    }
                 }
             };
             const int at = (col >> 3) * 64 + (col & 7) * 8;   // this lane's row within a chunk's two blocks, in 16-byte pieces
             auto produce = [&](int buf, int par) {
-                v4i acc[4] = {zero, zero, zero, zero};
+                v4i acc[4] = {zero, zero, zero, zero}, b[KX > 0 ? KX : 1];
 #pragma unroll
-                for (int k = 0; k < KX; ++k) {
-                    const v4i b = xs[buf * 2 * CH + 2 * k][at + ((4 * kh + grp) ^ (col & 7))];
+                for (int k = 0; k < KX; ++k) b[k] = xs[buf * 2 * CH + 2 * k][at + ((4 * kh + grp) ^ (col & 7))];
+                __builtin_amdgcn_sched_barrier(0);   // all of them first: two at a time a turn of two groups waited for LDS five times
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] = qr_mfma(Ax[i][k], b, acc[i]);
-                }
+                for (int k = 0; k < KX; ++k)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = qr_mfma(Ax[i][k], b[k], acc[i]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) px[par][kh][rh][i][lane] = acc[i];
             };
-            fetch(0, T > 1);
-            fetch(1, T > 2);
-            fetch(2, T > 3);
+            const int turns = T * ng, left = turns - ng;   // (a frame behind a group's last one: the last one again)
+            fetch(0, 0 < left);
+            fetch(1, 1 < left);
+            fetch(2, 2 < left);
             qr_wait_vmcnt<0>();
             lds_barrier();
             produce(0, 0);
             lds_barrier();
             if (adm.mode >= REC_SHARED) return;          // uniform
             int b1 = 1, b3 = 0;                          // buffers of frames s + 1 and s + 3
-            for (int s = 0; s < T; ++s) {
-                fetch(b3, s + 4 < T);                    // (frames behind the last one: the last one again)
-                if (s + 1 < T) produce(b1, (s + 1) & 1);
+            for (int s = 0; s < turns; ++s) {
+                fetch(b3, s + 3 < left);
+                if (s + 1 < turns) produce(b1, (s + 1) & 1);
                 qr_wait_vmcnt<LOADS>();                  // all but the newest fetch: frame s + 2 is there
                 lds_barrier();
                 if (__builtin_amdgcn_readfirstlane(s_fail[s & 1])) break;
@@ -501,14 +521,18 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
     }
     // ---- the cells this lane finishes: j0 .. j0 + CELLS - 1 of utterance n
     const int my_col = CELLS == 1 ? col & 7 : col;
-    const int n = ug * 16 + my_col;
-    const int nn = n < B ? n : B - 1;
+    int n[NG], nn[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        n[g] = (ug + g) * 16 + my_col;
+        nn[g] = n[g] < B ? n[g] : B - 1;
+    }
     const int sub = CELLS == 1 ? col >> 3 : 0;
     const int j0 = 16 * cgc + 4 * grp + 2 * kh + sub;
     // exact powers of two undo what the 4-bit operands carry: 16 (x as it is) and 256
     constexpr float X_UNIT = (W8 || KX == 0) ? 1.0f : 0.0625f, H_UNIT = W8 ? 1.0f : 0.00390625f;
     v4f sx[CELLS], sh[CELLS], bb[CELLS];
-    float c[CELLS];
+    float c[NG][CELLS];
 #pragma unroll
     for (int ct = 0; ct < CELLS; ++ct) {
 #pragma unroll
@@ -522,7 +546,8 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
             pk[ct][1][pt] = sh[ct];
             pk[ct][2][pt] = bb[ct];
         }
-        c[ct] = a.c0 ? a.c0[(int64_t)nn * H + j0 + ct] : 0.0f;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) c[g][ct] = a.c0 ? a.c0[(int64_t)nn[g] * H + j0 + ct] : 0.0f;
     }
     // ---- exchange addresses
     int ncol = 16;                              // columns kept per 16-cell group
@@ -537,16 +562,26 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
     }
     const unsigned st_off = (unsigned)(((cgc * ncol + (my_col & (ncol - 1))) * 16 + 4 * grp + 2 * kh + sub) * PER);
     const unsigned long long pub_mask = __ballot(have && my_col < ncol);
-    const bool store_ok = have && n < B;
-    const unsigned long long out_mask = __ballot(store_ok);
+    bool store_ok[NG];
+    unsigned long long out_mask[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        store_ok[g] = have && n[g] < B;
+        out_mask[g] = __ballot(store_ok[g]);
+    }
     // where this lane's sums of the input part lie in px[parity][K half]
     const int px_at = (rh * 4 + 2 * kh + sub) * 64 + grp * 16 + my_col;
 
     // ---- running pointers: output row of the step before, debug output
-    int8_t *hq = a.h_out + (t0 * B + nn) * a.ld_out + a.col_off + j0;
     const int64_t h_step = dir * B * a.ld_out;
     const bool dbg = a.dbg_c_all != nullptr;
-    float *dq = dbg ? a.dbg_c_all + (t0 * B + nn) * H + j0 : nullptr;
+    int8_t *hq[NG];
+    float *dq[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        hq[g] = a.h_out + (t0 * B + nn[g]) * a.ld_out + a.col_off + j0;
+        dq[g] = dbg ? a.dbg_c_all + (t0 * B + nn[g]) * H + j0 : nullptr;
+    }
 
     if (wave == 0) {                            // (the weights were on their way meanwhile)
         RecAdmission r = {REC_LOCAL, 0, 0};
@@ -558,7 +593,7 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
     if (adm.mode >= REC_SHARED) return;         // uniform
     __builtin_amdgcn_s_setprio(3);              // these waves are the chain, the input waves fill its gaps
     const bool local = adm.mode == REC_LOCAL && !a.spread;   // uniform over the group
-    unsigned codes = 0;                         // the codes of the step before, one per byte
+    unsigned codes[NG] = {};                    // the codes of the step before, one per byte
     v4i acc[4];
     float gx[CELLS][4];                         // this step's sums of the input part
     // What a step can do while its operands are on their way: its sums of the input part, and the start of its
@@ -566,8 +601,8 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
     // this in front of the loads or behind the wait for them.)  Where registers are short the sums wait for the end of
     // the contraction.
     constexpr bool LATE_X = PARK && W8;
-    auto load_x = [&](int s, v4i (&x0)[CELLS], v4i (&x1)[CELLS]) {
-        const v4i *p0 = &px[__builtin_amdgcn_readfirstlane(s & 1)][0][0][0][0] + px_at, *p1 = p0 + 2 * 4 * 64;
+    auto load_x = [&](int turn, v4i (&x0)[CELLS], v4i (&x1)[CELLS]) {
+        const v4i *p0 = &px[__builtin_amdgcn_readfirstlane(turn & 1)][0][0][0][0] + px_at, *p1 = p0 + 2 * 4 * 64;
 #pragma unroll
         for (int ct = 0; ct < CELLS; ++ct) {
             x0[ct] = p0[64 * ct];
@@ -582,11 +617,11 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
             asm volatile("" : "+v"(gx[ct][0]), "+v"(gx[ct][1]), "+v"(gx[ct][2]), "+v"(gx[ct][3]));
         }
     };
-    auto prepare = [&](int s) {
+    auto prepare = [&](int s, int turn) {
         int tag = s & 15;
         if (!W8) asm volatile("" : "+s"(tag));
         v4i x0[CELLS], x1[CELLS];
-        if (!LATE_X) load_x(s, x0, x1);
+        if (!LATE_X) load_x(turn, x0, x1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (PARK && !W8) nrsum[i] = pk_rsum[i][pt];
@@ -605,8 +640,10 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
         }
     };
     // The rest of the step; true: a wait ran out somewhere in the workgroup, leave.
-    auto step = [&](const v4i (&bf)[KH], int s) -> bool {
-        const int par = __builtin_amdgcn_readfirstlane(s & 1);
+    // ask(): more loads, once the sums have changed hands.
+    auto step = [&](auto g_tag, const v4i (&bf)[KH], int s, int turn, auto &&ask) __attribute__((always_inline)) -> bool {
+        constexpr int G = decltype(g_tag)::value;
+        const int par = __builtin_amdgcn_readfirstlane(turn & 1);
         constexpr int K0 = KH < 2 ? KH : 2;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -629,11 +666,11 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
         __builtin_amdgcn_sched_barrier(0);
         if (LATE_X) {                               // (in front of the barrier behind which they are overwritten)
             v4i x0[CELLS], x1[CELLS];
-            load_x(s, x0, x1);
+            load_x(turn, x0, x1);
             add_x(x0, x1);
         }
-        store_out<CELLS>(hq, codes, s > 0 ? out_mask : 0ull);   // the codes of the step before: here they hold nothing up
-        hq += s > 0 ? h_step : 0;
+        store_out<CELLS>(hq[G], codes[G], s > 0 ? out_mask[G] : 0ull);   // the codes of the step before: here they hold nothing up
+        hq[G] += s > 0 ? h_step : 0;
         lds_barrier();
         int fail_now = s_fail[par];   // a slot is written before its step's barrier only, and again two steps later: uniform
         v4i asum[CELLS];
@@ -641,7 +678,8 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
         for (int ct = 0; ct < CELLS; ++ct)
             asum[ct] = (CELLS == 1 ? upper_from(acc[0], acc[1]) : acc[ct]) + part[par][wave ^ 1][ct][lane];
         asm volatile("" : "+v"(fail_now), "+v"(asum[0]));       // (both reads now, not one of them in front of the next poll)
-        codes = 0u;
+        ask();
+        codes[G] = 0u;
         unsigned word = W8 ? (unsigned)((s + 1) & 0xFF) * 0x01000100u : (unsigned)((s + 1) & 15) * 0x0101u;
 #pragma unroll
         for (int ct = 0; ct < CELLS; ++ct) {
@@ -650,33 +688,39 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
                 sh[ct] = pk[ct][1][pt];
                 bb[ct] = pk[ct][2][pt];
             }
-            const unsigned code = (unsigned)rec_cell<W8, C_FIRST>(sx[ct], sh[ct], bb[ct], gx[ct], asum[ct], a.h_inv, c[ct]);
-            codes |= (code & 0xFFu) << (8 * ct);
+            const unsigned code = (unsigned)rec_cell<W8, C_FIRST>(sx[ct], sh[ct], bb[ct], gx[ct], asum[ct], a.h_inv, c[G][ct]);
+            codes[G] |= (code & 0xFFu) << (8 * ct);
             word |= W8 ? (code & 0xFFu) << (16 * ct) : ((code & 15u) << 4) << (8 * ct);
         }
-        store_codes<CELLS * PER>(par ? xb1 : xb0, st_off, word, pub_mask, local);
+        if constexpr (NG == 1) store_codes<CELLS * PER>(par ? xb1 : xb0, st_off, word, pub_mask, local);
+        else store_codes<CELLS * PER>(scalar((s & 1 ? xb1 : xb0) + G * ug_bytes), st_off, word, pub_mask, local);
         if (dbg) {
-            if (store_ok)
+            if (store_ok[G])
 #pragma unroll
-                for (int ct = 0; ct < CELLS; ++ct) dq[ct] = c[ct];
-            dq += dir * B * H;
+                for (int ct = 0; ct < CELLS; ++ct) dq[G][ct] = c[G][ct];
+            dq[G] += dir * B * H;
         }
         return __builtin_amdgcn_readfirstlane(fail_now) != 0;
     };
     // All steps but the first: the operands come from the exchange area.
-    auto later_steps = [&](auto local_tag) {
+    auto later_steps = [&](auto local_tag) __attribute__((always_inline)) {
         constexpr bool LOCAL = decltype(local_tag)::value;
-        for (int s = 1; s < T; ++s) {
+        // Group G's words for step s.  Two groups in turn: they are requested in the turn before, late enough for them to be there.
+        v4i v[NL];
+        auto request = [&](auto g_tag, int s) __attribute__((always_inline)) {
+            load_words<KH, PER, LOCAL>((__builtin_amdgcn_readfirstlane(s & 1) ? xb0 : xb1) + decltype(g_tag)::value * ug_bytes, (unsigned)ug_bytes, off, v);
+        };
+        const bool early = NG > 1 && ng > 1;   // uniform
+        auto turn_of = [&](auto g_tag, int s, int turn) __attribute__((always_inline)) -> bool {
+            constexpr int G = decltype(g_tag)::value;
             // words written at step s-1 carry tag s
             const int par = __builtin_amdgcn_readfirstlane(s & 1);
-            const char *src = par ? xb0 : xb1;
             const unsigned want = W8 ? (unsigned)(s & 0xFF) * 0x01000100u : (unsigned)(s & 15) * 0x01010101u;
             v4i bf[KH];
             asm volatile(".p2align 6");   // the poll on a cache line of its own: where it lay otherwise cost up to 3 % of a step
             for (int spins = 0;; ++spins) {
-                v4i v[NL];
-                load_words<KH, PER, LOCAL>(src, (unsigned)ug_bytes, off, v);
-                prepare(s);
+                if (!early || spins > 0) request(g_tag, s);
+                prepare(s, turn);
                 __builtin_amdgcn_sched_barrier(0);
                 unsigned bad0 = 0u, bad1 = 0u;
 #pragma unroll
@@ -703,41 +747,55 @@ __device__ __forceinline__ void member_steps(const QrRecArgs &a, int ug, int mem
                 if (spins >= a.spin_limit) {
                     if (lane == 0) {
                         atomicExch(a.err, 1);
-                        s_fail[par] = 1;
+                        s_fail[NG == 1 ? par : turn & 1] = 1;
                     }
                     break;
                 }
             }
-            if (step(bf, s)) break;
+            return step(g_tag, bf, s, turn, [&]() __attribute__((always_inline)) {
+                if (NG > 1 && early) request(std::integral_constant<int, 1 - G>{}, s + G);   // uniform
+            });
+        };
+        if (early) request(std::integral_constant<int, 0>{}, 1);
+        for (int s = 1; s < T; ++s) {
+            if (turn_of(std::integral_constant<int, 0>{}, s, s * ng)) break;
+            if constexpr (NG > 1)
+                if (ng > 1 && turn_of(std::integral_constant<int, 1>{}, s, s * ng + 1)) break;   // uniform
         }
     };
-    {
-        v4i bf[KH];   // first step: the caller's initial state
-        const int n0 = ug * 16 + col < B ? ug * 16 + col : B - 1;
+    // first step: the caller's initial state
+    auto first = [&](auto g_tag) __attribute__((always_inline)) -> bool {
+        v4i bf[KH];
+        const int nc = (ug + decltype(g_tag)::value) * 16 + col, n0 = nc < B ? nc : B - 1;
 #pragma unroll
         for (int k = 0; k < KH; ++k) {
             const int k0 = (kh + 2 * k) * 64 + grp * 16;
             bf[k] = (a.h0 && k0 < H) ? *(const v4i *)(a.h0 + (int64_t)n0 * H + k0) : zero;
             if (!W8) bf[k] = (bf[k] << 4) & m;
         }
-        prepare(0);
+        prepare(0, decltype(g_tag)::value);
         partner_tiles(bf);
-        if (!step(bf, 0)) {
-            if (local) later_steps(std::true_type{}); else later_steps(std::false_type{});
-        }
+        return step(g_tag, bf, 0, decltype(g_tag)::value, [] {});
+    };
+    bool failed = first(std::integral_constant<int, 0>{});
+    if constexpr (NG > 1)
+        if (!failed && ng > 1) failed = first(std::integral_constant<int, 1>{});   // uniform
+    if (!failed) {
+        if (local) later_steps(std::true_type{}); else later_steps(std::false_type{});
     }
-    if (store_ok) {
 #pragma unroll
-        for (int ct = 0; ct < CELLS; ++ct) {
-            const int8_t code = (int8_t)(codes >> (8 * ct));
-            hq[ct] = code;
-            if (a.h_last) a.h_last[(int64_t)n * H + j0 + ct] = code;
-            if (a.c_last) a.c_last[(int64_t)n * H + j0 + ct] = c[ct];
-        }
-    }
+    for (int g = 0; g < NG; ++g)
+        if (store_ok[g])
+#pragma unroll
+            for (int ct = 0; ct < CELLS; ++ct) {
+                const int8_t code = (int8_t)(codes[g] >> (8 * ct));
+                hq[g][ct] = code;
+                if (a.h_last) a.h_last[(int64_t)n[g] * H + j0 + ct] = code;
+                if (a.c_last) a.c_last[(int64_t)n[g] * H + j0 + ct] = c[g][ct];
+            }
 }
 
-template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST, int NG>
 __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
 {
     __shared__ v4i px[2][2][2][4][64];      // [parity][K half][cell group][row tile][lane] sums of the input part
@@ -747,21 +805,23 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
     // Grid: x = XCD (workgroups go out with x fastest, each to the next XCD), y = member, z = XCD's next group
     const int gi = g.group0 + (int)(blockIdx.z * gridDim.x + blockIdx.x), mem = (int)blockIdx.y, members = (int)gridDim.y;
     if (gi >= g.group_end) return;   // uniform
-    const int ug = gi >> (g.n - 1);  // one or two directions
+    const int ug = (gi >> (g.n - 1)) * NG;  // one or two directions
     const size_t ug_bytes = (size_t)(g.d[0].H >> 4) * 256 * (W8 ? 2 : 1);
     {
         const QrRecArgs a = g.d[gi & (g.n - 1)];   // a copy: a few wide scalar loads
         char *const xb = a.xbuf + (size_t)ug * ug_bytes;   // this group's exchange area, even steps
-        member_steps<KH, KX, W8, CELLS, C_FIRST>(a, ug, mem, members, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes, ug_bytes, px, xs,
+        member_steps<KH, KX, W8, CELLS, C_FIRST, NG>(a, ug, mem, members, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes, ug_bytes, px, xs,
                                                  s_fail, adm);
     }
     if (adm.mode == REC_SHARED) {   // uniform
         int d = gi & (g.n - 1);
         asm volatile("" : "+s"(d));   // a copy of its own: the one above need not outlive the loop
         const QrRecArgs a = g.d[d];
-        char *const xb = a.xbuf + (size_t)ug * ug_bytes;
-        shared_steps<KH, KX, W8, C_FIRST>(a, ug, members, adm.rank, adm.n, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes,
-                                          &px[0][0][0][0][0], &xs[0][0], s_fail);
+        for (int i = 0; i < NG && (ug + i) * 16 < a.B; ++i) {   // uniform
+            char *const xb = a.xbuf + (size_t)(ug + i) * ug_bytes;
+            shared_steps<KH, KX, W8, C_FIRST>(a, ug + i, members, adm.rank, adm.n, xb, xb + (size_t)((a.B + 15) >> 4) * ug_bytes,
+                                              &px[0][0][0][0][0], &xs[0][0], s_fail);
+        }
     }
 }
 
@@ -769,7 +829,7 @@ __global__ __launch_bounds__(512, 2) void lstm_rec_kernel(const QrRecGroup g)
 struct RecRoom {
     int n_xcd, per_xcd;
 };
-template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST, int NG>
 RecRoom room()
 {
     static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none, else per_xcd * 64 + n_xcd
@@ -779,7 +839,7 @@ RecRoom room()
         int n_cu = 0, n_xcd = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipDeviceGetAttribute(&n_xcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST>, 512, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST, NG>, 512, 0) != hipSuccess)
             return {0, 0};
         n_xcd = n_xcd < 1 || n_xcd > 32 ? 8 : n_xcd;
         v = n_cu / n_xcd * per_cu * 64 + n_xcd;
@@ -789,22 +849,38 @@ RecRoom room()
     return v > 0 ? RecRoom{v & 63, v >> 6} : RecRoom{0, 0};
 }
 
-template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
-bool launch_rec_t(const QrRecGroup &g, hipStream_t st)
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST, int NG>
+bool launch_rec_n(const QrRecGroup &g, hipStream_t st)
 {
     QrRecGroup gg = g;
     const int members = (g.d[0].H + 31) / 32;
-    const RecRoom r = room<KH, KX, W8, CELLS, C_FIRST>();
+    const RecRoom r = room<KH, KX, W8, CELLS, C_FIRST, NG>();
     const int q = r.per_xcd / members;   // groups that an XCD holds together; beyond H = 512 it is one
     if (q < 1) return false;
-    const int n_groups = g.n * ((g.d[0].B + 15) / 16), most = q * r.n_xcd;
+    const int n_groups = g.n * (((g.d[0].B + 15) / 16 + NG - 1) / NG), most = q * r.n_xcd;
+    // Two groups in turn take 1.6 to 1.75 times as long as one (2 x 640 cells, us a step, 64 -> 77 utterances: 320 inputs 0.95 ->
+    // 1.49, 1280 inputs 0.99 -> 1.72, two launches 1.90 and 1.99), so they pay where they save a third of the launches.
+    // (More than 640 cells leave no registers for a second state.)
+    if constexpr (NG == 1 && KH == 5 && KX > 0 && CELLS == 2) {
+        const int n_pairs = g.n * (((g.d[0].B + 15) / 16 + 1) / 2);
+        if (4 * ((n_groups + most - 1) / most) > 7 * ((n_pairs + most - 1) / most) && launch_rec_n<KH, KX, W8, CELLS, C_FIRST, 2>(g, st))
+            return true;
+    }
+    if (NG > 1)
+        for (int d = 0; d < g.n; ++d) gg.d[d].admit_ticks = gg.d[d].admit_ticks < (1 << 29) ? 2 * gg.d[d].admit_ticks : 1 << 30;
     for (int g0 = 0; g0 < n_groups; g0 += most) {
         gg.group0 = g0;
         gg.group_end = n_groups - g0 < most ? n_groups : g0 + most;
         const int turns = (gg.group_end - g0 + r.n_xcd - 1) / r.n_xcd;
-        lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST><<<dim3(r.n_xcd, members, turns), 512, 0, st>>>(gg);
+        lstm_rec_kernel<KH, KX, W8, CELLS, C_FIRST, NG><<<dim3(r.n_xcd, members, turns), 512, 0, st>>>(gg);
     }
     return true;
+}
+
+template <int KH, int KX, bool W8, int CELLS, bool C_FIRST>
+bool launch_rec_t(const QrRecGroup &g, hipStream_t st)
+{
+    return launch_rec_n<KH, KX, W8, CELLS, C_FIRST, 1>(g, st);
 }
 
 template <int KH, int KX>

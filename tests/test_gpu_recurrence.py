@@ -64,10 +64,12 @@ def test_recurrence_edges(gpu_lib, T, B, I, H, bits, reverse, state):
     assert torch.equal(again["h_out"], out["h_out"]) and torch.equal(again["c_last"], out["c_last"])
 
 
-@pytest.mark.parametrize("T,B,bits", [(18, 130, (4, 4)), (6, 3, (8, 4)), (5, 60, (8, 8))])
+@pytest.mark.parametrize("T,B,bits", [(18, 130, (4, 4)), (6, 3, (8, 4)), (5, 60, (8, 8)), (17, 65, (4, 4)), (1, 77, (4, 4)),
+                                      (6, 100, (8, 8)), (3, 200, (4, 4))])
 def test_two_directions(gpu_lib, T, B, bits):
     """130 utterances: 18 groups of 16 utterances and direction, more than one launch's worth; a backward direction of
-    another width than the forward one; 60 x 640 cells x 2 directions: the size class whose cell rounds f*c first."""
+    another width than the forward one; 60 x 640 cells x 2 directions: the size class whose cell rounds f*c first.  65 to
+    200 utterances: workgroups with two groups in turn, the last of them with one."""
     q = gpu_lib
     I, H = 340, 640
     s_x = 0.03
@@ -134,11 +136,12 @@ def test_which_product_of_the_cell_is_rounded_first(gpu_lib, H, B, bits, f_first
 
 
 @pytest.mark.parametrize("T,B,I,H,bits,state", [(20, 1, 64, 64, 4, True), (40, 3, 1280, 640, 4, False), (9, 17, 1300, 640, 4, True),
-                                                (6, 120, 340, 640, 4, True), (5, 8, 385, 656, 4, False), (280, 5, 40, 80, 8, True),
-                                                (6, 20, 1281, 48, 8, False), (7, 13, 340, 1024, 8, True), (4, 100, 64, 704, 8, False)])
+                                                (6, 120, 340, 640, 4, True), (5, 8, 385, 656, 4, False), (280, 5, 40, 80, 8, True), (19, 150, 1280, 640, 4, True),
+                                                (3, 400, 384, 272, 8, False), (6, 20, 1281, 48, 8, False), (7, 13, 340, 1024, 8, True), (4, 100, 64, 704, 8, False)])
 def test_routes_of_the_recurrence_agree(gpu_lib, T, B, I, H, bits, state):
     """A group whose workgroups run on several XCDs, and one whose workgroups are not resident together (whoever has come
-    shares the work), return the very bits of the usual route; 120 and 100 utterances: layers that round f*c first."""
+    shares the work), return the very bits of the usual route; 120 and 100 utterances: layers that round f*c first; 150 and
+    400: two groups to a workgroup."""
     q = gpu_lib
     q_max = 127 if bits == 8 else 7
     L, G = (_lstm8_pair if bits == 8 else _lstm_pair)(q, 5471 + I + H, I, H, 0.5 / q_max)
@@ -159,7 +162,7 @@ def test_routes_of_the_recurrence_agree(gpu_lib, T, B, I, H, bits, state):
             assert torch.equal(v, want[k]), f"route {route:#x}: {k}"
 
 
-@pytest.mark.parametrize("B,n_streams,layers", [(1, 4, 6), (40, 3, 4)])
+@pytest.mark.parametrize("B,n_streams,layers", [(1, 4, 6), (40, 3, 4), (77, 3, 2)])
 def test_recurrences_on_several_streams(gpu_lib, B, n_streams, layers):
     """Encoders on streams of their own, with workspaces of their own: each launch wants more than half of an XCD, so
     their workgroups meet on the same compute units and groups are cut short of members."""
