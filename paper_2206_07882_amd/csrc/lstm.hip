@@ -725,10 +725,15 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
             }
             codes = on ? codes : (unsigned)hp_code[q][nt];
             if (FAST ? (!rows || n_ok[nt]) : (jv && n_ok[nt])) {
-                // both or neither: one kind of modified line left in the L2 costs the write-back at the end (64 x 1000
-                // frames at beam 16: 189.4 ms with plain stores, 189.6 with c alone, 186.3 with both)
-                qr_store_through(a.c_next + (int64_t)n * H + jb[q], cn);
-                qr_store_through(a.h_next + (int64_t)n * a.ld_hn + jb[q], codes);
+                float *const c_to = a.c_next + (int64_t)n * H + jb[q];
+                int8_t *const h_to = a.h_next + (int64_t)n * a.ld_hn + jb[q];
+                if (g.through) {   // uniform; both or neither: one kind of modified line left in the L2 costs the write-back
+                    qr_store_through(c_to, cn);
+                    qr_store_through(h_to, codes);
+                } else {
+                    *(v4f *)c_to = cn;
+                    *(unsigned *)h_to = codes;
+                }
                 if (a.h_copy) *(unsigned *)(a.h_copy + (int64_t)n * H + jb[q]) = codes;
             }
         }
@@ -770,6 +775,10 @@ void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
     for (int w = 1; w <= 2; ++w)
         if (gg.row_blocks * ((max_n + (P::BN >> w) - 1) / (P::BN >> w)) <= gg.n_resident) width = w;
     gg.width = g.rows ? 0 : width;
+    // States go through the L2 as they are made while a round and a half of workgroups covers the launch; beyond, the L2
+    // writes back under the work of later workgroups anyway, and through costs more (64 utterances at beam 16, all rounds
+    // 186.3 against 189.4 ms; 128: 59.4 against 58.1 us a round, of the wider networks 109.7 against 106.8).
+    gg.through = 2 * gg.row_blocks * ((max_n + P::BN - 1) / P::BN) <= 3 * gg.n_resident;
     const int per = P::BN >> width;
     const int gz = (max_n + per - 1) / per;
     for (int z0 = 0; z0 < gz; z0 += 65535) {   // a grid's z extent ends at 65535
