@@ -13,6 +13,7 @@ namespace {
 struct NetBuf {
     int8_t *h[QRNNT_MAX_LAYERS];   // [pool + 1][H]; the last row stays zero: the state before the first symbol
     float *c[QRNNT_MAX_LAYERS];    // [pool + 1][H]
+    bool mid_in_round;             // the round contracts the bottleneck itself
     int32_t *gx0;                  // [V][4*H0]: input projection of layer 0 for every token
     float *tab0;                   // the same as fp32 pre-activation contributions (scales, bias folded in)
     int8_t *mid_q;                 // [pool][M]: codes of the bottleneck's output
@@ -29,7 +30,7 @@ struct Plan {
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
     v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the hypotheses that carry a label into round v of the frame, and how many
-    unsigned long long *words;     // [B][QR_ROUND_PARTS + 1][16][64]: see QrRoundArgs.words (beams of up to 16)
+    unsigned long long *words;     // [B][QR_ROUND_WORDS]: see QrRoundArgs.words (beams of up to 16)
     size_t n_clear;                // 32-bit words from `live` on that start at zero: live, n_rows, words
     size_t total;
 };
@@ -71,8 +72,22 @@ void take_cleared(Plan &p, Carver &cv, size_t n_counters)
     p.live = cv.take<int32_t>(n_counters);
     const size_t start = cv.off - n_counters * sizeof(int32_t);
     p.n_rows = cv.take<int32_t>(n_counters);
-    p.words = p.W <= 16 ? cv.take<unsigned long long>((size_t)p.B * (QR_ROUND_PARTS + 1) * 16 * 64) : nullptr;
+    p.words = p.W <= 16 ? cv.take<unsigned long long>((size_t)p.B * QR_ROUND_WORDS) : nullptr;
     p.n_clear = (cv.off - start) / 4;
+}
+
+// Which bottlenecks the rounds take in: those of the language models, if there is none in front of the joint.
+void place_mids(const qrnnt_model *m, Plan &p, bool alsd)
+{
+    int n = 0, rows = 0;
+    for (int k = 0; k < 3; ++k) {
+        p.net[k].mid_in_round = false;
+        if (!net_used(m, k) || net_of(m, k)->mid.packed == nullptr) continue;
+        ++n;
+        rows = k == 0 || net_of(m, k)->mid.rows > rows ? (k == 0 ? 1 << 30 : net_of(m, k)->mid.rows) : rows;
+    }
+    if (n == 0 || !qr_round_takes(rows, n, p.B, p.W, alsd)) return;
+    for (int k = 1; k < 3; ++k) p.net[k].mid_in_round = net_used(m, k) && net_of(m, k)->mid.packed != nullptr;
 }
 
 void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws, Plan &p)
@@ -245,7 +260,7 @@ void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, cons
     lg.rows = p.rows;
     lg.n_rows = n_rows;
     for (int k = 0; k < 3; ++k) {
-        if (!net_used(m, k) || net_of(m, k)->mid.packed == nullptr) continue;
+        if (!net_used(m, k) || net_of(m, k)->mid.packed == nullptr || p.net[k].mid_in_round) continue;
         const qrnnt_net *net = net_of(m, k);
         QrLinearArgs &la = lg.p[lg.n++];
         la = QrLinearArgs{};
@@ -271,6 +286,12 @@ QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_pro
         h.w8 = qr_bits(&net->out) == 8;  h.log_softmax = net->log_softmax;
         h.act = net->mid.packed ? p.net[k].mid_q : p.net[k].h[net->n_layers - 1];
         h.a_scale = net->mid.packed ? net->mid_scale : net->out_a_scale;
+        if (!p.net[k].mid_in_round) continue;
+        QrMidArgs &d = ja.mid[k - 1];
+        d.w = (const v4i *)net->mid.packed;  d.s_w = net->mid.row_scale;  d.bias = net->mid_bias;
+        d.act = p.net[k].h[net->n_layers - 1];  d.K = net->mid.cols;  d.nkc = qr_round_up(net->mid.cols, QRNNT_KCHUNK) / QRNNT_KCHUNK;
+        d.rows = net->mid.rows;  d.w8 = qr_bits(&net->mid) == 8;  d.q_bits = qr_bits(&net->out);
+        d.a_scale = net->out_a_scale;  d.q_inv = net->mid_inv_scale;
     }
     ja.enc = enc_proj;
     ja.w = (const v4i *)m->joint_out.packed;  ja.s_w = m->joint_out.row_scale;  ja.b_out = m->joint_bias;
@@ -349,6 +370,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     Plan p;
     make_plan(m, T, B, W, max_sym, workspace, p);
     QR_REQUIRE(workspace_bytes >= p.total, QRNNT_ERR_WORKSPACE);
+    place_mids(m, p, false);
     hipStream_t st = (hipStream_t)stream;
     const int N = p.N, V = p.V;
     const size_t Ns = (size_t)N;
@@ -492,6 +514,7 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
     make_alsd_plan(m, T, B, W, u_max, workspace, ap);
     const Plan &p = ap.p;
     QR_REQUIRE(workspace_bytes >= p.total, QRNNT_ERR_WORKSPACE);
+    place_mids(m, ap.p, true);
     hipStream_t st = (hipStream_t)stream;
     const int N = p.N, V = p.V;
     const size_t Ns = (size_t)N;

@@ -188,13 +188,16 @@ __device__ __forceinline__ v4f qr_token_values(v4i t, bool w8, const float *scal
 // ALSD: the same inside the alignment-length synchronous search (route.h, qr_alsd_route): every hypothesis reads its
 // own encoder frame (iteration - labels so far), a blank at the last frame finishes a hypothesis instead of being a
 // candidate, labels beyond the cap are no candidates.
-// CL (up to 16 hypotheses, and all workgroups of the launch resident): an utterance has up to QR_ROUND_PARTS workgroups that
+// CL (up to 16 hypotheses, and five sixths of the device hold all workgroups; nearer to its limit one workgroup each is the
+// faster form, 100 utterances at beam 1 30.7 us a round against 32.1): an utterance has up to QR_ROUND_PARTS workgroups that
 // share the joint, 64 columns at a time (its output layer's sums add up), and one that contracts the language models' output
 // layers and forms their log-probabilities; the first one collects and goes on alone.  One compute unit's path to L2 no
 // longer bounds the round: 36 KB to a workgroup instead of 225.  What they send goes through the L2 of the XCD they run on
 // (ids congruent modulo the number of XCDs; nothing but the time depends on that), value and round number in one 8-byte
-// word, so that every word says by itself whether it is there: no flag, no order of stores.  The others wait for nobody, and
-// the first one not for long: after `ticks` it does everything itself.  The last round of a frame has blanks to offer only,
+// word, so that every word says by itself whether it is there: no flag, no order of stores.  The others wait for nobody (the
+// one with the language models for bottlenecks only), and nobody waits for long: what has not come after `ticks` the first
+// one does itself.  A bottleneck in front of a language model's output layer is contracted in the round too, 64 rows to a
+// workgroup (qr_round_takes).  The last round of a frame has blanks to offer only,
 // and no use for the language models.  Stamps of the first workgroup (one utterance at beam 16, ns after its start, one
 // workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end 9900 -> 7500; a round of three
 // launches 23.3 -> 20.5 us, of 64 utterances (batch of 1000 frames, all rounds) 37.3 -> 36.5.
@@ -211,6 +214,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     __shared__ __attribute__((aligned(16))) float jc[3][2][64];   // row scales and biases: joint, source LM, external LM
     __shared__ __attribute__((aligned(16))) float pc[4][2][64];   // [wave] those of the prediction network's 64 rows at hand
     __shared__ __attribute__((aligned(16))) int8_t z_code[CL ? 16 : 1][80];   // a block's codes (the pitch spreads the rows over the banks)
+    __shared__ __attribute__((aligned(16))) int8_t mid_code[CL ? 2 : 1][CL ? 16 : 1][272];   // codes of the language models' bottlenecks
     __shared__ v4f lm_val[CL ? 2 : 1][CL ? 256 : 1];   // the language models' values for each thread of the scores
     __shared__ unsigned mask[64];
     __shared__ int n_cand, n_list, missed;
@@ -348,8 +352,59 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         }
         return sum;
     };
-    // Words on their way to the first workgroup: source q of a.parts + 1, hypothesis, token.
-    auto word_at = [&](int q, int hyp, int token) { return a.words + (((size_t)b * (QR_ROUND_PARTS + 1) + q) * 16 + hyp) * 64 + token; };
+    // CL: 64 rows of the bottleneck of language model 1 + net, as in joint_part: this thread's two codes.
+    auto mid_part = [&](int net, int part, int row) -> unsigned {
+        const QrMidArgs &h = a.mid[net];
+        const int n_tiles = h.rows >> 4, j = part * 64 + z_col < h.rows ? part * 64 + z_col : 0;
+        unsigned woff[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const int rt = 4 * part + mt < n_tiles ? 4 * part + mt : n_tiles - 1;
+            woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
+        }
+        v4i acc[4] = {zero, zero, zero, zero};
+        if (h.w8) qr_chunk_mma<true, 1>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
+        else qr_chunk_mma<false, 2>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
+        const float sw0 = h.a_scale * h.s_w[j], sw1 = h.a_scale * h.s_w[j + 1];
+        const float bs0 = h.bias ? h.bias[j] : 0.0f, bs1 = h.bias ? h.bias[j + 1] : 0.0f;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][lane] = acc[mt];
+        __syncthreads();
+        int s0 = 0, s1 = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const int *const q = (const int *)&sums[w][tid >> 7][z_lane] + 2 * (tid & 1);
+            s0 += q[0];
+            s1 += q[1];
+        }
+        s0 = h.w8 ? s0 : (s0 >> 4);
+        s1 = h.w8 ? s1 : (s1 >> 4);
+        const int c0 = qr_quant(sw0 * (float)s0 + bs0, h.q_inv, h.q_bits), c1 = qr_quant(sw1 * (float)s1 + bs1, h.q_inv, h.q_bits);
+        return (unsigned)(c0 & 0xFF) | (unsigned)(c1 & 0xFF) << 8;
+    };
+    // CL: output layer of language model 1 + net by this wave, chunks c0, c0 + step, ...; its operand may lie in mid_code.
+    auto lm_mma = [&](int net, int row, int c0, int step, v4i (&acc)[4]) {
+        const QrHeadArgs &h = a.head[1 + net];
+        if (!h.w) return;   // uniform
+        if (!a.mid[net].w) {
+            head_mma(std::integral_constant<int, 2>{}, h, row, c0, step, acc);
+            return;
+        }
+        for (int kc = c0; kc < h.nkc; kc += step) {   // (at most two chunks; columns beyond K meet zero weights)
+            const int k = kc * QRNNT_KCHUNK + grp * 16;
+            const v4i x0 = *(const v4i *)&mid_code[net][col][k], x1 = *(const v4i *)&mid_code[net][col][k + 64];
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
+                const v4i *const w = h.w + ((size_t)rt * h.nkc + kc) * (h.w8 ? 128 : 64) + lane;
+                const v4i f = w[0];
+                acc[mt] = qr_mfma(h.w8 ? f : ((f << 4) & m), x0, acc[mt]);
+                acc[mt] = qr_mfma(h.w8 ? w[64] : (f & m), x1, acc[mt]);
+            }
+        }
+    };
+    // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
+    auto word_at = [&](int q, int hyp, int token) { return a.words + (size_t)b * QR_ROUND_WORDS + (q * 16 + hyp) * 64 + token; };
     auto publish = [&](v4i v, int q, int hyp, int token) {
         v4i *const out = (v4i *)word_at(q, hyp, token);
         out[0] = v4i{v[0], (int)a.round, v[1], (int)a.round};
@@ -359,8 +414,18 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     if (CL && blockIdx.y + 1 < gridDim.y) {   // uniform: not the first workgroup
         if (!ALSD && r.gate && *r.gate == 0) return;   // uniform
         const int row = a.row[my_n];
-        if (blockIdx.y + a.parts >= gridDim.y) {       // a share of the joint
-            const int part = (int)(gridDim.y - 1 - blockIdx.y);
+        const int part = (int)(gridDim.y - 1 - blockIdx.y);   // first workgroup 0, shares of the joint, language models, bottlenecks
+        if (part > a.parts) {
+            int p = part - a.parts - 1;
+            const int n0 = a.mid[0].w ? (a.mid[0].rows + 63) >> 6 : 0, net = p < n0 ? 0 : 1;
+            p -= net ? n0 : 0;
+            const unsigned code = mid_part(net, p, row);
+            const unsigned next = (unsigned)__builtin_amdgcn_update_dpp(0, (int)code, 0xB1 /* the neighbour's */, 0xf, 0xf, true);
+            if ((tid & 1) == 0 && p * 64 + z_col < a.mid[net].rows)
+                *word_at(QR_ROUND_PARTS + 1 + net, z_hyp, (p * 64 + z_col) >> 2) = (unsigned long long)a.round << 32 | code | next << 16;
+            return;
+        }
+        if (part < a.parts) {                          // a share of the joint
             const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
             if (wave < 4) publish(sum, part, col, wave * 16 + 4 * grp);
             return;
@@ -368,8 +433,36 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         const int net = wave >> 2;                     // the language models: waves 0-3 source, 4-7 external, K split in four
         const QrHeadArgs &h = a.head[1 + net];
         v4i acc[4] = {zero, zero, zero, zero};
-        if (h.w) head_mma(std::integral_constant<int, 2>{}, h, row, wave & 3, 4, acc);   // uniform
         if ((wave & 3) == 3) row_constants(1 + net);
+        if (a.mid[0].w || a.mid[1].w) {                // uniform: the bottlenecks' codes, 16 of a hypothesis to a thread
+            if (tid == 0) missed = 0;
+            __syncthreads();
+            if (a.mid[net].w) {                        // uniform
+                const int hyp = (tid & 255) >> 4, c0 = (tid & 15) * 16;
+                const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc((void *)word_at(QR_ROUND_PARTS + 1 + net, 0, 0), 0,
+                                                                                      16 * 64 * 8, 0x00020000 /* raw bytes */);
+                const bool mine = c0 < a.mid[net].rows;
+                for (const unsigned long long t0 = wall_clock64();;) {
+                    const unsigned off = (unsigned)(hyp * 64 + (tid & 15) * 4) * 8;
+                    const v4i u = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off, 0, 16 /* sc1 */);
+                    const v4i v = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off + 16, 0, 16);
+                    asm volatile("" ::: "memory");     // every poll loads anew
+                    const bool ok = !mine || ((unsigned)u[1] == a.round && (unsigned)u[3] == a.round && (unsigned)v[1] == a.round &&
+                                              (unsigned)v[3] == a.round);
+                    if (__all(ok)) {
+                        *(v4i *)&mid_code[net][hyp][c0] = v4i{u[0], u[2], v[0], v[2]};
+                        break;
+                    }
+                    if (wall_clock64() - t0 > (unsigned long long)a.ticks) {
+                        if (lane == 0) missed = 1;
+                        break;
+                    }
+                }
+            }
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(missed)) return;   // uniform: the first workgroup does it all then
+        }
+        lm_mma(net, row, wave & 3, 4, acc);
         put_sums(acc);
         __syncthreads();
         const int hc = (tid & 255) >> 4, quad = lane & 15, mt = quad >> 2, at = (quad & 3) * 16 + (hc ^ quad);
@@ -567,9 +660,14 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                 if (wave < 4) t += sums[0][mt][at];
                 __syncthreads();
             }
+            for (int net = 0; net < 2; ++net)
+                for (int p = 0; use_lm && a.mid[net].w && p * 64 < a.mid[net].rows; ++p) {
+                    const unsigned code = mid_part(net, p, row);
+                    *(unsigned short *)&mid_code[net][z_hyp][p * 64 + z_col] = (unsigned short)code;
+                    __syncthreads();
+                }
             if (wave >= 4 && use_lm) {
-                const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
-                if (h.w) head_mma(std::integral_constant<int, 2>{}, h, row, wave & 1, 2, acc);   // uniform
+                lm_mma(wave >= 6 ? 1 : 0, row, wave & 1, 2, acc);
                 put_sums(acc);
             }
             __syncthreads();
@@ -684,15 +782,19 @@ int resident()
     return n > 0 ? n : 0;
 }
 
+int joint_parts(int J) { return (J + 63) / 64 < QR_ROUND_PARTS ? (J + 63) / 64 : QR_ROUND_PARTS; }
+
 template <bool ALSD>
 void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
     constexpr int N_XCD = 8;
     const bool use_lm = (ALSD || !r.last_round) && (a.head[1].w || a.head[2].w);
     QrRoundArgs c = a;
-    c.parts = (a.J + 63) / 64 < QR_ROUND_PARTS ? (a.J + 63) / 64 : QR_ROUND_PARTS;
-    const int wgs = c.parts + (use_lm ? 1 : 0);
-    if (r.W <= 16 && (wgs == 1 || r.B * wgs <= resident<ALSD>()))
+    c.parts = joint_parts(a.J);
+    int wgs = c.parts + (use_lm ? 1 : 0);
+    const bool share = r.W <= 16 && (wgs == 1 || 6 * r.B * wgs <= 5 * resident<ALSD>());
+    for (int net = 0; net < 2 && use_lm; ++net) wgs += a.mid[net].w ? (a.mid[net].rows + 63) / 64 : 0;
+    if (share)
         search_round_kernel<1, ALSD, true><<<dim3(N_XCD, a.alone ? 1 : wgs, (r.B + N_XCD - 1) / N_XCD), 512, 0, st>>>(c, r, s);
     else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
@@ -700,6 +802,16 @@ void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &
 }
 
 }  // namespace
+
+// A bottleneck in the round saves its own launch (6 us) and delays the language models by 2 us, as long as two thirds of the
+// workgroups are resident at once.  External language model of 2 x 2048 cells, bottleneck of 256, beam 16, us a round of
+// joint, steps and (before) bottleneck: 1 utterance 25.0 -> 22.4, 48 57.3 -> 54.8, 64 65.4 -> 62.6, 85 77.5 -> 74.9.
+bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd)
+{
+    const int room = alsd ? resident<true>() : resident<false>();
+    return W <= 16 && mid_rows <= 256 && 6 * B * (QR_ROUND_PARTS + 1) <= 5 * room &&
+           2 * B * (QR_ROUND_PARTS + 1 + n_mids * ((mid_rows + 63) / 64)) <= 3 * room;
+}
 
 void qr_launch_search_round(const QrRoundArgs &a, const QrRouteArgs &r, hipStream_t st) { launch_round<false>(a, r, QrAlsdArgs{}, st); }
 

@@ -91,16 +91,24 @@ struct QrHeadArgs {                    // output layer of one network
     int K, nkc, w8, log_softmax;
     float a_scale;
 };
+struct QrMidArgs {                     // bottleneck in front of a language model's output layer
+    const v4i *w;                      // null: none, or its codes lie where the head reads them
+    const float *s_w, *bias;
+    const int8_t *act;                 // [pool][K] codes it reads
+    int K, nkc, rows, w8, q_bits;
+    float a_scale, q_inv;
+};
 struct QrRoundArgs {
     QrHeadArgs head[3];                // prediction network (J rows), source and external LM (V rows)
+    QrMidArgs mid[2];                  // of the source and the external LM, where the round takes them in (qr_round_takes)
     const float *enc;  int frame_base; // time-synchronous search: utterance b reads row frame_base + b
     const int32_t *row;                // [N] pool row of every hypothesis
     const v4i *w;  const float *s_w;  const float *b_out;   // the joint's output layer
     float z_scale, z_inv;
     float lambda_src, lambda_ext, rho;
     int J, V, blank, nkc, w8;
-    // Beams of up to 16: values on their way between the workgroups of an utterance (joint.hip), [B][QR_ROUND_PARTS + 1][16][64]
-    // words of value and round number (never 0, no two rounds of a search the same); zeroed before the first round.
+    // Beams of up to 16: values on their way between the workgroups of an utterance (joint.hip), [B][QR_ROUND_WORDS] words of
+    // value and round number (never 0, no two rounds of a search the same), [16][64] to a source; zeroed before the first round.
     unsigned long long *words;
     unsigned round;
     int parts;                         // workgroups that share the joint (filled in by the launcher)
@@ -108,6 +116,8 @@ struct QrRoundArgs {
     int alone;                         // diagnostic: the others never come
 };
 #define QR_ROUND_PARTS 4
+#define QR_ROUND_WORDS ((QR_ROUND_PARTS + 3) * 16 * 64)   // sources: shares of the joint (of the first one: the source LM), external LM, bottlenecks
+QR_HIDDEN bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd);   // bottlenecks of so many rows
 
 struct QrRouteArgs {
     const float *score_src;                         // [B,W] of the current round

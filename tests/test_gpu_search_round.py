@@ -33,7 +33,8 @@ def test_round_at_the_edges_of_its_tiles(gpu_lib, J, V, B, W, mixed):
     _compare_beams(q.decode_alsd(G, dev(e), W, 4), oracle.decode_alsd(M, e, W, 4))
 
 
-def _model(J, V, mixed):
+def _model(J, V, mixed, mids=()):
+    """mids: (network, rows of its bottleneck)."""
     m = synth.make_model(0, weight_std=0.5)
     if mixed:
         m.mixed_precision = True
@@ -45,17 +46,25 @@ def _model(J, V, mixed):
         net.embed = synth.normal(910 + i, (V, net.embed.shape[1]), 0.5)
         if net is not m.pred:
             net.out = _linear(920 + 2 * i, V, net.layers[-1].w_hh.shape[1])
+    for i, rows in mids:
+        net = (m.pred, m.lm_src, m.lm_ext)[i]
+        net.mid, net.alpha_mid = _linear(940 + i, rows, net.layers[-1].w_hh.shape[1]), 4.0
+        net.out = _linear(950 + i, J if i == 0 else V, rows)
     return m
 
 
-@pytest.mark.parametrize("J,V,B,W,mixed", [(256, 46, 1, 16, False), (80, 17, 9, 5, False), (272, 48, 2, 16, True), (64, 33, 3, 1, False)])
-def test_a_workgroup_left_alone_returns_the_same_beams(gpu_lib, J, V, B, W, mixed):
+@pytest.mark.parametrize("J,V,B,W,mixed,mids", [(256, 46, 1, 16, False, ()), (80, 17, 9, 5, False, ()), (272, 48, 2, 16, True, ()),
+                                                (64, 33, 3, 1, False, ()), (256, 46, 1, 16, False, ((2, 256),)),
+                                                (80, 17, 3, 7, True, ((1, 80), (2, 144))), (64, 46, 2, 16, False, ((1, 16),)),
+                                                (64, 46, 2, 4, False, ((0, 48), (2, 64))), (64, 20, 2, 8, False, ((2, 272),))])
+def test_a_workgroup_left_alone_returns_the_same_beams(gpu_lib, J, V, B, W, mixed, mids):
     """The workgroups of a beam exchange whole numbers and the very values one of them would form: the bits are the same
     whether the others come or not.  A launch of more than about 100 utterances has one workgroup for each: the same beams
     (other step kernels run there, so the scores may differ in the last bits)."""
     from paper_2206_07882_amd import model as gmodel
     q = gpu_lib
-    G = gmodel.model_from_float(_model(J, V, mixed), "cuda:0")
+    m = _model(J, V, mixed, mids)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
     T, many = 6, 264 // B * B
     e = dev(synth.normal(930 + J, (T, B, J), 1.0))
     for alsd, limit, fn, size in ((0, 2, q.decode, q.decode_workspace), (1, 4, q.decode_alsd, q.decode_alsd_workspace)):
@@ -68,4 +77,7 @@ def test_a_workgroup_left_alone_returns_the_same_beams(gpu_lib, J, V, B, W, mixe
         batch = fn(G, e.repeat(1, many // B, 1).contiguous(), W, limit, max_len=2 * T)
         for w, g in zip(want, got):
             assert torch.equal(w, g)
+        if mids:   # in the round, or (272 rows, or one in front of the joint) in a launch of their own
+            ref = (oracle.decode_alsd if alsd else oracle.decode)(M, e.cpu().numpy(), W, limit, max_len=2 * T)
+            _compare_beams(want, ref)
         _compare_beams(batch, [np.tile(w.cpu().numpy(), (many // B,) + (1,) * (w.dim() - 1)) for w in want])
