@@ -43,6 +43,7 @@ struct QrStepGroup {
     // filled in by the launcher of the tiled kernel: row blocks of all members together, workgroups the device holds at once,
     // and (launches without a list) log2 of how many times narrower than the full column block a workgroup's share is
     int row_blocks = 0, n_resident = 0, width = 0;
+    int n_short = 0;                   // (likewise) lists up to this length are contracted with K split over the waves
     int through = 0;                   // (likewise) states are written through the L2
     int col_block0 = 0;                // first column block of this launch (a grid's z extent is limited to 65535)
 };

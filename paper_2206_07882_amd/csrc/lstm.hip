@@ -185,50 +185,33 @@ void launch_small(const QrStepGroup &g, hipStream_t st)
 }
 
 // Between the two: some dozens to some hundreds of hypotheses.  A workgroup owns 4 row tiles (16 cells) x 2 column tiles
-// (32 hypotheses); its 8 waves split K (the input part to waves 0-3, the recurrent part to waves 4-7; with a looked-up
-// input part all eight share the recurrent one), so no operand is wanted by two waves and every one goes from memory to
+// (32 hypotheses); its 8 waves (4 for a short list in the tiled kernel's launch) split K (the input part to the first half,
+// the recurrent part to the other; with a looked-up input part all share the recurrent one), so no operand is wanted by two waves and every one goes from memory to
 // registers, a whole batch of chunks in flight per wave, without a ring, its barriers and its index arithmetic.  One
-// exchange through LDS adds the partial sums, after which wave w finishes tile w, one (cell, hypothesis) per lane.
+// exchange through LDS adds the partial sums, after which wave w finishes tile w (and w + 4), one (cell, hypothesis) per lane.
 // Bound by its chain (arguments, list entry, codes, contraction, exchange, cell) while one round of workgroups covers
 // the list, by the path from L2 to the compute units beyond (a column block fetches the weights again, and codes in half
 // lines).  Measured against the tiled kernel: see split_n_max.
 // The arithmetic behind the sums is the tiled kernel's, so that a layer's results do not depend on which one ran.
 // Grid: x = groups of 4 row tiles, y = problem of a group, z = column blocks.
 
-
-template <bool USE_GX, bool TAB>
-__global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGroup g)
+// What it does: row tiles rt0 .. rt0 + 3, columns n0 .. n0 + 31 of problem `a`, by NW waves.  nn, s, xr: hypothesis, parent
+// and input row of the lane's columns, or (list) entry: the entries that hold them.  live() says how many columns there
+// are, after the first weights have been requested; -1: nothing to do.
+template <bool USE_GX, bool TAB, int NW, class Live>
+__device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const v4i (&entry)[2], int (&nn)[2], int (&s)[2], int (&xr)[2],
+                                           int rt0, int n0, v4i (*part)[8][64] /* [NW][tile: 4 * column tile + row tile][lane] */, Live &&live)
 {
-    __shared__ v4i part[8][8][64];   // [wave][tile: 4 * column tile + row tile][lane]
-    if (g.gate && *g.gate == 0) return;   // uniform: a decoding round without any live hypothesis
-    const QrStepArgs a = g.p[blockIdx.y];
-    const int H = a.H, N = a.N;
-    const int rt0 = blockIdx.x * 4;
-    const int n0 = (g.col_block0 + (int)blockIdx.z) * 32;
-    if (rt0 >= (H >> 2) || n0 >= N) return;   // uniform
+    static_assert(NW == 8 || NW == 4, "waves");
+    constexpr int TILES = 8 / NW;   // tiles that a wave finishes
+    const int H = a.H;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, grp = lane >> 4;
     const v4i zero = {0, 0, 0, 0};
-    const int m = (int)0xF0F0F0F0u;
-
-    // ---- row indices first, then the weights of the first batch, then what hangs on the indices
-    int nn[2], s[2], xr[2];
-    v4i entry[2] = {zero, zero};
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int j = n0 + 16 * i + col;
-        nn[i] = s[i] = xr[i] = j < N ? j : N - 1;
-        if (g.rows) {
-            entry[i] = g.rows[nn[i]];   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
-        } else {
-            if (a.parent) s[i] = a.parent[nn[i]];
-            if (a.x_row) xr[i] = a.x_row[nn[i]];
-        }
-    }
-    const bool is_x = !USE_GX && wave < 4;
-    constexpr int STEP = USE_GX ? 8 : 4, SPLIT_BATCH = USE_GX ? 1 : 2;   // chunks between a wave's, chunks per batch
-    const int first = USE_GX ? wave : wave & 3;
+    const bool is_x = !USE_GX && wave < NW / 2;
+    constexpr int STEP = USE_GX ? NW : NW / 2, SPLIT_BATCH = USE_GX && NW == 8 ? 1 : 2;   // chunks between a wave's, chunks per batch
+    const int first = USE_GX ? wave : wave & (NW / 2 - 1);
     const int nkc = is_x ? a.nkc_x : a.nkc_h, K = is_x ? a.I : H;
     const v4i *w = is_x ? a.wih : a.whh;
     __builtin_amdgcn_sched_barrier(0);
@@ -244,11 +227,9 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
     };
     load_weights(first);
     __builtin_amdgcn_sched_barrier(0);
-    int n_live = N;
-    if (g.rows) {
-        n_live = *g.n_rows;
-        if (n0 >= n_live) return;   // uniform
-        n_live = n_live < N ? n_live : N;
+    const int n_live = live();
+    if (n_live < 0) return;   // uniform
+    if (list) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             nn[i] = entry[i][0] < 0 ? 0 : (entry[i][0] >= a.n_out ? a.n_out - 1 : entry[i][0]);
@@ -263,20 +244,35 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
         xr[i] = xr[i] < 0 ? 0 : (xr[i] >= a.n_x_rows ? a.n_x_rows - 1 : xr[i]);
         row[i] = is_x ? a.x + (int64_t)xr[i] * a.ld_x + grp * 16 : a.h_prev + (int64_t)s[i] * a.ld_hp + grp * 16;
     }
-    // this wave's tile: row tile rt0 + mt, column tile nt; cell j of hypothesis n
-    const int mt_o = wave & 3, nt_o = wave >> 2;
-    const int n = nt_o ? nn[1] : nn[0], src = nt_o ? s[1] : s[0], xsrc = nt_o ? xr[1] : xr[0];
-    const int rt = rt0 + mt_o, j = qr_gates_cell(rt, grp);
-    const bool n_ok = n0 + 16 * nt_o + col < n_live;
+    // this wave's tiles (column tile by column tile): row tile rt0 + tile % 4, column tile tile / 4; cell j of hypothesis n
+    int n[TILES], src[TILES], xsrc[TILES], rt[TILES], j[TILES];
+    bool n_ok[TILES];
+#pragma unroll
+    for (int q = 0; q < TILES; ++q) {
+        const int tile = wave + NW * q, nt = tile >> 2;
+        n[q] = nt ? nn[1] : nn[0];
+        src[q] = nt ? s[1] : s[0];
+        xsrc[q] = nt ? xr[1] : xr[0];
+        rt[q] = rt0 + (tile & 3);
+        j[q] = qr_gates_cell(rt[q], grp);
+        n_ok[q] = n0 + 16 * nt + col < n_live;
+    }
 
     v4i acc[2][4];
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) acc[nt][mt] = zero;
-    float sx[4], sh[4], bb[4], cp = 0.0f;
-    int act = 1, hp_code = 0;
-    v4i gxv = zero;
+    float sx[TILES][4], sh[TILES][4], bb[TILES][4], cp[TILES];
+    int act[TILES], hp_code[TILES];
+    v4i gxv[TILES];
+#pragma unroll
+    for (int q = 0; q < TILES; ++q) {
+        cp[q] = 0.0f;
+        act[q] = 1;
+        hp_code[q] = 0;
+        gxv[q] = zero;
+    }
     for (int v0 = first; v0 == first || v0 < nkc; v0 += SPLIT_BATCH * STEP) {   // at least once: the loads of the cell
         if (v0 != first) load_weights(v0);
         v4i b0[SPLIT_BATCH][2], b1[SPLIT_BATCH][2];
@@ -294,11 +290,14 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
         }
         __builtin_amdgcn_sched_barrier(0);
         if (v0 == first) {   // what the cell will need, behind the first operands
-            cp = a.c_prev[(int64_t)src * H + j];
-            if (USE_GX) gxv = *(const v4i *)((TAB ? (const int32_t *)a.tabf : a.gx) + (int64_t)xsrc * a.ld_gx + rt * 16 + 4 * grp);
-            if (a.active) {
-                act = a.active[n];
-                hp_code = a.h_prev[(int64_t)src * a.ld_hp + j];
+#pragma unroll
+            for (int q = 0; q < TILES; ++q) {
+                cp[q] = a.c_prev[(int64_t)src[q] * H + j[q]];
+                if (USE_GX) gxv[q] = *(const v4i *)((TAB ? (const int32_t *)a.tabf : a.gx) + (int64_t)xsrc[q] * a.ld_gx + rt[q] * 16 + 4 * grp);
+                if (a.active) {
+                    act[q] = a.active[n[q]];
+                    hp_code[q] = a.h_prev[(int64_t)src[q] * a.ld_hp + j[q]];
+                }
             }
         }
 #pragma unroll
@@ -317,58 +316,97 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
     }
     // (the row constants come from the XCD's own cache and arrive during the exchange)
 #pragma unroll
-    for (int gt = 0; gt < 4; ++gt) {
-        sh[gt] = a.s_whh[gt * H + j];
-        if (!TAB) sx[gt] = a.s_wih[gt * H + j];
-        if (!TAB) bb[gt] = a.bias[gt * H + j];
-    }
+    for (int q = 0; q < TILES; ++q)
+#pragma unroll
+        for (int gt = 0; gt < 4; ++gt) {
+            sh[q][gt] = a.s_whh[gt * H + j[q]];
+            if (!TAB) sx[q][gt] = a.s_wih[gt * H + j[q]];
+            if (!TAB) bb[q][gt] = a.bias[gt * H + j[q]];
+        }
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) part[wave][4 * nt + mt][lane] = acc[nt][mt];
     __syncthreads();
-    v4i ax = zero, ah = zero;   // 16 x the sums
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        ax += part[q][wave][lane];
-        ah += part[4 + q][wave][lane];
-    }
-    if (USE_GX) ah += ax;
+    for (int q = 0; q < TILES; ++q) {
+        v4i ax = zero, ah = zero;   // 16 x the sums
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) {
+            ax += part[w][wave + NW * q][lane];
+            ah += part[NW / 2 + w][wave + NW * q][lane];
+        }
+        if (USE_GX) ah += ax;
 
-    float p[4];
+        float p[4];
 #pragma unroll
-    for (int gt = 0; gt < 4; ++gt) {
-        const float k = gt == 2 ? -2.885390081777927f : -1.4426950408889634f;   // the constant its activation feeds to exp2
-        const float shk = sh[gt] * a.h_scale * (0.0625f * k);
-        if (TAB) {
-            p[gt] = __builtin_fmaf(shk, (float)ah[gt], __int_as_float(gxv[gt]));
-        } else if (USE_GX) {
-            p[gt] = __builtin_fmaf(sx[gt] * a.x_scale * k, (float)gxv[gt], __builtin_fmaf(shk, (float)ah[gt], bb[gt] * k));
-        } else {
-            p[gt] = __builtin_fmaf(shk, (float)ah[gt], __builtin_fmaf(sx[gt] * a.x_scale * (0.0625f * k), (float)ax[gt], bb[gt] * k));
+        for (int gt = 0; gt < 4; ++gt) {
+            const float k = gt == 2 ? -2.885390081777927f : -1.4426950408889634f;   // the constant its activation feeds to exp2
+            const float shk = sh[q][gt] * a.h_scale * (0.0625f * k);
+            if (TAB) {
+                p[gt] = __builtin_fmaf(shk, (float)ah[gt], __int_as_float(gxv[q][gt]));
+            } else if (USE_GX) {
+                p[gt] = __builtin_fmaf(sx[q][gt] * a.x_scale * k, (float)gxv[q][gt], __builtin_fmaf(shk, (float)ah[gt], bb[q][gt] * k));
+            } else {
+                p[gt] = __builtin_fmaf(shk, (float)ah[gt], __builtin_fmaf(sx[q][gt] * a.x_scale * (0.0625f * k), (float)ax[gt], bb[q][gt] * k));
+            }
+        }
+        const float gi = qr_sigmoid_scaled(p[0]), gf = qr_sigmoid_scaled(p[1]);
+        const float gg = 2.0f * qr_sigmoid_scaled(p[2]) - 1.0f, go = qr_sigmoid_scaled(p[3]);
+        const float c1 = __builtin_fmaf(gf, cp[q], gi * gg);
+        const float rc = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.885390081777927f * c1));
+        const float hq = go * (2.0f * a.h_inv * rc - a.h_inv);
+        const bool on = act[q] != 0;
+        const int code = on ? (int)fminf(fmaxf(__builtin_rintf(hq), -8.0f), 7.0f) : hp_code[q];
+        if (!n_ok[q]) continue;
+        a.c_next[(int64_t)n[q] * H + j[q]] = on ? c1 : cp[q];
+        a.h_next[(int64_t)n[q] * a.ld_hn + j[q]] = (int8_t)code;
+        if (a.h_copy) a.h_copy[(int64_t)n[q] * H + j[q]] = (int8_t)code;
+        if (a.dbg_accx && (!USE_GX || !TAB))
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) a.dbg_accx[(int64_t)n[q] * 4 * H + gt * H + j[q]] = USE_GX ? gxv[q][gt] : (ax[gt] >> 4);
+        if (a.dbg_acch)
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt) a.dbg_acch[(int64_t)n[q] * 4 * H + gt * H + j[q]] = ah[gt] >> 4;
+        if (a.dbg_gates && on) {
+            float *dg = a.dbg_gates + (int64_t)n[q] * 4 * H + j[q];
+            dg[0] = gi; dg[H] = gf; dg[2 * H] = gg; dg[3 * H] = go;
         }
     }
-    const float gi = qr_sigmoid_scaled(p[0]), gf = qr_sigmoid_scaled(p[1]);
-    const float gg = 2.0f * qr_sigmoid_scaled(p[2]) - 1.0f, go = qr_sigmoid_scaled(p[3]);
-    const float c1 = __builtin_fmaf(gf, cp, gi * gg);
-    const float rc = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.885390081777927f * c1));
-    const float hq = go * (2.0f * a.h_inv * rc - a.h_inv);
-    const bool on = act != 0;
-    const int code = on ? (int)fminf(fmaxf(__builtin_rintf(hq), -8.0f), 7.0f) : hp_code;
-    if (!n_ok) return;
-    a.c_next[(int64_t)n * H + j] = on ? c1 : cp;
-    a.h_next[(int64_t)n * a.ld_hn + j] = (int8_t)code;
-    if (a.h_copy) a.h_copy[(int64_t)n * H + j] = (int8_t)code;
-    if (a.dbg_accx && (!USE_GX || !TAB))
+}
+
+template <bool USE_GX, bool TAB>
+__global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGroup g)
+{
+    __shared__ v4i part[8][8][64];   // [wave][tile: 4 * column tile + row tile][lane]
+    if (g.gate && *g.gate == 0) return;   // uniform: a decoding round without any live hypothesis
+    const QrStepArgs a = g.p[blockIdx.y];
+    const int H = a.H, N = a.N;
+    const int rt0 = blockIdx.x * 4;
+    const int n0 = (g.col_block0 + (int)blockIdx.z) * 32;
+    if (rt0 >= (H >> 2) || n0 >= N) return;   // uniform
+    const int col = threadIdx.x & 15;
+    const v4i zero = {0, 0, 0, 0};
+
+    // ---- row indices first, then the weights of the first batch, then what hangs on the indices
+    int nn[2], s[2], xr[2];
+    v4i entry[2] = {zero, zero};
 #pragma unroll
-        for (int gt = 0; gt < 4; ++gt) a.dbg_accx[(int64_t)n * 4 * H + gt * H + j] = USE_GX ? gxv[gt] : (ax[gt] >> 4);
-    if (a.dbg_acch)
-#pragma unroll
-        for (int gt = 0; gt < 4; ++gt) a.dbg_acch[(int64_t)n * 4 * H + gt * H + j] = ah[gt] >> 4;
-    if (a.dbg_gates && on) {
-        float *dg = a.dbg_gates + (int64_t)n * 4 * H + j;
-        dg[0] = gi; dg[H] = gf; dg[2 * H] = gg; dg[3 * H] = go;
+    for (int i = 0; i < 2; ++i) {
+        const int j = n0 + 16 * i + col;
+        nn[i] = s[i] = xr[i] = j < N ? j : N - 1;
+        if (g.rows) {
+            entry[i] = g.rows[nn[i]];   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
+        } else {
+            if (a.parent) s[i] = a.parent[nn[i]];
+            if (a.x_row) xr[i] = a.x_row[nn[i]];
+        }
     }
+    split_body<USE_GX, TAB, 8>(a, g.rows != nullptr, entry, nn, s, xr, rt0, n0, part, [&]() {
+        if (!g.rows) return N;
+        const int n_cnt = *g.n_rows;
+        return n0 >= n_cnt ? -1 : (n_cnt < N ? n_cnt : N);
+    });
 }
 
 template <bool USE_GX>
@@ -420,7 +458,7 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
     const int n_row_tiles = H >> 2;
     const int block_rt0 = blockIdx.x * 2 * MT;
     const int n0 = col_block * P::BN;
-    if (block_rt0 >= n_row_tiles) return;   // uniform per block
+    if (block_rt0 >= n_row_tiles && !g.n_short) return;   // uniform per block
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, grp = lane >> 4;
@@ -473,11 +511,24 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
         const int n0h = col_block * (P::BN / 2), n0q = col_block * (P::BN / 4);
         static_assert(P::BN + P::BN / 2 + P::BN / 4 <= 256, "one entry per thread");
         v4i *se = (v4i *)lds;
+        // A short list (n_short entries at most) goes the way of the kernel above, by four waves: unit u of the launch takes
+        // 16 cells x 32 entries, which are requested with the rest.
+        const int n_groups = H >> 4, unit = (int)(blockIdx.z * gridDim.x + blockIdx.x), n0s = unit / n_groups * 32;
+        v4i entry[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) entry[i] = rows[n0s + 16 * i + col < N ? n0s + 16 * i + col : N - 1];
         if (tid < P::BN + P::BN / 2 + P::BN / 4) {
             const int j = tid < P::BN ? n0 + tid : (tid < P::BN + P::BN / 2 ? n0h + tid - P::BN : n0q + tid - P::BN - P::BN / 2);
             se[tid] = rows[j < N ? j : N - 1];
         }
         const int n_cnt = *g.n_rows;
+        if (n_cnt <= g.n_short) {   // uniform
+            if (n0s >= n_cnt) return;   // uniform per block
+            __syncthreads();
+            int nn[2] = {0, 0}, s[2] = {0, 0}, xr[2] = {0, 0};
+            split_body<USE_GX, TAB, 4>(a, true, entry, nn, s, xr, unit % n_groups * 4, n0s, (v4i (*)[8][64])lds, [&]() { return n_cnt; });
+            return;
+        }
         if (HALF_OK) {   // uniform: the narrowest width that covers the list in one round of workgroups
 #pragma unroll
             for (int w = 1; w <= 2; ++w) {
@@ -486,7 +537,7 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
             }
         }
         const int n0w = width == 2 ? n0q : (width == 1 ? n0h : n0);
-        if (n0w >= n_cnt) return;   // uniform per block
+        if (n0w >= n_cnt || block_rt0 >= n_row_tiles) return;   // uniform per block
         __syncthreads();
         const int se0 = width == 2 ? P::BN + P::BN / 2 : (width == 1 ? P::BN : 0);   // where the range of this width starts in se
         nt_valid = NT >> width;
@@ -745,6 +796,13 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
     else run(std::integral_constant<int, NT>{});
 }
 
+// Lists up to this length go the way of the split kernel inside the tiled kernel's launch: the host does not know the length.
+// 1024 hypotheses at most, tiled / so, us: second layers of 2 x 1024 cells 16 10.8 / 5.4, 64 11.1 / 6.0, 96 11.2 / 7.9, 128
+// 11.2 / 8.2; of 2048 cells 64 17.5 / 8.3, 128 17.6 / 12.2; first layers of 768 and 2 x 1024 cells 16 7.1 / 4.7, 64 7.4 / 6.7,
+// 96 8.3 / 8.2 (as far as the tiled kernel), of 768, 768 and 2048 cells 64 11.0 / 9.9, 96 12.6 / 12.7.  Up to 192 it is still
+// the faster one, but takes half as many workgroups again, which a long list would only send away.
+static int n_short_max(bool use_gx, int max_n) { return use_gx ? 64 : (max_n <= 512 ? 192 : 128); }
+
 template <int MT, int NT, int S, bool USE_GX, bool TAB, bool DBG, bool FAST>
 void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
 {
@@ -780,7 +838,11 @@ void launch_pipe_f(const QrStepGroup &g, hipStream_t st)
     // 186.3 against 189.4 ms; 128: 59.4 against 58.1 us a round, of the wider networks 109.7 against 106.8).
     gg.through = 2 * gg.row_blocks * ((max_n + P::BN - 1) / P::BN) <= 3 * gg.n_resident;
     const int per = P::BN >> width;
-    const int gz = (max_n + per - 1) / per;
+    int gz = (max_n + per - 1) / per;
+    // A short list's workgroup has 16 cells and 32 columns: twice the row blocks, so 16 columns to a column block of the launch.
+    const int n_short = n_short_max(USE_GX, max_n);
+    if (g.rows && gz < n_short / 16) gz = n_short / 16;
+    gg.n_short = g.rows && gz <= 65535 ? n_short : 0;
     for (int z0 = 0; z0 < gz; z0 += 65535) {   // a grid's z extent ends at 65535
         gg.col_block0 = z0;
         kern<<<dim3(gx, g.n, gz - z0 < 65535 ? gz - z0 : 65535), 256, P::LDS_BYTES, st>>>(gg);
@@ -811,14 +873,14 @@ void launch_pipe(const QrStepGroup &g, hipStream_t st)
     else launch_pipe_f<MT, NT, S, USE_GX, false, false, false>(g, st);
 }
 
-// Hypothesis counts up to this go to the kernel that splits K over a workgroup's waves; what counts is how many advance,
-// and a list holds a third to a half of its hypotheses in most rounds.  Measured (this kernel / the tiled one, us):
-// second layers of 2 x 1024 cells 32 of 64 7.7 / 11.9, 64 of 128 7.5 / 11.1, 104 of 208 10.2 / 11.3, 208 of 208
-// 15.1 / 13.0; of 768 and 2048 cells 52 of 208 9.9 / 17.2, 104 of 208 14.7 / 17.6, 208 of 208 22.7 / 20.2.  A looked-up
-// input part halves the work that is split: first layers of 768 and 2 x 1024 cells 64 of 128 7.4 / 7.8, 104 of 208 11.2 / 8.8.
-// Where every hypothesis of a list advances the tiled kernel is the faster one from about 200 on (256 of 256: 13.0 / 11.9 and
-// 28.0 / 24.1), but the host does not know the length, and at a half the split pays more (8.8 / 10.4 and 17.0 / 19.8).
-static int split_n_max(bool use_gx, bool list) { return (use_gx ? 64 : 128) * (list ? 2 : 1); }
+// Hypothesis counts up to this go to the kernel that splits K over a workgroup's waves; chunks: of the longest K of the
+// launch, input and recurrent part together.  Measured (this kernel / the tiled one, us): second layers of 2 x 1024 cells 64
+// 6.1 / 11.9, 128 9.2 / 11.1, 208 15.1 / 13.0; of 2048 cells 128 14.0 / 17.6, 208 22.7 / 20.2.  A looked-up input part halves the
+// work that is split: first layers of 768 and 2 x 1024 cells 64 7.0 / 7.4, 128 10.7 / 8.1.  With a list this is the most it may
+// hold, and the tiled kernel's launch finds the same way by four waves if it turns out short (n_short_max): of 208, second
+// layers of 2 x 1024 cells 64 7.1 / 6.1, 128 8.8 / 8.2, 208 12.8 / 12.7; first layers, 128 of 128 10.7 / 8.6.  Over a long K eight
+// waves are the faster ones: of 208 and 2048 cells 128 11.9 / 11.8, 192 15.3 / 16.2, 208 18.4 / 19.7.
+static int split_n_max(bool use_gx, bool list, int chunks) { return use_gx ? 64 : (list && chunks > 24 ? 256 : 128); }
 
 // Hypothesis counts up to this go to the weight-streaming kernel.
 static int small_n_max()
@@ -835,7 +897,7 @@ void launch_step_t(const QrStepArgs &a, hipStream_t st)
     g.n = 1;
     g.gate = nullptr;
     if (a.N <= small_n_max()) launch_small<USE_GX>(g, st);
-    else if (a.N <= split_n_max(USE_GX, g.rows != nullptr)) launch_split<USE_GX>(g, st);
+    else if (a.N <= split_n_max(USE_GX, g.rows != nullptr, a.nkc_x + a.nkc_h)) launch_split<USE_GX>(g, st);
     else launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);
 }
 
@@ -1011,9 +1073,12 @@ static void launch_group_t(const QrStepGroup &g, hipStream_t st)
 {
     // one launch when every member is in the same regime, else member by member
     bool all_big = true, all_split = true, all_small = true;
+    int chunks = 0;
+    for (int i = 0; i < g.n; ++i) chunks = g.p[i].nkc_x + g.p[i].nkc_h > chunks ? g.p[i].nkc_x + g.p[i].nkc_h : chunks;
+    const int split_max = split_n_max(USE_GX, g.rows != nullptr, chunks);
     for (int i = 0; i < g.n; ++i) {
-        all_big = all_big && g.p[i].N > split_n_max(USE_GX, g.rows != nullptr);
-        all_split = all_split && g.p[i].N > small_n_max() && g.p[i].N <= split_n_max(USE_GX, g.rows != nullptr);
+        all_big = all_big && g.p[i].N > split_max;
+        all_split = all_split && g.p[i].N > small_n_max() && g.p[i].N <= split_max;
         all_small = all_small && g.p[i].N <= small_n_max();
     }
     if (all_big) launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);

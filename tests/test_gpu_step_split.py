@@ -1,6 +1,7 @@
 """The step kernel that splits K over a workgroup's waves, at the edges of its tiles: hypothesis counts around its column
 blocks and the counts that choose it, cell counts around its row groups, inputs that end inside a chunk or leave waves
-without one, gathered and inactive hypotheses, lists, and a looked-up input part with and without its fp32 table."""
+without one, gathered and inactive hypotheses, lists, and a looked-up input part with and without its fp32 table; short
+lists in the tiled kernel's launch."""
 import numpy as np
 import pytest
 import torch
@@ -17,7 +18,11 @@ pytestmark = pytest.mark.gpu
                                                     (33, 32, 1040, "sums", None), (64, 64, 272, "table", None),
                                                     (256, 64, 80, False, 1), (200, 144, 64, False, 32), (129, 64, 64, False, 129),
                                                     (128, 64, 96, "table", 77), (100, 64, 1040, "sums", 33), (70, 32, 48, "table", 0),
-                                                    (129, 64, 64, "table", 100), (208, 80, 1024, "table", 150)])
+                                                    (129, 64, 64, "table", 100), (208, 80, 1024, "table", 150),
+                                                    (300, 144, 80, False, 192), (300, 144, 80, False, 193), (600, 64, 48, False, 128),
+                                                    (600, 64, 48, False, 129), (257, 1040, 16, False, 1), (250, 3200, 32, False, 222),
+                                                    (257, 3200, 32, False, 33), (200, 64, 80, "table", 64), (130, 64, 1040, "sums", 65),
+                                                    (1030, 80, 272, "table", 63)])
 def test_split_step(gpu_lib, N, I, H, looked_up, listed):
     q = gpu_lib
     s_x = float(np.float32(4) / np.float32(7))
