@@ -198,11 +198,12 @@ void launch_small(const QrStepGroup &g, hipStream_t st)
 // What it does: row tiles rt0 .. rt0 + 3, columns n0 .. n0 + 31 of problem `a`, by NW waves.  nn, s, xr: hypothesis, parent
 // and input row of the lane's columns, or (list) entry: the entries that hold them.  live() says how many columns there
 // are, after the first weights have been requested; -1: nothing to do.
-template <bool USE_GX, bool TAB, int NW, class Live>
+// FEW: the cell in the arithmetic of lstm_step_small_kernel (no constants folded into the scales), for the same reason.
+template <bool USE_GX, bool TAB, int NW, bool FEW, class Live>
 __device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const v4i (&entry)[2], int (&nn)[2], int (&s)[2], int (&xr)[2],
                                            int rt0, int n0, v4i (*part)[8][64] /* [NW][tile: 4 * column tile + row tile][lane] */, Live &&live)
 {
-    static_assert(NW == 8 || NW == 4, "waves");
+    static_assert((NW == 8 || NW == 4) && !(TAB && FEW), "waves; sums looked up, not their folded form");
     constexpr int TILES = 8 / NW;   // tiles that a wave finishes
     const int H = a.H;
     const int lane = threadIdx.x & 63;
@@ -339,6 +340,13 @@ __device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const
         if (USE_GX) ah += ax;
 
         float p[4];
+        if (FEW) {
+            ah = ah >> 4;
+#pragma unroll
+            for (int gt = 0; gt < 4; ++gt)
+                p[gt] = __builtin_fmaf(a.x_scale * sx[q][gt], (float)(USE_GX ? gxv[q][gt] : ax[gt] >> 4),
+                                       __builtin_fmaf(a.h_scale * sh[q][gt], (float)ah[gt], bb[q][gt]));
+        } else
 #pragma unroll
         for (int gt = 0; gt < 4; ++gt) {
             const float k = gt == 2 ? -2.885390081777927f : -1.4426950408889634f;   // the constant its activation feeds to exp2
@@ -351,13 +359,14 @@ __device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const
                 p[gt] = __builtin_fmaf(shk, (float)ah[gt], __builtin_fmaf(sx[q][gt] * a.x_scale * (0.0625f * k), (float)ax[gt], bb[q][gt] * k));
             }
         }
-        const float gi = qr_sigmoid_scaled(p[0]), gf = qr_sigmoid_scaled(p[1]);
-        const float gg = 2.0f * qr_sigmoid_scaled(p[2]) - 1.0f, go = qr_sigmoid_scaled(p[3]);
+        const float gi = FEW ? qr_sigmoid(p[0]) : qr_sigmoid_scaled(p[0]), gf = FEW ? qr_sigmoid(p[1]) : qr_sigmoid_scaled(p[1]);
+        const float gg = FEW ? qr_tanh(p[2]) : 2.0f * qr_sigmoid_scaled(p[2]) - 1.0f, go = FEW ? qr_sigmoid(p[3]) : qr_sigmoid_scaled(p[3]);
         const float c1 = __builtin_fmaf(gf, cp[q], gi * gg);
         const float rc = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.885390081777927f * c1));
         const float hq = go * (2.0f * a.h_inv * rc - a.h_inv);
         const bool on = act[q] != 0;
-        const int code = on ? (int)fminf(fmaxf(__builtin_rintf(hq), -8.0f), 7.0f) : hp_code[q];
+        const int new_code = FEW ? qr_quant4(go * qr_tanh(c1), a.h_inv) : (int)fminf(fmaxf(__builtin_rintf(hq), -8.0f), 7.0f);
+        const int code = on ? new_code : hp_code[q];
         if (!n_ok[q]) continue;
         a.c_next[(int64_t)n[q] * H + j[q]] = on ? c1 : cp[q];
         a.h_next[(int64_t)n[q] * a.ld_hn + j[q]] = (int8_t)code;
@@ -367,7 +376,7 @@ __device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const
             for (int gt = 0; gt < 4; ++gt) a.dbg_accx[(int64_t)n[q] * 4 * H + gt * H + j[q]] = USE_GX ? gxv[q][gt] : (ax[gt] >> 4);
         if (a.dbg_acch)
 #pragma unroll
-            for (int gt = 0; gt < 4; ++gt) a.dbg_acch[(int64_t)n[q] * 4 * H + gt * H + j[q]] = ah[gt] >> 4;
+            for (int gt = 0; gt < 4; ++gt) a.dbg_acch[(int64_t)n[q] * 4 * H + gt * H + j[q]] = FEW ? ah[gt] : ah[gt] >> 4;
         if (a.dbg_gates && on) {
             float *dg = a.dbg_gates + (int64_t)n[q] * 4 * H + j[q];
             dg[0] = gi; dg[H] = gf; dg[2 * H] = gg; dg[3 * H] = go;
@@ -375,7 +384,7 @@ __device__ __forceinline__ void split_body(const QrStepArgs &a, bool list, const
     }
 }
 
-template <bool USE_GX, bool TAB>
+template <bool USE_GX, bool TAB, bool FEW>
 __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGroup g)
 {
     __shared__ v4i part[8][8][64];   // [wave][tile: 4 * column tile + row tile][lane]
@@ -402,7 +411,7 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
             if (a.x_row) xr[i] = a.x_row[nn[i]];
         }
     }
-    split_body<USE_GX, TAB, 8>(a, g.rows != nullptr, entry, nn, s, xr, rt0, n0, part, [&]() {
+    split_body<USE_GX, TAB, 8, FEW>(a, g.rows != nullptr, entry, nn, s, xr, rt0, n0, part, [&]() {
         if (!g.rows) return N;
         const int n_cnt = *g.n_rows;
         return n0 >= n_cnt ? -1 : (n_cnt < N ? n_cnt : N);
@@ -410,7 +419,7 @@ __global__ __launch_bounds__(512, 4) void lstm_step_split_kernel(const QrStepGro
 }
 
 template <bool USE_GX>
-void launch_split(const QrStepGroup &g, hipStream_t st)
+void launch_split(const QrStepGroup &g, hipStream_t st, bool few = false)
 {
     int max_n = 0, max_rg = 0;
     bool tab = USE_GX;
@@ -420,8 +429,9 @@ void launch_split(const QrStepGroup &g, hipStream_t st)
         tab = tab && g.p[i].tabf != nullptr;
     }
     const dim3 grid(max_rg, g.n, (max_n + 31) / 32);
-    if (tab) lstm_step_split_kernel<USE_GX, USE_GX><<<grid, 512, 0, st>>>(g);
-    else lstm_step_split_kernel<USE_GX, false><<<grid, 512, 0, st>>>(g);
+    if (few) lstm_step_split_kernel<USE_GX, false, true><<<grid, 512, 0, st>>>(g);
+    else if (tab) lstm_step_split_kernel<USE_GX, USE_GX, false><<<grid, 512, 0, st>>>(g);
+    else lstm_step_split_kernel<USE_GX, false, false><<<grid, 512, 0, st>>>(g);
 }
 
 // Compute-bound variant (many hypotheses): multi-stage LDS ring, see mma_pipe.h.
@@ -526,7 +536,7 @@ __global__ __launch_bounds__(256, step_workgroups_per_cu(USE_GX, DBG)) void lstm
             if (n0s >= n_cnt) return;   // uniform per block
             __syncthreads();
             int nn[2] = {0, 0}, s[2] = {0, 0}, xr[2] = {0, 0};
-            split_body<USE_GX, TAB, 4>(a, true, entry, nn, s, xr, unit % n_groups * 4, n0s, (v4i (*)[8][64])lds, [&]() { return n_cnt; });
+            split_body<USE_GX, TAB, 4, false>(a, true, entry, nn, s, xr, unit % n_groups * 4, n0s, (v4i (*)[8][64])lds, [&]() { return n_cnt; });
             return;
         }
         if (HALF_OK) {   // uniform: the narrowest width that covers the list in one round of workgroups
@@ -882,11 +892,20 @@ void launch_pipe(const QrStepGroup &g, hipStream_t st)
 // waves are the faster ones: of 208 and 2048 cells 128 11.9 / 11.8, 192 15.3 / 16.2, 208 18.4 / 19.7.
 static int split_n_max(bool use_gx, bool list, int chunks) { return use_gx ? 64 : (list && chunks > 24 ? 256 : 128); }
 
-// Hypothesis counts up to this go to the weight-streaming kernel.
-static int small_n_max()
+// Hypothesis counts up to this have their cells updated in the arithmetic of the weight-streaming kernel.
+static int small_n_max() { return 32; }
+
+// Up to 16 of them, one column tile, that kernel does it (one utterance at beam 16: 13.3 ms, split 13.8); with a second one
+// they are contracted in the way of the kernel that splits K (32 hypotheses, us, streaming / splitting: second layers of 2 x
+// 1024 cells 6.3 / 5.3, of 2048 cells 9.0 / 7.0; first layers of 768 and 2 x 1024 cells 7.3 / 5.2, of 768, 768 and 2048 cells
+// 10.3 / 7.8; 20 hypotheses 5.6 / 4.8, 8.2 / 6.2, 6.3 / 4.7, 8.7 / 6.5).
+template <bool USE_GX>
+static void launch_few(const QrStepGroup &g, hipStream_t st)
 {
-    return 32;   // measured per decoding round: 64 hypotheses 21.4 us here, 19.1 us in the tiled kernel at 32 per
-                 // workgroup; 32 hypotheses 13.3 us here, 18.8 us there
+    int max_n = 0;
+    for (int i = 0; i < g.n; ++i) max_n = g.p[i].N > max_n ? g.p[i].N : max_n;
+    if (max_n <= 16) launch_small<USE_GX>(g, st);
+    else launch_split<USE_GX>(g, st, true);
 }
 
 template <bool USE_GX>
@@ -896,7 +915,7 @@ void launch_step_t(const QrStepArgs &a, hipStream_t st)
     g.p[0] = a;
     g.n = 1;
     g.gate = nullptr;
-    if (a.N <= small_n_max()) launch_small<USE_GX>(g, st);
+    if (a.N <= small_n_max()) launch_few<USE_GX>(g, st);
     else if (a.N <= split_n_max(USE_GX, g.rows != nullptr, a.nkc_x + a.nkc_h)) launch_split<USE_GX>(g, st);
     else launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);
 }
@@ -1083,7 +1102,7 @@ static void launch_group_t(const QrStepGroup &g, hipStream_t st)
     }
     if (all_big) launch_pipe<4, 4, USE_GX ? 2 : 3, USE_GX>(g, st);
     else if (all_split) launch_split<USE_GX>(g, st);
-    else if (all_small) launch_small<USE_GX>(g, st);
+    else if (all_small) launch_few<USE_GX>(g, st);
     else
         for (int i = 0; i < g.n; ++i) launch_step_t<USE_GX>(g.p[i], st);
 }
