@@ -212,21 +212,27 @@ qrnnt_status check_model(const qrnnt_model *m)
     return QRNNT_OK;
 }
 
+// The launches of an advance, the same in every round but for the gate and the count: prepared once a search.
+struct Advance {
+    QrStepGroup layer[QRNNT_MAX_LAYERS];
+    int n_layers;
+    QrLinearGroup mids;
+};
+
 // The networks advance for the *n_rows hypotheses listed in p.rows, (row written, row read, token) each.  Layer l
 // of every network goes out as one grouped launch (the networks are independent).
-void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, const int32_t *n_rows, hipStream_t st)
+void prepare_advance(const qrnnt_model *m, const Plan &p, Advance &ad)
 {
     const int pool = p.B * p.P;
     const int32_t *const from_list = (const int32_t *)p.rows;   // row and token of an entry take the place of these arrays
     int max_layers = 0;
     for (int k = 0; k < 3; ++k)
         if (net_used(m, k) && net_of(m, k)->n_layers > max_layers) max_layers = net_of(m, k)->n_layers;
+    ad.n_layers = max_layers;
     for (int l = 0; l < max_layers; ++l) {
-        QrStepGroup g;
+        QrStepGroup &g = ad.layer[l];
         g.n = 0;
-        g.gate = gate;
         g.rows = p.rows;
-        g.n_rows = n_rows;
         for (int k = 0; k < 3; ++k) {
             if (!net_used(m, k)) continue;
             const qrnnt_net *net = net_of(m, k);
@@ -250,15 +256,12 @@ void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, cons
             a.c_prev = a.c_next = p.net[k].c[l];
             a.N = p.N;  a.n_out = pool;
         }
-        qr_launch_lstm_step_group(g, l == 0, st);
     }
     // The output layers belong to the round that reads them (joint.hip); a bottleneck in front of one is a layer of the
     // advance, fused with the quantizer of its output.
-    QrLinearGroup lg;
+    QrLinearGroup &lg = ad.mids;
     lg.n = 0;
-    lg.gate = gate;
     lg.rows = p.rows;
-    lg.n_rows = n_rows;
     for (int k = 0; k < 3; ++k) {
         if (!net_used(m, k) || net_of(m, k)->mid.packed == nullptr || p.net[k].mid_in_round) continue;
         const qrnnt_net *net = net_of(m, k);
@@ -270,11 +273,22 @@ void advance_nets(const qrnnt_model *m, const Plan &p, const int32_t *gate, cons
         la.act = p.net[k].h[net->n_layers - 1];  la.K = net->mid.cols;  la.N = p.N;  la.n_out = pool;
         la.q_out = p.net[k].mid_q;  la.q_inv = net->mid_inv_scale;  la.q_bits = qr_bits(&net->out);  la.w8 = qr_bits(&net->mid) == 8;
     }
-    if (lg.n) qr_launch_linear_group(lg, st);
+}
+
+void advance_nets(Advance &ad, const int32_t *gate, const int32_t *n_rows, hipStream_t st)
+{
+    for (int l = 0; l < ad.n_layers; ++l) {
+        ad.layer[l].gate = gate;
+        ad.layer[l].n_rows = n_rows;
+        qr_launch_lstm_step_group(ad.layer[l], l == 0, st);
+    }
+    ad.mids.gate = gate;
+    ad.mids.n_rows = n_rows;
+    if (ad.mids.n) qr_launch_linear_group(ad.mids, st);
 }
 
 // What a decoding round reads of the model.
-QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj, bool alone)
+QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj, bool alone, bool alsd)
 {
     QrRoundArgs ja = {};
     for (int k = 0; k < 3; ++k) {
@@ -303,12 +317,13 @@ QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_pro
     ja.words = p.words;
     ja.ticks = alone ? 10 : 1000;   // 10 us; the other workgroups need 3
     ja.alone = alone;
+    qr_plan_round(ja, p.B, p.W, alsd);
     return ja;
 }
 
 // Everything a search starts from: a row of zero states, the first layers' input tables, empty counters and lists
 // and the start symbol consumed by the empty sequence of every utterance.
-void start_decode(const qrnnt_model *m, const Plan &p, int32_t *n_taken, int32_t *nx_count, hipStream_t st)
+void start_decode(const qrnnt_model *m, const Plan &p, Advance &ad, int32_t *n_taken, int32_t *nx_count, hipStream_t st)
 {
     auto fill = [&](void *at, size_t nw) {
         fill_words_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>((uint32_t *)at, nw, 0u);
@@ -330,7 +345,8 @@ void start_decode(const qrnnt_model *m, const Plan &p, int32_t *n_taken, int32_t
     decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, nx_count,
                                                                        p.rows, p.n_rows, p.node_tok, p.node_prev, p.W, p.B, p.P,
                                                                        m->blank);
-    advance_nets(m, p, nullptr, p.n_rows, st);
+    prepare_advance(m, p, ad);
+    advance_nets(ad, nullptr, p.n_rows, st);
 }
 
 }  // namespace
@@ -376,9 +392,10 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     const size_t Ns = (size_t)N;
     const int ZB = p.NB - 1;   // the beam's buffer in every second frame (else 0)
 
-    start_decode(m, p, p.n_taken, p.nx_count, st);
+    Advance ad;
+    start_decode(m, p, ad, p.n_taken, p.nx_count, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj, alone);
+    QrRoundArgs ja = round_args(m, p, enc_proj, alone, false);
 
     int a0 = 0;   // buffer of the beam at the current frame
     for (int t = 0; t < T; ++t) {
@@ -414,7 +431,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
             ra.n_rows_next = p.n_rows + (size_t)(t & 1) * (max_sym + 2) + v + 1;
             ra.n_rows_clear = p.n_rows + (size_t)((t + 1) & 1) * (max_sym + 2) + v + 1;
             qr_launch_search_round(ja, ra, st);
-            if (!last) advance_nets(m, p, early ? ra.live_next : nullptr, ra.n_rows_next, st);
+            if (!last) advance_nets(ad, early ? ra.live_next : nullptr, ra.n_rows_next, st);
         }
         a0 = (a0 == 0) ? ZB : 0;   // the new beam's buffer
     }
@@ -526,9 +543,10 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_node, Ns, 0u);
         fill_words_kernel<<<(unsigned)((Ns + 255) / 256), 256, 0, st>>>((uint32_t *)ap.fin_len, Ns, 0u);
     }
-    start_decode(m, p, nullptr, nullptr, st);
+    Advance ad;
+    start_decode(m, p, ad, nullptr, nullptr, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj, alone);
+    QrRoundArgs ja = round_args(m, p, enc_proj, alone, true);
 
     int cur = 0;
     for (int i = 0; i < ap.n_iter; ++i) {
@@ -554,7 +572,7 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
         sa.fin_score = ap.fin_score;  sa.fin_node = ap.fin_node;  sa.fin_len = ap.fin_len;
         sa.reuse = (flags & QRNNT_ALSD_REUSE) ? 1 : 0;  sa.stats = stats;
         qr_launch_search_round_alsd(ja, ra, sa, st);
-        if (i + 1 < ap.n_iter) advance_nets(m, p, ra.live_next, ra.n_rows_next, st);
+        if (i + 1 < ap.n_iter) advance_nets(ad, ra.live_next, ra.n_rows_next, st);
         cur = nxt;
     }
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(ap.fin_score, ap.fin_node, ap.fin_len, p.node_tok, p.node_prev, N,

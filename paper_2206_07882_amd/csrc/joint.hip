@@ -788,20 +788,28 @@ template <bool ALSD>
 void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
     constexpr int N_XCD = 8;
-    const bool use_lm = (ALSD || !r.last_round) && (a.head[1].w || a.head[2].w);
-    QrRoundArgs c = a;
-    c.parts = joint_parts(a.J);
-    int wgs = c.parts + (use_lm ? 1 : 0);
-    const bool share = r.W <= 16 && (wgs == 1 || 6 * r.B * wgs <= 5 * resident<ALSD>());
-    for (int net = 0; net < 2 && use_lm; ++net) wgs += a.mid[net].w ? (a.mid[net].rows + 63) / 64 : 0;
-    if (share)
-        search_round_kernel<1, ALSD, true><<<dim3(N_XCD, a.alone ? 1 : wgs, (r.B + N_XCD - 1) / N_XCD), 512, 0, st>>>(c, r, s);
+    const int wgs = ALSD || !r.last_round ? a.wgs_lm : a.wgs_last;
+    if (wgs) search_round_kernel<1, ALSD, true><<<dim3(N_XCD, a.alone ? 1 : wgs, (r.B + N_XCD - 1) / N_XCD), 512, 0, st>>>(a, r, s);
     else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else search_round_kernel<4, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
 }
 
 }  // namespace
+
+void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
+{
+    const int room = alsd ? resident<true>() : resident<false>();
+    a.parts = joint_parts(a.J);
+    a.wgs_lm = a.wgs_last = 0;
+    auto fits = [&](int wgs) { return W <= 16 && (wgs == 1 || 6 * B * wgs <= 5 * room); };
+    const bool use_lm = a.head[1].w || a.head[2].w;
+    if (fits(a.parts)) a.wgs_last = a.parts;
+    if (fits(a.parts + (use_lm ? 1 : 0))) {
+        a.wgs_lm = a.parts + (use_lm ? 1 : 0);
+        for (int net = 0; net < 2; ++net) a.wgs_lm += a.mid[net].w ? (a.mid[net].rows + 63) / 64 : 0;
+    }
+}
 
 // A bottleneck in the round saves its own launch (6 us) and delays the language models by 2 us, as long as two thirds of the
 // workgroups are resident at once.  External language model of 2 x 2048 cells, bottleneck of 256, beam 16, us a round of

@@ -112,12 +112,15 @@ struct QrRoundArgs {
     // value and round number (never 0, no two rounds of a search the same), [16][64] to a source; zeroed before the first round.
     unsigned long long *words;
     unsigned round;
-    int parts;                         // workgroups that share the joint (filled in by the launcher)
+    int parts;                         // workgroups that share the joint, and (a round with language models, one without) all of
+    int wgs_lm, wgs_last;              // an utterance, 0 where it has one that does it all (qr_plan_round)
     int ticks;                         // how long to wait for the others, in 10 ns
     int alone;                         // diagnostic: the others never come
 };
 #define QR_ROUND_PARTS 4
 #define QR_ROUND_WORDS ((QR_ROUND_PARTS + 3) * 16 * 64)   // sources: shares of the joint (of the first one: the source LM), external LM, bottlenecks
+struct QrRoundArgs;
+QR_HIDDEN void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd);
 QR_HIDDEN bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd);   // bottlenecks of so many rows
 
 struct QrRouteArgs {
