@@ -81,3 +81,20 @@ def test_a_workgroup_left_alone_returns_the_same_beams(gpu_lib, J, V, B, W, mixe
             ref = (oracle.decode_alsd if alsd else oracle.decode)(M, e.cpu().numpy(), W, limit, max_len=2 * T)
             _compare_beams(want, ref)
         _compare_beams(batch, [np.tile(w.cpu().numpy(), (many // B,) + (1,) * (w.dim() - 1)) for w in want])
+
+
+def test_a_search_over_more_utterances_than_a_grid_has_layers(gpu_lib):
+    """A joint of 64 columns and no language model: one workgroup to an utterance.  A grid's z extent ends at 65535, and
+    8 x 65535 utterances are not the most that a search takes."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    m = _model(64, 17, False)
+    G, M = gmodel.model_from_float(m, "cuda:0", use_src=False, use_ext=False), omodels.model_from_float(m, use_src=False, use_ext=False)
+    T, few, many = 2, 8, 8 * 65535 + 16
+    e = synth.normal(960, (T, few, 64), 1.0)
+    E = dev(e).repeat(1, many // few, 1).contiguous()
+    for got, ref in ((q.decode(G, E, 1, 1, max_len=T), oracle.decode(M, e, 1, 1, max_len=T)),
+                     (q.decode_alsd(G, E, 1, 1), oracle.decode_alsd(M, e, 1, 1))):
+        _compare_beams([t[:few] for t in got], ref)
+        for t in got:
+            assert torch.equal(t.view(many // few, few, *t.shape[1:]), t[:few].expand(many // few, *t[:few].shape))
