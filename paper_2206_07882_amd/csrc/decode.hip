@@ -30,7 +30,8 @@ struct Plan {
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
     v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the hypotheses that carry a label into round v of the frame, and how many
-    unsigned long long *words;     // [B][QR_ROUND_WORDS]: see QrRoundArgs.words (beams of up to 16)
+    unsigned long long *words;     // [B][n_words]: see QrRoundArgs.words
+    size_t n_words;
     size_t n_clear;                // 32-bit words from `live` on that start at zero: live, n_rows, words
     size_t total;
 };
@@ -67,12 +68,15 @@ void take_nets(const qrnnt_model *m, Plan &p, Carver &cv)
 }
 
 // What starts at zero, in one piece: two sets of counters, and the words on their way between an utterance's workgroups.
-void take_cleared(Plan &p, Carver &cv, size_t n_counters)
+void take_cleared(const qrnnt_model *m, Plan &p, Carver &cv, size_t n_counters)
 {
+    bool mids = false;
+    for (int k = 1; k < 3; ++k) mids = mids || (net_used(m, k) && net_of(m, k)->mid.packed);
+    p.n_words = qr_round_words(p.J, net_used(m, 1) || net_used(m, 2), mids, p.B, p.W);
     p.live = cv.take<int32_t>(n_counters);
     const size_t start = cv.off - n_counters * sizeof(int32_t);
     p.n_rows = cv.take<int32_t>(n_counters);
-    p.words = p.W <= 16 ? cv.take<unsigned long long>((size_t)p.B * QR_ROUND_WORDS) : nullptr;
+    p.words = p.n_words ? cv.take<unsigned long long>(p.B * p.n_words) : nullptr;
     p.n_clear = (cv.off - start) / 4;
 }
 
@@ -111,7 +115,7 @@ void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws,
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
     p.rows = cv.take<v4i>(N);
-    take_cleared(p, cv, 2 * (size_t)(max_sym + 2));
+    take_cleared(m, p, cv, 2 * (size_t)(max_sym + 2));
     p.total = (cv.off + 255) / 256 * 256;
 }
 
@@ -314,7 +318,7 @@ QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_pro
     ja.J = p.J;  ja.V = p.V;  ja.blank = m->blank;
     ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
     ja.w8 = qr_bits(&m->joint_out) == 8;
-    ja.words = p.words;
+    ja.words = p.words;  ja.n_words = p.n_words;
     ja.ticks = alone ? 10 : 1000;   // 10 us; the other workgroups need 3
     ja.alone = alone;
     qr_plan_round(ja, p.B, p.W, alsd);
@@ -486,7 +490,7 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
     p.rows = cv.take<v4i>(N);
-    take_cleared(p, cv, (size_t)ap.n_iter + 2);
+    take_cleared(m, p, cv, (size_t)ap.n_iter + 2);
     p.total = (cv.off + 255) / 256 * 256;
 }
 

@@ -404,7 +404,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         }
     };
     // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
-    auto word_at = [&](int q, int hyp, int token) { return a.words + (size_t)b * QR_ROUND_WORDS + (q * 16 + hyp) * 64 + token; };
+    auto word_at = [&](int q, int hyp, int token) { return a.words + b * a.n_words + (q * 16 + hyp) * 64 + token; };
     auto publish = [&](v4i v, int q, int hyp, int token) {
         v4i *const out = (v4i *)word_at(q, hyp, token);
         out[0] = v4i{v[0], (int)a.round, v[1], (int)a.round};
@@ -764,7 +764,9 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
 
 namespace {
 
-// Workgroups of search_round_kernel<1, ALSD, true> that the device holds at once.
+// Workgroups of search_round_kernel<1, ALSD, true> that the device holds at once; taken to be no more than two to each of 256
+// compute units (registers), so that the size of a search's workspace does not hang on the device.
+constexpr int MOST_RESIDENT = 512;
 template <bool ALSD>
 int resident()
 {
@@ -779,8 +781,10 @@ int resident()
         n = n_cu * per_cu > 0 ? n_cu * per_cu : -1;
         known[dev].store(n, std::memory_order_relaxed);
     }
-    return n > 0 ? n : 0;
+    return n > MOST_RESIDENT ? MOST_RESIDENT : (n > 0 ? n : 0);
 }
+
+bool fit_together(int B, int W, int wgs, int room) { return W <= 16 && 6 * (int64_t)B * wgs <= 5 * (int64_t)room; }
 
 int joint_parts(int J) { return (J + 63) / 64 < QR_ROUND_PARTS ? (J + 63) / 64 : QR_ROUND_PARTS; }
 
@@ -799,6 +803,14 @@ void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &
 
 }  // namespace
 
+// Sources of words: shares of the joint (of the first one: the source LM), external LM, bottlenecks.
+size_t qr_round_words(int J, bool use_lm, bool mids, int B, int W)
+{
+    const int parts = joint_parts(J);
+    if (!(parts > 1 && fit_together(B, W, parts, MOST_RESIDENT)) && !(use_lm && fit_together(B, W, parts + 1, MOST_RESIDENT))) return 0;
+    return (size_t)(mids ? QR_ROUND_PARTS + 3 : (use_lm ? QR_ROUND_PARTS + 1 : parts)) * 16 * 64;
+}
+
 void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
 {
     const int room = alsd ? resident<true>() : resident<false>();
@@ -807,7 +819,7 @@ void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
     // One workgroup to an utterance (a joint of up to 64 columns and no language model) is the faster form at any number of
     // them, K over eight waves and half the registers: 40 frames, ms, 64 utterances at beam 16 3.46 -> 3.39, 420 5.65 -> 3.79,
     // 4000 33.8 -> 19.3.
-    auto fits = [&](int wgs) { return W <= 16 && (wgs == 1 || 6 * B * wgs <= 5 * room); };
+    auto fits = [&](int wgs) { return wgs == 1 ? W <= 16 : fit_together(B, W, wgs, room); };
     const bool use_lm = a.head[1].w || a.head[2].w;
     if (fits(a.parts)) a.wgs_last = a.parts;
     if (fits(a.parts + (use_lm ? 1 : 0))) {
@@ -822,7 +834,7 @@ void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
 bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd)
 {
     const int room = alsd ? resident<true>() : resident<false>();
-    return W <= 16 && mid_rows <= 256 && 6 * B * (QR_ROUND_PARTS + 1) <= 5 * room &&
+    return mid_rows <= 256 && fit_together(B, W, QR_ROUND_PARTS + 1, room) &&
            2 * B * (QR_ROUND_PARTS + 1 + n_mids * ((mid_rows + 63) / 64)) <= 3 * room;
 }
 

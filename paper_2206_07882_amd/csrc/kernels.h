@@ -108,9 +108,10 @@ struct QrRoundArgs {
     float z_scale, z_inv;
     float lambda_src, lambda_ext, rho;
     int J, V, blank, nkc, w8;
-    // Beams of up to 16: values on their way between the workgroups of an utterance (joint.hip), [B][QR_ROUND_WORDS] words of
-    // value and round number (never 0, no two rounds of a search the same), [16][64] to a source; zeroed before the first round.
+    // Several workgroups to an utterance: values on their way between them (joint.hip), n_words (qr_round_words) of value and
+    // round number (never 0, no two rounds of a search the same) each, [16][64] to a source; zeroed before the first round.
     unsigned long long *words;
+    size_t n_words;
     unsigned round;
     int parts;                         // workgroups that share the joint, and (a round with language models, one without) all of
     int wgs_lm, wgs_last;              // an utterance, 0 where it has one that does it all (qr_plan_round)
@@ -118,8 +119,7 @@ struct QrRoundArgs {
     int alone;                         // diagnostic: the others never come
 };
 #define QR_ROUND_PARTS 4
-#define QR_ROUND_WORDS ((QR_ROUND_PARTS + 3) * 16 * 64)   // sources: shares of the joint (of the first one: the source LM), external LM, bottlenecks
-struct QrRoundArgs;
+QR_HIDDEN size_t qr_round_words(int J, bool use_lm, bool mids, int B, int W);   // of an utterance, 0 where it has one workgroup on any device
 QR_HIDDEN void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd);
 QR_HIDDEN bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd);   // bottlenecks of so many rows
 

@@ -177,6 +177,29 @@ def test_validation_of_the_row_quantizer_static_layer_and_diagnostics():
     assert dr(sink=P(0x1002)) == 3
 
 
+@pytest.mark.parametrize("J,lms,W,shared", [(256, True, 1, (1, 85)), (256, True, 16, (1, 85)), (64, True, 4, (1, 213)), (80, False, 2, (1, 213)),
+                                            (64, False, 1, None), (256, True, 17, None)])
+def test_a_search_has_words_between_workgroups_only_where_an_utterance_has_several(J, lms, W, shared):
+    """16 to 57 KB an utterance: far more than the states of a small net, and of no use to a full device.  shared: the
+    range of utterances that may have several workgroups on some device."""
+    import torch
+    mem = torch.zeros(64, dtype=torch.float32)   # (addresses only: nothing is read)
+    mat = lambda rows, cols, layout: qrnnt.QMat(mem, mem, rows, cols, layout)
+    layer = qrnnt.Lstm(mat(64, 16, qrnnt.LAYOUT_TILED_GATES), mat(64, 16, qrnnt.LAYOUT_TILED_GATES), mem, 0.1)
+    net = lambda rows, lm: qrnnt.Net(mem, [layer], mat(rows, 16, qrnnt.LAYOUT_TILED), None, 0.1, lm)
+    model = qrnnt.Model(net(J, False), net(17, True) if lms else None, net(17, True) if lms else None, mat(17, J, qrnnt.LAYOUT_TILED),
+                        None, 0.3, 0.5)
+    for size in (qrnnt.decode_workspace, qrnnt.decode_alsd_workspace):
+        each = lambda lo, hi: (size(model, 1, hi, W, 1) - size(model, 1, lo, W, 1)) / (hi - lo)
+        states = each(10000, 20000)
+        assert 0 < states < 1024 * W
+        assert each(100000, 400000) < 1024 * W
+        assert size(model, 1, 1, W, 1) < 100000 + (0 if shared is None else 7 * 8192)
+        if shared is not None:
+            assert each(*shared) > 2 * 8192
+            assert size(model, 1, 256, W, 1) < size(model, 1, shared[1], W, 1) + 1024 * W * 256
+
+
 def test_product_path_does_not_reference_the_oracle():
     """The GPU package must never import or call the test oracle."""
     pkg = os.path.join(ROOT, "paper_2206_07882_amd")
