@@ -167,6 +167,21 @@ __device__ __forceinline__ v4f qr_token_values(v4i t, bool w8, const float *scal
     return v - lse;
 }
 
+// Words of value and round number for another workgroup, one or four next to each other.  What a reader finds is a whole word
+// or none of it: the store is one instruction, here and not by the compiler's leave, and its 8-byte words are aligned.  It
+// reaches the XCD's L2; at the scope of the device, as 8-byte atomics or as these with sc1, the same stores cost 3 to 11 % of a
+// search (64 x 300 frames, alignment-length search, ms: 16.65, sc1 17.19, atomics 18.42).
+__device__ __forceinline__ void qr_send(unsigned long long *to, unsigned v, unsigned round)
+{
+    asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(to), "v"((unsigned long long)round << 32 | v) : "memory");
+}
+__device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned round)
+{
+    const v4i lo = {v[0], (int)round, v[1], (int)round}, hi = {v[2], (int)round, v[3], (int)round};
+    asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:16\n\ts_nop 1" ::"v"(to), "v"(lo), "v"(hi)
+                 : "memory");   // (s_nop: see qr_store_through)
+}
+
 // One decoding round of an utterance in one workgroup (or several: see CL): output layers of the three networks, joint,
 // log-softmax and fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
 // (route.h), and after the last round of a frame the new beam.  Between the networks' top hidden codes and the picks
@@ -405,11 +420,6 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     };
     // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
     auto word_at = [&](int q, int hyp, int token) { return a.words + b * a.n_words + (q * 16 + hyp) * 64 + token; };
-    auto publish = [&](v4i v, int q, int hyp, int token) {
-        v4i *const out = (v4i *)word_at(q, hyp, token);
-        out[0] = v4i{v[0], (int)a.round, v[1], (int)a.round};
-        out[1] = v4i{v[2], (int)a.round, v[3], (int)a.round};
-    };
 
     if (CL && blockIdx.y + 1 < gridDim.y) {   // uniform: not the first workgroup
         if (!ALSD && r.gate && *r.gate == 0) return;   // uniform
@@ -422,12 +432,12 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             const unsigned code = mid_part(net, p, row);
             const unsigned next = (unsigned)__builtin_amdgcn_update_dpp(0, (int)code, 0xB1 /* the neighbour's */, 0xf, 0xf, true);
             if ((tid & 1) == 0 && p * 64 + z_col < a.mid[net].rows)
-                *word_at(QR_ROUND_PARTS + 1 + net, z_hyp, (p * 64 + z_col) >> 2) = (unsigned long long)a.round << 32 | code | next << 16;
+                qr_send(word_at(QR_ROUND_PARTS + 1 + net, z_hyp, (p * 64 + z_col) >> 2), code | next << 16, a.round);
             return;
         }
         if (part < a.parts) {                          // a share of the joint
             const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
-            if (wave < 4) publish(sum, part, col, wave * 16 + 4 * grp);
+            if (wave < 4) qr_send(word_at(part, col, wave * 16 + 4 * grp), sum, a.round);
             return;
         }
         const int net = wave >> 2;                     // the language models: waves 0-3 source, 4-7 external, K split in four
@@ -470,8 +480,8 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
 #pragma unroll
         for (int k = 0; k < 4; ++k) t += sums[4 * net + k][mt][at];
         const v4f v = qr_token_values(t, h.w8 != 0, jc[1 + net][0], jc[1 + net][1], 4 * quad, V, h.log_softmax != 0);
-        publish(v4i{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])},
-                net == 0 ? 0 : QR_ROUND_PARTS, hc, 4 * quad);
+        qr_send(word_at(net == 0 ? 0 : QR_ROUND_PARTS, hc, 4 * quad),
+                v4i{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])}, a.round);
         return;
     }
 

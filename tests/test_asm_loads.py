@@ -27,3 +27,13 @@ def test_the_search_finds_what_it_looks_for():
     assert _unwaited('#define LD(i) "buffer_load_dword %[v" #i "], %[o], %[r], 0 offen"') == ["buffer_load_dword"]
     assert not _unwaited('asm volatile("global_load_dword %0, %1, off\\n\\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p));')
     assert not _unwaited('asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p));')
+
+
+def test_words_between_workgroups_are_stored_by_their_helper_only():
+    """A word of value and number that another workgroup polls has to be stored in one piece: by qr_send, never by an
+    assignment that the compiler may split."""
+    text = open(os.path.join(CSRC, "joint.hip")).read()
+    uses = re.findall(r".*\bword_at\(.*", text)
+    assert len(uses) >= 5
+    for line in uses:
+        assert "qr_send(word_at(" in line or "(void *)word_at(" in line, line   # (the latter: where loads start)
