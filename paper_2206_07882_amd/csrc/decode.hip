@@ -32,7 +32,8 @@ struct Plan {
     v4i *rows;  int32_t *n_rows;   // [N], [2][max_sym+2]: the hypotheses that carry a label into round v of the frame, and how many
     unsigned long long *words;     // [B][n_words]: see QrRoundArgs.words
     size_t n_words;
-    size_t n_clear;                // 32-bit words from `live` on that start at zero: live, n_rows, words
+    int32_t *late;                 // [B]
+    size_t n_clear;                // 32-bit words from `live` on that start at zero: live, n_rows, late, words
     size_t total;
 };
 
@@ -76,6 +77,7 @@ void take_cleared(const qrnnt_model *m, Plan &p, Carver &cv, size_t n_counters)
     p.live = cv.take<int32_t>(n_counters);
     const size_t start = cv.off - n_counters * sizeof(int32_t);
     p.n_rows = cv.take<int32_t>(n_counters);
+    p.late = p.n_words ? cv.take<int32_t>(p.B) : nullptr;
     p.words = p.n_words ? cv.take<unsigned long long>(p.B * p.n_words) : nullptr;
     p.n_clear = (cv.off - start) / 4;
 }
@@ -291,8 +293,14 @@ void advance_nets(Advance &ad, const int32_t *gate, const int32_t *n_rows, hipSt
     if (ad.mids.n) qr_launch_linear_group(ad.mids, st);
 }
 
+// What a diagnostic call changes (qrnnt_diag_decode_shared).
+struct RoundDiag {
+    int come = 0, n_xcd = 0;
+    int32_t *late_out = nullptr;
+};
+
 // What a decoding round reads of the model.
-QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj, bool alone, bool alsd)
+QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_proj, const RoundDiag &diag, bool alsd)
 {
     QrRoundArgs ja = {};
     for (int k = 0; k < 3; ++k) {
@@ -318,11 +326,18 @@ QrRoundArgs round_args(const qrnnt_model *m, const Plan &p, const float *enc_pro
     ja.J = p.J;  ja.V = p.V;  ja.blank = m->blank;
     ja.nkc = qr_round_up(p.J, QRNNT_KCHUNK) / QRNNT_KCHUNK;
     ja.w8 = qr_bits(&m->joint_out) == 8;
-    ja.words = p.words;  ja.n_words = p.n_words;
-    ja.ticks = alone ? 10 : 1000;   // 10 us; the other workgroups need 3
-    ja.alone = alone;
+    ja.words = p.words;  ja.n_words = p.n_words;  ja.late = p.late;
+    ja.ticks = diag.come == 1 ? 10 : 1000;   // 10 us; the other workgroups need 3
+    ja.come = diag.come;
     qr_plan_round(ja, p.B, p.W, alsd);
+    ja.n_xcd = diag.n_xcd ? diag.n_xcd : ja.n_xcd;
     return ja;
+}
+
+// The end of a diagnostic call: how many rounds of each utterance had a word come late.
+void report_late(const Plan &p, const RoundDiag &diag, hipStream_t st)
+{
+    if (diag.late_out && p.late) (void)hipMemcpyAsync(diag.late_out, p.late, (size_t)p.B * sizeof(int32_t), hipMemcpyDeviceToDevice, st);
 }
 
 // Everything a search starts from: a row of zero states, the first layers' input tables, empty counters and lists
@@ -371,11 +386,10 @@ extern "C" qrnnt_status qrnnt_decode(const qrnnt_model *m, const float *enc_proj
                            workspace_bytes, stream);
 }
 
-// alone: every utterance's other workgroups stay away (QrRoundArgs).
 static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                                      int32_t max_sym, int32_t max_len, uint32_t flags, int32_t *tokens_out,
                                      int32_t *len_out, float *score_out, void *workspace, size_t workspace_bytes,
-                                     void *stream, bool alone)
+                                     void *stream, const RoundDiag &diag = {})
 {
     qrnnt_status s = check_model(m);
     if (s != QRNNT_OK) return s;
@@ -399,7 +413,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     Advance ad;
     start_decode(m, p, ad, p.n_taken, p.nx_count, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj, alone, false);
+    QrRoundArgs ja = round_args(m, p, enc_proj, diag, false);
 
     int a0 = 0;   // buffer of the beam at the current frame
     for (int t = 0; t < T; ++t) {
@@ -442,6 +456,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(p.score + (size_t)a0 * Ns, p.node + (size_t)a0 * Ns,
                                                    p.len + (size_t)a0 * Ns, p.node_tok, p.node_prev, N, max_len,
                                                    tokens_out, len_out, score_out);
+    report_late(p, diag, st);
     return qr_launch_status();
 }
 
@@ -451,7 +466,7 @@ extern "C" qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_p
                                         void *stream)
 {
     return time_synchronous(m, enc_proj, T, B, W, max_sym, max_len, flags, tokens_out, len_out, score_out, workspace,
-                            workspace_bytes, stream, false);
+                            workspace_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -520,7 +535,7 @@ extern "C" qrnnt_status qrnnt_decode_alsd(const qrnnt_model *m, const float *enc
 static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                                                  int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats,
                                                  int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,
-                                                 size_t workspace_bytes, void *stream, bool alone)
+                                                 size_t workspace_bytes, void *stream, const RoundDiag &diag = {})
 {
     qrnnt_status s = check_model(m);
     if (s != QRNNT_OK) return s;
@@ -550,7 +565,7 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
     Advance ad;
     start_decode(m, p, ad, nullptr, nullptr, st);
 
-    QrRoundArgs ja = round_args(m, p, enc_proj, alone, true);
+    QrRoundArgs ja = round_args(m, p, enc_proj, diag, true);
 
     int cur = 0;
     for (int i = 0; i < ap.n_iter; ++i) {
@@ -581,6 +596,7 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
     }
     backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(ap.fin_score, ap.fin_node, ap.fin_len, p.node_tok, p.node_prev, N,
                                                    max_len, tokens_out, len_out, score_out);
+    report_late(p, diag, st);
     return qr_launch_status();
 }
 
@@ -590,15 +606,37 @@ extern "C" qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *
                                              size_t workspace_bytes, void *stream)
 {
     return alignment_length_synchronous(m, enc_proj, T, B, W, u_max, max_len, flags, stats, tokens_out, len_out, score_out,
-                                        workspace, workspace_bytes, stream, false);
+                                        workspace, workspace_bytes, stream);
+}
+
+static qrnnt_status diag_decode(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W, int32_t alsd, int32_t limit,
+                                int32_t max_len, int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,
+                                size_t workspace_bytes, void *stream, const RoundDiag &diag)
+{
+    return alsd ? alignment_length_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, nullptr, tokens_out, len_out, score_out,
+                                               workspace, workspace_bytes, stream, diag)
+                : time_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, tokens_out, len_out, score_out, workspace,
+                                   workspace_bytes, stream, diag);
 }
 
 extern "C" qrnnt_status qrnnt_diag_decode(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                                           int32_t alsd, int32_t limit, int32_t max_len, int32_t *tokens_out, int32_t *len_out,
                                           float *score_out, void *workspace, size_t workspace_bytes, void *stream)
 {
-    return alsd ? alignment_length_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, nullptr, tokens_out, len_out, score_out,
-                                               workspace, workspace_bytes, stream, true)
-                : time_synchronous(m, enc_proj, T, B, W, limit, max_len, 0u, tokens_out, len_out, score_out, workspace,
-                                   workspace_bytes, stream, true);
+    RoundDiag diag;
+    diag.come = 1;
+    return diag_decode(m, enc_proj, T, B, W, alsd, limit, max_len, tokens_out, len_out, score_out, workspace, workspace_bytes, stream, diag);
+}
+
+extern "C" qrnnt_status qrnnt_diag_decode_shared(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
+                                                 int32_t alsd, int32_t limit, int32_t max_len, int32_t come, int32_t n_xcd,
+                                                 int32_t *late_out, int32_t *tokens_out, int32_t *len_out, float *score_out,
+                                                 void *workspace, size_t workspace_bytes, void *stream)
+{
+    QR_REQUIRE(come >= 0 && n_xcd >= 0 && n_xcd <= 32, QRNNT_ERR_RANGE);
+    RoundDiag diag;
+    diag.come = come;
+    diag.n_xcd = n_xcd;
+    diag.late_out = late_out;
+    return diag_decode(m, enc_proj, T, B, W, alsd, limit, max_len, tokens_out, len_out, score_out, workspace, workspace_bytes, stream, diag);
 }

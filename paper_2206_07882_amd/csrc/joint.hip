@@ -211,7 +211,8 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 // (ids congruent modulo the number of XCDs; nothing but the time depends on that), value and round number in one 8-byte
 // word, so that every word says by itself whether it is there: no flag, no order of stores.  The others wait for nobody (the
 // one with the language models for bottlenecks only), and nobody waits for long: what has not come after `ticks` the first
-// one does itself.  A bottleneck in front of a language model's output layer is contracted in the round too, 64 rows to a
+// one does itself, and counts the round; where this keeps happening (words that stay in another XCD's L2, say) a quarter of the
+// time has to do from then on.  A bottleneck in front of a language model's output layer is contracted in the round too, 64 rows to a
 // workgroup (qr_round_takes).  The last round of a frame has blanks to offer only,
 // and no use for the language models.  Stamps of the first workgroup (one utterance at beam 16, ns after its start, one
 // workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end 9900 -> 7500; a round of three
@@ -418,6 +419,12 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             }
         }
     };
+    // A wait for words has lasted `limit` (a quarter of the time at first): true if it is enough.
+    auto enough = [&](unsigned &limit) {
+        if (limit == (unsigned)a.ticks || a.late[b] >= 8) return true;   // uniform
+        limit = (unsigned)a.ticks;
+        return false;
+    };
     // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
     auto word_at = [&](int q, int hyp, int token) { return a.words + b * a.n_words + (q * 16 + hyp) * 64 + token; };
 
@@ -452,6 +459,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                 const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc((void *)word_at(QR_ROUND_PARTS + 1 + net, 0, 0), 0,
                                                                                       16 * 64 * 8, 0x00020000 /* raw bytes */);
                 const bool mine = c0 < a.mid[net].rows;
+                unsigned limit = (unsigned)a.ticks / 4;
                 for (const unsigned long long t0 = wall_clock64();;) {
                     const unsigned off = (unsigned)(hyp * 64 + (tid & 15) * 4) * 8;
                     const v4i u = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off, 0, 16 /* sc1 */);
@@ -463,7 +471,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
                         *(v4i *)&mid_code[net][hyp][c0] = v4i{u[0], u[2], v[0], v[2]};
                         break;
                     }
-                    if (wall_clock64() - t0 > (unsigned long long)a.ticks) {
+                    if (wall_clock64() - t0 > limit && enough(limit)) {
                         if (lane == 0) missed = 1;
                         break;
                     }
@@ -563,13 +571,14 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             const v4i sum = joint_part(0, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
             request();
             if (wave < 4) sums[0][wave][grp * 16 + (col ^ (4 * wave + grp))] = sum;
+            unsigned limit = (unsigned)a.ticks / 4;
             for (const unsigned long long t0 = wall_clock64();; request()) {
                 bool ok = true;
 #pragma unroll
                 for (int i = 0; i < 2 * (QR_ROUND_PARTS - 1); ++i)
                     if (i < 2 * n_src) ok = ok && (unsigned)word[i][1] == a.round && (unsigned)word[i][3] == a.round;
                 if (__all(ok)) break;
-                if (wall_clock64() - t0 > (unsigned long long)a.ticks) {
+                if (wall_clock64() - t0 > limit && enough(limit)) {
                     if (lane == 0) missed = 1;
                     break;
                 }
@@ -660,6 +669,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         if (wave < 4) t += sums[0][mt][at];
         if (!CL && wave < 4) t += sums[1][mt][at] + sums[2][mt][at] + sums[3][mt][at];
         if (CL && __builtin_amdgcn_readfirstlane(missed)) {   // uniform: everything that should have come
+            if (tid == 0) a.late[b] += 1;
             if (wave < 4) t = sums[0][mt][at];
             own_lm = use_lm;
             __syncthreads();
@@ -777,21 +787,27 @@ namespace {
 // Workgroups of search_round_kernel<1, ALSD, true> that the device holds at once; taken to be no more than two to each of 256
 // compute units (registers), so that the size of a search's workspace does not hang on the device.
 constexpr int MOST_RESIDENT = 512;
+struct RoundRoom {
+    int n_xcd, wgs;
+};
 template <bool ALSD>
-int resident()
+RoundRoom resident()
 {
-    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none
+    static std::atomic<int> known[QR_MAX_DEVICES];   // 0: not asked yet, -1: none, else wgs * 64 + n_xcd
     const int dev = qr_current_device();
     int n = known[dev].load(std::memory_order_relaxed);
     if (n == 0) {
-        int n_cu = 0, per_cu = 0;
+        int n_cu = 0, per_cu = 0, n_xcd = 0;
         if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n_xcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, search_round_kernel<1, ALSD, true>, 512, 0) != hipSuccess)
-            return 0;
-        n = n_cu * per_cu > 0 ? n_cu * per_cu : -1;
+            return {1, 0};
+        n_xcd = n_xcd < 1 || n_xcd > 32 ? 8 : n_xcd;
+        n = n_cu * per_cu < MOST_RESIDENT ? n_cu * per_cu : MOST_RESIDENT;
+        n = n > 0 ? n * 64 + n_xcd : -1;
         known[dev].store(n, std::memory_order_relaxed);
     }
-    return n > MOST_RESIDENT ? MOST_RESIDENT : (n > 0 ? n : 0);
+    return n > 0 ? RoundRoom{n & 63, n >> 6} : RoundRoom{1, 0};
 }
 
 bool fit_together(int B, int W, int wgs, int room) { return W <= 16 && 6 * (int64_t)B * wgs <= 5 * (int64_t)room; }
@@ -801,11 +817,11 @@ int joint_parts(int J) { return (J + 63) / 64 < QR_ROUND_PARTS ? (J + 63) / 64 :
 template <bool ALSD>
 void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &s, hipStream_t st)
 {
-    constexpr int N_XCD = 8;
-    const int wgs = ALSD || !r.last_round ? a.wgs_lm : a.wgs_last;
+    int wgs = ALSD || !r.last_round ? a.wgs_lm : a.wgs_last;
+    if (a.come > 0 && a.come < wgs) wgs = a.come;
     // (one workgroup to an utterance: any number of utterances, and a grid's z extent ends at 65535)
-    if (wgs == 1 || (wgs && a.alone)) search_round_kernel<1, ALSD, true><<<r.B, 512, 0, st>>>(a, r, s);
-    else if (wgs) search_round_kernel<1, ALSD, true><<<dim3(N_XCD, wgs, (r.B + N_XCD - 1) / N_XCD), 512, 0, st>>>(a, r, s);
+    if (wgs == 1) search_round_kernel<1, ALSD, true><<<r.B, 512, 0, st>>>(a, r, s);
+    else if (wgs) search_round_kernel<1, ALSD, true><<<dim3(a.n_xcd, wgs, (r.B + a.n_xcd - 1) / a.n_xcd), 512, 0, st>>>(a, r, s);
     else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else search_round_kernel<4, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
@@ -823,7 +839,9 @@ size_t qr_round_words(int J, bool use_lm, bool mids, int B, int W)
 
 void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
 {
-    const int room = alsd ? resident<true>() : resident<false>();
+    const RoundRoom on = alsd ? resident<true>() : resident<false>();
+    const int room = on.wgs;
+    a.n_xcd = on.n_xcd;
     a.parts = joint_parts(a.J);
     a.wgs_lm = a.wgs_last = 0;
     // One workgroup to an utterance (a joint of up to 64 columns and no language model) is the faster form at any number of
@@ -843,7 +861,7 @@ void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd)
 // joint, steps and (before) bottleneck: 1 utterance 25.0 -> 22.4, 48 57.3 -> 54.8, 64 65.4 -> 62.6, 85 77.5 -> 74.9.
 bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd)
 {
-    const int room = alsd ? resident<true>() : resident<false>();
+    const int room = (alsd ? resident<true>() : resident<false>()).wgs;
     return mid_rows <= 256 && fit_together(B, W, QR_ROUND_PARTS + 1, room) &&
            2 * B * (QR_ROUND_PARTS + 1 + n_mids * ((mid_rows + 63) / 64)) <= 3 * room;
 }

@@ -64,7 +64,8 @@ EXPORTS = ["qrnnt_status_str", "qrnnt_abi_version", "qrnnt_pack_int4_bytes", "qr
            "qrnnt_bilstm_layer_workspace", "qrnnt_bilstm_layer", "qrnnt_lstm_layer_static",
            "qrnnt_joint_fuse", "qrnnt_beam_step", "qrnnt_decode_workspace", "qrnnt_decode", "qrnnt_decode_ex",
            "qrnnt_decode_alsd_workspace", "qrnnt_decode_alsd", "qrnnt_decode_alsd_ex",
-           "qrnnt_diag_mfma_forms", "qrnnt_diag_mfma_form_name", "qrnnt_diag_mfma_rate", "qrnnt_diag_lstm_layer", "qrnnt_diag_decode"]
+           "qrnnt_diag_mfma_forms", "qrnnt_diag_mfma_form_name", "qrnnt_diag_mfma_rate", "qrnnt_diag_lstm_layer", "qrnnt_diag_decode",
+           "qrnnt_diag_decode_shared"]
 
 DECODE_EARLY_STOP = 1
 

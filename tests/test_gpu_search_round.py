@@ -98,3 +98,70 @@ def test_a_search_over_more_utterances_than_a_grid_has_layers(gpu_lib):
         _compare_beams([t[:few] for t in got], ref)
         for t in got:
             assert torch.equal(t.view(many // few, few, *t.shape[1:]), t[:few].expand(many // few, *t[:few].shape))
+
+
+def _diag_shared(q, G, e, W, alsd, limit, max_len, come, n_xcd=0):
+    T, B, _ = e.shape
+    size = q.decode_alsd_workspace if alsd else q.decode_workspace
+    ws = torch.empty(size(G, T, B, W, limit), dtype=torch.uint8, device="cuda:0")
+    late = torch.full((B,), -1, dtype=torch.int32, device="cuda:0")
+    out = [torch.empty(s, dtype=d, device="cuda:0") for s, d in (((B, W, max_len), torch.int32), ((B, W), torch.int32), ((B, W), torch.float32))]
+    q._check(q.load().qrnnt_diag_decode_shared(C.byref(G.c()), C.c_void_p(e.data_ptr()), T, B, W, alsd, limit, max_len, come, n_xcd,
+                                               C.c_void_p(late.data_ptr()), *(C.c_void_p(t.data_ptr()) for t in out),
+                                               C.c_void_p(ws.data_ptr()), C.c_size_t(ws.numel()), q._stream()), "qrnnt_diag_decode_shared")
+    return out, late.cpu().numpy()
+
+
+@pytest.mark.parametrize("J,V,B,W,mixed,mids", [(256, 46, 1, 16, False, ()), (272, 48, 2, 16, True, ()), (64, 33, 3, 1, False, ()),
+                                                (256, 46, 9, 16, False, ((2, 256),)), (80, 17, 3, 7, True, ((1, 80), (2, 144)))])
+@pytest.mark.parametrize("alsd", [0, 1])
+def test_some_of_a_beams_workgroups_come(gpu_lib, J, V, B, W, mixed, mids, alsd):
+    """Whichever of them stay away (shares of the joint, the language models', the bottlenecks' that those wait for), or do
+    their work on other XCDs: the same bits, and the first one has to step in.  When all come it hardly ever has to."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    G = gmodel.model_from_float(_model(J, V, mixed, mids), "cuda:0")
+    T, limit = 24, 6 if alsd else 2
+    e = dev(synth.normal(970 + J, (T, B, J), 1.0))
+    parts = min((J + 63) // 64, 4)
+    total = parts + 1 + sum((rows + 63) // 64 for _, rows in mids)
+    want = (q.decode_alsd if alsd else q.decode)(G, e, W, limit, max_len=2 * T)
+    for come in range(1, total + 1):
+        got, late = _diag_shared(q, G, e, W, alsd, limit, 2 * T, come)
+        for w, g in zip(want, got):
+            assert torch.equal(w, g), come
+        if come == total:
+            assert late.max() <= T // 4, late
+        else:   # every round that has a use for them: all but a frame's last one, and that too for the joint
+            assert late.min() >= (T - 1 if alsd else T * (limit + (come < parts))), (come, late)
+    got, _ = _diag_shared(q, G, e, W, alsd, limit, 2 * T, 0, n_xcd=7)
+    for w, g in zip(want, got):
+        assert torch.equal(w, g)
+
+
+def test_searches_on_several_streams(gpu_lib):
+    """Three searches of 48 utterances, each alone worth more than half of the device, and an encoder layer beside them: a
+    beam's workgroups come late or one by one, and the results are those of a search on its own."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    T, B, W = 20, 48, 16
+    m = _model(256, 46, False, ((2, 256),))
+    G = gmodel.model_from_float(m, "cuda:0")
+    L = gmodel.lstm_from_float(synth.make_model(4, enc_layers=1).enc_layers[0][0], gmodel.S_H, "cuda:0")
+    x = dev(synth.codes(981, (200, 32, L.I)))
+    es = [dev(synth.normal(982 + i, (T, B, 256), 1.0)) for i in range(3)]
+    want = [fn(G, e, W, 4, max_len=2 * T) for e in es for fn in (q.decode, q.decode_alsd)]
+    want_h = q.lstm_layer(L, x)["h_out"]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    torch.cuda.synchronize()
+    got = []
+    for e, s in zip(es, streams):
+        with torch.cuda.stream(s):
+            got += [fn(G, e, W, 4, max_len=2 * T) for fn in (q.decode, q.decode_alsd)]
+    with torch.cuda.stream(streams[3]):
+        hs = [q.lstm_layer(L, x)["h_out"] for _ in range(4)]
+    torch.cuda.synchronize()
+    for a, b in zip(want, got):
+        for w, g in zip(a, b):
+            assert torch.equal(w, g)
+    assert all(torch.equal(h, want_h) for h in hs)
