@@ -544,11 +544,20 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         float e_score = 0.0f;
         v4i e_info = zero;
         const int e0 = tid - 256;
-        if (frame_end && nt == 0 && e0 >= 0 && e0 < n_entries) {
-            e_score = r.nx_score[nx + e0];
-            e_info = r.nx_info[nx + e0];
-        }
-        if (ALSD && nt == 0 && wave == 5) finished = qr_alsd_load_finished(r, s, b, lane);
+        auto load_rest = [&]() {
+            if (frame_end && nt == 0 && e0 >= 0 && e0 < n_entries) {
+                e_score = r.nx_score[nx + e0];
+                e_info = r.nx_info[nx + e0];
+            }
+            if (ALSD && nt == 0 && wave == 5) finished = qr_alsd_load_finished(r, s, b, lane);
+        };
+        auto enter_rest = [&]() {
+            if (frame_end && nt == 0 && e0 >= 0) {
+                if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
+                for (int e = e0 + 256; e < n_entries; e += 256) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
+            }
+        };
+        if (CL) load_rest();
         // CL: the words of the other workgroups that this thread of the scores (waves 0-3: shares of the joint; waves 4-7, for
         // the same thread of waves 0-3: language models) waits for, past this CU's cache
         v4i word[2 * (CL ? QR_ROUND_PARTS - 1 : 1)];
@@ -651,14 +660,13 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             }
         } else {
             const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
-            if (h.w && use_lm) head_mma(std::integral_constant<int, NTW == 1 ? 4 : 2>{}, h, row, wave & 1, 2, acc);   // uniform
+            load_rest();
+            if (h.w && !frame_end) head_mma(std::integral_constant<int, NTW == 1 ? 4 : 2>{}, h, row, wave & 1, 2, acc);   // uniform
+            enter_rest();
         }
-        if (frame_end && nt == 0 && e0 >= 0) {
-            if (e0 < n_entries) list_entry(e0, e_score, e_info);   // (entries behind the end of the list are overwritten or not counted)
-            for (int e = e0 + 256; e < n_entries; e += 256) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
-        }
+        if (CL) enter_rest();
         if (!CL) put_sums(acc);
-        if (ALSD && r.gate && *r.gate == 0) return;   // uniform: no live hypothesis anywhere, the finals stay as they are
+        if (ALSD && nt == 0 && r.gate && *r.gate == 0) return;   // uniform: no live hypothesis anywhere, the finals stay as they are
         __syncthreads();
 
         // ---- scores: hypothesis 16 * nt + hc, tokens 4 * quad .. 4 * quad + 3
@@ -666,8 +674,9 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         const int at = (quad & 3) * 16 + (hc ^ quad), k0 = 4 * quad;
         v4f v[3];   // joint, source LM, external LM
         bool own_lm = !CL;   // the language models' sums lie in LDS
-        if (wave < 4) t += sums[0][mt][at];
-        if (!CL && wave < 4) t += sums[1][mt][at] + sums[2][mt][at] + sums[3][mt][at];
+        if (!CL && wave >= 4) continue;
+        if (!CL) t = (sums[0][mt][at] + sums[1][mt][at]) + (sums[2][mt][at] + sums[3][mt][at]);
+        if (CL && wave < 4) t += sums[0][mt][at];
         if (CL && __builtin_amdgcn_readfirstlane(missed)) {   // uniform: everything that should have come
             if (tid == 0) a.late[b] += 1;
             if (wave < 4) t = sums[0][mt][at];
@@ -692,7 +701,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             }
             __syncthreads();
         }
-        if (wave >= 4) continue;
+        if (CL && wave >= 4) continue;
         v[0] = qr_token_values(t, a.w8 != 0, jc[0][0], jc[0][1], k0, V, true);
 #pragma unroll
         for (int q = 1; q < 3; ++q) {
