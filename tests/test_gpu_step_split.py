@@ -22,7 +22,8 @@ pytestmark = pytest.mark.gpu
                                                     (300, 144, 80, False, 192), (300, 144, 80, False, 193), (600, 64, 48, False, 128),
                                                     (600, 64, 48, False, 129), (257, 1040, 16, False, 1), (250, 3200, 32, False, 222),
                                                     (257, 3200, 32, False, 33), (200, 64, 80, "table", 64), (130, 64, 1040, "sums", 65),
-                                                    (1030, 80, 272, "table", 63)])
+                                                    (1030, 80, 272, "table", 63), (300, 64, 1376, False, 160), (300, 64, 1376, False, 161),
+                                                    (144, 64, 1376, False, 144)])
 def test_split_step(gpu_lib, N, I, H, looked_up, listed):
     q = gpu_lib
     s_x = float(np.float32(4) / np.float32(7))
