@@ -11,9 +11,9 @@
 
 namespace {
 
-// Bandwidth-bound variant (few hypotheses, e.g. one utterance at beam 16).
-// The packed weights are streamed exactly once per 16 hypotheses: a workgroup owns one row
-// tile (4 cells) x one column tile (16 hypotheses); its 128-column chunks of W_ih and W_hh are
+// Bandwidth-bound variant (up to 16 hypotheses, e.g. one utterance at beam 16).
+// The packed weights are streamed exactly once: a workgroup owns one row
+// tile (4 cells) x all hypotheses; its 128-column chunks of W_ih and W_hh are
 // dealt round-robin to the 4 waves, every wave issues all of its loads before its first MFMA
 // (what keeps the whole matrix in flight across the chip), and the partial sums meet in LDS.
 // Wave 0 then finishes the 4 cells, one (cell, hypothesis) per lane.  N = 16 is exactly one
@@ -21,7 +21,7 @@ namespace {
 // weight stream and by its chain of dependent loads, which is kept to two links: the row indices
 // go first, then the weight loads (which depend on nothing), then, while those arrive, everything
 // that depends on the indices, including what the cell update will need.
-// Grid: x = row tiles, y = column tiles, z = problem of a group.
+// Grid: x = row tiles, y = problem of a group.
 constexpr int SMALL_BATCH = 4;   // chunks per wave per batch (K <= 2048 in one batch)
 
 template <bool USE_GX>
@@ -29,11 +29,10 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
 {
     __shared__ v4i part[3][2][64];   // waves 1..3: [x|h][lane]
     if (g.gate && *g.gate == 0) return;   // uniform: a decoding round without any live hypothesis
-    const QrStepArgs a = g.p[blockIdx.z];   // a copy: the fields arrive with a few wide scalar loads up front
+    const QrStepArgs a = g.p[blockIdx.y];   // a copy: the fields arrive with a few wide scalar loads up front
     const int H = a.H, N = a.N;
     const int rt = blockIdx.x;
-    const int n0 = blockIdx.y * 16;
-    if (rt >= (H >> 2) || n0 >= N) return;   // uniform
+    if (rt >= (H >> 2)) return;   // uniform
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: MFMAs below sit under wave-uniform branches
     const int col = lane & 15, grp = lane >> 4;
@@ -44,8 +43,8 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
 
     // ---- indices first (memory answers in order: what hangs on them can then go out while the weights arrive), then the
     // first batch of weight fragments, which depends on nothing
-    bool n_ok = n0 + col < N;
-    int nn = n_ok ? n0 + col : N - 1;
+    bool n_ok = col < N;
+    int nn = n_ok ? col : N - 1;
     v4i entry = zero;
     int s = nn, xr = nn;
     if (g.rows) {   // row j of the problem stands for the hypothesis of entry j (see QrStepGroup.rows)
@@ -72,8 +71,8 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
     __builtin_amdgcn_sched_barrier(0);
     if (g.rows) {
         const int n_cnt = *g.n_rows;
-        if (n0 >= n_cnt) return;   // uniform
-        n_ok = n0 + col < n_cnt;
+        if (n_cnt <= 0) return;   // uniform
+        n_ok = col < n_cnt;
         nn = entry[0] < 0 ? 0 : (entry[0] >= a.n_out ? a.n_out - 1 : entry[0]);
         s = a.parent ? entry[1] : nn;
         xr = a.x_row ? entry[2] : nn;
@@ -148,9 +147,9 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
     ah = ah >> 4;
     float p[4];
 #pragma unroll
-    for (int gt = 0; gt < 4; ++gt) p[gt] = sx[gt] * (float)ax[gt] + (sh[gt] * (float)ah[gt] + bb[gt]);
+    for (int gt = 0; gt < 4; ++gt) p[gt] = __builtin_fmaf(sx[gt], (float)ax[gt], __builtin_fmaf(sh[gt], (float)ah[gt], bb[gt]));
     const float gi = qr_sigmoid(p[0]), gf = qr_sigmoid(p[1]), gg = qr_tanh(p[2]), go = qr_sigmoid(p[3]);
-    float cn = gf * cp + gi * gg;
+    float cn = __builtin_fmaf(gf, cp, gi * gg);   // (the roundings of split_body's FEW form, and of no other choice)
     const float h = go * qr_tanh(cn);
     int code = qr_quant4(h, a.h_inv);
     const bool on = act != 0;
@@ -176,12 +175,9 @@ __global__ __launch_bounds__(256) void lstm_step_small_kernel(const QrStepGroup 
 template <bool USE_GX>
 void launch_small(const QrStepGroup &g, hipStream_t st)
 {
-    int max_n = 0, max_rt = 0;
-    for (int i = 0; i < g.n; ++i) {
-        max_n = g.p[i].N > max_n ? g.p[i].N : max_n;
-        max_rt = (g.p[i].H >> 2) > max_rt ? (g.p[i].H >> 2) : max_rt;
-    }
-    lstm_step_small_kernel<USE_GX><<<dim3(max_rt, (max_n + 15) / 16, g.n), 256, 0, st>>>(g);
+    int max_rt = 0;
+    for (int i = 0; i < g.n; ++i) max_rt = (g.p[i].H >> 2) > max_rt ? (g.p[i].H >> 2) : max_rt;
+    lstm_step_small_kernel<USE_GX><<<dim3(max_rt, g.n), 256, 0, st>>>(g);
 }
 
 // Between the two: some dozens to some hundreds of hypotheses.  A workgroup owns 4 row tiles (16 cells) x 2 column tiles

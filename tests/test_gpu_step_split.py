@@ -23,7 +23,9 @@ pytestmark = pytest.mark.gpu
                                                     (600, 64, 48, False, 129), (257, 1040, 16, False, 1), (250, 3200, 32, False, 222),
                                                     (257, 3200, 32, False, 33), (200, 64, 80, "table", 64), (130, 64, 1040, "sums", 65),
                                                     (1030, 80, 272, "table", 63), (300, 64, 1376, False, 160), (300, 64, 1376, False, 161),
-                                                    (144, 64, 1376, False, 144)])
+                                                    (144, 64, 1376, False, 144), (17, 48, 80, False, None), (20, 272, 48, "sums", None),
+                                                    (31, 32, 1040, "table", None), (32, 2080, 32, False, None), (32, 144, 272, False, 17),
+                                                    (32, 64, 80, "table", 31), (20, 80, 1040, "sums", 16)])
 def test_split_step(gpu_lib, N, I, H, looked_up, listed):
     q = gpu_lib
     s_x = float(np.float32(4) / np.float32(7))
@@ -69,3 +71,30 @@ def test_split_step(gpu_lib, N, I, H, looked_up, listed):
     assert_codes_close(h[on], hr[on], dbg["h_real"][on] * 7.0, "h")
     off = np.setdiff1d(who, on)
     assert np.array_equal(h[off], hp[parent[off]])
+
+
+@pytest.mark.parametrize("I,H", [(48, 80), (1040, 272), (64, 1040)])
+@pytest.mark.parametrize("looked_up", [False, "sums", "table"])
+def test_up_to_32_hypotheses_one_arithmetic(gpu_lib, I, H, looked_up):
+    """Up to 16 hypotheses the weights are streamed, with 17 to 32 K is split: a hypothesis gets the same bits either way."""
+    q = gpu_lib
+    s_x = float(np.float32(4) / np.float32(7))
+    _, G = _lstm_pair(q, 2400 + I + H, I, H, s_x)
+    x, hp, cp = dev(synth.codes(2401, (32, I), -8, 7)), dev(synth.codes(2402, (32, H), -7, 7)), dev(synth.normal(2403, (32, H), 0.6))
+    active = dev((np.arange(32) % 5 != 1).astype(np.uint8))
+    rows = dev(np.arange(32, dtype=np.int32)[::-1].copy())
+    first = {}
+    for N in (16, 17, 20, 31, 32):
+        d = dict(L=G, N=N, x_codes=x, x_row=rows[:N].contiguous(), parent=(rows[:N] % N).contiguous(),
+                 h_prev=hp[:N].contiguous(), c_prev=cp[:N].contiguous(), active=active[:N].contiguous(),
+                 h_next=torch.empty((N, H), dtype=torch.int8, device="cuda:0"), c_next=torch.empty((N, H), device="cuda:0"))
+        d["parent"][:16] = torch.arange(16, dtype=torch.int32, device="cuda:0").flip(0)   # (the first 16 are the same hypotheses in all)
+        if looked_up:
+            d["gx"] = q.input_projection(G, x)[0]
+            if looked_up == "table":
+                d["gx_table"] = q.input_table(G, d["gx"])
+        q.StepGroup([d]).launch()
+        got = d["h_next"][:16], d["c_next"][:16]
+        first = first or dict(zip("hc", got))
+        for k, v in zip("hc", got):
+            assert torch.equal(v, first[k]), (N, k)
