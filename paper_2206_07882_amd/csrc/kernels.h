@@ -104,7 +104,6 @@ struct QrRoundArgs {
     QrMidArgs mid[2];                  // of the source and the external LM, where the round takes them in (qr_round_takes)
     const float *enc;  int frame_base; // time-synchronous search: utterance b reads row frame_base + b
     const int32_t *row;                // [N] pool row of every hypothesis
-    int32_t *late;                     // [B] rounds so far in which a word (see below) had not come in time
     const v4i *w;  const float *s_w;  const float *b_out;   // the joint's output layer
     float z_scale, z_inv;
     float lambda_src, lambda_ext, rho;
@@ -119,6 +118,8 @@ struct QrRoundArgs {
     int ticks;                         // how long to wait for the others, in 10 ns
     int n_xcd;                         // XCDs that the workgroups of a launch go to in turn
     int come;                          // diagnostic: how many of an utterance's workgroups there are, the first one included (0: all)
+    // (Last: between what every workgroup reads first it cost one utterance 0.6 % of its search.)
+    int32_t *late;                     // [B] rounds so far in which a word had not come in time
 };
 #define QR_ROUND_PARTS 4
 QR_HIDDEN size_t qr_round_words(int J, bool use_lm, bool mids, int B, int W);   // of an utterance, 0 where it has one workgroup on any device
