@@ -184,8 +184,8 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 
 // One decoding round of an utterance in one workgroup (or several: see CL): output layers of the three networks, joint,
 // log-softmax and fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
-// (route.h), and after the last round of a frame the new beam.  Between the networks' top hidden codes and the picks
-// nothing touches memory.
+// (route.h), and after the last round of a frame the new beam.  In one workgroup nothing touches memory between the networks'
+// top hidden codes and the picks.
 //   contraction, waves 0-3: the prediction network's output layer and the joint.  A wave owns 64-column blocks of the
 //     joint: it contracts the 64 rows of the output layer that produce them, 16 to an MFMA, dealt so that a lane ends
 //     up with the 16 consecutive columns that are its operand of the joint's contraction (row r of tile mt is row
@@ -195,11 +195,11 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 //     hypothesis, four tokens each, and form the three log-softmaxes and the fused score together.
 //   selection, waves 0-3: the W-th best of the best ones of 64 groups of candidates or more bounds the W-th best
 //     candidate from below; what passes the bound is gathered in LDS and ranked by counting.
-// The kernel is bound by its chain of dependent steps, and the chain by one compute unit's path to L2 (145 KB of weights
-// and 80 KB of codes: 44 KB of them, the prediction network's fetched by four waves; 36 bytes a cycle measured) and by
-// single waves running straight-line code, hence the split of every step over four waves.  Measured, one utterance at
-// beam 16: 10.1 us, where a launch for the output layers and one for joint, selection and routing in single waves took
-// 7.0 + 10.9 us.
+// One workgroup (beams of more than 16, more than about 100 utterances) is bound by its chain of dependent steps, and the
+// chain by one compute unit's path to L2 (145 KB of weights and 80 KB of codes: 44 KB of them, the prediction network's
+// fetched by four waves; 36 bytes a cycle measured) and by single waves running straight-line code, hence the split of every
+// step over four waves.  Measured in this form, one utterance at beam 16: 10.1 us, where a launch for the output layers and
+// one for joint, selection and routing in single waves took 7.0 + 10.9 us.
 // ALSD: the same inside the alignment-length synchronous search (route.h, qr_alsd_route): every hypothesis reads its
 // own encoder frame (iteration - labels so far), a blank at the last frame finishes a hypothesis instead of being a
 // candidate, labels beyond the cap are no candidates.
@@ -207,16 +207,16 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 // faster form, 100 utterances at beam 1 30.7 us a round against 32.1): an utterance has up to QR_ROUND_PARTS workgroups that
 // share the joint, 64 columns at a time (its output layer's sums add up), and one that contracts the language models' output
 // layers and forms their log-probabilities; the first one collects and goes on alone.  One compute unit's path to L2 no
-// longer bounds the round: 36 KB to a workgroup instead of 225.  What they send goes through the L2 of the XCD they run on
-// (ids congruent modulo the number of XCDs; nothing but the time depends on that), value and round number in one 8-byte
-// word, so that every word says by itself whether it is there: no flag, no order of stores.  The others wait for nobody (the
-// one with the language models for bottlenecks only), and nobody waits for long: what has not come after `ticks` the first
-// one does itself, and counts the round; where this keeps happening (words that stay in another XCD's L2, say) a quarter of the
-// time has to do from then on.  A bottleneck in front of a language model's output layer is contracted in the round too, 64 rows to a
-// workgroup (qr_round_takes).  The last round of a frame has blanks to offer only,
-// and no use for the language models.  Stamps of the first workgroup (one utterance at beam 16, ns after its start, one
-// workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end 9900 -> 7500; a round of three
-// launches 23.3 -> 20.5 us, of 64 utterances (batch of 1000 frames, all rounds) 37.3 -> 36.5.
+// longer bounds the round: 36 KB to a share of the joint and 80 KB to the language models (base networks) instead of 225.
+// What they send goes through the L2 of the XCD they run on (ids congruent modulo the number of XCDs; nothing but the time
+// depends on that), value and round number in one 8-byte word, so that every word says by itself whether it is there: no
+// flag, no order of stores.  The others wait for nobody (the one with the language models for bottlenecks only), and nobody
+// waits for long: what has not come after `ticks` the first one does itself, and counts the round; where this keeps happening
+// (words that stay in another XCD's L2, say) a quarter of the time has to do from then on.  A bottleneck in front of a
+// language model's output layer is contracted in the round too, 64 rows to a workgroup (qr_round_takes).  The last round of a
+// frame has blanks to offer only, and no use for the language models.  Stamps of the first workgroup (one utterance at beam
+// 16, ns after its start, one workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end
+// 9900 -> 7500; a round of three launches 23.3 -> 20.5 us, of 64 utterances (batch of 1000 frames, all rounds) 37.3 -> 36.5.
 // (Two workgroups, the second with the language models: the first one's share still took 4.2 us, no gain.)
 template <int NTW, bool ALSD, bool CL>
 __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)

@@ -182,8 +182,9 @@ void launch_small(const QrStepGroup &g, hipStream_t st)
 
 // Between the two: some dozens to some hundreds of hypotheses.  A workgroup owns 4 row tiles (16 cells) x 2 column tiles
 // (32 hypotheses); its 8 waves (4 for a short list in the tiled kernel's launch) split K (the input part to the first half,
-// the recurrent part to the other; with a looked-up input part all share the recurrent one), so no operand is wanted by two waves and every one goes from memory to
-// registers, a whole batch of chunks in flight per wave, without a ring, its barriers and its index arithmetic.  One
+// the recurrent part to the other; with a looked-up input part all share the recurrent one), so no operand is wanted by two
+// waves and every one goes from memory to registers, a whole batch of chunks in flight per wave, without a ring, its barriers
+// and its index arithmetic.  One
 // exchange through LDS adds the partial sums, after which wave w finishes tile w (and w + 4), one (cell, hypothesis) per lane.
 // Bound by its chain (arguments, list entry, codes, contraction, exchange, cell) while one round of workgroups covers
 // the list, by the path from L2 to the compute units beyond (a column block fetches the weights again, and codes in half

@@ -859,8 +859,11 @@ bool launch_rec_n(const QrRecGroup &g, hipStream_t st)
     if (q < 1) return false;
     const int n_groups = g.n * (((g.d[0].B + 15) / 16 + NG - 1) / NG), most = q * r.n_xcd;
     // Two groups in turn take 1.6 to 1.75 times as long as one (2 x 640 cells, us a step, 64 -> 77 utterances: 320 inputs 0.95 ->
-    // 1.49, 1280 inputs 0.99 -> 1.72, two launches 1.90 and 1.99), so they pay where they save a third of the launches.
-    // (More than 640 cells leave no registers for a second state.)
+    // 1.49, 1280 inputs 0.99 -> 1.72, two launches 1.90 and 1.99), so they pay where they save more than three launches of seven:
+    // 2 -> 1 and 4 -> 2, but not 3 -> 2 or 5 -> 3.  Narrower layers, 100 steps of two directions at 320 inputs, us: 272 cells and 300
+    // utterances 227 -> 180, 400 and 130 224 -> 176, 512 and 130 229 -> 180, 576 and 80 228 -> 176.  (More than 640 cells leave no
+    // registers for a second state.  Up to 256, where an XCD holds four groups or more, a second launch begins at 257
+    // utterances and more, and 100 steps of 300 take 190 us against 99 of 130: not built.)
     if constexpr (NG == 1 && KH == 5 && KX > 0 && CELLS == 2) {
         const int n_pairs = g.n * (((g.d[0].B + 15) / 16 + 1) / 2);
         if (4 * ((n_groups + most - 1) / most) > 7 * ((n_pairs + most - 1) / most) && launch_rec_n<KH, KX, W8, CELLS, C_FIRST, 2>(g, st))

@@ -162,6 +162,26 @@ def test_routes_of_the_recurrence_agree(gpu_lib, T, B, I, H, bits, state):
             assert torch.equal(v, want[k]), f"route {route:#x}: {k}"
 
 
+@pytest.mark.parametrize("B,I,H,two", [(128, 340, 640, False), (129, 340, 640, True), (150, 1280, 640, True), (256, 340, 640, True),
+                                       (257, 340, 640, False), (400, 384, 272, True), (384, 384, 272, False), (150, 340, 656, False),
+                                       (300, 64, 256, False), (150, 1296, 640, False)])
+def test_when_a_workgroup_has_two_groups_in_turn(gpu_lib, B, I, H, two):
+    """Where that saves more than three launches of seven (2 -> 1, not 3 -> 2): the members of a pair count themselves in with
+    the first group's admission word only.  (The words lie in front of the exchange area, which the error flag follows.)"""
+    q = gpu_lib
+    _, G = _lstm_pair(q, 6100 + I + H, I, H, 0.03)
+    T, groups, members = 3, (B + 15) // 16, (H + 31) // 32
+    need = q.lstm_layer_workspace(G, T, B)
+    ws = torch.full((need,), 0x55, dtype=torch.uint8, device=DEV)
+    q.lstm_layer(G, dev(synth.codes(6101, (T, B, q.act_pitch(I)), -8, 7)), workspace=ws)
+    assert q.layer_error_flag(ws, need) == 0
+    exchange = (2 * groups * ((H + 63) // 64) * 64 * 4 * 8 + 255) // 256 * 256
+    at = need - 256 - exchange - (8 * groups + 15) // 16 * 16
+    words = ws[at:at + 8 * groups].cpu().numpy().view(np.uint64)
+    counts = [sum((int(w) >> (6 * i)) & 63 for i in range(9)) for w in words]
+    assert counts == [members if not two or g % 2 == 0 else 0 for g in range(groups)]
+
+
 @pytest.mark.parametrize("B,n_streams,layers", [(1, 4, 6), (40, 3, 4), (77, 3, 2)])
 def test_recurrences_on_several_streams(gpu_lib, B, n_streams, layers):
     """Encoders on streams of their own, with workspaces of their own: each launch wants more than half of an XCD, so
