@@ -26,6 +26,7 @@ struct Plan {
     float *score;        // [NB][B][W]
     int32_t *node, *len, *row; // [NB][N]
     int32_t *free_rows, *n_taken;                         // [B][P], [B]
+    v4i *tags;                                            // [B][P]: see QrRouteArgs.tags
     float *nx_score;  v4i *nx_info;  int32_t *nx_count; // [B][R*W], [B]
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
@@ -110,6 +111,7 @@ void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws,
     p.row = cv.take<int32_t>(NB * N);
     p.free_rows = cv.take<int32_t>((size_t)B * p.P);
     p.n_taken = cv.take<int32_t>(B);
+    p.tags = cv.take<v4i>((size_t)B * p.P);
     p.nx_score = cv.take<float>((size_t)B * p.R * W);
     p.nx_info = cv.take<v4i>((size_t)B * p.R * W);
     p.nx_count = cv.take<int32_t>(B);
@@ -130,7 +132,7 @@ __global__ void fill_words_kernel(uint32_t *p, size_t n_words, uint32_t v)
 // Start of an utterance: slot 0 holds the empty sequence with score 0 and advances from the zero state (row B*P) into
 // the utterance's first row with the start symbol; the other slots are empty.
 __global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0, int32_t *row0, int32_t *free_rows, int32_t *n_taken,
-                                   int32_t *nx_count, v4i *rows, int32_t *n_rows, int32_t *node_tok, int32_t *node_prev,
+                                   v4i *tags, int32_t *nx_count, v4i *rows, int32_t *n_rows, int32_t *node_tok, int32_t *node_prev,
                                    int W, int B, int P, int start_symbol)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -143,6 +145,7 @@ __global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0,
     if (n < B * P) {   // (the last entry of an utterance is never looked at)
         const int i = n % P;
         free_rows[n] = i + 1 < P ? n + 1 : n;
+        if (tags) tags[n] = v4i{-1, -1, 0, -1};   // the first row's sequence, the empty one, has serial 0
     }
     if (n >= B * W) return;
     score0[n] = (n % W == 0) ? 0.0f : -INFINITY;
@@ -361,7 +364,7 @@ void start_decode(const qrnnt_model *m, const Plan &p, Advance &ad, int32_t *n_t
     }
     fill(p.live, p.n_clear);
     // the start symbol's list is counted in the first counter, which no round uses
-    decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, nx_count,
+    decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, p.tags, nx_count,
                                                                        p.rows, p.n_rows, p.node_tok, p.node_prev, p.W, p.B, p.P,
                                                                        m->blank);
     prepare_advance(m, p, ad);
@@ -433,6 +436,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
             ra.len_dst = p.len + (size_t)nxt * Ns;
             ra.row_src = p.row + (size_t)cur * Ns;  ra.row_dst = p.row + (size_t)nxt * Ns;
             ra.P = p.P;  ra.free_rows = p.free_rows;  ra.n_taken = p.n_taken;
+            ra.tags = p.tags;  ra.serial0 = (t * max_sym + v) * W;  ra.now = t;
             ra.nx_score = p.nx_score;  ra.nx_info = p.nx_info;  ra.nx_count = p.nx_count;
             ra.node_tok = p.node_tok;  ra.node_prev = p.node_prev;
             ra.fe_dst_buf = (a0 == 0) ? ZB : 0;

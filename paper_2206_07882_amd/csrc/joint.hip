@@ -233,6 +233,11 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     __shared__ __attribute__((aligned(16))) int8_t mid_code[CL ? 2 : 1][CL ? 16 : 1][272];   // codes of the language models' bottlenecks
     __shared__ v4f lm_val[CL ? 2 : 1][CL ? 256 : 1];   // the language models' values for each thread of the scores
     __shared__ unsigned mask[64];
+    constexpr int LOG_SLOTS = NTW == 1 ? 9 : 11;
+    __shared__ v4i tag_lds[MAX_LIST];       // (W * (max_sym + 1) rows an utterance, as many as candidates)
+    __shared__ unsigned short tag_slot[ALSD ? 1 : 1 << LOG_SLOTS];
+    __shared__ unsigned char tag_twin[ALSD ? 1 : 1 << LOG_SLOTS];
+    const QrTags tags = {tag_lds, tag_slot, tag_twin};
     __shared__ int n_cand, n_list, missed;
     QrCand *const gathered = (QrCand *)&sums[0][0][0];
     static_assert(sizeof(sums) >= 16 * 4 * 64 * sizeof(QrCand), "all candidates of 64 hypotheses x 64 tokens");
@@ -253,6 +258,12 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
 
     // The new beam of the frame: the W best of the candidate list in LDS (n_list of them) by (score descending,
     // insertion order), each with its trie node, length and pool row; the rows it does not name are free again.
+    int first_free = 0;
+    // where the next frame's list of free rows begins: behind the row that this one's took last
+    auto load_first_free = [&](int taken) {
+        const int f = r.free_rows[(size_t)b * r.P + (taken > 0 ? taken - 1 : 0)] - b * r.P + (taken > 0 ? 1 : 0);
+        first_free = f < r.P ? f : 0;
+    };
     auto finish_frame = [&]() {
         __syncthreads();
         if (wave < 4) qr_rank(list, n_list, W, tid, best_fe);
@@ -274,7 +285,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             r.nx_count[b] = 0;
             r.n_taken[b] = 0;
         }
-        qr_list_free_rows(r, b, lane, found, row, mask);
+        qr_list_free_rows(r, b, lane, found, row, mask, first_free);
     };
     auto list_entry = [&](int e, float v, const v4i &info) {
         list[e] = qr_cand(qr_float_key(v + 0.0f), e);   // + 0: one key per value
@@ -501,6 +512,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         for (int e = tid; e < n0; e += 512) list_entry(e, r.nx_score[nx + e], r.nx_info[nx + e]);
         if (tid == 0) n_list = n0;
         if (tid < 64) best_fe[tid] = 0;
+        if (wave == 0) load_first_free(r.n_taken[b]);
         finish_frame();
         return;
     }
@@ -739,7 +751,11 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         }
         group_best[nt * 256 + tid] = top;
     }
-    if (wave == 0) own.free_row = qr_free_row(r, b, lane, own.taken);
+    if (wave == 0) {
+        if (frame_end) load_first_free(own.taken);
+        else own.free_row = qr_free_row(r, b, lane, own.taken);
+    }
+    if (!ALSD && !frame_end && wave == 6) qr_load_tags<LOG_SLOTS>(r, b, lane, tags);
     __syncthreads();
 
     // ---- the W best under (value descending, flat index ascending)
@@ -771,7 +787,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             alsd_own.h = own;
             qr_alsd_route(r, s, b, lane, my_c, my_v, alsd_own, mask);
         } else {
-            const int cnt = qr_route_picks(r, b, lane, my_c, my_v, own, nx0, [&](int e, float v, const v4i &info) {
+            const int cnt = qr_route_picks<LOG_SLOTS>(r, b, lane, my_c, my_v, own, nx0, tags, mask, [&](int e, float v, const v4i &info) {
                 if (frame_end) {
                     list_entry(e, v, info);
                 } else {

@@ -134,6 +134,10 @@ struct QrRouteArgs {
     // Rows of the state pool: utterance b owns rows b*P .. b*P + P-1.  free_rows[b*P + i]: its free ones;
     // n_taken[b]: how many of them this frame's earlier rounds have taken.
     int P;  int32_t *free_rows, *n_taken;
+    // Which label sequence a row's states belong to (route.h): [B][P] (serial of the sequence one label shorter, -1: none;
+    // the label; the sequence's own serial; `now` of the last round that named the row).
+    v4i *tags;
+    int serial0, now;                               // serials of this round's sequences: from serial0 + 1 on, W at most; the frame
     float *nx_score;  v4i *nx_info;  int32_t *nx_count;   // the frame's candidate list; info = (pool row, trie node, length, -)
     int32_t *node_tok, *node_prev;                  // label trie
     // end of the frame (used when last_round): the W best of the candidate list become the beam in buffer fe_dst_buf

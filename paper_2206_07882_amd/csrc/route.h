@@ -18,9 +18,99 @@
 // kernel, so that nothing in the routing waits for memory.
 struct QrOwn {
     int node, len, row;
-    int taken;                         // rows of the pool that earlier rounds of the frame have taken (uniform)
-    int free_row;                      // the utterance's w-th free row after those (qr_free_row)
+    int taken;                         // entries of the list of free rows that earlier rounds of the frame have passed (uniform)
+    int free_row;                      // the w-th entry after those (qr_free_row)
 };
+
+__device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane, int taken);
+
+// States that are already there.  What the networks hold after a label sequence depends on the sequence alone, and a row
+// keeps it until another sequence takes the row: a free one still has it.  So every row carries a tag (QrRouteArgs.tags) that
+// says which sequence it stands for, and a label pick whose parent's row and label lead to a tag of the utterance names that
+// row, be it in use or free, instead of taking one and advancing the networks; of several picks with the same sequence in one
+// round one advances.  Sequences are compared exactly: by the label and the serial of the sequence before it, which a row
+// gets together with its states and never shares with an earlier owner.  The same proposals come back from frame to frame,
+// as most of them fall out of the beam again: of 64 utterances at beam 16 and 4 labels a frame (base networks) 29 of 32 label
+// picks a frame find their states, and the launches of an advance are those of a list a tenth as long.  Finding a row takes
+// three dependent LDS reads.  Whole calls, ms: 64 x 1000 frames 168.0 -> 104.5, 13 x 301 (2 x 2048 LM) 51.8 -> 33.9, 1 x 152
+// 13.28 -> 10.85 (its rounds without a row to advance cost two launches that return); beam 1 level.
+struct QrTags {
+    v4i *tag;                          // LDS, [P]: the utterance's
+    unsigned short *slot;              // LDS, [1 << LOG]: hash table, row (relative) or anything at all
+    unsigned char *twin;               // LDS, [1 << LOG]: the lane of a pick without a row
+};
+
+template <int LOG>
+__device__ __forceinline__ unsigned qr_tag_hash(int serial, int tok)
+{
+    return ((unsigned)serial * 64u + (unsigned)tok) * 0x9E3779B1u >> (32 - LOG);
+}
+
+// The tags of utterance b into LDS, by one wave.  (Of rows that share a place in the table one is found.)
+template <int LOG>
+__device__ __forceinline__ void qr_load_tags(const QrRouteArgs &a, int b, int lane, const QrTags &t)
+{
+    for (int i = lane; i < a.P; i += 64) {
+        const v4i g = a.tags[(size_t)b * a.P + i];
+        t.tag[i] = g;
+        if (g[0] >= 0) t.slot[qr_tag_hash<LOG>(g[0], g[1])] = (unsigned short)i;
+    }
+}
+
+// Rows for this round's label picks (lanes with is_lab: parent's row, label): a row that holds the sequence, or the next
+// free one that no pick of this frame names.  Returns the row; steps: the networks have to advance into it.  n_passed: how
+// much of the list of free rows lies behind the round.  There is always enough of it: a frame's picks name or take
+// W * max_sym rows at most, the list is that long.  mask: 64 words of LDS, private to the wave.
+template <int LOG>
+__device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lane, bool is_lab, int par_row, int tok, const QrOwn &own,
+                                            const QrTags &t, unsigned *mask, bool &steps, int &n_passed)
+{
+    const int row0 = b * a.P;
+    const int serial = is_lab ? t.tag[par_row - row0][2] : -1;
+    const unsigned at = qr_tag_hash<LOG>(serial, tok);
+    int held = is_lab ? t.slot[at] : a.P;      // (an entry that nobody has written may be any number)
+    if (held < a.P) {
+        const v4i g = t.tag[held];
+        held = g[0] == serial && g[1] == tok ? held : a.P;
+    }
+    const bool hit = held < a.P;
+    if (hit) {
+        t.tag[held][3] = a.now;
+        a.tags[(size_t)row0 + held][3] = a.now;
+    }
+    if (is_lab && !hit) t.twin[at] = (unsigned char)lane;
+    __builtin_amdgcn_wave_barrier();
+    int first = is_lab && !hit ? t.twin[at] : lane;
+    const int first_serial = __shfl(serial, first), first_tok = __shfl(tok, first);
+    first = first_serial == serial && first_tok == tok ? first : lane;
+    steps = is_lab && !hit && first == lane;
+    const unsigned long long sm = __ballot(steps);
+    const int n_new = (int)__popcll(sm);
+    int row = row0 + held;
+    n_passed = own.taken;
+    if (n_new > 0) {   // uniform
+        const int k_new = (int)__popcll(sm & ((1ull << lane) - 1ull));
+        int got = 0, entry = own.free_row;
+        for (;;) {     // (once, unless most of the next 64 free rows are named already)
+            const bool ok = t.tag[entry - row0][3] != a.now;
+            const unsigned long long om = __ballot(ok);
+            const int k = got + (int)__popcll(om & ((1ull << lane) - 1ull));
+            if (ok && k < n_new) mask[k] = (unsigned)(entry - row0) | (unsigned)lane << 16;
+            got += (int)__popcll(om);
+            if (got >= n_new) break;
+            n_passed += 64;
+            entry = qr_free_row(a, b, lane, n_passed);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const unsigned mine = mask[k_new < n_new ? k_new : 0], last = mask[n_new - 1];
+        n_passed += (int)(last >> 16) + 1;
+        const int new_row = row0 + (int)(mine & 0xFFFFu);
+        if (steps) a.tags[new_row] = v4i{serial, tok, a.serial0 + 1 + k_new, a.now};
+        const int first_row = __shfl(new_row, first);
+        row = hit ? row : first_row;
+    }
+    return row;
+}
 
 __device__ __forceinline__ QrOwn qr_load_own(const QrRouteArgs &a, int b, int lane)
 {
@@ -41,9 +131,10 @@ __device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane
     return a.free_rows[(size_t)b * a.P + f];
 }
 
-// The utterance's free rows for what follows: all of its P rows except the ones that lanes with `held` name.
+// The utterance's free rows for what follows: all of its P rows except the ones that lanes with `held` name, from row
+// `first` (relative) on, so that what was taken last is taken again last.
 // mask: 64 words of LDS, private to the calling wave (P <= 64 * 17 bits).
-__device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, int lane, bool held, int row, unsigned *mask)
+__device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, int lane, bool held, int row, unsigned *mask, int first = 0)
 {
     __builtin_amdgcn_wave_barrier();
     mask[lane] = 0u;
@@ -53,8 +144,11 @@ __device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, i
     __builtin_amdgcn_wave_barrier();
     int n = 0;
     for (int i0 = 0; i0 < a.P; i0 += 64) {
-        const int i = i0 + lane;
-        const bool is_free = i < a.P && ((mask[i >> 5] >> (i & 31)) & 1u) == 0u;
+        const bool in = i0 + lane < a.P;
+        int i = i0 + lane + first;
+        i = i < a.P ? i : i - a.P;
+        i = in ? i : 0;
+        const bool is_free = in && ((mask[i >> 5] >> (i & 31)) & 1u) == 0u;
         const unsigned long long fm = __ballot(is_free);
         const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(fm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)fm, 0u));
         if (is_free) a.free_rows[(size_t)b * a.P + pos] = b * a.P + i;
@@ -67,8 +161,9 @@ __device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, i
 // own: hypothesis `lane` of the current round; a pick reads its parent's from that lane.
 // nx0: the length of the utterance's candidate list before this round (a.nx_count[b], fetched early as well);
 // add(e, score, info) puts a candidate at its end.
-template <class Add>
-__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0, Add &&add)
+template <int LOG, class Add>
+__device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0,
+                                              const QrTags &tags, unsigned *mask, Add &&add)
 {
     if (lane == 0 && b == 0 && a.live_clear) *a.live_clear = 0;
     if (lane == 0 && b == 0 && a.n_rows_clear) *a.n_rows_clear = 0;
@@ -82,7 +177,6 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int par_node = __shfl(own.node, par), par_len = __shfl(own.len, par), par_row = __shfl(own.row, par);
     const int k_lab = (int)__popcll(lm & lt);            // this pick's number among the label picks
-    const int new_row = __shfl(own.free_row, k_lab);
     if (is_blank) {
         add(nx0 + (int)__popcll(bm & lt), v, v4i{par_row, par_node, par_len, 0});
     }
@@ -90,14 +184,20 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     if (a.last_round) return cnt;
     const int n_lab = __popcll(lm);
     if (lane == 0 && n_lab > 0 && a.live_next) atomicAdd(a.live_next, 1);
-    // The place of the utterance's labels in the list (the order of the utterances in it does not matter): asked for
-    // now, used last.  A single utterance has the list to itself.
-    int base = 0;
+    // Rows for the labels, and the place of those that advance in the list (the order of the utterances in it does not
+    // matter): asked for now, used last.  A single utterance has the list to itself.
+    int base = 0, row = 0, n_new = 0, k_new = 0;
+    bool steps = false;
     if (n_lab > 0) {   // uniform
-        if (lane == 0) {
-            if (a.B == 1) *a.n_rows_next = n_lab;
-            else base = atomicAdd(a.n_rows_next, n_lab);
-            a.n_taken[b] = own.taken + n_lab;
+        int n_passed;
+        row = qr_find_rows<LOG>(a, b, lane, is_lab, par_row, tok, own, tags, mask, steps, n_passed);
+        const unsigned long long sm = __ballot(steps);
+        n_new = (int)__popcll(sm);
+        k_new = (int)__popcll(sm & lt);
+        if (lane == 0 && n_new > 0) {
+            if (a.B == 1) *a.n_rows_next = n_new;
+            else base = atomicAdd(a.n_rows_next, n_new);
+            a.n_taken[b] = n_passed;
         }
     }
     if (is_lab) {
@@ -108,7 +208,7 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
         a.score_dst[dst] = v;
         a.node_dst[dst] = id;
         a.len_dst[dst] = par_len + 1;
-        a.row_dst[dst] = new_row;
+        a.row_dst[dst] = row;
     }
     if (in && lane >= n_lab) {
         const int dst = b * W + lane;
@@ -117,9 +217,9 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
         a.len_dst[dst] = 0;
         a.row_dst[dst] = b * a.P;   // any row of the utterance
     }
-    if (n_lab > 0) {
+    if (n_new > 0) {   // uniform
         base = __builtin_amdgcn_readfirstlane(base);
-        if (is_lab) a.rows_next[base + k_lab] = v4i{new_row, par_row, tok, 0};
+        if (steps) a.rows_next[base + k_new] = v4i{row, par_row, tok, 0};
     }
     return cnt;
 }

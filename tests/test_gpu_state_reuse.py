@@ -1,0 +1,31 @@
+"""Label picks that lead to a sequence whose states a row of the pool still holds name that row.  Frames that change slowly
+bring the same proposals back: most picks find their states, in rows of the beam, in free ones, and in a row that another
+pick of the same round is about to fill.  The widest beams look for free rows beyond the first 64 of their list."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import models as omodels
+from paper_2206_07882_amd import synth
+
+from .test_gpu_decode import _compare_beams, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,W,max_sym,T", [(1, 16, 4, 40), (3, 16, 4, 24), (2, 5, 1, 60), (2, 1, 4, 60), (2, 20, 4, 20),
+                                           (1, 16, 16, 8), (2, 40, 4, 12), (1, 64, 16, 4), (33, 4, 2, 20)])
+def test_slow_frames(gpu_lib, B, W, max_sym, T):
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    m = synth.make_model(0, weight_std=0.5)
+    m.rho = 0.4
+    e = (synth.normal(500 + W, (1, B, m.J), 1.0) + 0.1 * synth.normal(600 + W, (T, B, m.J), 1.0)).astype(np.float32)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
+    ref = oracle.decode(M, e, W, max_sym, max_len=T * max_sym)
+    got = q.decode(G, dev(e), W, max_sym, max_len=T * max_sym)
+    _compare_beams(got, ref)
+    assert ref[1].max() > 2   # there were labels
+    early = q.decode(G, dev(e), W, max_sym, max_len=T * max_sym, flags=q.DECODE_EARLY_STOP)
+    for a, b in zip(got, early):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
