@@ -443,13 +443,14 @@ qrnnt_status qrnnt_decode_alsd(const qrnnt_model *m, const float *enc_proj, int3
                                void *workspace, size_t workspace_bytes, void *stream);
 
 /* qrnnt_decode_alsd with options.  QRNNT_ALSD_REUSE: reuse of cached hypotheses (Sec. 4.1 names it as what
- * makes the decoding time fall sub-linearly at small beams).  The states of the prediction network and of the
- * LMs after a label sequence depend on that sequence alone; with this flag a label pick whose resulting
- * sequence a live hypothesis of the current beam already holds takes over that hypothesis' states (both then
- * name the same row of the state pool) instead of advancing the networks from its own parent.  Results are bit for bit those of qrnnt_decode_alsd; sequences are compared
- * by (length, 64-bit hash) as in the recombination.  The cache is the current beam: a sequence that left the
- * beam is not remembered.  stats [device] int32[2] or NULL: the call adds the number of label picks that kept
- * their slot to stats[0] and the number of those that reused states to stats[1] (the caller zeroes it). */
+ * makes the decoding time fall sub-linearly at small beams), counted.  The states of the prediction network and of
+ * the LMs after a label sequence depend on that sequence alone, and every search of this library has a label pick
+ * whose resulting sequence still has its states in a row of the pool name that row instead of advancing the networks
+ * from its own parent.  With this flag and with stats, a label pick whose resulting sequence a live hypothesis of the
+ * current beam already holds is counted as reused; sequences are compared by (length, 64-bit hash) as in the
+ * recombination.  Results are bit for bit those of qrnnt_decode_alsd.  stats [device] int32[2] or NULL: the call adds
+ * the number of label picks that kept their slot to stats[0] and, with the flag, the number of those whose sequence
+ * the beam held to stats[1] (the caller zeroes it). */
 #define QRNNT_ALSD_REUSE 1u
 qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                                   int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats, int32_t *tokens_out,

@@ -145,7 +145,7 @@ __global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0,
     if (n < B * P) {   // (the last entry of an utterance is never looked at)
         const int i = n % P;
         free_rows[n] = i + 1 < P ? n + 1 : n;
-        if (tags) tags[n] = v4i{-1, -1, 0, -1};   // the first row's sequence, the empty one, has serial 0
+        tags[n] = v4i{-1, -1, 0, -1};   // the first row's sequence, the empty one, has serial 0
     }
     if (n >= B * W) return;
     score0[n] = (n % W == 0) ? 0.0f : -INFINITY;
@@ -491,7 +491,7 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     p = Plan{};
     p.T = T; p.B = B; p.W = W; p.N = B * W; p.max_sym = 0;
     p.R = 1; p.NB = 2; p.V = m->V; p.J = m->joint_out.cols;
-    p.P = 2 * W;   // the beam's rows and those of an iteration's labels
+    p.P = QR_ALSD_ROWS * W;   // the beam's rows and those of an iteration's labels
     ap.n_iter = T + u_max;
     Carver cv{(char *)ws, 0};
     const size_t N = (size_t)p.N, NB = 2;
@@ -502,6 +502,7 @@ void make_alsd_plan(const qrnnt_model *m, int T, int B, int W, int u_max, void *
     ap.hash = cv.take<unsigned long long>(NB * N);
     p.row = cv.take<int32_t>(NB * N);
     p.free_rows = cv.take<int32_t>((size_t)B * p.P);
+    p.tags = cv.take<v4i>((size_t)B * p.P);
     ap.fin_score = cv.take<float>(N);
     ap.fin_node = cv.take<int32_t>(N);
     ap.fin_len = cv.take<int32_t>(N);
@@ -585,6 +586,7 @@ static qrnnt_status alignment_length_synchronous(const qrnnt_model *m, const flo
         ra.len_dst = p.len + (size_t)nxt * Ns;
         ra.row_src = p.row + (size_t)cur * Ns;  ra.row_dst = p.row + (size_t)nxt * Ns;
         ra.P = p.P;  ra.free_rows = p.free_rows;
+        ra.tags = p.tags;  ra.serial0 = i * W;  ra.now = i;
         ra.node_tok = p.node_tok;  ra.node_prev = p.node_prev;
         ra.gate = i > 0 ? p.live + i : nullptr;   // live[i]: utterances with a live hypothesis entering iteration i
         ra.live_next = p.live + i + 1;

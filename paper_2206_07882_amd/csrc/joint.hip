@@ -218,7 +218,10 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 // 16, ns after its start, one workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end
 // 9900 -> 7500; a round of three launches 23.3 -> 20.5 us, of 64 utterances (batch of 1000 frames, all rounds) 37.3 -> 36.5.
 // (Two workgroups, the second with the language models: the first one's share still took 4.2 us, no gain.)
-template <int NTW, bool ALSD, bool CL>
+// TAGS: label picks look for rows that hold their states (route.h).  Without (alignment-length search of up to 16 hypotheses:
+// the step kernels take as long for one as for all of them, and the list is hardly ever empty): looking cost 228 iterations at
+// beam 4 2 %, 60 us, and saved none.
+template <int NTW, bool ALSD, bool CL, bool TAGS = true>
 __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
 {
     constexpr int MAX_LIST = ALSD ? 1 : 16 * NTW * 17;   // a frame's candidates: W blanks in each of at most 17 rounds
@@ -233,10 +236,10 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     __shared__ __attribute__((aligned(16))) int8_t mid_code[CL ? 2 : 1][CL ? 16 : 1][272];   // codes of the language models' bottlenecks
     __shared__ v4f lm_val[CL ? 2 : 1][CL ? 256 : 1];   // the language models' values for each thread of the scores
     __shared__ unsigned mask[64];
-    constexpr int LOG_SLOTS = NTW == 1 ? 9 : 11;
-    __shared__ v4i tag_lds[MAX_LIST];       // (W * (max_sym + 1) rows an utterance, as many as candidates)
-    __shared__ unsigned short tag_slot[ALSD ? 1 : 1 << LOG_SLOTS];
-    __shared__ unsigned char tag_twin[ALSD ? 1 : 1 << LOG_SLOTS];
+    constexpr int LOG_SLOTS = !TAGS ? 0 : (NTW == 1 ? 9 : 11);
+    __shared__ v4i tag_lds[TAGS ? (16 * NTW * (ALSD ? QR_ALSD_ROWS : 17) + 63) / 64 * 64 : 1];   // (a row of the pool for every candidate of a frame)
+    __shared__ unsigned short tag_slot[1 << LOG_SLOTS];
+    __shared__ unsigned char tag_twin[1 << LOG_SLOTS];
     const QrTags tags = {tag_lds, tag_slot, tag_twin};
     __shared__ int n_cand, n_list, missed;
     QrCand *const gathered = (QrCand *)&sums[0][0][0];
@@ -537,6 +540,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         if (ALSD) alsd_own = qr_alsd_load_own(r, s, b, lane);
         else nx0 = r.nx_count[b];
     }
+    if (TAGS && !frame_end && wave == 6) qr_request_tags(r, b, lane, tags);
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
         const int w = nt * 16 + ((tid >> 4) & 15);
@@ -755,8 +759,9 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         if (frame_end) load_first_free(own.taken);
         else own.free_row = qr_free_row(r, b, lane, own.taken);
     }
-    if (!ALSD && !frame_end && wave == 6) qr_load_tags<LOG_SLOTS>(r, b, lane, tags);
+    if (TAGS && !frame_end && wave == 6) qr_enter_tags<LOG_SLOTS>(r, lane, tags);
     __syncthreads();
+    if (TAGS && !frame_end && wave == 0) own.serial = tag_lds[own.row - b * r.P][2];
 
     // ---- the W best under (value descending, flat index ascending)
     if (wave < 4) {
@@ -785,7 +790,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         const float my_v = found ? qr_cand_value(p) : -INFINITY;
         if (ALSD) {
             alsd_own.h = own;
-            qr_alsd_route(r, s, b, lane, my_c, my_v, alsd_own, mask);
+            qr_alsd_route<LOG_SLOTS, TAGS>(r, s, b, lane, my_c, my_v, alsd_own, tags, mask);
         } else {
             const int cnt = qr_route_picks<LOG_SLOTS>(r, b, lane, my_c, my_v, own, nx0, tags, mask, [&](int e, float v, const v4i &info) {
                 if (frame_end) {
@@ -845,8 +850,9 @@ void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &
     int wgs = ALSD || !r.last_round ? a.wgs_lm : a.wgs_last;
     if (a.come > 0 && a.come < wgs) wgs = a.come;
     // (one workgroup to an utterance: any number of utterances, and a grid's z extent ends at 65535)
-    if (wgs == 1) search_round_kernel<1, ALSD, true><<<r.B, 512, 0, st>>>(a, r, s);
-    else if (wgs) search_round_kernel<1, ALSD, true><<<dim3(a.n_xcd, wgs, (r.B + a.n_xcd - 1) / a.n_xcd), 512, 0, st>>>(a, r, s);
+    const dim3 grid = wgs == 1 ? dim3(r.B) : dim3(a.n_xcd, wgs, (r.B + a.n_xcd - 1) / a.n_xcd);
+    if (ALSD && wgs && r.B * r.W <= 16) search_round_kernel<1, ALSD, true, !ALSD><<<grid, 512, 0, st>>>(a, r, s);   // (without tags)
+    else if (wgs) search_round_kernel<1, ALSD, true><<<grid, 512, 0, st>>>(a, r, s);
     else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else search_round_kernel<4, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);

@@ -122,6 +122,7 @@ struct QrRoundArgs {
     int32_t *late;                     // [B] rounds so far in which a word had not come in time
 };
 #define QR_ROUND_PARTS 4
+#define QR_ALSD_ROWS 2                 // rows of the state pool to a slot of the alignment-length search's beam
 QR_HIDDEN size_t qr_round_words(int J, bool use_lm, bool mids, int B, int W);   // of an utterance, 0 where it has one workgroup on any device
 QR_HIDDEN void qr_plan_round(QrRoundArgs &a, int B, int W, bool alsd);
 QR_HIDDEN bool qr_round_takes(int mid_rows, int n_mids, int B, int W, bool alsd);   // bottlenecks of so many rows
@@ -134,10 +135,6 @@ struct QrRouteArgs {
     // Rows of the state pool: utterance b owns rows b*P .. b*P + P-1.  free_rows[b*P + i]: its free ones;
     // n_taken[b]: how many of them this frame's earlier rounds have taken.
     int P;  int32_t *free_rows, *n_taken;
-    // Which label sequence a row's states belong to (route.h): [B][P] (serial of the sequence one label shorter, -1: none;
-    // the label; the sequence's own serial; `now` of the last round that named the row).
-    v4i *tags;
-    int serial0, now;                               // serials of this round's sequences: from serial0 + 1 on, W at most; the frame
     float *nx_score;  v4i *nx_info;  int32_t *nx_count;   // the frame's candidate list; info = (pool row, trie node, length, -)
     int32_t *node_tok, *node_prev;                  // label trie
     // end of the frame (used when last_round): the W best of the candidate list become the beam in buffer fe_dst_buf
@@ -149,6 +146,10 @@ struct QrRouteArgs {
     // list of the hypotheses that took a label (see QrStepGroup.rows): every utterance appends its own at
     // rows_next[old *n_rows_next ...]; workgroup 0 clears *n_rows_clear for a later frame
     v4i *rows_next;  int32_t *n_rows_next, *n_rows_clear;
+    // Which label sequence a row's states belong to (route.h): [B][P] (serial of the sequence one label shorter, -1: none;
+    // the label; the sequence's own serial; `now` of the last round that named the row).
+    v4i *tags;
+    int serial0, now;                               // serials of this round's sequences: from serial0 + 1 on, W at most; the frame
 };
 
 // Alignment-length synchronous search: what one iteration needs beyond QrRouteArgs (of which it uses score/node/len/row
@@ -158,7 +159,7 @@ struct QrAlsdArgs {
     const unsigned long long *hash_src;              // [N] hash of the label sequence (recombination key, with the length)
     unsigned long long *hash_dst;
     float *fin_score;  int32_t *fin_node, *fin_len;  // [B,W] the W best finished hypotheses so far, best first
-    int reuse;                                       // a label pick whose sequence a live hypothesis of the beam holds takes over its states
+    int reuse;                                       // with stats: count label picks whose sequence a live hypothesis of the beam holds
     int32_t *stats;                                  // optional [device] int32[2]: += label picks that kept their slot, += those that reused states
 };
 

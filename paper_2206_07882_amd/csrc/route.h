@@ -12,6 +12,7 @@
 #pragma once
 
 #include "kernels.h"
+#include "mma_pipe.h"
 #include "select.h"
 
 // What lane w < W of the routing wave knows about hypothesis w of the current round: fetched at the start of the
@@ -20,6 +21,7 @@ struct QrOwn {
     int node, len, row;
     int taken;                         // entries of the list of free rows that earlier rounds of the frame have passed (uniform)
     int free_row;                      // the w-th entry after those (qr_free_row)
+    int serial;                        // of its sequence (QrTags)
 };
 
 __device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane, int taken);
@@ -33,9 +35,10 @@ __device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane
 // as most of them fall out of the beam again: of 64 utterances at beam 16 and 4 labels a frame (base networks) 29 of 32 label
 // picks a frame find their states, and the launches of an advance are those of a list a tenth as long.  Finding a row takes
 // three dependent LDS reads.  Whole calls, ms: 64 x 1000 frames 168.0 -> 104.5, 13 x 301 (2 x 2048 LM) 51.8 -> 33.9, 1 x 152
-// 13.28 -> 10.85 (its rounds without a row to advance cost two launches that return); beam 1 level.
+// 13.28 -> 11.1 (its rounds without a row to advance cost two launches that return); beam 1 level.  Alignment-length search
+// (its pool of two rows to a slot of the beam; three, four and six find no more), 64 x 300 16.65 -> 14.56, 1 x 152 at beam 4 level.
 struct QrTags {
-    v4i *tag;                          // LDS, [P]: the utterance's
+    v4i *tag;                          // LDS, [P rounded up to 64]: the utterance's
     unsigned short *slot;              // LDS, [1 << LOG]: hash table, row (relative) or anything at all
     unsigned char *twin;               // LDS, [1 << LOG]: the lane of a pick without a row
 };
@@ -46,13 +49,22 @@ __device__ __forceinline__ unsigned qr_tag_hash(int serial, int tok)
     return ((unsigned)serial * 64u + (unsigned)tok) * 0x9E3779B1u >> (32 - LOG);
 }
 
-// The tags of utterance b into LDS, by one wave.  (Of rows that share a place in the table one is found.)
-template <int LOG>
-__device__ __forceinline__ void qr_load_tags(const QrRouteArgs &a, int b, int lane, const QrTags &t)
+// The tags of utterance b go to LDS, by one wave: requested at the kernel's start, straight into LDS (wanted much later, and
+// registers are short), and entered in the table when they are there.  (Of rows that share a place in the table one is found.)
+__device__ __forceinline__ void qr_request_tags(const QrRouteArgs &a, int b, int lane, const QrTags &t)
 {
+    for (int i0 = 0; i0 < a.P; i0 += 64) {
+        const int i = i0 + lane < a.P ? i0 + lane : a.P - 1;
+        qr_load_lds16(a.tags + (size_t)b * a.P + i, (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(t.tag + i0));
+    }
+}
+
+template <int LOG>
+__device__ __forceinline__ void qr_enter_tags(const QrRouteArgs &a, int lane, const QrTags &t)
+{
+    qr_wait_vmcnt<0>();
     for (int i = lane; i < a.P; i += 64) {
-        const v4i g = a.tags[(size_t)b * a.P + i];
-        t.tag[i] = g;
+        const v4i g = t.tag[i];
         if (g[0] >= 0) t.slot[qr_tag_hash<LOG>(g[0], g[1])] = (unsigned short)i;
     }
 }
@@ -60,13 +72,15 @@ __device__ __forceinline__ void qr_load_tags(const QrRouteArgs &a, int b, int la
 // Rows for this round's label picks (lanes with is_lab: parent's row, label): a row that holds the sequence, or the next
 // free one that no pick of this frame names.  Returns the row; steps: the networks have to advance into it.  n_passed: how
 // much of the list of free rows lies behind the round.  There is always enough of it: a frame's picks name or take
-// W * max_sym rows at most, the list is that long.  mask: 64 words of LDS, private to the wave.
-template <int LOG>
-__device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lane, bool is_lab, int par_row, int tok, const QrOwn &own,
-                                            const QrTags &t, unsigned *mask, bool &steps, int &n_passed)
+// W * max_sym rows at most (an iteration's of the alignment-length search W), the list is that long.  last: the row
+// (relative) that was taken last, if any.  mask: 64 words of LDS, private to the wave.
+// TWINS: two hypotheses may have one sequence, so that two picks want one new row.
+template <int LOG, bool TWINS>
+__device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lane, bool is_lab, int par_serial, int tok, const QrOwn &own,
+                                            const QrTags &t, unsigned *mask, bool &steps, int &n_passed, int &last)
 {
     const int row0 = b * a.P;
-    const int serial = is_lab ? t.tag[par_row - row0][2] : -1;
+    const int serial = is_lab ? par_serial : -1;
     const unsigned at = qr_tag_hash<LOG>(serial, tok);
     int held = is_lab ? t.slot[at] : a.P;      // (an entry that nobody has written may be any number)
     if (held < a.P) {
@@ -78,11 +92,14 @@ __device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lan
         t.tag[held][3] = a.now;
         a.tags[(size_t)row0 + held][3] = a.now;
     }
-    if (is_lab && !hit) t.twin[at] = (unsigned char)lane;
-    __builtin_amdgcn_wave_barrier();
-    int first = is_lab && !hit ? t.twin[at] : lane;
-    const int first_serial = __shfl(serial, first), first_tok = __shfl(tok, first);
-    first = first_serial == serial && first_tok == tok ? first : lane;
+    int first = lane;
+    if (TWINS) {
+        if (is_lab && !hit) t.twin[at] = (unsigned char)lane;
+        __builtin_amdgcn_wave_barrier();
+        first = is_lab && !hit ? t.twin[at] : lane;
+        const int first_serial = __shfl(serial, first), first_tok = __shfl(tok, first);
+        first = first_serial == serial && first_tok == tok ? first : lane;
+    }
     steps = is_lab && !hit && first == lane;
     const unsigned long long sm = __ballot(steps);
     const int n_new = (int)__popcll(sm);
@@ -90,23 +107,32 @@ __device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lan
     n_passed = own.taken;
     if (n_new > 0) {   // uniform
         const int k_new = (int)__popcll(sm & ((1ull << lane) - 1ull));
-        int got = 0, entry = own.free_row;
-        for (;;) {     // (once, unless most of the next 64 free rows are named already)
-            const bool ok = t.tag[entry - row0][3] != a.now;
-            const unsigned long long om = __ballot(ok);
-            const int k = got + (int)__popcll(om & ((1ull << lane) - 1ull));
-            if (ok && k < n_new) mask[k] = (unsigned)(entry - row0) | (unsigned)lane << 16;
-            got += (int)__popcll(om);
-            if (got >= n_new) break;
-            n_passed += 64;
-            entry = qr_free_row(a, b, lane, n_passed);
+        int got = 0, entry = own.free_row, new_row;
+        bool ok = t.tag[entry - row0][3] != a.now;
+        unsigned long long om = __ballot(ok);
+        if ((~om & ((2ull << (n_new - 1)) - 1ull)) == 0ull) {   // uniform: the next ones are all there to take
+            new_row = __shfl(entry, k_new < n_new ? k_new : 0);
+            last = __builtin_amdgcn_readlane(entry, n_new - 1) - row0;
+            n_passed += n_new;
+        } else {
+            for (;;) {     // (once, unless most of the next 64 free rows are named already)
+                const int k = got + (int)__popcll(om & ((1ull << lane) - 1ull));
+                if (ok && k < n_new) mask[k] = (unsigned)(entry - row0) | (unsigned)lane << 16;
+                got += (int)__popcll(om);
+                if (got >= n_new) break;
+                n_passed += 64;
+                entry = qr_free_row(a, b, lane, n_passed);
+                ok = t.tag[entry - row0][3] != a.now;
+                om = __ballot(ok);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const unsigned mine = mask[k_new < n_new ? k_new : 0], end = mask[n_new - 1];
+            n_passed += (int)(end >> 16) + 1;
+            last = (int)(end & 0xFFFFu);
+            new_row = row0 + (int)(mine & 0xFFFFu);
         }
-        __builtin_amdgcn_wave_barrier();
-        const unsigned mine = mask[k_new < n_new ? k_new : 0], last = mask[n_new - 1];
-        n_passed += (int)(last >> 16) + 1;
-        const int new_row = row0 + (int)(mine & 0xFFFFu);
         if (steps) a.tags[new_row] = v4i{serial, tok, a.serial0 + 1 + k_new, a.now};
-        const int first_row = __shfl(new_row, first);
+        const int first_row = TWINS ? __shfl(new_row, first) : new_row;
         row = hit ? row : first_row;
     }
     return row;
@@ -176,6 +202,7 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     const unsigned long long bm = __ballot(is_blank), lm = __ballot(is_lab);
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int par_node = __shfl(own.node, par), par_len = __shfl(own.len, par), par_row = __shfl(own.row, par);
+    const int par_serial = __shfl(own.serial, par);
     const int k_lab = (int)__popcll(lm & lt);            // this pick's number among the label picks
     if (is_blank) {
         add(nx0 + (int)__popcll(bm & lt), v, v4i{par_row, par_node, par_len, 0});
@@ -189,8 +216,8 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     int base = 0, row = 0, n_new = 0, k_new = 0;
     bool steps = false;
     if (n_lab > 0) {   // uniform
-        int n_passed;
-        row = qr_find_rows<LOG>(a, b, lane, is_lab, par_row, tok, own, tags, mask, steps, n_passed);
+        int n_passed, last;
+        row = qr_find_rows<LOG, true>(a, b, lane, is_lab, par_serial, tok, own, tags, mask, steps, n_passed, last);
         const unsigned long long sm = __ballot(steps);
         n_new = (int)__popcll(sm);
         k_new = (int)__popcll(sm & lt);
@@ -250,8 +277,9 @@ __device__ __forceinline__ QrAlsdOwn qr_alsd_load_own(const QrRouteArgs &a, cons
     return o;
 }
 
+template <int LOG, bool TAGS>
 __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsdArgs &s, int b, int lane, int c, float v,
-                                              const QrAlsdOwn &o, unsigned *mask)
+                                              const QrAlsdOwn &o, const QrTags &tags, unsigned *mask)
 {
     const int W = a.W, V = a.V;
     const bool in = lane < W;
@@ -262,6 +290,7 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     const int len_p = __shfl(o.h.len, par);
     const int node_p = __shfl(o.h.node, par);
     const int row_p = __shfl(o.h.row, par);
+    const int serial_p = __shfl(o.h.serial, par);
     const unsigned long long hash_p = ((unsigned long long)(unsigned)__shfl((int)(unsigned)(o.hash >> 32), par) << 32) |
                                       (unsigned long long)(unsigned)__shfl((int)(unsigned)o.hash, par);
     const int new_len = len_p + (is_lab ? 1 : 0);
@@ -302,12 +331,12 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     const bool keep = found && leader == lane;
     const unsigned long long km = __ballot(keep);
     if (lane == 0 && km != 0ull && a.live_next) atomicAdd(a.live_next, 1);
-    // Reuse of cached hypotheses (Sec. 4.1): the networks' states after a label sequence depend on the sequence
-    // alone.  When a live hypothesis of the current beam already holds the sequence this label pick produces (the
-    // usual case: y + k is in the beam and y proposes k again one frame later), the new slot names that
-    // hypothesis' row instead of stepping the networks from y.
+    // Reuse of cached hypotheses (Sec. 4.1): when a live hypothesis of the current beam already holds the sequence this label
+    // pick produces (y + k is in the beam and y proposes k again one frame later), the new slot names that hypothesis' row.
+    // Looked for in this way, by the sequences' hashes, only where the caller counts them or the rows have no tags, which find
+    // nearly all of these and others.
     int reuse_slot = -1;
-    if (s.reuse) {   // uniform
+    if (s.reuse && (s.stats || !TAGS)) {   // uniform
         const int o_hlo = (int)(unsigned)o.hash, o_hhi = (int)(unsigned)(o.hash >> 32);
         for (int j = 0; j < W; ++j) {
             const bool live_j = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o.score), j)) > -INFINITY;
@@ -321,12 +350,24 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
         if (lane == 0 && n_req) atomicAdd(s.stats, n_req);
         if (lane == 0 && n_hit) atomicAdd(s.stats + 1, n_hit);
     }
-    const bool steps = keep && is_lab && reuse_slot < 0;   // the networks advance for this pick
+    const bool wants = keep && is_lab && reuse_slot < 0;   // a row that holds the sequence, or one that the networks advance into
+    bool steps = false;
+    int first = TAGS ? __shfl(o.h.free_row, 0) - b * a.P : 0;   // where the next list of free rows begins
+    const int reuse_row = __shfl(o.h.row, reuse_slot >= 0 ? reuse_slot : 0);
+    int row = reuse_slot >= 0 ? reuse_row : row_p;
+    if (!TAGS) {
+        const unsigned long long wm = __ballot(wants);
+        const int new_row = __shfl(o.h.free_row, (int)__popcll(wm & ((1ull << lane) - 1ull)));
+        row = wants ? new_row : row;
+        steps = wants;
+    } else if (__ballot(wants) != 0ull) {   // uniform
+        int n_passed, last = -1;
+        const int found_row = qr_find_rows<LOG, false>(a, b, lane, wants, serial_p, tok, o.h, tags, mask, steps, n_passed, last);
+        row = wants ? found_row : row;
+        if (last >= 0) first = last + 1 < a.P ? last + 1 : 0;   // uniform
+    }
     const unsigned long long sm = __ballot(steps);
     const int k_step = (int)__popcll(sm & ((1ull << lane) - 1ull));
-    const int new_row = __shfl(o.h.free_row, k_step);
-    const int reuse_row = __shfl(o.h.row, reuse_slot >= 0 ? reuse_slot : 0);
-    const int row = steps ? new_row : (reuse_slot >= 0 ? reuse_row : row_p);
     int base = 0;   // the place of the utterance's labels in the list: asked for now, used last (see qr_route_picks)
     if (sm != 0ull && lane == 0) {
         if (a.B == 1) *a.n_rows_next = (int)__popcll(sm);
@@ -354,10 +395,10 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
             a.row_dst[dst] = b * a.P;   // any row of the utterance
         }
     }
-    qr_list_free_rows(a, b, lane, keep, row, mask);
+    qr_list_free_rows(a, b, lane, keep, row, mask, first);
     if (sm != 0ull) {   // uniform
         base = __builtin_amdgcn_readfirstlane(base);
-        if (steps) a.rows_next[base + k_step] = v4i{new_row, row_p, tok, 0};
+        if (steps) a.rows_next[base + k_step] = v4i{row, row_p, tok, 0};
     }
 }
 

@@ -29,3 +29,23 @@ def test_slow_frames(gpu_lib, B, W, max_sym, T):
     early = q.decode(G, dev(e), W, max_sym, max_len=T * max_sym, flags=q.DECODE_EARLY_STOP)
     for a, b in zip(got, early):
         assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+@pytest.mark.parametrize("B,W,u_max,T", [(1, 16, 30, 40), (3, 16, 20, 24), (2, 5, 30, 60), (2, 1, 30, 60), (2, 20, 20, 20), (1, 64, 10, 12)])
+def test_slow_frames_alignment_length(gpu_lib, B, W, u_max, T):
+    import torch
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    m = synth.make_model(0, weight_std=0.5)
+    m.rho = 0.4
+    e = (synth.normal(700 + W, (1, B, m.J), 1.0) + 0.1 * synth.normal(800 + W, (T, B, m.J), 1.0)).astype(np.float32)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
+    ref = oracle.decode_alsd(M, e, W, u_max)
+    got = q.decode_alsd(G, dev(e), W, u_max)
+    _compare_beams(got, ref)
+    assert ref[1].max() > 2   # there were labels
+    stats = torch.zeros(2, dtype=torch.int32, device="cuda:0")
+    for more in (dict(flags=q.ALSD_REUSE), dict(flags=q.ALSD_REUSE, stats=stats)):   # (counting looks for them in another way)
+        again = q.decode_alsd(G, dev(e), W, u_max, **more)
+        for a, b in zip(got, again):
+            assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
