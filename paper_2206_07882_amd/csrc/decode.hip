@@ -4,6 +4,9 @@
 // hypotheses on an attached CPU and is limited by the link to it (Sec. 4.1);
 // here the selection and the bookkeeping are kernels and the host only enqueues
 // a data-independent launch sequence.
+#include <chrono>
+#include <thread>
+
 #include "kernels.h"
 #include "select.h"
 
@@ -27,6 +30,7 @@ struct Plan {
     int32_t *node, *len, *row; // [NB][N]
     int32_t *free_rows, *n_taken;                         // [B][P], [B]
     v4i *tags;                                            // [B][P]: see QrRouteArgs.tags
+    v4i *prog;  float *pred_out, *lm_out;                 // see QrRunArgs; null where the search does not run ahead
     float *nx_score;  v4i *nx_info;  int32_t *nx_count; // [B][R*W], [B]
     int32_t *node_tok, *node_prev;   // [1 + T*max_sym*N]
     int32_t *live;       // [2][max_sym+2]: utterances that carried a label into round v of the frame (early stop)
@@ -119,6 +123,10 @@ void make_plan(const qrnnt_model *m, int T, int B, int W, int max_sym, void *ws,
     p.node_tok = cv.take<int32_t>(pool);
     p.node_prev = cv.take<int32_t>(pool);
     p.rows = cv.take<v4i>(N);
+    const bool use_lm = net_used(m, 1) || net_used(m, 2), runs = qr_run_takes(p.J, use_lm, B, W);
+    p.pred_out = runs ? cv.take<float>((size_t)B * p.P * p.J) : nullptr;
+    p.lm_out = runs && use_lm ? cv.take<float>((size_t)B * p.P * 128) : nullptr;
+    p.prog = runs ? cv.take<v4i>(B) : nullptr;
     take_cleared(m, p, cv, 2 * (size_t)(max_sym + 2));
     p.total = (cv.off + 255) / 256 * 256;
 }
@@ -132,7 +140,7 @@ __global__ void fill_words_kernel(uint32_t *p, size_t n_words, uint32_t v)
 // Start of an utterance: slot 0 holds the empty sequence with score 0 and advances from the zero state (row B*P) into
 // the utterance's first row with the start symbol; the other slots are empty.
 __global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0, int32_t *row0, int32_t *free_rows, int32_t *n_taken,
-                                   v4i *tags, int32_t *nx_count, v4i *rows, int32_t *n_rows, int32_t *node_tok, int32_t *node_prev,
+                                   v4i *tags, v4i *prog, int32_t *nx_count, v4i *rows, int32_t *n_rows, int32_t *node_tok, int32_t *node_prev,
                                    int W, int B, int P, int start_symbol)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -140,12 +148,13 @@ __global__ void decode_init_kernel(float *score0, int32_t *node0, int32_t *len0,
     if (n < B) {
         if (nx_count) nx_count[n] = 0;
         if (n_taken) n_taken[n] = 0;
+        if (prog) prog[n] = v4i{0, 0, 1 < P ? 1 : 0, 0};
         rows[n] = v4i{n * P, B * P, start_symbol, 0};
     }
     if (n < B * P) {   // (the last entry of an utterance is never looked at)
         const int i = n % P;
         free_rows[n] = i + 1 < P ? n + 1 : n;
-        tags[n] = v4i{-1, -1, 0, -1};   // the first row's sequence, the empty one, has serial 0
+        tags[n] = v4i{-1, -1, 0, i == 0 ? 0 : -1};   // the first row's sequence, the empty one, has serial 0
     }
     if (n >= B * W) return;
     score0[n] = (n % W == 0) ? 0.0f : -INFINITY;
@@ -364,7 +373,7 @@ void start_decode(const qrnnt_model *m, const Plan &p, Advance &ad, int32_t *n_t
     }
     fill(p.live, p.n_clear);
     // the start symbol's list is counted in the first counter, which no round uses
-    decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, p.tags, nx_count,
+    decode_init_kernel<<<(unsigned)((pool + 255) / 256), 256, 0, st>>>(p.score, p.node, p.len, p.row, p.free_rows, n_taken, p.tags, p.prog, nx_count,
                                                                        p.rows, p.n_rows, p.node_tok, p.node_prev, p.W, p.B, p.P,
                                                                        m->blank);
     prepare_advance(m, p, ad);
@@ -417,6 +426,48 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     start_decode(m, p, ad, p.n_taken, p.nx_count, st);
 
     QrRoundArgs ja = round_args(m, p, enc_proj, diag, false);
+
+    // Beams of up to 16 run ahead until the networks have to advance, which is after a frame's last round never the case.
+    if (const int wgs = p.prog ? qr_plan_run(ja, B, W) : 0) {
+        QrRunArgs r = {};
+        r.B = B;  r.W = W;  r.P = p.P;  r.T = T;  r.max_sym = max_sym;  r.n_entries = p.R * W;
+        r.every_round = diag.come > 0;
+        r.prog = p.prog;  r.score = p.score;  r.node = p.node;  r.len = p.len;  r.row = p.row;
+        r.tags = p.tags;  r.nx_score = p.nx_score;  r.nx_info = p.nx_info;
+        r.node_tok = p.node_tok;  r.node_prev = p.node_prev;
+        r.pred_out = p.pred_out;  r.lm_out = p.lm_out;  r.rows_next = p.rows;
+        // An utterance that does not have to wait makes the others wait for the launch it is in: six rounds of a large batch
+        // (64 x 1000 frames, ms: 4 rounds 72, 6 65 to 70, 8 67, 12 81; 13 x 301, wider networks: 25, 20.5, 21.5, 25), more of few
+        // utterances (5 at beam 1: 3.3, 3.0, 2.9, 2.8, 20 2.7; 1 x 152: 8.5, 7.6, 7.3, 6.2, 6.0, without a limit 6.4).
+        r.max_rounds = 64 / B < 6 ? 6 : (64 / B > 20 ? 20 : 64 / B);
+        const int64_t n = r.every_round ? (int64_t)T * p.R : (int64_t)T * max_sym + (T + r.max_rounds - 1) / r.max_rounds + 1;
+        r.n_through = p.live;
+        // As many launches as the search can need, of which it mostly needs a small part: what is left of them when it is
+        // through, as the host happens to see, is not enqueued, and the host keeps no more than LEAD of them ahead, as long as
+        // all this takes no longer than enqueueing them all would.
+        constexpr int LEAD = 32;
+        qr_take_ticket(r, st);
+        const auto start = std::chrono::steady_clock::now();
+        auto limit = start;
+        for (int64_t i = 0; i < n; ++i) {
+            unsigned far = qr_how_far(r);
+            if (i == LEAD) limit = start + (std::chrono::steady_clock::now() - start) / LEAD * n;
+            while (r.told && far != ~0u && i >= (int64_t)far + LEAD && std::chrono::steady_clock::now() < limit) {
+                std::this_thread::yield();
+                far = qr_how_far(r);
+            }
+            if (far == ~0u) break;
+            ja.round = 1u + (unsigned)i;
+            r.n_rows_next = p.n_rows + 1 + i % 3;   // (the first counter is the start symbol's)
+            r.n_rows_clear = p.n_rows + 1 + (i + 1) % 3;
+            ja.row = p.row;
+            qr_launch_search_run(ja, r, wgs, st);
+            if (i + 1 < n) advance_nets(ad, nullptr, r.n_rows_next, st);
+        }
+        backtrack_kernel<<<(N + 63) / 64, 64, 0, st>>>(p.score, p.node, p.len, p.node_tok, p.node_prev, N, max_len, tokens_out, len_out, score_out);
+        report_late(p, diag, st);
+        return qr_launch_status();
+    }
 
     int a0 = 0;   // buffer of the beam at the current frame
     for (int t = 0; t < T; ++t) {

@@ -6,6 +6,7 @@
 
 #include "head.h"
 #include "kernels.h"
+#include "round.h"
 #include "route.h"
 #include "select.h"
 
@@ -112,76 +113,6 @@ __global__ __launch_bounds__(256) void joint_fuse_kernel(const QrJointArgs a)
         }
 }
 
-// Maximum over the 16 lanes of a row, in each of them.
-__device__ __forceinline__ float qr_row_max(float x)
-{
-#define QR_ROW_STEP(ctrl) x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true)));
-    QR_ROW_STEP(0xB1)    // quad_perm [1,0,3,2]
-    QR_ROW_STEP(0x4E)    // quad_perm [2,3,0,1]
-    QR_ROW_STEP(0x141)   // row_half_mirror
-    QR_ROW_STEP(0x140)   // row_mirror
-#undef QR_ROW_STEP
-    return x;
-}
-
-// Sum over the 16 x 4 values of a row, in each of its lanes, in the order of the kernels that hold a hypothesis' tokens
-// in four lanes (linear.hip): lane 4*mt + g has tokens 16*mt + 4*g + i; for each g one chain over mt and i, then
-// (g0 + g1) + (g2 + g3).  The same bits as there matter: equal hypotheses tie, and a tie decides a beam.
-__device__ __forceinline__ float qr_row_sum(const v4f &e)
-{
-    float sum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {   // after t passes the lanes of mt < t hold their chain's value (row_shr:4 brings 0 to mt = 0)
-        const float from = t == 0 ? 0.0f : __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sum), 0x114, 0xf, 0xf, true));
-        sum = (((from + e[0]) + e[1]) + e[2]) + e[3];
-    }
-    int x = __float_as_int(sum);   // of interest: lanes 12..15 of the row
-#define QR_ROW_ADD(ctrl) x = __float_as_int(__int_as_float(x) + __int_as_float(__builtin_amdgcn_update_dpp(0, x, ctrl, 0xf, 0xf, true)));
-    QR_ROW_ADD(0xB1)
-    QR_ROW_ADD(0x4E)
-#undef QR_ROW_ADD
-    x = __builtin_amdgcn_update_dpp(x, x, 0x128 /* row_ror:8 */, 0xf, 0x2, false);   // lanes 4..7
-    x = __builtin_amdgcn_update_dpp(x, x, 0x124 /* row_ror:4 */, 0xf, 0x5, false);   // lanes 0..3 and 8..11
-    return __int_as_float(x);
-}
-
-// Four tokens (k0 ..) of an output layer from the sums of their rows, as log-probabilities if it ends in a log-softmax; the
-// 16 lanes of a row hold all tokens of a hypothesis.
-__device__ __forceinline__ v4f qr_token_values(v4i t, bool w8, const float *scale, const float *bias, int k0, int V, bool log_softmax)
-{
-    t = w8 ? t : (t >> 4);   // 4-bit operands carry a factor 16
-    const v4f ws = *(const v4f *)(scale + k0), wb = *(const v4f *)(bias + k0);
-    float mx = -INFINITY;
-    v4f v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = k0 + i < V ? ws[i] * (float)t[i] + wb[i] : -INFINITY;
-        mx = fmaxf(mx, v[i]);
-    }
-    mx = qr_row_max(mx);
-    v4f e;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) e[i] = qr_exp(v[i] - mx);   // (0 behind the last token)
-    float lse = mx + qr_log(qr_row_sum(e));
-    if (!log_softmax) lse = 0.0f;
-    return v - lse;
-}
-
-// Words of value and round number for another workgroup, one or four next to each other.  What a reader finds is a whole word
-// or none of it: the store is one instruction, here and not by the compiler's leave, and its 8-byte words are aligned.  It
-// reaches the XCD's L2; at the scope of the device, as 8-byte atomics or as these with sc1, the same stores cost 3 to 11 % of a
-// search (64 x 300 frames, alignment-length search, ms: 16.65, sc1 17.19, atomics 18.42).
-__device__ __forceinline__ void qr_send(unsigned long long *to, unsigned v, unsigned round)
-{
-    asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(to), "v"((unsigned long long)round << 32 | v) : "memory");
-}
-__device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned round)
-{
-    const v4i lo = {v[0], (int)round, v[1], (int)round}, hi = {v[2], (int)round, v[3], (int)round};
-    asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:16\n\ts_nop 1" ::"v"(to), "v"(lo), "v"(hi)
-                 : "memory");   // (s_nop: see qr_store_through)
-}
-
 // One decoding round of an utterance in one workgroup (or several: see CL): output layers of the three networks, joint,
 // log-softmax and fusion for its W hypotheses (NTW column tiles of 16), selection of the W best (parent, token) extensions, routing
 // (route.h), and after the last round of a frame the new beam.  In one workgroup nothing touches memory between the networks'
@@ -222,7 +153,7 @@ __device__ __forceinline__ void qr_send(unsigned long long *to, v4i v, unsigned 
 // the step kernels take as long for one as for all of them, and the list is hardly ever empty): looking cost 228 iterations at
 // beam 4 2 %, 60 us, and saved none.
 template <int NTW, bool ALSD, bool CL, bool TAGS = true>
-__global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
+__global__ __launch_bounds__(512, CL ? 4 : 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
 {
     constexpr int MAX_LIST = ALSD ? 1 : 16 * NTW * 17;   // a frame's candidates: W blanks in each of at most 17 rounds
     __shared__ v4i sums[8][4][64];          // [wave][row tile][lane, swizzled] partial sums; then the gathered candidates
@@ -236,7 +167,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
     __shared__ __attribute__((aligned(16))) int8_t mid_code[CL ? 2 : 1][CL ? 16 : 1][272];   // codes of the language models' bottlenecks
     __shared__ v4f lm_val[CL ? 2 : 1][CL ? 256 : 1];   // the language models' values for each thread of the scores
     __shared__ unsigned mask[64];
-    constexpr int LOG_SLOTS = !TAGS ? 0 : (NTW == 1 ? 9 : 11);
+    constexpr int LOG_SLOTS = !TAGS ? 1 : (NTW == 1 ? 9 : 11);
     __shared__ v4i tag_lds[TAGS ? (16 * NTW * (ALSD ? QR_ALSD_ROWS : 17) + 63) / 64 * 64 : 1];   // (a row of the pool for every candidate of a frame)
     __shared__ unsigned short tag_slot[1 << LOG_SLOTS];
     __shared__ unsigned char tag_twin[1 << LOG_SLOTS];
@@ -299,30 +230,9 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
 
     const int n_row_tiles = (V + 15) >> 4;
     const int my_n = b * W + (col < W ? col : W - 1);   // this lane's column of the (first) tile
-    // Contraction of output layer h by this wave: chunks c0, c0 + step, ...
-    auto head_mma = [&](auto batch, const QrHeadArgs &h, int row, int c0, int step, v4i (&acc)[4]) {
-        constexpr int NB = decltype(batch)::value, NB8 = NB > 1 ? NB / 2 : 1;   // chunks in flight
-        unsigned woff[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
-            woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
-        }
-        if (h.w8) qr_chunk_mma<true, NB8>(h.w, woff, h.act, row, h.K, h.nkc, c0, step, grp, acc, [] {});
-        else qr_chunk_mma<false, NB>(h.w, woff, h.act, row, h.K, h.nkc, c0, step, grp, acc, [] {});
-    };
-    // where a lane's sums of row tile mt go, and where the thread of the scores with hypothesis hc finds those of its quad
-    auto put_sums = [&](const v4i (&acc)[4]) {
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][grp * 16 + (col ^ (4 * mt + grp))] = acc[mt];
-    };
-    // row scales and biases of the joint (q = 0) or a language model into LDS, by one wave
-    auto row_constants = [&](int q) {
-        const int kk = lane < V ? lane : V - 1;
-        const float *sw = q == 0 ? a.s_w : a.head[q].s_w, *bs = q == 0 ? a.b_out : a.head[q].bias;
-        jc[q][0][lane] = sw ? (q == 0 ? a.z_scale : a.head[q].a_scale) * sw[kk] : 0.0f;
-        jc[q][1][lane] = bs ? bs[kk] : 0.0f;
-    };
+    QrShare share = {a, sums, (int8_t(*)[16][272])mid_code, jc, &missed, b, V};   // what the workgroups of an utterance do for one another
+    auto word_at = [&](int q, int hyp, int token) { return share.word_at(q, hyp, token); };
+    auto enough = [&](unsigned &limit) { return share.enough(limit); };
 
     // CL: this workgroup's share of the joint: blocks of 64 columns first, first + a.parts, ...  A block: the 64 rows of the
     // prediction network's output layer, K dealt to the eight waves; a thread adds up two columns of a hypothesis and forms
@@ -382,128 +292,16 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         }
         return sum;
     };
-    // CL: 64 rows of the bottleneck of language model 1 + net, as in joint_part: this thread's two codes.
-    auto mid_part = [&](int net, int part, int row) -> unsigned {
-        const QrMidArgs &h = a.mid[net];
-        const int n_tiles = h.rows >> 4, j = part * 64 + z_col < h.rows ? part * 64 + z_col : 0;
-        unsigned woff[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const int rt = 4 * part + mt < n_tiles ? 4 * part + mt : n_tiles - 1;
-            woff[mt] = (unsigned)rt * h.nkc * (h.w8 ? 2048 : 1024) + lane * 16;
-        }
-        v4i acc[4] = {zero, zero, zero, zero};
-        if (h.w8) qr_chunk_mma<true, 1>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
-        else qr_chunk_mma<false, 2>(h.w, woff, h.act, row, h.K, h.nkc, wave, 8, grp, acc, [] {});
-        const float sw0 = h.a_scale * h.s_w[j], sw1 = h.a_scale * h.s_w[j + 1];
-        const float bs0 = h.bias ? h.bias[j] : 0.0f, bs1 = h.bias ? h.bias[j + 1] : 0.0f;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) sums[wave][mt][lane] = acc[mt];
-        __syncthreads();
-        int s0 = 0, s1 = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const int *const q = (const int *)&sums[w][tid >> 7][z_lane] + 2 * (tid & 1);
-            s0 += q[0];
-            s1 += q[1];
-        }
-        s0 = h.w8 ? s0 : (s0 >> 4);
-        s1 = h.w8 ? s1 : (s1 >> 4);
-        const int c0 = qr_quant(sw0 * (float)s0 + bs0, h.q_inv, h.q_bits), c1 = qr_quant(sw1 * (float)s1 + bs1, h.q_inv, h.q_bits);
-        return (unsigned)(c0 & 0xFF) | (unsigned)(c1 & 0xFF) << 8;
-    };
-    // CL: output layer of language model 1 + net by this wave, chunks c0, c0 + step, ...; its operand may lie in mid_code.
-    auto lm_mma = [&](int net, int row, int c0, int step, v4i (&acc)[4]) {
-        const QrHeadArgs &h = a.head[1 + net];
-        if (!h.w) return;   // uniform
-        if (!a.mid[net].w) {
-            head_mma(std::integral_constant<int, 2>{}, h, row, c0, step, acc);
-            return;
-        }
-        for (int kc = c0; kc < h.nkc; kc += step) {   // (at most two chunks; columns beyond K meet zero weights)
-            const int k = kc * QRNNT_KCHUNK + grp * 16;
-            const v4i x0 = *(const v4i *)&mid_code[net][col][k], x1 = *(const v4i *)&mid_code[net][col][k + 64];
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                const int rt = mt < n_row_tiles ? mt : n_row_tiles - 1;
-                const v4i *const w = h.w + ((size_t)rt * h.nkc + kc) * (h.w8 ? 128 : 64) + lane;
-                const v4i f = w[0];
-                acc[mt] = qr_mfma(h.w8 ? f : ((f << 4) & m), x0, acc[mt]);
-                acc[mt] = qr_mfma(h.w8 ? w[64] : (f & m), x1, acc[mt]);
-            }
-        }
-    };
-    // A wait for words has lasted `limit` (a quarter of the time at first): true if it is enough.
-    auto enough = [&](unsigned &limit) {
-        if (limit == (unsigned)a.ticks || a.late[b] >= 8) return true;   // uniform
-        limit = (unsigned)a.ticks;
-        return false;
-    };
-    // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
-    auto word_at = [&](int q, int hyp, int token) { return a.words + b * a.n_words + (q * 16 + hyp) * 64 + token; };
-
     if (CL && blockIdx.y + 1 < gridDim.y) {   // uniform: not the first workgroup
         if (!ALSD && r.gate && *r.gate == 0) return;   // uniform
         const int row = a.row[my_n];
         const int part = (int)(gridDim.y - 1 - blockIdx.y);   // first workgroup 0, shares of the joint, language models, bottlenecks
-        if (part > a.parts) {
-            int p = part - a.parts - 1;
-            const int n0 = a.mid[0].w ? (a.mid[0].rows + 63) >> 6 : 0, net = p < n0 ? 0 : 1;
-            p -= net ? n0 : 0;
-            const unsigned code = mid_part(net, p, row);
-            const unsigned next = (unsigned)__builtin_amdgcn_update_dpp(0, (int)code, 0xB1 /* the neighbour's */, 0xf, 0xf, true);
-            if ((tid & 1) == 0 && p * 64 + z_col < a.mid[net].rows)
-                qr_send(word_at(QR_ROUND_PARTS + 1 + net, z_hyp, (p * 64 + z_col) >> 2), code | next << 16, a.round);
+        if (part >= a.parts) {
+            share.send_lm(part - a.parts, row);
             return;
         }
-        if (part < a.parts) {                          // a share of the joint
-            const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);
-            if (wave < 4) qr_send(word_at(part, col, wave * 16 + 4 * grp), sum, a.round);
-            return;
-        }
-        const int net = wave >> 2;                     // the language models: waves 0-3 source, 4-7 external, K split in four
-        const QrHeadArgs &h = a.head[1 + net];
-        v4i acc[4] = {zero, zero, zero, zero};
-        if ((wave & 3) == 3) row_constants(1 + net);
-        if (a.mid[0].w || a.mid[1].w) {                // uniform: the bottlenecks' codes, 16 of a hypothesis to a thread
-            if (tid == 0) missed = 0;
-            __syncthreads();
-            if (a.mid[net].w) {                        // uniform
-                const int hyp = (tid & 255) >> 4, c0 = (tid & 15) * 16;
-                const __amdgpu_buffer_rsrc_t area = __builtin_amdgcn_make_buffer_rsrc((void *)word_at(QR_ROUND_PARTS + 1 + net, 0, 0), 0,
-                                                                                      16 * 64 * 8, 0x00020000 /* raw bytes */);
-                const bool mine = c0 < a.mid[net].rows;
-                unsigned limit = (unsigned)a.ticks / 4;
-                for (const unsigned long long t0 = wall_clock64();;) {
-                    const unsigned off = (unsigned)(hyp * 64 + (tid & 15) * 4) * 8;
-                    const v4i u = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off, 0, 16 /* sc1 */);
-                    const v4i v = (v4i)__builtin_amdgcn_raw_buffer_load_b128(area, off + 16, 0, 16);
-                    asm volatile("" ::: "memory");     // every poll loads anew
-                    const bool ok = !mine || ((unsigned)u[1] == a.round && (unsigned)u[3] == a.round && (unsigned)v[1] == a.round &&
-                                              (unsigned)v[3] == a.round);
-                    if (__all(ok)) {
-                        *(v4i *)&mid_code[net][hyp][c0] = v4i{u[0], u[2], v[0], v[2]};
-                        break;
-                    }
-                    if (wall_clock64() - t0 > limit && enough(limit)) {
-                        if (lane == 0) missed = 1;
-                        break;
-                    }
-                }
-            }
-            __syncthreads();
-            if (__builtin_amdgcn_readfirstlane(missed)) return;   // uniform: the first workgroup does it all then
-        }
-        lm_mma(net, row, wave & 3, 4, acc);
-        put_sums(acc);
-        __syncthreads();
-        const int hc = (tid & 255) >> 4, quad = lane & 15, mt = quad >> 2, at = (quad & 3) * 16 + (hc ^ quad);
-        v4i t = zero;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) t += sums[4 * net + k][mt][at];
-        const v4f v = qr_token_values(t, h.w8 != 0, jc[1 + net][0], jc[1 + net][1], 4 * quad, V, h.log_softmax != 0);
-        qr_send(word_at(net == 0 ? 0 : QR_ROUND_PARTS, hc, 4 * quad),
-                v4i{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])}, a.round);
+        const v4i sum = joint_part(part, row, ALSD ? r.len_src[b * W + (z_hyp < W ? z_hyp : W - 1)] : 0);   // a share of the joint
+        if (wave < 4) qr_send(word_at(part, col, wave * 16 + 4 * grp), sum, a.round);
         return;
     }
 
@@ -526,7 +324,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         else if (k < 128) best_fe[k - 64] = 0;
         else if (k < 192) fin_new[k - 128] = -INFINITY;
         else if (k == 192) n_cand = missed = 0;
-        if (wave < 7) row_constants(wave - 4);   // joint, source LM, external LM
+        if (wave < 7) share.row_constants(wave - 4);   // joint, source LM, external LM
     }
     // What the routing wave and the scoring threads will need: requested first, used last.
     QrOwn own = {};
@@ -540,7 +338,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         if (ALSD) alsd_own = qr_alsd_load_own(r, s, b, lane);
         else nx0 = r.nx_count[b];
     }
-    if (TAGS && !frame_end && wave == 6) qr_request_tags(r, b, lane, tags);
+    if (TAGS && !frame_end && wave == 6) qr_request_tags(r.tags + (size_t)b * r.P, r.P, lane, tags);
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
         const int w = nt * 16 + ((tid >> 4) & 15);
@@ -677,11 +475,11 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         } else {
             const QrHeadArgs &h = a.head[wave >= 6 ? 2 : 1];
             load_rest();
-            if (h.w && !frame_end) head_mma(std::integral_constant<int, NTW == 1 ? 4 : 2>{}, h, row, wave & 1, 2, acc);   // uniform
+            if (h.w && !frame_end) share.head_mma<NTW == 1 ? 4 : 2>(h, row, wave & 1, 2, acc);   // uniform
             enter_rest();
         }
         if (CL) enter_rest();
-        if (!CL) put_sums(acc);
+        if (!CL) share.put_sums(acc);
         if (ALSD && nt == 0 && r.gate && *r.gate == 0) return;   // uniform: no live hypothesis anywhere, the finals stay as they are
         __syncthreads();
 
@@ -707,13 +505,13 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
             }
             for (int net = 0; net < 2; ++net)
                 for (int p = 0; use_lm && a.mid[net].w && p * 64 < a.mid[net].rows; ++p) {
-                    const unsigned code = mid_part(net, p, row);
+                    const unsigned code = share.mid_part(net, p, row);
                     *(unsigned short *)&mid_code[net][z_hyp][p * 64 + z_col] = (unsigned short)code;
                     __syncthreads();
                 }
             if (wave >= 4 && use_lm) {
-                lm_mma(wave >= 6 ? 1 : 0, row, wave & 1, 2, acc);
-                put_sums(acc);
+                share.lm_mma(wave >= 6 ? 1 : 0, row, wave & 1, 2, acc);
+                share.put_sums(acc);
             }
             __syncthreads();
         }
@@ -759,7 +557,7 @@ __global__ __launch_bounds__(512, 2) void search_round_kernel(const QrRoundArgs 
         if (frame_end) load_first_free(own.taken);
         else own.free_row = qr_free_row(r, b, lane, own.taken);
     }
-    if (TAGS && !frame_end && wave == 6) qr_enter_tags<LOG_SLOTS>(r, lane, tags);
+    if (TAGS && !frame_end && wave == 6) qr_enter_tags<LOG_SLOTS>(r.P, lane, tags);
     __syncthreads();
     if (TAGS && !frame_end && wave == 0) own.serial = tag_lds[own.row - b * r.P][2];
 

@@ -152,6 +152,36 @@ struct QrRouteArgs {
     int serial0, now;                               // serials of this round's sequences: from serial0 + 1 on, W at most; the frame
 };
 
+// Time-synchronous search that runs ahead (search.hip): an utterance's state between launches, and what it writes.
+struct QrRunArgs {
+    int B, W, P, T, max_sym;
+    int n_entries;                                  // W * (max_sym + 1)
+    int max_rounds;                                 // of a launch
+    int every_round;                                // diagnostic: one round to a launch, none of them empty by knowledge
+    v4i *prog;                                      // [B]: frame and round that are pending, row to be taken next, candidates so far
+    float *score;  int32_t *node, *len, *row;       // [N]: hypotheses of the pending round
+    v4i *tags;                                      // [B][P]: see QrRouteArgs.tags
+    float *nx_score;  v4i *nx_info;                 // [B][n_entries]: the frame's candidates so far
+    int32_t *node_tok, *node_prev;
+    float *pred_out, *lm_out;                       // [B * P][J], [B * P][2][64]: outputs of a row of the state pool
+    v4i *rows_next;  int32_t *n_rows_next, *n_rows_clear;   // as in QrRouteArgs; cleared for the next launch
+    int32_t *n_through;                             // utterances that are through
+    unsigned long long *told;                       // host memory, or null: takes ticket << 32 | launch, ~0u when all are through
+    unsigned ticket;
+};
+// Beams and joints that it takes, on any device; the workgroups of an utterance on this one, 0: it does not.
+inline bool qr_run_takes(int J, bool use_lm, int B, int W) { return W <= 16 && J <= 64 * QR_ROUND_PARTS && (J <= 64 && !use_lm ? true : B <= 256); }
+QR_HIDDEN int qr_plan_run(const QrRoundArgs &a, int B, int W);
+// Where a search on stream st can tell the host how far it is (r.told, r.ticket), if there is such a place; 0: not started,
+// ~0u: through, else the last launch that has begun (round: from 1 on).
+QR_HIDDEN void qr_take_ticket(QrRunArgs &r, hipStream_t st);
+inline unsigned qr_how_far(const QrRunArgs &r)
+{
+    const unsigned long long w = r.told ? __atomic_load_n(r.told, __ATOMIC_RELAXED) : 0ull;
+    return (unsigned)(w >> 32) == r.ticket ? (unsigned)w : 0u;
+}
+QR_HIDDEN void qr_launch_search_run(const QrRoundArgs &a, const QrRunArgs &r, int wgs, hipStream_t st);
+
 // Alignment-length synchronous search: what one iteration needs beyond QrRouteArgs (of which it uses score/node/len/row
 // src and dst, the pool rows, the label trie, node_base, gate, live_next and the list of rows).
 struct QrAlsdArgs {

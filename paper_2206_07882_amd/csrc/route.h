@@ -51,22 +51,49 @@ __device__ __forceinline__ unsigned qr_tag_hash(int serial, int tok)
 
 // The tags of utterance b go to LDS, by one wave: requested at the kernel's start, straight into LDS (wanted much later, and
 // registers are short), and entered in the table when they are there.  (Of rows that share a place in the table one is found.)
-__device__ __forceinline__ void qr_request_tags(const QrRouteArgs &a, int b, int lane, const QrTags &t)
+__device__ __forceinline__ void qr_request_tags(const v4i *tags, int P, int lane, const QrTags &t)
 {
-    for (int i0 = 0; i0 < a.P; i0 += 64) {
-        const int i = i0 + lane < a.P ? i0 + lane : a.P - 1;
-        qr_load_lds16(a.tags + (size_t)b * a.P + i, (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(t.tag + i0));
+    for (int i0 = 0; i0 < P; i0 += 64) {
+        const int i = i0 + lane < P ? i0 + lane : P - 1;
+        qr_load_lds16(tags + i, (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(t.tag + i0));
     }
 }
 
 template <int LOG>
-__device__ __forceinline__ void qr_enter_tags(const QrRouteArgs &a, int lane, const QrTags &t)
+__device__ __forceinline__ void qr_enter_tags(int P, int lane, const QrTags &t)
 {
     qr_wait_vmcnt<0>();
-    for (int i = lane; i < a.P; i += 64) {
+    for (int i = lane; i < P; i += 64) {
         const v4i g = t.tag[i];
         if (g[0] >= 0) t.slot[qr_tag_hash<LOG>(g[0], g[1])] = (unsigned short)i;
     }
+}
+
+// The row (relative) that holds the sequence of this lane's label pick, P: none.  steps: none, and the networks have to advance;
+// first: the lane of the pick that does so for this one's sequence.
+template <int LOG, bool TWINS>
+__device__ __forceinline__ int qr_held_row(int P, int lane, bool is_lab, int serial, int tok, int now, const QrTags &t, bool &steps, int &first)
+{
+    const unsigned at = qr_tag_hash<LOG>(serial, tok);
+    int held = is_lab ? t.slot[at] : P;      // (an entry that nobody has written may be any number)
+    if (held < P) {
+        const v4i g = t.tag[held];
+        held = g[0] == serial && g[1] == tok ? held : P;
+    } else {
+        held = P;
+    }
+    const bool hit = held < P;
+    if (hit) t.tag[held][3] = now;
+    first = lane;
+    if (TWINS) {
+        if (is_lab && !hit) t.twin[at] = (unsigned char)lane;
+        __builtin_amdgcn_wave_barrier();
+        first = is_lab && !hit ? t.twin[at] : lane;
+        const int first_serial = __shfl(serial, first), first_tok = __shfl(tok, first);
+        first = first_serial == serial && first_tok == tok ? first : lane;
+    }
+    steps = is_lab && !hit && first == lane;
+    return held;
 }
 
 // Rows for this round's label picks (lanes with is_lab: parent's row, label): a row that holds the sequence, or the next
@@ -81,26 +108,10 @@ __device__ __forceinline__ int qr_find_rows(const QrRouteArgs &a, int b, int lan
 {
     const int row0 = b * a.P;
     const int serial = is_lab ? par_serial : -1;
-    const unsigned at = qr_tag_hash<LOG>(serial, tok);
-    int held = is_lab ? t.slot[at] : a.P;      // (an entry that nobody has written may be any number)
-    if (held < a.P) {
-        const v4i g = t.tag[held];
-        held = g[0] == serial && g[1] == tok ? held : a.P;
-    }
+    int first;
+    const int held = qr_held_row<LOG, TWINS>(a.P, lane, is_lab, serial, tok, a.now, t, steps, first);
     const bool hit = held < a.P;
-    if (hit) {
-        t.tag[held][3] = a.now;
-        a.tags[(size_t)row0 + held][3] = a.now;
-    }
-    int first = lane;
-    if (TWINS) {
-        if (is_lab && !hit) t.twin[at] = (unsigned char)lane;
-        __builtin_amdgcn_wave_barrier();
-        first = is_lab && !hit ? t.twin[at] : lane;
-        const int first_serial = __shfl(serial, first), first_tok = __shfl(tok, first);
-        first = first_serial == serial && first_tok == tok ? first : lane;
-    }
-    steps = is_lab && !hit && first == lane;
+    if (hit) a.tags[(size_t)row0 + held][3] = a.now;
     const unsigned long long sm = __ballot(steps);
     const int n_new = (int)__popcll(sm);
     int row = row0 + held;
@@ -155,6 +166,43 @@ __device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane
     int f = taken + lane;              // (a pick never needs more than there are, see the pool's size in decode.hip)
     f = f < a.P ? f : a.P - 1;
     return a.free_rows[(size_t)b * a.P + f];
+}
+
+// The same where the tags stay in LDS and no list is kept: a row is free if it has not been named in frame `now` (those of the
+// beam are marked when the frame begins), and the free ones are taken in turn from row `cursor` (relative) on.  There is always
+// one: a frame names W * (max_sym + 1) = P rows at most.  Serials serial0 + 1 ... go to the new sequences.
+template <int LOG>
+__device__ __forceinline__ int qr_find_rows_in_turn(int P, int row0, int lane, bool is_lab, int par_serial, int tok, int now, int serial0,
+                                                    int &cursor, const QrTags &t, unsigned *mask, bool &steps)
+{
+    const int serial = is_lab ? par_serial : -1;
+    int first;
+    const int held = qr_held_row<LOG, true>(P, lane, is_lab, serial, tok, now, t, steps, first);
+    const unsigned long long sm = __ballot(steps), lt = (1ull << lane) - 1ull;
+    const int n_new = (int)__popcll(sm);
+    int row = held;
+    if (n_new > 0) {   // uniform
+        const int k_new = (int)__popcll(sm & lt);
+        int got = 0;
+        for (int i0 = 0; i0 < P; i0 += 64) {
+            int i = cursor + i0 + lane;
+            i = i < P ? i : i - P;
+            i = i0 + lane < P ? i : 0;
+            const bool ok = i0 + lane < P && t.tag[i][3] != now;
+            const unsigned long long om = __ballot(ok);
+            const int k = got + (int)__popcll(om & lt);
+            if (ok && k < n_new) mask[k] = (unsigned)i;
+            got += (int)__popcll(om);
+            if (got >= n_new) break;   // uniform
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int new_row = (int)mask[k_new < n_new ? k_new : 0], last = (int)mask[n_new - 1];
+        cursor = last + 1 < P ? last + 1 : 0;
+        if (steps) t.tag[new_row] = v4i{serial, tok, serial0 + 1 + k_new, now};
+        const int first_row = __shfl(new_row, first);
+        row = held < P ? held : first_row;
+    }
+    return row0 + row;
 }
 
 // The utterance's free rows for what follows: all of its P rows except the ones that lanes with `held` name, from row

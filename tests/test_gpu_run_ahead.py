@@ -1,0 +1,60 @@
+"""Beams of up to 16 and joints of up to 256 columns: an utterance runs ahead inside a launch.  The edges: one round to a frame,
+no label at all, every frame the same, joints that end inside a 64-column share, bottlenecks, the beams on both sides of the
+limit, more utterances than run at once; and the launches of a graph, which are all that can be needed."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import models as omodels
+from paper_2206_07882_amd import synth
+
+from .test_gpu_decode import _compare_beams, dev
+from .test_gpu_search_round import _model
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("J,V,B,W,max_sym,T,rho,mids", [(256, 46, 1, 16, 4, 30, 0.1, ()), (80, 17, 3, 5, 1, 40, 0.4, ()),
+                                                        (16, 2, 2, 1, 4, 30, 0.4, ()), (240, 64, 2, 16, 0, 12, 0.1, ()),
+                                                        (256, 33, 9, 3, 2, 20, 8.0, ()), (64, 20, 2, 8, 3, 20, 0.4, ((2, 80),)),
+                                                        (256, 46, 2, 17, 2, 10, 0.4, ()), (272, 46, 2, 16, 2, 10, 0.4, ()),
+                                                        (128, 46, 130, 2, 2, 6, 0.4, ())])
+def test_running_ahead(gpu_lib, J, V, B, W, max_sym, T, rho, mids):
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    m = _model(J, V, False, mids)
+    m.rho = rho
+    e = (synth.normal(1000 + J, (1, B, J), 1.0) + 0.1 * synth.normal(1001 + J, (T, B, J), 1.0)).astype(np.float32)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
+    max_len = max(1, T * max_sym)
+    got = q.decode(G, dev(e), W, max_sym, max_len=max_len)
+    _compare_beams(got, oracle.decode(M, e, W, max_sym, max_len=max_len))
+    early = q.decode(G, dev(e), W, max_sym, max_len=max_len, flags=q.DECODE_EARLY_STOP)
+    for a, b in zip(got, early):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,W", [(1, 16), (7, 4)])
+def test_a_graph_of_a_search(gpu_lib, B, W):
+    """A graph holds the launches of the longest search, and its replays read what is in the inputs then."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    T, max_sym = 12, 3
+    G = gmodel.model_from_float(_model(80, 17, False), "cuda:0")
+    es = [dev(synth.normal(1100 + i, (T, B, 80), 1.0)) for i in range(3)]
+    want = [q.decode(G, e, W, max_sym) for e in es]
+    e = es[0].clone()
+    ws = torch.empty(q.decode_workspace(G, T, B, W, max_sym), dtype=torch.uint8, device="cuda:0")
+    q.decode(G, e, W, max_sym, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = q.decode(G, e, W, max_sym, workspace=ws)
+    for i in (1, 0, 2, 1):
+        e.copy_(es[i])
+        graph.replay()
+        torch.cuda.synchronize()
+        for w, g in zip(want[i], out):
+            assert torch.equal(w, g)
+        assert all(torch.equal(a, b) for a, b in zip(q.decode(G, es[i], W, max_sym), want[i]))
