@@ -35,6 +35,21 @@ def test_running_ahead(gpu_lib, J, V, B, W, max_sym, T, rho, mids):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 8, 16])
+def test_equal_candidates(gpu_lib, W):
+    """Pairs of tokens with the same row of the joint's output layer and no language model: their candidates are equal, and the
+    last place of the beam goes to the first of a pair."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    m = _model(80, 17, False)
+    for a in (m.joint_out.w, m.joint_out.bias):
+        a[2::2] = a[1::2]
+    T, max_sym = 10, 3
+    e = synth.normal(1200, (T, 3, 80), 1.0)
+    G, M = gmodel.model_from_float(m, "cuda:0", use_src=False, use_ext=False), omodels.model_from_float(m, use_src=False, use_ext=False)
+    _compare_beams(q.decode(G, dev(e), W, max_sym), oracle.decode(M, e, W, max_sym))
+
+
 @pytest.mark.parametrize("B,W", [(1, 16), (7, 4)])
 def test_a_graph_of_a_search(gpu_lib, B, W):
     """A graph holds the launches of the longest search, and its replays read what is in the inputs then."""
