@@ -169,8 +169,13 @@ struct QrRunArgs {
     unsigned long long *told;                       // host memory, or null: takes ticket << 32 | launch, ~0u when all are through
     unsigned ticket;
 };
-// Beams and joints that it takes, on any device; the workgroups of an utterance on this one, 0: it does not.
-inline bool qr_run_takes(int J, bool use_lm, int B, int W) { return W <= 16 && J <= 64 * QR_ROUND_PARTS && (J <= 64 && !use_lm ? true : B <= 256); }
+// What it takes on any device (taken to hold 512 workgroups at most, as for the words; a search of more utterances keeps no
+// outputs and has a launch to a round); the workgroups of an utterance on this one, 0: it does not.
+inline bool qr_run_takes(int J, bool use_lm, int B, int W)
+{
+    const int wgs = (J + 63) / 64 + (use_lm ? 1 : 0);
+    return W <= 16 && J <= 64 * QR_ROUND_PARTS && (wgs == 1 ? B <= 512 : 6 * (int64_t)B * wgs <= 5 * 512);
+}
 QR_HIDDEN int qr_plan_run(const QrRoundArgs &a, int B, int W);
 // Where a search on stream st can tell the host how far it is (r.told, r.ticket), if there is such a place; 0: not started,
 // ~0u: through, else the last launch that has begun (round: from 1 on).
