@@ -152,7 +152,7 @@ struct QrRouteArgs {
     int serial0, now;                               // serials of this round's sequences: from serial0 + 1 on, W at most; the frame
 };
 
-// Time-synchronous search that runs ahead (search.hip): an utterance's state between launches, and what it writes.
+// Time-synchronous search that runs ahead (joint.hip): an utterance's state between launches, and what it writes.
 struct QrRunArgs {
     int B, W, P, T, max_sym;
     int n_entries;                                  // W * (max_sym + 1)
