@@ -396,9 +396,12 @@ size_t qrnnt_decode_workspace(const qrnnt_model *m, int32_t T, int32_t B, int32_
  * score, label picks form the next A with all networks advanced from the
  * parent's state (qrnnt_lstm_step with parent gather); after the last round the
  * beam becomes the W best candidates by (score descending, insertion order).
- * Equal label sequences are not merged.  All rounds always run (dead slots carry
- * score -inf), so the launch sequence does not depend on the data and nothing
- * is copied to the host.
+ * Equal label sequences are not merged.  The call enqueues as many launches as
+ * the longest search of these sizes can need and waits for nothing; launches
+ * behind the end of the search return at once.  Outside of graph capture it
+ * leaves out those that it has not enqueued yet when it happens to see, in a
+ * word of host memory that the kernels write, that the search is through: the
+ * number of launches may differ from call to call, their results do not.
  * Outputs [device], best first: tokens_out int32 [B,W,max_len] (padded with
  * -1), len_out int32 [B,W] (-1 for an empty rank), score_out fp32 [B,W].
  * workspace [device]: qrnnt_decode_workspace bytes, 256-byte aligned. */
@@ -411,7 +414,10 @@ qrnnt_status qrnnt_decode(const qrnnt_model *m, const float *enc_proj, int32_t T
  * a label into that round and return at once when it is zero (then no later round
  * of the frame can pick anything either): same results, a few loads more per
  * kernel, and the cost of a frame follows the labels it actually emits.  The host
- * still enqueues the same launch sequence.  flags == 0 is qrnnt_decode. */
+ * still enqueues the same launch sequence.  Without effect where utterances run
+ * ahead, which pass over such rounds by themselves (W <= 16 and J <= 256, while
+ * the device holds the workgroups of all utterances).  flags == 0 is
+ * qrnnt_decode. */
 #define QRNNT_DECODE_EARLY_STOP 1u
 qrnnt_status qrnnt_decode_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                              int32_t max_sym, int32_t max_len, uint32_t flags, int32_t *tokens_out, int32_t *len_out,

@@ -2,11 +2,8 @@
 // selection, hypothesis bookkeeping and the advance of the prediction network
 // and both language models (Sec. 2).  The paper's simulated system sorts
 // hypotheses on an attached CPU and is limited by the link to it (Sec. 4.1);
-// here the selection and the bookkeeping are kernels and the host only enqueues
-// a data-independent launch sequence.
-#include <chrono>
-#include <thread>
-
+// here the selection and the bookkeeping are kernels and the host only enqueues,
+// as many launches as the longest search can need, and waits for nothing.
 #include "kernels.h"
 #include "select.h"
 
@@ -437,26 +434,15 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
         r.node_tok = p.node_tok;  r.node_prev = p.node_prev;
         r.pred_out = p.pred_out;  r.lm_out = p.lm_out;  r.rows_next = p.rows;
         // An utterance that does not have to wait makes the others wait for the launch it is in: six rounds of a large batch
-        // (64 x 1000 frames, ms: 4 rounds 72, 6 65 to 70, 8 67, 12 81; 13 x 301, wider networks: 25, 20.5, 21.5, 25), more of few
-        // utterances (5 at beam 1: 3.3, 3.0, 2.9, 2.8, 20 2.7; 1 x 152: 8.5, 7.6, 7.3, 6.2, 6.0, without a limit 6.4).
+        // (64 x 1000 frames, ms: 4 rounds 73.3, 6 69.9, 8 74.3, 12 81.6, 20 98; 13 x 301, wider networks: 26.6, 24.0, 25.0, 26.8,
+        // 31.1), more of few utterances (5 at beam 1: 5.3, -, 4.5, 4.7, 4.3, 40 4.2; 1 x 152: 8.9, -, 8.0, 7.3, 7.1, 40 7.1).
         r.max_rounds = 64 / B < 6 ? 6 : (64 / B > 20 ? 20 : 64 / B);
         const int64_t n = r.every_round ? (int64_t)T * p.R : (int64_t)T * max_sym + (T + r.max_rounds - 1) / r.max_rounds + 1;
         r.n_through = p.live;
-        // As many launches as the search can need, of which it mostly needs a small part: what is left of them when it is
-        // through, as the host happens to see, is not enqueued, and the host keeps no more than LEAD of them ahead, as long as
-        // all this takes no longer than enqueueing them all would.
-        constexpr int LEAD = 32;
+        // As many launches as the search can need, of which it mostly needs a small part.  The host never waits for the search;
+        // where it happens to see that the search is through, it leaves out what it has not enqueued yet.
         qr_take_ticket(r, st);
-        const auto start = std::chrono::steady_clock::now();
-        auto limit = start;
-        for (int64_t i = 0; i < n; ++i) {
-            unsigned far = qr_how_far(r);
-            if (i == LEAD) limit = start + (std::chrono::steady_clock::now() - start) / LEAD * n;
-            while (r.told && far != ~0u && i >= (int64_t)far + LEAD && std::chrono::steady_clock::now() < limit) {
-                std::this_thread::yield();
-                far = qr_how_far(r);
-            }
-            if (far == ~0u) break;
+        for (int64_t i = 0; i < n && qr_how_far(r) != ~0u; ++i) {
             ja.round = 1u + (unsigned)i;
             r.n_rows_next = p.n_rows + 1 + i % 3;   // (the first counter is the start symbol's)
             r.n_rows_clear = p.n_rows + 1 + (i + 1) % 3;

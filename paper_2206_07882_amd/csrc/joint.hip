@@ -898,8 +898,8 @@ namespace {
 // Time-synchronous search, beams of up to 16 hypotheses: an utterance runs ahead, round after round and frame after frame,
 // until a label pick leads to a sequence whose states no row of the pool holds (route.h).  Only then does it need the networks;
 // it leaves what is pending in memory and goes on in the next launch, behind the step kernels.  The utterances of a batch
-// are in different frames.  (64 x 1000 frames at beam 16, with a launch to a round 104.5 ms, now 66 to 71; 13 x 301, wider
-// networks and 8-bit layers 33.9 / 23; 1 x 152 11.1 / 5.8 to 7.3; 5 x 237 at beam 1, early stop 12.1 / 2.8.)
+// are in different frames.  (64 x 1000 frames at beam 16, with a launch to a round 104.5 ms, now 70; 13 x 301, wider
+// networks and 8-bit layers 33.9 / 24.0; 1 x 152 11.1 / 7.1; 5 x 237 at beam 1, early stop 12.1 / 4.3.)
 //
 // The outputs of a row (prediction network's output layer, language models' log-probabilities) depend on the row alone, as its
 // states do: they are formed in the round after the networks have advanced into it and kept beside it.  So only the first
