@@ -17,8 +17,10 @@
  *     allocates no device memory.  The only state it keeps between calls is what
  *     it has learned about each device on first use (number of compute units,
  *     how many workgroups of the persistent recurrence fit at once, kernel
- *     attributes already set), cached per device; no call's result depends on
- *     an earlier call.
+ *     attributes already set), cached per device, and one page of pinned host
+ *     memory, taken by the first qrnnt_decode of the process outside of graph
+ *     capture, where the kernels of a search say how far they are; no call's
+ *     result depends on an earlier call.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All work is enqueued asynchronously; nothing synchronises.
  *   - Every call validates its arguments on the host before launching

@@ -2,6 +2,7 @@
 // encoder and prediction outputs are combined multiplicatively, a linear layer
 // and a log-softmax follow; Eq. 1 adds the weighted LM log-probabilities).
 #include <atomic>
+#include <mutex>
 #include <type_traits>
 
 #include "head.h"
@@ -1354,27 +1355,45 @@ int qr_plan_run(const QrRoundArgs &a, int B, int W)
     return wgs == 1 || 6 * (int64_t)B * wgs <= 5 * (int64_t)room ? a.wgs_lm : 0;
 }
 
-// A word of host memory for a call, by turns: a search that ends late may write into the word of another one, which then
-// enqueues more launches than it needs.  One allocation in a process, of one page, kept to its end; none while a graph is
-// captured (a graph's launches are all of them anyway).
+// One page of pinned host memory for all searches of the process, kept to its end.  Taken under the relaxed capture mode, so that
+// another thread's capture does not mind; a failure is not kept, the next search tries again.
+static std::atomic<unsigned long long *> ticket_words{nullptr};
+constexpr int TICKET_WORDS = 64, TICKET_APART = 8;   // a cache line each
+
+static unsigned long long *take_ticket_words()
+{
+    static std::mutex one;
+    std::unique_lock<std::mutex> lock(one, std::try_to_lock);
+    if (!lock) return nullptr;   // another thread is at it; this search does without
+    if (unsigned long long *const w = ticket_words.load(std::memory_order_acquire)) return w;
+    constexpr size_t n = (size_t)TICKET_WORDS * TICKET_APART;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+    void *at = nullptr;
+    const hipError_t e = hipHostMalloc(&at, n * sizeof(unsigned long long), hipHostMallocPortable | hipHostMallocMapped);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return nullptr;
+    unsigned long long *const w = (unsigned long long *)at;
+    for (size_t i = 0; i < n; ++i) w[i] = 0;
+    ticket_words.store(w, std::memory_order_release);
+    return w;
+}
+
+// A word of that page for a call, by turns: a search that ends late may write into the word of another one, which then enqueues
+// more launches than it needs.  None while a graph is captured (a graph's launches are all of them anyway).
 void qr_take_ticket(QrRunArgs &r, hipStream_t st)
 {
-    constexpr int WORDS = 64, APART = 8;   // a cache line each
     static std::atomic<unsigned> next{1};
+    const bool clean = hipPeekAtLastError() == hipSuccess;   // (what the call's launches left is reported at its end)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     r.told = nullptr;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-    static unsigned long long *const words = [] {
-        void *at = nullptr;
-        if (hipHostMalloc(&at, WORDS * APART * sizeof(unsigned long long), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-            (void)hipGetLastError();
-            return (unsigned long long *)nullptr;
-        }
-        for (int i = 0; i < WORDS * APART; ++i) ((unsigned long long *)at)[i] = 0;
-        return (unsigned long long *)at;
-    }();
-    r.ticket = next.fetch_add(1, std::memory_order_relaxed);
-    r.told = words ? words + r.ticket % WORDS * APART : nullptr;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        unsigned long long *w = ticket_words.load(std::memory_order_acquire);
+        if (!w) w = take_ticket_words();
+        r.ticket = next.fetch_add(1, std::memory_order_relaxed);
+        r.told = w ? w + r.ticket % TICKET_WORDS * TICKET_APART : nullptr;
+    }
+    if (clean) (void)hipGetLastError();
 }
 
 void qr_launch_search_run(const QrRoundArgs &a, const QrRunArgs &r, int wgs, hipStream_t st)

@@ -1,4 +1,7 @@
 """A search is enqueued and its call returns: the host waits for nothing that the device does."""
+import os
+import subprocess
+import sys
 import time
 
 import pytest
@@ -43,3 +46,54 @@ def test_a_search_on_a_busy_stream_is_enqueued_at_once(gpu_lib):
             assert all(torch.equal(g, w) for g, w in zip(got, want[i]))
     assert all(busy)   # (the calls came back in front of what is ahead of them)
     assert best[0] < 1.2 * best[1], best
+
+
+FIRST_SEARCH = """
+import ctypes as C
+import threading
+
+import torch
+
+from paper_2206_07882_amd import model as gmodel, qrnnt as q, synth
+from tests.test_gpu_decode import dev
+from tests.test_gpu_search_round import _model
+
+T, B, W, max_sym = 12, 2, 4, 3
+G = gmodel.model_from_float(_model(80, 17, False), "cuda:0")
+e = dev(synth.normal(1400, (T, B, 80), 1.0))
+q.decode_alsd(G, e, W, 4)   # (the library's code is on the device)
+ws = torch.empty(q.decode_workspace(G, T, B, W, max_sym), dtype=torch.uint8, device="cuda:0")
+shapes = ((B, W, T), torch.int32), ((B, W), torch.int32), ((B, W), torch.float32)
+got = [torch.empty(s, dtype=d, device="cuda:0") for s, d in shapes]
+x, y = torch.ones(1000, device="cuda:0"), torch.zeros(1000, device="cuda:0")
+side, model, status = torch.cuda.Stream(), G.c(), []
+
+def search():
+    status.append(q.load().qrnnt_decode(C.byref(model), C.c_void_p(e.data_ptr()), T, B, W, max_sym, T, *(C.c_void_p(t.data_ptr()) for t in got),
+                                        C.c_void_p(ws.data_ptr()), C.c_size_t(ws.numel()), C.c_void_p(side.cuda_stream)))
+
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    y.copy_(x)
+    thread = threading.Thread(target=search)
+    thread.start()
+    thread.join()
+    y.add_(1.0)
+torch.cuda.synchronize()
+assert status == [0], status
+for i in range(3):
+    x.fill_(i)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert bool((y == i + 1).all())
+assert all(torch.equal(g, w) for g, w in zip(got, q.decode(G, e, W, max_sym, max_len=T)))
+print("as it should be")
+"""
+
+
+def test_the_first_search_of_a_process_beside_a_capture(gpu_lib):
+    """What a process' first search takes from the system does not spoil the graph that another thread captures meanwhile."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FIRST_SEARCH], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "as it should be" in r.stdout, r.stderr[-2000:]
