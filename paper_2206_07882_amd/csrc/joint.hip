@@ -341,9 +341,7 @@ struct QrShare {
 // 16, ns after its start, one workgroup -> several): sums of the output layers 5000 -> 2100, scores begin 6100 -> 3600, end
 // 9900 -> 7500; a round of three launches 23.3 -> 20.5 us, of 64 utterances (batch of 1000 frames, all rounds) 37.3 -> 36.5.
 // (Two workgroups, the second with the language models: the first one's share still took 4.2 us, no gain.)
-// TAGS: label picks look for rows that hold their states (route.h).  Without (alignment-length search of up to 16 hypotheses:
-// the step kernels take as long for one as for all of them, and the list is hardly ever empty): looking cost 228 iterations at
-// beam 4 2 %, 60 us, and saved none.
+// TAGS: label picks look for rows that hold their states (route.h); see launch_round.
 template <int NTW, bool ALSD, bool CL, bool TAGS = true>
 __global__ __launch_bounds__(512, CL ? 4 : 2) void search_round_kernel(const QrRoundArgs a, const QrRouteArgs r, const QrAlsdArgs s)
 {
@@ -782,7 +780,7 @@ __global__ __launch_bounds__(512, CL ? 4 : 2) void search_round_kernel(const QrR
             alsd_own.h = own;
             qr_alsd_route<LOG_SLOTS, TAGS>(r, s, b, lane, my_c, my_v, alsd_own, tags, mask);
         } else {
-            const int cnt = qr_route_picks<LOG_SLOTS>(r, b, lane, my_c, my_v, own, nx0, tags, mask, [&](int e, float v, const v4i &info) {
+            const int cnt = qr_route_picks<LOG_SLOTS, TAGS>(r, b, lane, my_c, my_v, own, nx0, tags, mask, [&](int e, float v, const v4i &info) {
                 if (frame_end) {
                     list_entry(e, v, info);
                 } else {
@@ -839,11 +837,18 @@ void launch_round(const QrRoundArgs &a, const QrRouteArgs &r, const QrAlsdArgs &
 {
     int wgs = ALSD || !r.last_round ? a.wgs_lm : a.wgs_last;
     if (a.come > 0 && a.come < wgs) wgs = a.come;
+    // No label pick looks for its states at beam 1, where every one stays and no sequence comes back (looking and not looking, ms:
+    // time-synchronous, 60 frames, 100 utterances 6.38 and 6.27, 300 9.00 and 8.83; alignment-length search, 180 iterations, 32
+    // utterances 4.07 and 4.01, 100 4.76 and 4.72; at beam 2 looking takes 64 utterances of 150 frames from 5.85 to 5.10), and none in
+    // an alignment-length search of up to 16 hypotheses, whose step kernels take as long for one as for all of them and whose
+    // list is hardly ever empty (228 iterations at beam 4 2 %, 60 us).
+    const bool tags = r.W > 1 && !(ALSD && r.B * r.W <= 16);
     // (one workgroup to an utterance: any number of utterances, and a grid's z extent ends at 65535)
     const dim3 grid = wgs == 1 ? dim3(r.B) : dim3(a.n_xcd, wgs, (r.B + a.n_xcd - 1) / a.n_xcd);
-    if (ALSD && wgs && r.B * r.W <= 16) search_round_kernel<1, ALSD, true, !ALSD><<<grid, 512, 0, st>>>(a, r, s);   // (without tags)
-    else if (wgs) search_round_kernel<1, ALSD, true><<<grid, 512, 0, st>>>(a, r, s);
-    else if (r.W <= 16) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
+    if (wgs && tags) search_round_kernel<1, ALSD, true><<<grid, 512, 0, st>>>(a, r, s);
+    else if (wgs) search_round_kernel<1, ALSD, true, false><<<grid, 512, 0, st>>>(a, r, s);
+    else if (r.W <= 16 && tags) search_round_kernel<1, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
+    else if (r.W <= 16) search_round_kernel<1, ALSD, false, false><<<r.B, 512, 0, st>>>(a, r, s);
     else if (r.W <= 32) search_round_kernel<2, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
     else search_round_kernel<4, ALSD, false><<<r.B, 512, 0, st>>>(a, r, s);
 }

@@ -35,7 +35,7 @@ __device__ __forceinline__ int qr_free_row(const QrRouteArgs &a, int b, int lane
 // as most of them fall out of the beam again: of 64 utterances at beam 16 and 4 labels a frame (base networks) 29 of 32 label
 // picks a frame find their states, and the launches of an advance are those of a list a tenth as long.  Finding a row takes
 // three dependent LDS reads.  Whole calls, ms: 64 x 1000 frames 168.0 -> 104.5, 13 x 301 (2 x 2048 LM) 51.8 -> 33.9, 1 x 152
-// 13.28 -> 11.1 (its rounds without a row to advance cost two launches that return); beam 1 level.  Alignment-length search
+// 13.28 -> 11.1 (its rounds without a row to advance cost two launches that return); which searches look: launch_round (joint.hip).  Alignment-length search
 // (its pool of two rows to a slot of the beam; three, four and six find no more), 64 x 300 16.65 -> 14.56, 1 x 152 at beam 4 level.
 struct QrTags {
     v4i *tag;                          // LDS, [P rounded up to 64]: the utterance's
@@ -235,7 +235,7 @@ __device__ __forceinline__ void qr_list_free_rows(const QrRouteArgs &a, int b, i
 // own: hypothesis `lane` of the current round; a pick reads its parent's from that lane.
 // nx0: the length of the utterance's candidate list before this round (a.nx_count[b], fetched early as well);
 // add(e, score, info) puts a candidate at its end.
-template <int LOG, class Add>
+template <int LOG, bool TAGS, class Add>
 __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int lane, int c, float v, const QrOwn &own, int nx0,
                                               const QrTags &tags, unsigned *mask, Add &&add)
 {
@@ -264,8 +264,13 @@ __device__ __forceinline__ int qr_route_picks(const QrRouteArgs &a, int b, int l
     int base = 0, row = 0, n_new = 0, k_new = 0;
     bool steps = false;
     if (n_lab > 0) {   // uniform
-        int n_passed, last;
-        row = qr_find_rows<LOG, true>(a, b, lane, is_lab, par_serial, tok, own, tags, mask, steps, n_passed, last);
+        int n_passed = own.taken + n_lab, last;
+        if (TAGS) {
+            row = qr_find_rows<LOG, true>(a, b, lane, is_lab, par_serial, tok, own, tags, mask, steps, n_passed, last);
+        } else {
+            row = __shfl(own.free_row, k_lab);
+            steps = is_lab;
+        }
         const unsigned long long sm = __ballot(steps);
         n_new = (int)__popcll(sm);
         k_new = (int)__popcll(sm & lt);
