@@ -133,7 +133,7 @@ struct QrShare {
     __device__ __forceinline__ int row_tiles() const { return (V + 15) >> 4; }
 
     // Words on their way between the workgroups: source q, hypothesis, token (of a bottleneck: four codes to a word).
-    __device__ __forceinline__ unsigned long long *(word_at)(int q, int hyp, int token) const
+    __device__ __forceinline__ unsigned long long *word_at(int q, int hyp, int token) const
     {
         return a.words + b * a.n_words + (q * 16 + hyp) * 64 + token;
     }
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(512, CL ? 4 : 2) void search_round_kernel(const QrR
     const int n_row_tiles = (V + 15) >> 4;
     const int my_n = b * W + (col < W ? col : W - 1);   // this lane's column of the (first) tile
     QrShare share = {a, sums, (int8_t(*)[16][272])mid_code, jc, &missed, b, V};   // what the workgroups of an utterance do for one another
-    auto word_at = [&](int q, int hyp, int token) { return (share.word_at)(q, hyp, token); };
+    auto word_at = [&](int q, int hyp, int token) { return share.word_at(q, hyp, token); };
     auto enough = [&](unsigned &limit) { return share.enough(limit); };
 
     // CL: this workgroup's share of the joint: blocks of 64 columns first, first + a.parts, ...  A block: the 64 rows of the
@@ -957,7 +957,7 @@ __global__ __launch_bounds__(512, 4) void search_run_kernel(const QrRoundArgs a,
     int t = __builtin_amdgcn_readfirstlane(prog[0]), v = __builtin_amdgcn_readfirstlane(prog[1]);
     if (t >= r.T) return;   // uniform: the utterance is through
     QrShare share = {a, sums, mid_code, jc, &missed, b, V};
-    auto word_at = [&](int q, int hyp, int token) { return (share.word_at)(q, hyp, token); };
+    auto word_at = [&](int q, int hyp, int token) { return share.word_at(q, hyp, token); };
     const int z_hyp = share.z_hyp(), z_col = share.z_col();
     const v4i zero = {0, 0, 0, 0};
 

@@ -29,11 +29,32 @@ def test_the_search_finds_what_it_looks_for():
     assert not _unwaited('asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p));')
 
 
+WORD_USES = (r"qr_send\(word_at\(", r"\(void \*\)word_at\(",                # a store; where loads start
+             r"__device__ __forceinline__ unsigned long long \*word_at\(int q, int hyp, int token\) const",
+             r"auto word_at = \[&\]\(int q, int hyp, int token\) \{ return share\.word_at\(q, hyp, token\); \};")
+
+
+def _other_word_uses(text):
+    """Lines that mention a word's place (word_at, however it is written) or the area of the words itself, and are none of the above."""
+    for use in WORD_USES:
+        text = re.sub(use, "", text)
+    return [line for line in text.splitlines() if re.search(r"\bword_at\b|\ba\.words\b", line) and "return a.words + b * a.n_words" not in line]
+
+
 def test_words_between_workgroups_are_stored_by_their_helper_only():
     """A word of value and number that another workgroup polls has to be stored in one piece: by qr_send, never by an
     assignment that the compiler may split."""
-    text = open(os.path.join(CSRC, "joint.hip")).read()
-    uses = re.findall(r".*\bword_at\(.*", text)
-    assert len(uses) >= 5
-    for line in uses:
-        assert "qr_send(word_at(" in line or "(void *)word_at(" in line, line   # (the latter: where loads start)
+    found = {}
+    for f in glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.hip")):
+        text = open(f).read()
+        if f.endswith("joint.hip"):
+            assert len(re.findall(r"qr_send\(word_at\(", text)) >= 4
+        found[os.path.basename(f)] = _other_word_uses(text)
+    assert not any(found.values()), {k: v for k, v in found.items() if v}
+
+
+def test_the_search_for_words_finds_other_uses():
+    for line in ("*word_at(0, 1, 2) = v;", "(share.word_at)(q, 0, 0)[1] = v;", "auto *p = share.word_at(0, 0, 0);",
+                 "unsigned long long *(word_at)(int q, int hyp, int token) const", "a.words[3] = 0;"):
+        assert _other_word_uses(line) == [line]
+    assert not _other_word_uses("qr_send(word_at(part, col, 4 * grp), sum, a.round);")
