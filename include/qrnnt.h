@@ -451,14 +451,15 @@ qrnnt_status qrnnt_decode_alsd(const qrnnt_model *m, const float *enc_proj, int3
                                void *workspace, size_t workspace_bytes, void *stream);
 
 /* qrnnt_decode_alsd with options.  QRNNT_ALSD_REUSE: reuse of cached hypotheses (Sec. 4.1 names it as what
- * makes the decoding time fall sub-linearly at small beams), counted.  The states of the prediction network and of
- * the LMs after a label sequence depend on that sequence alone, and every search of this library has a label pick
- * whose resulting sequence still has its states in a row of the pool name that row instead of advancing the networks
- * from its own parent.  With this flag and with stats, a label pick whose resulting sequence a live hypothesis of the
- * current beam already holds is counted as reused; sequences are compared by (length, 64-bit hash) as in the
+ * makes the decoding time fall sub-linearly at small beams).  The states of the prediction network and of the LMs
+ * after a label sequence depend on that sequence alone, so a label pick may name a row of the state pool that still
+ * holds the states of its resulting sequence instead of advancing the networks from its own parent.  Searches of more
+ * than 16 hypotheses (B * W) at beams of two and more do so with and without the flag, for any row of the pool; there
+ * the flag only counts (with stats).  Smaller searches, and those at beam 1, do so only with the flag, for the rows of
+ * live hypotheses of the current beam.  What the flag finds and counts is found by (length, 64-bit hash) as in the
  * recombination.  Results are bit for bit those of qrnnt_decode_alsd.  stats [device] int32[2] or NULL: the call adds
- * the number of label picks that kept their slot to stats[0] and, with the flag, the number of those whose sequence
- * the beam held to stats[1] (the caller zeroes it). */
+ * the number of label picks that kept their slot to stats[0] and, with the flag, the number of those whose sequence a
+ * live hypothesis of the current beam held to stats[1] (the caller zeroes it). */
 #define QRNNT_ALSD_REUSE 1u
 qrnnt_status qrnnt_decode_alsd_ex(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W,
                                   int32_t u_max, int32_t max_len, uint32_t flags, int32_t *stats, int32_t *tokens_out,

@@ -194,8 +194,10 @@ struct QrAlsdArgs {
     const unsigned long long *hash_src;              // [N] hash of the label sequence (recombination key, with the length)
     unsigned long long *hash_dst;
     float *fin_score;  int32_t *fin_node, *fin_len;  // [B,W] the W best finished hypotheses so far, best first
-    int reuse;                                       // with stats: count label picks whose sequence a live hypothesis of the beam holds
-    int32_t *stats;                                  // optional [device] int32[2]: += label picks that kept their slot, += those that reused states
+    // label picks whose sequence a live hypothesis of the beam holds are looked for by hash: to name its row where rows are not
+    // looked for by their tags (launch_round), and to be counted where there are stats
+    int reuse;
+    int32_t *stats;                                  // optional [device] int32[2]: += label picks that kept their slot, += those
 };
 
 // One direction of the persistent recurrence (see recurrence.hip).

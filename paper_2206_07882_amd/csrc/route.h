@@ -386,8 +386,8 @@ __device__ __forceinline__ void qr_alsd_route(const QrRouteArgs &a, const QrAlsd
     if (lane == 0 && km != 0ull && a.live_next) atomicAdd(a.live_next, 1);
     // Reuse of cached hypotheses (Sec. 4.1): when a live hypothesis of the current beam already holds the sequence this label
     // pick produces (y + k is in the beam and y proposes k again one frame later), the new slot names that hypothesis' row.
-    // Looked for in this way, by the sequences' hashes, only where the caller counts them or the rows have no tags, which find
-    // nearly all of these and others.
+    // Looked for in this way, by the sequences' hashes, only where the caller counts them or rows are not looked for by their
+    // tags, which find nearly all of these and others.
     int reuse_slot = -1;
     if (s.reuse && (s.stats || !TAGS)) {   // uniform
         const int o_hlo = (int)(unsigned)o.hash, o_hhi = (int)(unsigned)(o.hash >> 32);

@@ -558,8 +558,9 @@ ALSD_REUSE = 1
 def decode_alsd(model: Model, enc_proj: torch.Tensor, W: int, u_max: int, max_len: Optional[int] = None,
                 workspace: Optional[torch.Tensor] = None, flags: int = 0, stats: Optional[torch.Tensor] = None):
     """Alignment-length synchronous search with recombination; at most u_max labels per utterance.
-    flags = ALSD_REUSE: label picks take over the states of a live hypothesis that holds their sequence;
-    stats (int32 [2] on the device, zeroed by the caller) counts label picks and reuses."""
+    flags = ALSD_REUSE: label picks take over the states of a live hypothesis that holds their sequence (searches of more than
+    16 hypotheses at beams above 1 do so, and more, without it); stats (int32 [2] on the device, zeroed by the caller) counts
+    label picks and, with the flag, those whose sequence the beam held."""
     T, B, J = enc_proj.shape
     dev = enc_proj.device
     if max_len is None:
