@@ -503,7 +503,8 @@ qrnnt_status qrnnt_diag_decode(const qrnnt_model *m, const float *enc_proj, int3
 /* The same with the first `come` workgroups of each beam (0: all of them), laid out as if the workgroups of a launch went to
  * n_xcd XCDs in turn (0: as the device says; otherwise those of a beam may run on several XCDs).  late_out [device, B], or
  * NULL: the number of rounds of each utterance in which the first workgroup had to do some of the others' work; not written
- * where an utterance has one workgroup by plan. */
+ * where an utterance has one workgroup by plan.  With come > 0 and late_out every round has a launch of its own also where
+ * the search would run ahead. */
 qrnnt_status qrnnt_diag_decode_shared(const qrnnt_model *m, const float *enc_proj, int32_t T, int32_t B, int32_t W, int32_t alsd,
                                       int32_t limit, int32_t max_len, int32_t come, int32_t n_xcd, int32_t *late_out,
                                       int32_t *tokens_out, int32_t *len_out, float *score_out, void *workspace,

@@ -428,7 +428,7 @@ static qrnnt_status time_synchronous(const qrnnt_model *m, const float *enc_proj
     if (const int wgs = p.prog ? qr_plan_run(ja, B, W) : 0) {
         QrRunArgs r = {};
         r.B = B;  r.W = W;  r.P = p.P;  r.T = T;  r.max_sym = max_sym;  r.n_entries = p.R * W;
-        r.every_round = diag.come > 0;
+        r.every_round = diag.come > 0 && diag.late_out;   // (rounds to be counted)
         r.prog = p.prog;  r.score = p.score;  r.node = p.node;  r.len = p.len;  r.row = p.row;
         r.tags = p.tags;  r.nx_score = p.nx_score;  r.nx_info = p.nx_info;
         r.node_tok = p.node_tok;  r.node_prev = p.node_prev;
