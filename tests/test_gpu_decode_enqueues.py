@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import threading
 import time
 
 import pytest
@@ -46,6 +47,39 @@ def test_a_search_on_a_busy_stream_is_enqueued_at_once(gpu_lib):
             assert all(torch.equal(g, w) for g, w in zip(got, want[i]))
     assert all(busy)   # (the calls came back in front of what is ahead of them)
     assert best[0] < 1.2 * best[1], best
+
+
+def test_searches_of_two_threads(gpu_lib):
+    """Two threads, a stream each, more searches than there are words of host memory to tell where they are: whoever reads another
+    one's word, the results are those of a search on its own."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    T, W, max_sym, many = 10, 4, 3, 50
+    G = gmodel.model_from_float(_model(80, 17, False), "cuda:0")
+    es = [dev(synth.normal(1350 + i, (T, 2, 80), 1.0)) for i in range(4)]
+    want = [q.decode(G, e, W, max_sym) for e in es]
+    torch.cuda.synchronize()
+    got, errors = {}, []
+
+    def search(k):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for i in range(many):
+                    got[k, i] = q.decode(G, es[(i + k) % 4], W, max_sym)
+            stream.synchronize()
+        except Exception as err:
+            errors.append(err)
+
+    threads = [threading.Thread(target=search, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for (k, i), out in got.items():
+        assert all(torch.equal(g, w) for g, w in zip(out, want[(i + k) % 4])), (k, i)
+    assert len(got) == 2 * many
 
 
 FIRST_SEARCH = """

@@ -165,3 +165,26 @@ def test_searches_on_several_streams(gpu_lib):
         for w, g in zip(a, b):
             assert torch.equal(w, g)
     assert all(torch.equal(h, want_h) for h in hs)
+
+
+@pytest.mark.parametrize("J,B,W", [(272, 2, 16), (272, 3, 1), (32, 5, 20), (32, 2, 40), (256, 105, 2), (256, 110, 2), (256, 110, 1)])
+@pytest.mark.parametrize("blank_bias", [0.0, 6.0])
+def test_early_stop_where_a_round_is_a_launch(gpu_lib, J, B, W, blank_bias):
+    """Searches that do not run ahead (a wide joint, a wide beam, many utterances: one workgroup each, in 105 but for a frame's
+    last round): kernels that return because no utterance carried a label into their round leave the same beams.  With the blank
+    made likely most rounds after a frame's first are such."""
+    from paper_2206_07882_amd import model as gmodel
+    q = gpu_lib
+    T, max_sym, few = 6, 3, 5
+    m = _model(J, 20, False)
+    m.joint_out.bias = m.joint_out.bias.copy()
+    m.joint_out.bias[0] += np.float32(blank_bias)   # blank is token 0
+    e = synth.normal(990 + J, (T, few, J), 1.0)
+    G, M = gmodel.model_from_float(m, "cuda:0"), omodels.model_from_float(m)
+    E = dev(e)[:, torch.arange(B, device="cuda:0") % few].contiguous()
+    n = min(B, few)
+    plain = q.decode(G, E, W, max_sym, max_len=T * max_sym)
+    early = q.decode(G, E, W, max_sym, max_len=T * max_sym, flags=q.DECODE_EARLY_STOP)
+    _compare_beams([t[:n] for t in early], [r[:n] for r in oracle.decode(M, e, W, max_sym, max_len=T * max_sym)])
+    for a, b in zip(plain, early):
+        assert torch.equal(a, b)
