@@ -227,7 +227,8 @@ def test_decode_utterance_alone_equals_batched(gpu_lib, B, W, max_sym, blank_bia
 @pytest.mark.parametrize("blank_bias", [0.0, 6.0])
 def test_decode_early_stop_gives_the_same_beams(gpu_lib, blank_bias):
     """With the early-stop flag the kernels of a round return at once when no utterance carried a label
-    into it.  Same beams as the fixed-round search and as the oracle; the blank-heavy variant (joint bias
+    into it (not of a search that runs ahead, as this one does: those that do not are in
+    test_gpu_search_round.py).  Same beams as the fixed-round search and as the oracle; the blank-heavy variant (joint bias
     of blank raised) makes most rounds after the first die, the plain one keeps them all alive."""
     from paper_2206_07882_amd import model as gmodel
     m = synth.make_model(0, weight_std=0.6)
